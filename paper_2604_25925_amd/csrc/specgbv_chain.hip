@@ -38,7 +38,8 @@ namespace {
 
 constexpr int kChainThreads = 512;
 constexpr int kChainWaves = kChainThreads / kWave;
-constexpr int kLdsSlots = 9;
+constexpr int kLdsSlots = 9;       // LDS slots of a workgroup that has its compute unit to itself
+constexpr int kPairLdsSlots = 4;   // ... and of one that shares it with a second one (rows of at most 7 + 4 slots)
 
 // t[j] <- t[j]^K.  KP > 0 fixes K at compile time; KP = 0 takes the wave-uniform K >= 1.
 template <int KP, int N>
@@ -278,7 +279,7 @@ constexpr int kLag = 6;    // slots between the load of a vector and its first u
 constexpr double kTokenRefLimit = 1073741824.0;   // 2^30: largest row sum accepted relative to the drafted token's weight
 
 struct LdsSlots {
-    U4 *all;                 // [kLdsSlots][2][kChainThreads]: slot s, half 0 = target vectors, half 1 = draft vectors
+    U4 *all;                 // [LS][2][kChainThreads]: slot s, half 0 = target vectors, half 1 = draft vectors
     unsigned wave_base;      // LDS byte address of this wave's 1 KiB window in slot 0, half 0
 };
 __device__ __forceinline__ const U4 &lds_vec(const LdsSlots &lds, int s, int half, unsigned t)
@@ -303,8 +304,8 @@ struct StepCtx {
 // the asynchronous global->LDS fills, which are inline assembly.  With the fills at the start of the row no fill
 // follows a register load inside an iteration, so the compiler's count for every register slot is exact, and it
 // never waits for more than the slot it is about to read.
-template <int RS>
-constexpr int slot_at(int i) { return i < kLdsSlots ? RS + kLdsSlots - 1 - i : i - kLdsSlots; }
+template <int RS, int LS>
+constexpr int slot_at(int i) { return i < LS ? RS + LS - 1 - i : i - LS; }
 
 // Step I of the slot pipeline (all indices are compile-time constants so that the slot arrays stay in registers):
 // sweep 2 of the old row on slot J = slot_at(I), the load of the new row into slot J, and sweep 1 of the new row
@@ -312,11 +313,11 @@ constexpr int slot_at(int i) { return i < kLdsSlots ? RS + kLdsSlots - 1 - i : i
 // asynchronous global->LDS loads, so a manual wait precedes their first read: every one of the kLag steps after the
 // fill of a used LDS slot issues two vector-memory operations (the used LDS slots are contiguous and the register
 // slots follow them), none of which may be pending once the fill has landed.
-template <typename T, int KP, int RS, int I>
+template <typename T, int KP, int RS, int LS, int I>
 __device__ __forceinline__ void pipeline_step(const StepCtx<T> &cx, U4 (&rq)[RS], U4 (&rp)[RS],
                                               const LdsSlots &lds, float &Zq, float &Zp, float &acc)
 {
-    constexpr int NS = RS + kLdsSlots;
+    constexpr int NS = RS + LS;
     static_assert(RS >= kLag, "the steps after the last LDS fill must all be register loads");
     constexpr size_t kSlotBytes = static_cast<size_t>(kChainThreads) * 16;
     // Opaque copies: everything derived from them is recomputed per step instead of being
@@ -324,7 +325,7 @@ __device__ __forceinline__ void pipeline_step(const StepCtx<T> &cx, U4 (&rq)[RS]
     unsigned t = cx.tid, off = cx.off_new;
     asm volatile("" : "+v"(t), "+v"(off));
     if constexpr (I < NS) {
-        constexpr int J = slot_at<RS>(I);
+        constexpr int J = slot_at<RS, LS>(I);
         if constexpr (J < RS) {
             // Opaque touch of the slot: without it the compiler keeps the floats that sweep 1
             // unpacked from these registers alive until sweep 2, which doubles the footprint of
@@ -353,7 +354,7 @@ __device__ __forceinline__ void pipeline_step(const StepCtx<T> &cx, U4 (&rq)[RS]
     }
     constexpr int II = I - kLag;                            // lagged sweep 1 of the new row
     if constexpr (II >= 0 && II < NS) {
-        constexpr int JJ = slot_at<RS>(II);
+        constexpr int JJ = slot_at<RS, LS>(II);
         if constexpr (JJ < RS) {
             if (cx.do_new) sweep1_vec<T>(rq[JJ], rp[JJ], cx.rc_new, Zq, Zp, JJ == cx.tok_slot, cx.tok_mine);
         } else {
@@ -369,11 +370,11 @@ __device__ __forceinline__ void pipeline_step(const StepCtx<T> &cx, U4 (&rq)[RS]
     }
 }
 
-template <typename T, int KP, int RS, int... Js>
+template <typename T, int KP, int RS, int LS, int... Js>
 __device__ __forceinline__ void run_steps(std::integer_sequence<int, Js...>, const StepCtx<T> &cx, U4 (&rq)[RS],
                                           U4 (&rp)[RS], const LdsSlots &lds, float &Zq, float &Zp, float &acc)
 {
-    (pipeline_step<T, KP, RS, Js>(cx, rq, rp, lds, Zq, Zp, acc), ...);
+    (pipeline_step<T, KP, RS, LS, Js>(cx, rq, rp, lds, Zq, Zp, acc), ...);
 }
 
 // log2 of a positive finite double from its exponent and a float log of the mantissa
@@ -597,7 +598,7 @@ struct ChainPend {
 
 // sum over this thread's on-chip vectors of the row pair of the weights w (ot_weights, or pending_weights
 // when tab holds levels), relative to 2^shift_q.  Register slots are all full (the host picks RS so).
-template <typename T, int RS, int... Js>
+template <typename T, int RS, int LS, int... Js>
 __device__ __forceinline__ float onchip_sum(std::integer_sequence<int, Js...>, U4 (&rq)[RS], U4 (&rp)[RS],
                                             const LdsSlots &lds, unsigned tid, int rem, int n_on, float c, float shift_q,
                                             const PendTable &tab, const RatioConst &rc, int K)
@@ -627,22 +628,22 @@ __device__ __forceinline__ float onchip_sum(std::integer_sequence<int, Js...>, U
         one(q, p);
     };
     (reg(rq[Js], rp[Js]), ...);
-    for (int s = 0; s < kLdsSlots; ++s) {
+    for (int s = 0; s < LS; ++s) {
         const int J = RS + s;
         if (J < n_on && J * kChainThreads < rem) one(lds_vec(lds, s, 0, tid), lds_vec(lds, s, 1, tid));
     }
     return acc;
 }
 
-template <typename T, int KP, int RS, bool PEND>
-__global__ void __launch_bounds__(kChainThreads)
+template <typename T, int KP, int RS, int LS, bool PEND>
+__global__ void __launch_bounds__(kChainThreads, LS < kLdsSlots ? 4 : 2)
 k_chain(const T *__restrict__ target, const T *__restrict__ draft, const int32_t *__restrict__ tokens,
         int K, int L, int V, long long nchains, float c, RowStat *__restrict__ stats, double *__restrict__ s_out,
         double *__restrict__ e_out,
         int32_t *__restrict__ final_counter, ChainPend pend, int first_row, const Row0Part *__restrict__ row0, double c_rel,
         int32_t *__restrict__ later, int later_stride)
 {
-    __shared__ U4 lds_all[kLdsSlots * 2 * kChainThreads];
+    __shared__ U4 lds_all[LS * 2 * kChainThreads];
     __shared__ double sh_d[3 * kChainWaves];
     __shared__ double sh_sumrow[2][2];                     // log2 of the block ratio and of the drafts' joint probability in front
                                                            // of the row in sweep 2: written by thread 0 when the row's statistics
@@ -665,7 +666,7 @@ k_chain(const T *__restrict__ target, const T *__restrict__ draft, const int32_t
     constexpr unsigned kSumThread = kWave;
     if (threadIdx.x == kSumThread) sh_nlater = 0;
     constexpr int PV = Elem<T>::kPerVec;
-    constexpr int NS = RS + kLdsSlots;                     // slots kept on chip
+    constexpr int NS = RS + LS;                            // slots kept on chip
     const unsigned tid = threadIdx.x;
     const unsigned lds_wave_addr = static_cast<unsigned>(
         reinterpret_cast<uintptr_t>(static_cast<void *>(&lds_all[tid & ~(kWave - 1u)])));
@@ -764,7 +765,7 @@ k_chain(const T *__restrict__ target, const T *__restrict__ draft, const int32_t
         float Zq = 0.0f, Zp = 0.0f, acc = 0.0f;
         StepCtx<T> cx{qnew, pnew, rc_sum, rc_new, tid, off_new, nvec, rem, n_on, do_new, do_sum,
                       (tok_new / PV) / kChainThreads, tid == static_cast<unsigned>((tok_new / PV) % kChainThreads)};
-        run_steps<T, KP, RS>(std::make_integer_sequence<int, NS + kLag>{}, cx, rq, rp, lds, Zq, Zp, acc);
+        run_steps<T, KP, RS, LS>(std::make_integer_sequence<int, NS + kLag>{}, cx, rq, rp, lds, Zq, Zp, acc);
         // vectors that do not fit on chip: read for the statistics now, once more for the sum; the
         // loads of the next slot are issued before the arithmetic of the current one
         if (NS < nslots) {
@@ -897,7 +898,7 @@ k_chain(const T *__restrict__ target, const T *__restrict__ draft, const int32_t
                         __syncthreads();
                         RatioConst rc(0.0);
                         rc.C2_hi = sh_row.rc_hi; rc.neg_kappa = sh_row.rc_nk;
-                        double S = static_cast<double>(onchip_sum<T, RS>(std::make_integer_sequence<int, RS>{}, rq, rp, lds, tid, rem,
+                        double S = static_cast<double>(onchip_sum<T, RS, LS>(std::make_integer_sequence<int, RS>{}, rq, rp, lds, tid, rem,
                                                                          n_on, c, ref_q, sh_tab, rc, K));
                         double unused = 0.0;
                         block_sum2(S, unused, sh_d);
@@ -1048,14 +1049,31 @@ int resident_workgroups()
     return cached[dev];
 }
 
+// Rows short enough that two workgroups' row pairs fit a compute unit (RS = 7, kPairLdsSlots).  With 32000 bfloat16
+// entries a workgroup alone takes 9.4 us a row, of which 5 are arithmetic and the rest the row's own latencies; two of
+// them take 15.6 together.  K = L = 8: 320 drafts 165 -> 143 us a call, 512 drafts 172 -> 152, 256 drafts unchanged.
+bool chain_shares_unit(const Problem &p)
+{
+    const int nslots = (p.V / (p.dtype == 1 ? 8 : 4) + kChainThreads - 1) / kChainThreads;
+    return p.pend_levels == 0 && nslots <= 7 + kPairLdsSlots;
+}
+
+// Workgroups of k_chain for this problem: a list of rows for each, one or two of them per compute unit.
+long long chain_grid(const Problem &p)
+{
+    const long long nchains = static_cast<long long>(p.batch) * p.K;
+    long long room = resident_workgroups();
+    if (chain_shares_unit(p)) room = 2 * room < kMaxChainGrid ? 2 * room : kMaxChainGrid;
+    return nchains < room ? nchains : room;
+}
+
 template <typename T, int KP, bool PEND>
 hipError_t launch_kp(const Problem &p)
 {
     RowStat *stats = reinterpret_cast<RowStat *>(p.ws + p.lay.stats);
     double *s = reinterpret_cast<double *>(p.ws + p.lay.s);
     const long long nchains = static_cast<long long>(p.batch) * p.K;
-    const long long cus = resident_workgroups();
-    const dim3 grid(static_cast<unsigned>(nchains < cus ? nchains : cus));
+    const dim3 grid(static_cast<unsigned>(chain_grid(p)));
     const int stride = later_list_entries(nchains, grid.x, p.L);
     const T *target = static_cast<const T *>(p.target);
     const T *draft = static_cast<const T *>(p.draft);
@@ -1070,15 +1088,16 @@ hipError_t launch_kp(const Problem &p)
     if (first_row)
         hipLaunchKernelGGL((k_row0_parts<T>), dim3(kRow0Parts, static_cast<unsigned>(p.batch), 2), dim3(kRow0Threads), 0,
                            p.stream, target, draft, p.tokens, p.K, p.L, p.V, p.c, row0);
-#define SPECGBV_LAUNCH(RS)                                                                                  \
-    hipLaunchKernelGGL((k_chain<T, KP, RS, PEND>), grid, dim3(kChainThreads), 0, p.stream, target, draft,  \
+#define SPECGBV_LAUNCH(RS, LS)                                                                              \
+    hipLaunchKernelGGL((k_chain<T, KP, RS, LS, PEND>), grid, dim3(kChainThreads), 0, p.stream, target, draft,  \
                        p.tokens, p.K, p.L, p.V, nchains, p.c, stats, s,                                    \
                        reinterpret_cast<double *>(p.ws + p.lay.excess),                                    \
                        reinterpret_cast<int32_t *>(p.ws + p.lay.counter), pend, first_row, row0, p.c_rel,     \
                        reinterpret_cast<int32_t *>(p.ws + p.lay.later), stride)
-    if (full_slots >= 23) SPECGBV_LAUNCH(23);
-    else if (full_slots >= 15) SPECGBV_LAUNCH(15);
-    else SPECGBV_LAUNCH(7);
+    if (full_slots >= 23) SPECGBV_LAUNCH(23, kLdsSlots);
+    else if (full_slots >= 15) SPECGBV_LAUNCH(15, kLdsSlots);
+    else if (chain_shares_unit(p)) { if constexpr (!PEND) SPECGBV_LAUNCH(7, kPairLdsSlots); }
+    else SPECGBV_LAUNCH(7, kLdsSlots);
 #undef SPECGBV_LAUNCH
     return hipGetLastError();
 }
@@ -1088,7 +1107,7 @@ hipError_t launch_excess_typed(const Problem &p)
 {
     const long long nchains = static_cast<long long>(p.batch) * p.K;
     const long long cus = resident_workgroups();
-    const long long grid = nchains < cus ? nchains : cus;                  // k_chain's grid: one list per workgroup
+    const long long grid = chain_grid(p);                                  // k_chain's: one list per workgroup
     hipLaunchKernelGGL((k_chain_excess<T>), dim3(static_cast<unsigned>(cus)), dim3(kExcessThreads), 0, p.stream,
                        static_cast<const T *>(p.target), static_cast<const T *>(p.draft), p.K, p.L, p.V, p.c,
                        reinterpret_cast<const RowStat *>(p.ws + p.lay.stats),
