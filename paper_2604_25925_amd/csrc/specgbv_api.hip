@@ -3,6 +3,7 @@
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
+#include <cstdlib>
 #include <cstring>
 
 #include "../../include/specgbv.h"
@@ -66,6 +67,26 @@ Workspace make_workspace(int batch, int K, int L, int V)
     w.kseq_pos = take(static_cast<size_t>(batch) * L * 2 * sizeof(int32_t));
     w.total = off;
     return w;
+}
+
+int compute_units()
+{
+    static int cached[kMaxDevices] = {};
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= kMaxDevices) return 256;
+    if (cached[dev] == 0) {
+        int n = 0;
+        cached[dev] = (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) ? n : 256;
+    }
+    return cached[dev];
+}
+
+int wait_polls()
+{
+    const char *polls = std::getenv("SPECGBV_EXCESS_POLLS");
+    if (!polls) return 1024;
+    const long n = std::strtol(polls, nullptr, 10);
+    return n < 0 ? 0 : (n > 1048576 ? 1048576 : static_cast<int>(n));
 }
 
 static bool shape_ok(int batch, int K, int L, int V)
@@ -188,19 +209,25 @@ specgbv_status specgbv_verify_ex(
         // With pending modifications the two-pass schedule is the default: its extra passes spread over the whole
         // chip, while a chain pays for its modified rows alone (measured: the chain is ahead only while at most
         // about three rows per draft are modified, and a batch waits for its most modified prefix).
-        use_chain = !pending && chain_preferred(p);
+        // Without pending modifications every row pair is read once: by the chain schedule where there are enough
+        // drafts for it, else by the rows schedule (which takes all but rows shorter than a vector or longer than
+        // its registers hold; those go the two-pass way).
+        if (!pending) {
+            use_chain = chain_preferred(p);
+            if (!use_chain) p.rows_parts = rows_schedule_parts(p);
+        }
     }
 
-    p.s_parts = use_chain ? 1 : split_sum_parts(p);
+    p.s_parts = use_chain ? 1 : (p.rows_parts > 0 ? p.rows_parts : split_sum_parts(p));
     p.e_parts = (use_chain && !pending) ? chain_excess_parts(p) : 0;
-    p.e_coop = use_chain ? 0 : 1;
+    p.e_coop = (use_chain || p.rows_parts == 1) ? 0 : 1;
 
     hipError_t e;
     if (options && options->ev_main_start) {
         e = hipEventRecord(static_cast<hipEvent_t>(options->ev_main_start), p.stream);
         if (e != hipSuccess) return fail(SPECGBV_EHIP, "hipEventRecord: %s", hipGetErrorString(e));
     }
-    e = use_chain ? launch_chain_main(p) : launch_split_main(p);
+    e = use_chain ? launch_chain_main(p) : (p.rows_parts > 0 ? launch_rows_main(p) : launch_split_main(p));
     if (e != hipSuccess) return fail(SPECGBV_EHIP, "main kernel launch: %s", hipGetErrorString(e));
     if (options && options->ev_main_stop) {
         e = hipEventRecord(static_cast<hipEvent_t>(options->ev_main_stop), p.stream);

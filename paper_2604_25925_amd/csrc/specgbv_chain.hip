@@ -29,6 +29,7 @@
 // modifies the row gets its normaliser from one more sweep over the on-chip copy (no memory
 // traffic), and so does the row's Eq. (hik) sum against the modified row; such a row's slots
 // are then simply reloaded in the next iteration.  Needs the whole row pair on chip.
+#include <cmath>
 #include <utility>
 
 #include "specgbv_internal.hpp"
@@ -1154,12 +1155,31 @@ bool chain_supports_pending(const Problem &p)
     return nslots <= RS + kLdsSlots;
 }
 
-// The chain schedule takes about the same time for any number of chains up to one per compute unit
-// (each workgroup streams its own rows), the two-pass schedule takes time in proportion to the
-// bytes: measured at V = 128256, bf16, L = 8 on 256 compute units they cross at about 170 chains.
+// Chain or rows?  The chain schedule's time is that of the rows a workgroup walks, whatever the number of workgroups
+// (up to one or two per compute unit); the rows schedule's goes with the number of row pairs.  Measured on 256 compute
+// units, K = L = 8, in microseconds of the streaming kernel (the call less the 30 that both spend elsewhere):
+//   one row of a chain:  3 + 1.44e-3 per vector (bfloat16: 8.8 / 15.5 / 26 at 4000 / 8000 / 16032 vectors),
+//                        2 + 0.85e-3 per vector (float32), but not faster than 6.3 TB/s over all chains;
+//   two chains per compute unit (short rows): 1.75 times the time of one;
+//   rows schedule:       8.8e-6 per vector of a row pair (7.7 - 9.4), e.g. bfloat16, V = 128256: 156 / 220 / 295 at
+//                        128 / 192 / 256 drafts against 200 / 210 / 215 on the chain schedule; V = 32000, 320 drafts: 97
+//                        against 113, 512 drafts: 156 against 122.
 bool chain_preferred(const Problem &p)
 {
-    return chain_supported(p) && static_cast<long long>(p.batch) * p.K * 100 >= static_cast<long long>(resident_workgroups()) * 66;
+    if (!chain_supported(p)) return false;
+    const long long chains = static_cast<long long>(p.batch) * p.K, units = resident_workgroups();
+    // a caller who states that rows 0 are shared gets the schedule that reads them once wherever it is near the fastest
+    if (p.shared_row0 && chains * 100 >= units * 66) return true;
+    if (rows_schedule_parts(p) == 0) return chains * 100 >= units * 66;       // against the two-pass schedule: crossover at 170 of 256
+    const double nv = p.V / (p.dtype == 1 ? 8 : 4), rows = static_cast<double>(chains) * p.L, scale = 256.0 / static_cast<double>(units);
+    const double one = p.L * (p.dtype == 1 ? 3.0 + 1.44e-3 * nv : 2.0 + 0.85e-3 * nv);
+    double t_chain;
+    if (chain_shares_unit(p)) {
+        const long long left = chains % (2 * units);
+        t_chain = one * (1.75 * static_cast<double>(chains / (2 * units)) + (left == 0 ? 0.0 : (left <= units ? 1.0 : 1.75)));
+    } else t_chain = one * static_cast<double>((chains + units - 1) / units);
+    t_chain = fmax(t_chain, rows * nv * 32.0 / 6.3e6);                        // (bytes over bytes per microsecond)
+    return t_chain < rows * nv * 8.8e-6 * scale;
 }
 
 hipError_t launch_chain_main(const Problem &p)

@@ -17,8 +17,6 @@
 //                  inverse-CDF search: the first token id whose running weight exceeds
 //                  u * total (segment by a workgroup-wide scan of the partial sums, entry by
 //                  a wave scan inside that segment).
-#include <cstdlib>
-
 #include "specgbv_internal.hpp"
 
 namespace specgbv {
@@ -1038,12 +1036,7 @@ hipError_t launch_final_typed(const Problem &p)
     io.e_parts = p.e_parts;
     io.e_coop = (p.e_coop != 0 && p.kseq_ndrafts == 0) ? 1 : 0;
     io.e_part_rw = reinterpret_cast<double *>(p.ws + p.lay.excess_part);
-    // (the environment variable lets a test take the fall-back of the bounded wait: 0 looks, every workgroup sums all parts)
-    io.e_polls = 1024;
-    if (const char *polls = std::getenv("SPECGBV_EXCESS_POLLS")) {
-        const long n = std::strtol(polls, nullptr, 10);
-        io.e_polls = n < 0 ? 0 : (n > 1048576 ? 1048576 : static_cast<int>(n));
-    }
+    io.e_polls = wait_polls();
     io.log_nu_out = reinterpret_cast<double *>(p.ws + p.lay.log_nu);
     io.log_P_out = reinterpret_cast<double *>(p.ws + p.lay.log_P);
     io.h_out = reinterpret_cast<double *>(p.ws + p.lay.h);

@@ -130,6 +130,18 @@ __device__ __forceinline__ U4 load16_stream(const void *p) {
     return U4{v.x, v.y, v.z, v.w};
 }
 
+// The same from an address with the alignment of one element only (rows of a vocabulary that is not a multiple of the
+// vector's length start anywhere): this hardware's global loads take any address.
+template <typename T>
+__device__ __forceinline__ U4 load16_stream_any(const T *p) {
+    typedef unsigned int V4 __attribute__((ext_vector_type(4)));
+    typedef V4 V4any __attribute__((aligned(2)));
+    static_assert(sizeof(T) >= 2, "element types of two bytes or more");
+    // (a global address, also where the compiler cannot tell: a flat load would be counted as an LDS access too)
+    const V4 v = __builtin_nontemporal_load((const __attribute__((address_space(1))) V4any *)p);
+    return U4{v.x, v.y, v.z, v.w};
+}
+
 // ------------------------------------------------------------------- math
 
 // v_exp_f32: 2^x, about 1 ulp, flushes results below 2^-126.
@@ -138,38 +150,6 @@ __device__ __forceinline__ float exp2_fast(float x) { return __builtin_amdgcn_ex
 // max(1 - r, 0) for r >= 0, as one clamped subtract.
 __device__ __forceinline__ float one_minus_clamped(float r) {
     return __builtin_amdgcn_fmed3f(1.0f - r, 0.0f, 1.0f);
-}
-
-// The ratio p[x] / (nu q[x]) = 2^(c (z_p - z_q) - C2) with a float64 constant C2 that can be
-// large while the exponent itself is small for the entries that matter.  C2 is split into
-// a float part used inside the exponent and a factor kappa = 2^-(C2 - float(C2)) applied in
-// the following "1 - ratio" (as one fused multiply-add), so the rounding of C2 to float
-// costs neither accuracy nor an instruction.
-struct RatioConst {
-    float C2_hi;
-    float neg_kappa;
-    __device__ __forceinline__ explicit RatioConst(double C2) {
-        C2_hi = static_cast<float>(C2);
-        const double kappa = exp2(static_cast<double>(C2_hi) - C2);
-        neg_kappa = (kappa > 0.5 && kappa < 2.0) ? -static_cast<float>(kappa) : -1.0f;   // non-finite C2
-    }
-    // max(1 - p/(nu q), 0) for logit difference d = z_p - z_q
-    __device__ __forceinline__ float one_minus_ratio(float d, float c) const {
-        const float r = __builtin_amdgcn_exp2f(fmaf(d, c, -C2_hi));
-        return __builtin_amdgcn_fmed3f(fmaf(r, neg_kappa, 1.0f), 0.0f, 1.0f);
-    }
-};
-
-// C2 for the sweeps' ratio p[x] / (nu q[x]) = 2^(c (z_p - z_q) - C2), C2 = log2 Z_p - log2 Z_q + log2 nu, with the part
-// of the rounding of c that a constant can carry.  The float c differs from log2(e) / T by the relative amount
-// c_rel, which puts c_rel (c (z_p - z_q) - (E_p[c z] - E_q[c z])) into the exponent (the normalisers, summed with the
-// same c, move with it).  For the entries whose ratio is of order one - the only ones whose factor 1 - ratio is
-// sensitive - c (z_p - z_q) is C2 itself up to a few units, i.e. the error is c_rel (log2 nu + H_p - H_q) with the
-// two rows' entropies in bits: a block ratio of 2^-28 (a long block of improbable tokens) shifts every such ratio by
-// 1e-6, and the K-th power of a factor 0.2 by 1e-5.  The log2 nu part is taken out here; the entropies are not known.
-__device__ __forceinline__ double ratio_const(double lse2_p, double lse2_q, double log2nu, double c_rel)
-{
-    return (lse2_p - lse2_q) + log2nu * (1.0 - c_rel);
 }
 
 // 2^x in float64 (0 below x = -1000, infinity above x = 1000) by a degree-12 polynomial on [-1/2, 1/2] and an exponent shift
@@ -196,6 +176,38 @@ __device__ __forceinline__ double exp2_small(double x)
     p = fma(p, f, 1.0);
     p = fma(p, f, 1.0);
     return ldexp(p, static_cast<int>(n));
+}
+
+// The ratio p[x] / (nu q[x]) = 2^(c (z_p - z_q) - C2) with a float64 constant C2 that can be
+// large while the exponent itself is small for the entries that matter.  C2 is split into
+// a float part used inside the exponent and a factor kappa = 2^-(C2 - float(C2)) applied in
+// the following "1 - ratio" (as one fused multiply-add), so the rounding of C2 to float
+// costs neither accuracy nor an instruction.
+struct RatioConst {
+    float C2_hi;
+    float neg_kappa;
+    __device__ __forceinline__ explicit RatioConst(double C2) {
+        C2_hi = static_cast<float>(C2);
+        const double kappa = exp2_small(static_cast<double>(C2_hi) - C2);     // (a non-finite C2 gives 0)
+        neg_kappa = (kappa > 0.5 && kappa < 2.0) ? -static_cast<float>(kappa) : -1.0f;   // non-finite C2
+    }
+    // max(1 - p/(nu q), 0) for logit difference d = z_p - z_q
+    __device__ __forceinline__ float one_minus_ratio(float d, float c) const {
+        const float r = __builtin_amdgcn_exp2f(fmaf(d, c, -C2_hi));
+        return __builtin_amdgcn_fmed3f(fmaf(r, neg_kappa, 1.0f), 0.0f, 1.0f);
+    }
+};
+
+// C2 for the sweeps' ratio p[x] / (nu q[x]) = 2^(c (z_p - z_q) - C2), C2 = log2 Z_p - log2 Z_q + log2 nu, with the part
+// of the rounding of c that a constant can carry.  The float c differs from log2(e) / T by the relative amount
+// c_rel, which puts c_rel (c (z_p - z_q) - (E_p[c z] - E_q[c z])) into the exponent (the normalisers, summed with the
+// same c, move with it).  For the entries whose ratio is of order one - the only ones whose factor 1 - ratio is
+// sensitive - c (z_p - z_q) is C2 itself up to a few units, i.e. the error is c_rel (log2 nu + H_p - H_q) with the
+// two rows' entropies in bits: a block ratio of 2^-28 (a long block of improbable tokens) shifts every such ratio by
+// 1e-6, and the K-th power of a factor 0.2 by 1e-5.  The log2 nu part is taken out here; the entropies are not known.
+__device__ __forceinline__ double ratio_const(double lse2_p, double lse2_q, double log2nu, double c_rel)
+{
+    return (lse2_p - lse2_q) + log2nu * (1.0 - c_rel);
 }
 
 // max(1 - kappa r / tK, 0) for the second ratio of a row under a pending modification: r / tK is
@@ -584,6 +596,26 @@ __device__ __forceinline__ double token_term(double log2q, double log2r, int K)
 {
     const double t = fmax(1.0 - exp2_small(log2r), 0.0);
     return exp2_small(log2q) * powi_uniform(t, K);
+}
+
+// The drafted token's term of a row's Eq. (hik) sum in float64 in place of the sweep's float32 value (see
+// token_term): called by one thread with the sum `total` (relative to 2^shift_q) of the entries [lo, hi) of the
+// row; returns total with the term exchanged if the token (*token) is among them, or total itself where the term
+// needs no second look (decided from the row's statistics: the token is not even fetched then).
+template <typename T>
+__device__ __forceinline__ double with_token_term(double total, const RowStat &st, double log2nu, const T *rq, const T *rp,
+                                                  const int32_t *token, int V, int lo, int hi, float c, float shift_q,
+                                                  const RatioConst &rc, int K)
+{
+    const double log2q = st.tok2_q - st.lse2_q, log2r = (st.tok2_p - st.lse2_p) - log2q - log2nu;
+    if (!(fabs(1.0 - exp2_small(log2r)) < static_cast<double>(kTokenTermBelow))) return total;
+    int tok = *token;
+    tok = tok < 0 ? 0 : (tok >= V ? V - 1 : tok);
+    if (tok < lo || tok >= hi) return total;
+    const float zq[1] = {Elem<T>::scalar(rq + tok)}, zp[1] = {Elem<T>::scalar(rp + tok)};
+    float wq[1], w[1];
+    ot_weights(zq, zp, c, shift_q, rc, K, wq, w);            // the same operations as in the sweep: the same bits
+    return (total - static_cast<double>(w[0])) + token_term(log2q, log2r, K) * exp2_small(st.lse2_q - static_cast<double>(shift_q));
 }
 
 // Integral reference exponent of a group of entries whose largest logit is m (partial sums taken relative to

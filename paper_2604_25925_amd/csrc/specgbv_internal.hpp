@@ -52,6 +52,9 @@ struct Row0Part { double ref; double Z; };     // sum over the slice of 2^(c z -
 constexpr int kSegThreads = 256;               // final-token kernels: 4 waves per workgroup
 constexpr int kSegElems = kWave * 8;           // vocabulary entries per residual segment (one wave)
 
+int compute_units();                           // of the current device
+int wait_polls();                              // looks a workgroup takes at what another one owes before it computes that itself
+
 Workspace make_workspace(int batch, int K, int L, int V);
 
 struct Problem {
@@ -79,6 +82,7 @@ struct Problem {
     bool shared_row0;              // rows 0 of a prefix's drafts are copies of one another (caller's statement)
     int s_parts;                   // > 1: the sums of Eq. (hik) are left as this many partial sums per row (small batches)
     int e_parts;                   // > 0 (chain schedule): rows marked kExcessPending have their E in this many parts
+    int rows_parts;                // > 0: the rows schedule, with this many parts per row
     int e_coop;                    // != 0 (two-pass schedule): the final-token kernel finds the rows that need E and sums it
     int kseq_ndrafts;              // > 0: the comparison verifier (K-SEQ rule of Section 3.2) on the first kseq_ndrafts drafts
 };
@@ -91,6 +95,11 @@ hipError_t launch_kseq_rows(const Problem &p, int ndrafts);
 hipError_t launch_split_main(const Problem &p);
 // Parts the two-pass schedule leaves every Eq. (hik) sum in for this problem (1: the sums are complete).
 int split_sum_parts(const Problem &p);
+
+// Schedule "rows": every row pair (or one of its parts, a power of two of them) in the registers of one workgroup.
+// rows_schedule_parts(): the number of parts, 0 where the schedule does not take the shape.
+int rows_schedule_parts(const Problem &p);
+hipError_t launch_rows_main(const Problem &p);
 
 // Schedule "chain": one workgroup per (prefix, draft) keeps each row pair on chip between
 // the statistics sweep and the Eq. (hik) sweep.  chain_supported() says whether the shape

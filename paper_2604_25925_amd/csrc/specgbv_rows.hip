@@ -1,0 +1,470 @@
+// Schedule "rows": every (target, draft) row pair is read from HBM once, by workgroups that each keep one row pair
+// (or one of its P parts) in registers.
+//
+//   k_rows_begin : marks the parts' normalisers as "not there yet" and clears the final-token kernel's counters
+//   k_rows       : workgroup (prefix, draft, row, part), part fastest:
+//                    1. loads its part of the row pair (every load issued before the first is used)
+//                    2. sweep 1: the part's soft-max statistics, log2 sum_x 2^(c z[x]) of either row, which it leaves in
+//                       the workspace (one 64-bit device-scope store per row: the value says by itself that it is there)
+//                    3. collects the statistics of its draft's rows 0 .. i from the workgroups that own them
+//                    4. sweep 2, from the registers: the part's share of the vocabulary sum of Eq. (hik)
+//                         s_i = sum_x q_i[x] max(1 - p_i[x] / (nu_i q_i[x]), 0)^K
+//
+// What bounds it: the chain schedule walks a draft's rows in one workgroup per compute unit, which is right where a
+// row pair fills the compute unit; shorter rows leave it waiting on the row's own latencies (9.4 us per row of 32000
+// bfloat16 entries, of which 5 us are arithmetic), and a number of drafts that is not a multiple of the compute units
+// leaves some idle for a whole draft.  Here a row is the unit of work, two to four workgroups share a compute unit,
+// and one's loads run beside another's arithmetic.
+//
+// Step 3 waits for workgroups with a lower index only (the same draft's earlier rows) or with the same row (its other
+// parts); workgroups are dispatched in index order, so what is waited for is running or has run.  Nothing relies on
+// it: after `polls` looks a workgroup computes what is missing itself, from memory, by the code of steps 1 and 2 (the
+// same bits).
+//
+// Rows may start at any address and have any length of at least one vector: 16-byte loads need no alignment on this
+// hardware, and a last vector that is not whole is loaded from the row's last 16 bytes with the entries that belong
+// to the vector before it masked.
+#include "specgbv_internal.hpp"
+
+namespace specgbv {
+namespace {
+
+constexpr int kRowsMaxL = 64;                          // rows of a draft (L <= 62)
+constexpr double kRowsRefLimit = 1073741824.0;         // 2^30: largest sum accepted relative to the reference of a wave's first vectors
+
+struct RowsArgs {
+    const int32_t *tokens;
+    unsigned long long *words;     // [n_rows][2][kRowParts] log2-normalisers of the parts (float64 bits; all ones: not there yet)
+    RowStat *stats;
+    double *s_out, *e_out;         // P = 1: the row's sum, and nu^2 (s - g) where it is needed (else -1)
+    double *s_part, *e_part;       // P > 1: the parts' sums; the final-token kernel's parts of E start as "not there yet"
+    int K, L, V, logP, polls;      // P = 1 << logP parts per row
+    float c;
+    double c_rel;
+};
+
+constexpr unsigned long long kNotThere = ~0ull;        // (a NaN that no sum produces)
+
+__global__ void __launch_bounds__(256)
+k_rows_begin(unsigned long long *__restrict__ words, long long nwords, int P, int32_t *__restrict__ final_counter, int batch)
+{
+    const long long step = static_cast<long long>(gridDim.x) * blockDim.x;
+    const long long at = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
+    for (long long i = at; i < nwords; i += step) words[(i / P) * kRowParts + i % P] = kNotThere;
+    for (long long i = at; i < batch; i += step) final_counter[i] = 0;
+}
+
+// What lanes past a part's end load: masked entries, of weight zero in every sum.
+__device__ const float4 g_masked_f32 = {-__builtin_inff(), -__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
+__device__ const uint4 g_masked_bf16 = {0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u};
+template <typename T> __device__ __forceinline__ const T *masked_vector();
+template <> __device__ __forceinline__ const float *masked_vector<float>() { return reinterpret_cast<const float *>(&g_masked_f32); }
+template <> __device__ __forceinline__ const uint16_t *masked_vector<uint16_t>() { return reinterpret_cast<const uint16_t *>(&g_masked_bf16); }
+
+// This thread's vectors of units [lo, lo + n) of a row pair, n <= NS * TH.  Every slot is loaded, without a
+// branch (a load under one is waited for where the branch ends): lanes and slots past the part's end read masked
+// entries, so that the sweeps need not look at the lane, and a row's last vector that is not whole is loaded from the
+// row's last 16 bytes, with the entries that belong to the vector before it masked (Slots::unpack).
+template <typename T, int TH, int NS>
+__device__ __forceinline__ void rows_load(const T *rq, const T *rp, int lo, int n, int V, U4 (&q)[NS], U4 (&p)[NS])
+{
+    constexpr int PV = Elem<T>::kPerVec;
+    const int tid = threadIdx.x;
+    const T *dead = masked_vector<T>();
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        const int v = j * TH + tid;
+        const bool live = v < n;
+        int e = (lo + v) * PV;
+        e = e < V - PV ? e : V - PV;
+        q[j] = load16_stream_any(live ? rq + e : dead);
+        p[j] = load16_stream_any(live ? rp + e : dead);
+    }
+}
+
+// Which of the loaded entries count.
+template <typename T, int TH>
+struct Slots {
+    int n, before;           // vectors of the part; entries of its last vector that belong to the one before (0: it is whole)
+    __device__ __forceinline__ Slots(int lo, int n_, int V)
+    {
+        constexpr int PV = Elem<T>::kPerVec;
+        const int rem = V % PV;
+        n = n_;
+        before = (rem != 0 && lo + n_ == (V + PV - 1) / PV) ? PV - rem : 0;
+    }
+    __device__ __forceinline__ bool used(int j) const { return j * TH < n; }          // uniform
+    template <int N>
+    __device__ __forceinline__ void unpack(const U4 &v, int j, float (&z)[N]) const
+    {
+        Elem<T>::unpack(v, z);
+        if (before > 0) {                                  // uniform
+            asm volatile("");
+            if (j * TH + static_cast<int>(threadIdx.x) == n - 1) {
+#pragma unroll
+                for (int e = 0; e < N; ++e) z[e] = e < before ? -__builtin_inff() : z[e];
+            }
+        }
+    }
+};
+
+template <typename T>
+__device__ __forceinline__ float rows_vec_max(const U4 &v)
+{
+    constexpr int PV = Elem<T>::kPerVec;
+    float z[PV];
+    Elem<T>::unpack(v, z);
+    float m = z[0];
+#pragma unroll
+    for (int j = 1; j < PV; ++j) m = fmaxf(m, z[j]);
+    return m;
+}
+
+// A slot's registers (and a running value) pass through a point in program order: the floats unpacked from a slot are
+// neither formed ahead of time nor kept for the next sweep, which would double the registers the slots take.
+__device__ __forceinline__ void rows_touch(U4 &v, float &acc)
+{
+    asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w), "+v"(acc));
+}
+
+// Sum over this wave's vectors (the drafted token's entry left out) of 2^(c z - ref), ref integral.
+struct WaveSum { float ref; double Z; };
+struct TokenAt { int slot, elem; bool mine; };             // where the drafted token lies: slot (uniform, -1: not here), entry, this lane?
+
+template <typename T, int TH, int NS>
+__device__ __forceinline__ double rows_wave_sum(U4 (&v)[NS], const Slots<T, TH> &sl, float c, float ref, const TokenAt &tk)
+{
+    constexpr int PV = Elem<T>::kPerVec;
+    float Z = 0.0f;
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        if (sl.used(j)) {
+            rows_touch(v[j], Z);
+            float z[PV];
+            sl.unpack(v[j], j, z);
+            if (j == tk.slot) {                            // uniform
+                asm volatile("");
+                leave_out(z, tk.mine, tk.elem);
+            }
+            float a = exp2_fast(fmaf(z[0], c, -ref));
+#pragma unroll
+            for (int e = 1; e < PV; ++e) a += exp2_fast(fmaf(z[e], c, -ref));
+            Z += a;
+        }
+    }
+    return wave_sum(static_cast<double>(Z));
+}
+
+// The same with the largest entry of the wave as reference: taken where the reference of the wave's first vectors is
+// far below an entry of the others (the exponents formed in float32 then lose absolute accuracy, or overflow).
+template <typename T, int TH, int NS>
+__device__ __forceinline__ WaveSum rows_wave_exact(U4 (&v)[NS], const Slots<T, TH> &sl, float c, const TokenAt &tk)
+{
+    float m = -3.0e38f;
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        rows_touch(v[j], m);
+        m = fmaxf(m, rows_vec_max<T>(v[j]));               // (a vector read twice changes no maximum)
+    }
+    WaveSum s;
+    s.ref = integral_reference(wave_max(m), c);
+    s.Z = rows_wave_sum<T, TH, NS>(v, sl, c, s.ref, tk);
+    return s;
+}
+
+// log2 of a positive finite double: a float logarithm and one Newton step on 2^y = m (error about 1e-14).
+__device__ __forceinline__ double rows_log2(double z)
+{
+    int e;
+    const double m = frexp(z, &e);
+    const double y0 = static_cast<double>(__log2f(static_cast<float>(m)));
+    return static_cast<double>(e) + (y0 + (m * exp2_small(-y0) - 1.0) * 1.44269504088896340736);
+}
+
+// E = nu^2 (s - g) of a whole row pair, from memory (rare rows; see excess_needed), by the whole workgroup.
+template <typename T, int TH>
+__device__ __forceinline__ double rows_excess(const T *rq, const T *rp, int V, double lse2_q, double lse2_p, double log2nu, int K,
+                                           float c, double *sh_d)
+{
+    constexpr int PV = Elem<T>::kPerVec;
+    constexpr int kAhead = 2;
+    const ExcessConst ec = make_excess_const(lse2_q, lse2_p, log2nu, K, c);
+    const int nv = (V + PV - 1) / PV, rem = V % PV;
+    float acc = 0.0f;
+    for (int v0 = threadIdx.x; v0 < nv; v0 += kAhead * TH) {
+        U4 q[kAhead], p[kAhead];
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) {
+            const int v = v0 + a * TH;
+            int e = (v < nv ? v : v0) * PV;
+            e = e < V - PV ? e : V - PV;
+            q[a] = load16_stream_any(rq + e);
+            p[a] = load16_stream_any(rp + e);
+        }
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) {
+            const int v = v0 + a * TH;
+            float zq[PV], zp[PV];
+            Elem<T>::unpack(q[a], zq);
+            Elem<T>::unpack(p[a], zp);
+            if (rem != 0 && v == nv - 1) {
+#pragma unroll
+                for (int e = 0; e < PV; ++e)
+                    if (e < PV - rem) { zq[e] = -__builtin_inff(); zp[e] = -__builtin_inff(); }
+            }
+            if (v < nv) acc += excess_terms(zq, zp, ec);
+        }
+    }
+    return block_sum(static_cast<double>(acc), sh_d) * ec.scale;
+}
+
+template <typename T, int TH, int NS>
+__global__ void __launch_bounds__(TH, NS >= 4 ? 4 : 6)
+k_rows(const T *__restrict__ target, const T *__restrict__ draft, RowsArgs ar)
+{
+    constexpr int kRowsWaves = TH / kWave;
+    __shared__ double sh_word[2 * kRowsMaxL * kRowParts];  // the parts' log2-normalisers of rows 0 .. i
+    __shared__ double sh_lse[2 * kRowsMaxL], sh_tok[2 * kRowsMaxL];
+    __shared__ double sh_Z[2 * kRowsWaves], sh_own[2];
+    __shared__ float sh_ref[2 * kRowsWaves];
+    __shared__ int sh_missing, sh_again;
+    constexpr int PV = Elem<T>::kPerVec;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+    const int K = ar.K, L = ar.L, V = ar.V, logP = ar.logP, P = 1 << logP;
+    const float c = ar.c;
+    const unsigned pair_u = blockIdx.x >> logP;
+    const int part = static_cast<int>(blockIdx.x & (P - 1));
+    const long long pair = pair_u, bk = pair_u / static_cast<unsigned>(L);
+    const int i = static_cast<int>(pair - bk * L);
+    const int nv = (V + PV - 1) / PV, per = (nv + P - 1) >> logP;
+    if (tid == 0) sh_missing = 0x7fffffff;
+
+    // the drafted tokens of rows 0 .. i: thread 2 j + m looks after row j of the target (m = 0) or the draft (1)
+    const int nstat = 2 * (i + 1);
+    // (threads beyond them repeat the last row's: a load under a branch is waited for where the branch ends)
+    const int jt = (tid >> 1) < i ? (tid >> 1) : i, mt = tid & 1;
+    uint32_t ztok = 0;
+    U4 q[NS], p[NS];
+    int r_now = i, part_now = part;                        // whose vectors q, p hold (uniform)
+    unsigned long long *const words = ar.words + bk * L * (2 * kRowParts);
+    const int nwords = nstat * P;                          // word w: row w / (2 P), model w / P % 2, part w % P
+    auto word_at = [&](int w) { return words + (w >> logP) * kRowParts + (w & (P - 1)); };
+    for (bool first = true;; first = false) {
+        const T *rq = target + (bk * (L + 1) + r_now) * static_cast<long long>(V);
+        const T *rp = draft + (bk * L + r_now) * static_cast<long long>(V);
+        const int lo = part_now * per, hi = lo + per < nv ? lo + per : nv, n = hi > lo ? hi - lo : 0;
+        const int tok_raw = token_index_queued(ar.tokens, bk * L + r_now), tok_t = ar.tokens[bk * L + jt];
+        rows_load<T, TH, NS>(rq, rp, lo, n, V, q, p);
+        {                                                  // (behind the row's loads, needed after sweep 1 only)
+            const int x = token_index_used(tok_t, V);
+            ztok = Elem<T>::bits(mt ? draft + (bk * L + jt) * static_cast<long long>(V) + x
+                                    : target + (bk * (L + 1) + jt) * static_cast<long long>(V) + x);
+        }
+        const Slots<T, TH> sl(lo, n, V);
+        const int tok = token_index_used(tok_raw, V), tok_v = tok / PV - lo;   // the token's vector, counted from the part's first
+        const bool tok_here = tok_v >= 0 && tok_v < n;
+        TokenAt tk;
+        tk.slot = __builtin_amdgcn_readfirstlane(tok_here ? tok_v / TH : -1);
+        tk.mine = tok_here && tid == tok_v % TH;
+        tk.elem = tok - (tok / PV * PV < V - PV ? tok / PV * PV : V - PV);     // counted from where that vector was loaded
+        // sweep 1
+        WaveSum sq, sp;
+        sq.ref = integral_reference(wave_max(rows_vec_max<T>(q[0])), c);
+        sp.ref = integral_reference(wave_max(rows_vec_max<T>(p[0])), c);
+        sq.Z = rows_wave_sum<T, TH, NS>(q, sl, c, sq.ref, tk);
+        sp.Z = rows_wave_sum<T, TH, NS>(p, sl, c, sp.ref, tk);
+        if (!(sq.Z < kRowsRefLimit)) sq = rows_wave_exact<T, TH, NS>(q, sl, c, tk);
+        if (!(sp.Z < kRowsRefLimit)) sp = rows_wave_exact<T, TH, NS>(p, sl, c, tk);
+        if (lane == 0) {
+            sh_ref[wid] = sq.ref; sh_ref[kRowsWaves + wid] = sp.ref;
+            sh_Z[wid] = sq.Z; sh_Z[kRowsWaves + wid] = sp.Z;
+        }
+        __syncthreads();
+        if (tid < 2) {                                     // thread m: the waves' sums and, where it lies here, the token's weight
+            float M = -3.0e38f;
+#pragma unroll
+            for (int w = 0; w < kRowsWaves; ++w) M = fmaxf(M, sh_Z[tid * kRowsWaves + w] > 0.0 ? sh_ref[tid * kRowsWaves + w] : -3.0e38f);
+            double Z = 0.0;
+#pragma unroll
+            for (int w = 0; w < kRowsWaves; ++w)
+                Z += ldexp(sh_Z[tid * kRowsWaves + w], reference_shift(sh_ref[tid * kRowsWaves + w], M));
+            double ref = static_cast<double>(M);
+            if (tok_here) {
+                const double t = static_cast<double>(Elem<T>::scalar((tid ? rp : rq) + tok)) * static_cast<double>(c);
+                const double top = Z > 0.0 ? fmax(ref, t) : t;
+                Z = (Z > 0.0 ? Z * exp2_small(ref - top) : 0.0) + (t - top == 0.0 ? 1.0 : exp2_small(t - top));
+                ref = top;
+            }
+            const double l = (Z > 0.0 && ref > -1.0e300) ? ref + rows_log2(Z) : -static_cast<double>(__builtin_inff());
+            sh_own[tid] = l;
+            if (first)
+                __hip_atomic_store(words + (2 * r_now + tid) * kRowParts + part_now, static_cast<unsigned long long>(__double_as_longlong(l)),
+                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (first && i == 0 && L > 1) return;              // row 0 has no sum; the workgroup of row 1 stores its statistics
+        __syncthreads();
+        // collect (first pass), or put what this pass has computed in its place; then look for what is still missing
+        for (int w = tid; w < nwords; w += TH) {
+            const int m = (w >> logP) & 1;
+            unsigned long long bits;
+            if ((w >> (logP + 1)) == r_now && (w & (P - 1)) == part_now) bits = static_cast<unsigned long long>(__double_as_longlong(sh_own[m]));
+            else if (first) {
+                bits = kNotThere;
+                for (int look = 0; look < ar.polls && bits == kNotThere; ++look) {
+                    bits = __hip_atomic_load(word_at(w), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if (bits == kNotThere) __builtin_amdgcn_s_sleep(2);
+                }
+            } else bits = static_cast<unsigned long long>(__double_as_longlong(sh_word[w]));
+            sh_word[w] = __longlong_as_double(static_cast<long long>(bits));
+            if (bits == kNotThere) atomicMin(&sh_missing, w);
+        }
+        __syncthreads();
+        const int miss = __builtin_amdgcn_readfirstlane(sh_missing);
+        __syncthreads();
+        if (tid == 0) sh_missing = 0x7fffffff;
+        if (miss == 0x7fffffff) break;
+        r_now = miss >> (logP + 1); part_now = miss & (P - 1);       // computed here, both models of it, in the next pass
+    }
+    const T *rq = target + (bk * (L + 1) + i) * static_cast<long long>(V);
+    const T *rp = draft + pair * static_cast<long long>(V);
+    const int lo = part * per, hi = lo + per < nv ? lo + per : nv, n = hi > lo ? hi - lo : 0;
+    if (r_now != i || part_now != part) {                  // (uniform) the registers hold another row's part: this one's again
+        rows_load<T, TH, NS>(rq, rp, lo, n, V, q, p);
+    }
+    // the parts of each normaliser meet (groups of P lanes, P a power of two: the same bits in every workgroup)
+    for (int w0 = 0; w0 < nwords; w0 += TH) {    // uniform
+        const int w = w0 + tid;
+        const double l = w < nwords ? sh_word[w] : -static_cast<double>(__builtin_inff());
+        double top = l;
+        for (int o = 1; o < P; o <<= 1) top = fmax(top, __shfl_xor(top, o));
+        double lse = l;
+        if (P > 1) {
+            double Z = l > -1.0e300 ? exp2_small(l - top) : 0.0;
+            for (int o = 1; o < P; o <<= 1) Z += __shfl_xor(Z, o);
+            lse = top > -1.0e300 ? top + rows_log2(Z) : top;
+        }
+        if (w < nwords && (w & (P - 1)) == 0) sh_lse[w >> logP] = lse;
+    }
+    __syncthreads();
+    if (tid < nstat) sh_tok[tid] = token_scaled(static_cast<double>(Elem<T>::from_bits(ztok)) * static_cast<double>(c), sh_lse[tid], ar.c_rel);
+    __syncthreads();
+    RowStat st;
+    st.lse2_q = sh_lse[2 * i]; st.lse2_p = sh_lse[2 * i + 1];
+    st.tok2_q = sh_tok[2 * i]; st.tok2_p = sh_tok[2 * i + 1];
+    if (part == 0 && tid == 0) {
+        ar.stats[pair] = st;
+        if (i == 1) {
+            RowStat s0;
+            s0.lse2_q = sh_lse[0]; s0.lse2_p = sh_lse[1]; s0.tok2_q = sh_tok[0]; s0.tok2_p = sh_tok[1];
+            ar.stats[bk * L] = s0;
+        }
+    }
+    if (i == 0) return;                                    // (L = 1)
+    double log2nu = 0.0, log2P = 0.0;
+    for (int j = 0; j < i; ++j) {
+        const double lp = sh_tok[2 * j + 1] - sh_lse[2 * j + 1];
+        log2nu += (sh_tok[2 * j] - sh_lse[2 * j]) - lp;
+        log2P += lp;
+    }
+    // sweep 2
+    const float shift_q = static_cast<float>(st.lse2_q);
+    const RatioConst rc(ratio_const(st.lse2_p, st.lse2_q, log2nu, ar.c_rel));
+    const Slots<T, TH> sl(lo, n, V);
+    float acc = 0.0f;
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        if (sl.used(j)) {
+            rows_touch(q[j], acc);
+            rows_touch(p[j], acc);
+            float zq[PV], zp[PV], wq[PV], w[PV], a = 0.0f;
+            sl.unpack(q[j], j, zq);
+            sl.unpack(p[j], j, zp);
+            ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
+#pragma unroll
+            for (int e = 0; e < PV; ++e) a += w[e];
+            acc += a;
+        }
+    }
+    double total = block_sum(static_cast<double>(acc), sh_Z);
+    if (tid == 0) {
+        total = with_token_term<T>(total, st, log2nu, rq, rp, ar.tokens + pair, V, lo * PV, hi * PV < V ? hi * PV : V, c, shift_q, rc, K);
+        const double s = total * exp2_small(static_cast<double>(shift_q) - st.lse2_q);
+        if (P > 1) {
+            ar.s_part[pair * kPendParts + part] = s;
+        } else {
+            ar.s_out[pair] = s;
+            // where s and g nearly cancel, Eq. (hik) needs nu^2 (s - g) summed term by term (see excess_wanted)
+            const bool again = excess_wanted(static_cast<float>(log2nu), static_cast<float>(s), K) && excess_needed(log2nu, log2P, s, K);
+            sh_again = again ? 1 : 0;
+            if (!again) ar.e_out[pair] = -1.0;
+        }
+    }
+    if (P > 1) {                                           // only the sum over all parts can tell: the final-token kernel looks at it
+        if (part == 0 && tid < kPendParts) ar.e_part[pair * kPendParts + tid] = -1.0;
+        return;
+    }
+    __syncthreads();
+    if (sh_again) {                                        // uniform
+        const double e = rows_excess<T, TH>(rq, rp, V, st.lse2_q, st.lse2_p, log2nu, K, c, sh_Z);
+        if (tid == 0) ar.e_out[pair] = e;
+    }
+}
+
+template <typename T>
+hipError_t launch_rows_typed(const Problem &p)
+{
+    constexpr int PV = Elem<T>::kPerVec;
+    const long long pairs = static_cast<long long>(p.batch) * p.K * p.L;
+    const int P = p.rows_parts;
+    RowsArgs ar;
+    ar.tokens = p.tokens;
+    ar.words = reinterpret_cast<unsigned long long *>(p.ws + p.lay.stat_part);
+    ar.stats = reinterpret_cast<RowStat *>(p.ws + p.lay.stats);
+    ar.s_out = reinterpret_cast<double *>(p.ws + p.lay.s);
+    ar.e_out = reinterpret_cast<double *>(p.ws + p.lay.excess);
+    ar.s_part = reinterpret_cast<double *>(p.ws + p.lay.pend_part);
+    ar.e_part = reinterpret_cast<double *>(p.ws + p.lay.excess_part);
+    ar.K = p.K; ar.L = p.L; ar.V = p.V; ar.logP = __builtin_ctz(static_cast<unsigned>(P)); ar.polls = wait_polls();
+    ar.c = p.c; ar.c_rel = p.c_rel;
+    const long long nwords = pairs * 2 * P;
+    const long long want = (nwords + 255) / 256;
+    hipLaunchKernelGGL(k_rows_begin, dim3(static_cast<unsigned>(want < 1024 ? want : 1024)), dim3(256), 0, p.stream, ar.words,
+                       nwords, P, reinterpret_cast<int32_t *>(p.ws + p.lay.counter), p.batch);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const T *target = static_cast<const T *>(p.target), *draft = static_cast<const T *>(p.draft);
+    const int nv = (p.V + PV - 1) / PV, per = (nv + P - 1) / P;
+    const dim3 grid(static_cast<unsigned>(pairs * P));
+#define SPECGBV_ROWS_LAUNCH(TH, NS) hipLaunchKernelGGL((k_rows<T, TH, NS>), grid, dim3(TH), 0, p.stream, target, draft, ar)
+    if (per <= 1024) SPECGBV_ROWS_LAUNCH(512, 2);
+    else if (per <= 2048) SPECGBV_ROWS_LAUNCH(256, 8);
+    else SPECGBV_ROWS_LAUNCH(512, 8);
+#undef SPECGBV_ROWS_LAUNCH
+    return hipGetLastError();
+}
+
+}  // namespace
+
+int rows_schedule_parts(const Problem &p)
+{
+    const int pv = p.dtype == 1 ? 8 : 4;
+    const long long pairs = static_cast<long long>(p.batch) * p.K * p.L;
+    if (p.V < pv || p.L >= kRowsMaxL) return 0;
+    const int nv = (p.V + pv - 1) / pv;
+    // a handful of rows shorter than one load per thread: the two-pass kernels, which need no marks to wait on (V = 1000,
+    // 8 float32 row pairs: 19.0 us a call against 20.0; from 200 row pairs on, or with longer rows, this schedule is ahead)
+    if (nv < 512 && pairs * 2 <= compute_units()) return 0;
+    static_assert((kRowParts & (kRowParts - 1)) == 0, "a power of two");
+    int P = 1;
+    while (P < kRowParts && (nv + P - 1) / P > 4096) P *= 2;
+    if ((nv + P - 1) / P > 4096) return 0;
+    while (P < kRowParts && pairs * P * 2 <= 2LL * compute_units() && nv / (P * 2) >= 512) P *= 2;
+    return pairs * P < (1LL << 31) ? P : 0;
+}
+
+hipError_t launch_rows_main(const Problem &p)
+{
+    return p.dtype == 1 ? launch_rows_typed<uint16_t>(p) : launch_rows_typed<float>(p);
+}
+
+}  // namespace specgbv

@@ -207,26 +207,6 @@ __device__ __forceinline__ double lse2_from_parts(const Row0Part *pp, int P)
     return ref + log2(Z);
 }
 
-// The drafted token's term of a row's Eq. (hik) sum in float64 in place of the sweep's float32 value (see
-// token_term): called by one thread with the sum `total` (relative to 2^shift_q) of the entries [lo, hi) of the
-// row; returns total with the term exchanged if the token (*token) is among them, or total itself where the term
-// needs no second look (decided from the row's statistics: the token is not even fetched then).
-template <typename T>
-__device__ __forceinline__ double with_token_term(double total, const RowStat &st, double log2nu, const T *rq, const T *rp,
-                                                  const int32_t *token, int V, int lo, int hi, float c, float shift_q,
-                                                  const RatioConst &rc, int K)
-{
-    const double log2q = st.tok2_q - st.lse2_q, log2r = (st.tok2_p - st.lse2_p) - log2q - log2nu;
-    if (!(fabs(1.0 - exp2_small(log2r)) < static_cast<double>(kTokenTermBelow))) return total;
-    int tok = *token;
-    tok = tok < 0 ? 0 : (tok >= V ? V - 1 : tok);
-    if (tok < lo || tok >= hi) return total;
-    const float zq[1] = {Elem<T>::scalar(rq + tok)}, zp[1] = {Elem<T>::scalar(rp + tok)};
-    float wq[1], w[1];
-    ot_weights(zq, zp, c, shift_q, rc, K, wq, w);            // the same operations as in the sweep: the same bits
-    return (total - static_cast<double>(w[0])) + token_term(log2q, log2r, K) * exp2_small(st.lse2_q - static_cast<double>(shift_q));
-}
-
 // grid rows * P, rows = batch * K * (L - 1): block row * P + part sums part `part` of the Eq. (hik) terms of row
 // pair i = 1 .. L-1 of a draft (PEND: against the row as the pending levels leave it, exactly as k_ot_sum does).
 // With stat_P > 1 the statistics of the draft's rows 0 .. i are still in parts
@@ -504,18 +484,6 @@ k_ot_sum(const T *__restrict__ target, const T *__restrict__ draft, const int32_
     const double e_val = -1.0;
     if (threadIdx.x < kPendParts) e_part[(bk * L + i) * kPendParts + threadIdx.x] = -1.0;
     if (threadIdx.x == 0) { s_out[bk * L + i] = s_val; e_out[bk * L + i] = e_val; }
-}
-
-int compute_units()
-{
-    static int cached[64] = {};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    if (cached[dev] == 0) {
-        int n = 0;
-        cached[dev] = (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && n > 0) ? n : 256;
-    }
-    return cached[dev];
 }
 
 // Parts a row is cut into so that about four workgroups per compute unit are launched (1: one workgroup per row).

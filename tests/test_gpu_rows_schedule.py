@@ -1,0 +1,72 @@
+"""The row-at-a-time schedule (the default where there are too few drafts for a workgroup each) at the sizes where its
+tiles end (needs an MI355X: run with -m gpu).
+
+The default takes the row schedule here: rows of at least one vector, too short or too few for the chain kernel, more
+than half as many row pairs as compute units or rows of 512 vectors and more.
+"""
+import numpy as np
+import pytest
+
+import test_gpu_peaked_rows as peaked
+from parity_util import check_case
+from specgbv_synth import Workload, make_inputs
+
+pytestmark = pytest.mark.gpu
+
+
+def _inputs(B, K, L, V, dtype, T=0.8, seed=5, sigma=2.5):
+    return make_inputs(Workload("rows", B, K, L, V, dtype, sigma, 0.9, head=min(20, V // 4), temperature=T), seed=seed)
+
+
+@pytest.mark.parametrize("B,K,L,V,dtype", [
+    # rows of one and two vectors, every remainder, more than half as many rows as compute units
+    (11, 3, 4, 8, "bf16"), (11, 3, 4, 9, "bf16"), (11, 3, 4, 15, "bf16"), (17, 4, 2, 4, "f32"), (17, 4, 2, 7, "f32"),
+    # the edges of the three tiles (1024, 2048 and 4096 vectors) and of the parts, with and without a remainder
+    (5, 4, 8, 8192, "bf16"), (5, 4, 8, 8193, "bf16"), (5, 4, 8, 16384, "bf16"), (5, 4, 8, 16391, "bf16"),
+    (9, 4, 8, 32767, "bf16"), (9, 4, 8, 32768, "bf16"), (9, 4, 8, 32769, "bf16"), (9, 4, 8, 16387, "f32"),
+    # few rows: up to sixteen parts; parts that end in the middle of a slot; long rows in eight and sixteen parts
+    (1, 1, 2, 4096, "bf16"), (1, 3, 3, 65543, "bf16"), (1, 2, 4, 300007, "bf16"), (2, 1, 2, 262145, "f32"),
+    # a single row per draft (no Eq. (hik) sum at all), and the longest drafts
+    (140, 1, 1, 1003, "bf16"), (1, 3, 62, 2051, "f32"),
+])
+def test_rows_at_the_edges_of_tiles_and_parts(B, K, L, V, dtype):
+    t, d, tok = _inputs(B, K, L, V, dtype)
+    check_case(t, d, tok, 0.8, 3, 1, "auto", "rows %s" % ((B, K, L, V, dtype),))
+
+
+@pytest.mark.parametrize("V,dtype", [(20003, "bf16"), (10002, "f32"), (70001, "bf16")])
+def test_first_entries_masked_or_far_below_the_rest(V, dtype):
+    """The reference exponent of a wave comes from its first vectors: here those are masked in one draft's rows and lie
+    a hundred base-2 units and more below the others in the next one's."""
+    t, d, tok = _inputs(4, 4, 5, V, "f32", T=0.3)
+    n = V // 3
+    tok = np.maximum(tok, n + 1).astype(np.int32) % V
+    t[:, 1, :, :n], d[:, 1, :, :n] = -np.inf, -np.inf
+    t[:, 2, :, :n] -= 40.0
+    d[:, 2, :, :n] -= 35.0
+    t[:, 3, :, ::2] = -np.inf
+    tok[:, 3] |= 1
+    t[:, :, :, V - 1], d[:, :, :, V - 1] = 1.0, 0.5
+    tok = np.minimum(tok, V - 1)
+    if dtype == "bf16":
+        from specgbv_synth import f32_to_bf16_bits
+        t, d = f32_to_bf16_bits(t), f32_to_bf16_bits(d)
+    check_case(t, d, tok, 0.3, 9, 2, "auto", "masked rows V=%d %s" % (V, dtype))
+
+
+@pytest.mark.parametrize("B,K,L,V,dtype", [(9, 4, 8, 9001, "bf16"), (1, 2, 6, 65543, "bf16")])
+def test_bounded_wait_falls_back_to_the_waiting_workgroups_own_statistics(B, K, L, V, dtype, monkeypatch):
+    """With no look at all at what the other workgroups leave, every workgroup computes the statistics of its draft's
+    earlier rows (and of its row's other parts) itself; the results have the same bits."""
+    from parity_util import run_gpu
+    t, d, tok = _inputs(B, K, L, V, dtype)
+    _, waited, _ = check_case(t, d, tok, 0.8, 3, 1, "auto", "rows, waiting")
+    monkeypatch.setenv("SPECGBV_EXCESS_POLLS", "0")
+    alone = run_gpu(t, d, tok, 0.8, 3, 1, "auto")
+    for key in waited:
+        assert np.array_equal(waited[key], alone[key], equal_nan=True), key
+
+
+@pytest.mark.parametrize("V,dtype,B,K,L", [(9001, "bf16", 20, 2, 5), (16387, "f32", 12, 3, 4), (131077, "bf16", 2, 2, 4)])
+def test_rows_that_need_the_cancellation_free_sum(V, dtype, B, K, L):
+    peaked.test_block_ratio_runs_away("auto", dtype, V, B, K, L)
