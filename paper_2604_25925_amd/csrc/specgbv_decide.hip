@@ -1,7 +1,7 @@
 // Decision scan of Algorithm 1 and the final-token draw, in one kernel.
 //
 // k_final runs on a grid of (segment groups, prefixes); a workgroup has four waves and each
-// wave owns four consecutive 512-entry vocabulary segments of the row the final token is drawn from.
+// wave owns some consecutive 512-entry vocabulary segments of the row the final token is drawn from.
 //   1. decision  : every workgroup of a prefix rebuilds the prefix's decision (it is a few
 //                  microseconds of scalar work and saves a kernel boundary): nu_i, P_i, the
 //                  acceptance table (Eq. (hik) for i < L, Eq. (hLk) for i = L, both divided
@@ -15,15 +15,22 @@
 //   3. locate    : the workgroup that finishes last for its prefix (a counter in the
 //                  workspace, zeroed by the streaming kernel that runs before) does the
 //                  inverse-CDF search: the first token id whose running weight exceeds
-//                  u * total (segment by a workgroup-wide scan of the partial sums, entry by
-//                  a wave scan inside that segment).
+//                  u * total (one wave: segment by a scan of the partial sums, entry by
+//                  a scan inside that segment).
+//
+// What bounds it: one chain of latencies (statistics, table, decision, row, counter, partial sums, segment), 11 - 20 us
+// whatever the bytes.  So the uniforms are drawn while the statistics travel, common prefixes are counted beside the
+// table by waves it leaves idle, a wave's loads all leave before the first is unpacked (behind a branch each they were
+// waited for one by one), and the search runs in one wave without a barrier.  Before / after, us in this kernel:
+// V = 1000, one prefix 11.4 / 9.5; V = 128256, one prefix 17.7 / 12.2; 32 prefixes 23.4 / 19.2; rows at odd addresses
+// (entry by entry before) 41 prefixes of V = 32003 74 / 18.
 #include "specgbv_internal.hpp"
 
 namespace specgbv {
 namespace {
 
 constexpr int kDecideThreads = 256;
-constexpr int kSegPerWave = 4;               // residual segments per wave of the final-token kernel
+constexpr int kSegAtOnce = 4;                // residual segments whose loads a wave of the final-token kernel keeps in flight
 
 // ---------------------------------------------------------------- k_decide
 
@@ -137,7 +144,8 @@ __device__ __forceinline__ void decide_prefix(const DecideIO &io, int b, int K, 
     double *ex = lds + 5 * KL;                              // [K*L] nu^2 (s - g) where it was summed without cancellation, else < 0
     unsigned long long *acc_bits = reinterpret_cast<unsigned long long *>(lds + 6 * KL);   // [K] bit i: eta_{k,i} < h_{k,i}
     int *tok = reinterpret_cast<int *>(acc_bits + K);       // [K*L]
-    unsigned char *cpl = reinterpret_cast<unsigned char *>(tok + KL);   // [K*K] common prefix lengths (at most L <= 62)
+    float *et = reinterpret_cast<float *>(tok + KL);        // [K*L + 1] the uniforms (24 bits: exact in float32)
+    unsigned char *cpl = reinterpret_cast<unsigned char *>(et + KL + 1);   // [K*K] common prefix lengths (at most L <= 62)
     const int tid = threadIdx.x;
     const long long base = static_cast<long long>(b) * KL;
     constexpr double kLn2 = 0.693147180559945309417;
@@ -145,11 +153,13 @@ __device__ __forceinline__ void decide_prefix(const DecideIO &io, int b, int K, 
     for (int idx = tid; idx < K; idx += kDecideThreads) acc_bits[idx] = 0ull;
     for (int idx = tid; idx < KL; idx += kDecideThreads) {
         const RowStat st = stats[base + idx];
+        const int tok_raw = tokens[base + idx];
+        et[idx] = static_cast<float>(philox_uniform(seed, offset, static_cast<uint32_t>(b), static_cast<uint32_t>(idx)));   // while the loads travel
         tq[idx] = st.tok2_q - st.lse2_q;
         if (io.pend) tq[idx] += pend_token_adjust(io.pend, io.n_rows, io.nlev, base + idx);   // log2 q'[token]
         tp[idx] = st.tok2_p - st.lse2_p;
         lq[idx] = st.lse2_q; lp[idx] = st.lse2_p;
-        tok[idx] = tokens[base + idx];
+        tok[idx] = tok_raw;
         // the Eq. (hik) sum this thread needs for entry idx of the table below, loaded alongside the statistics
         // (one memory latency instead of two); parked where the entry's log2 nu goes afterwards
         const int k = idx / L, i = idx % L + 1;
@@ -170,14 +180,22 @@ __device__ __forceinline__ void decide_prefix(const DecideIO &io, int b, int K, 
         l2nu[idx] = s;
         ex[idx] = e;
     }
+    if (tid == kDecideThreads - 1)
+        *u_final_out = philox_uniform(seed, offset, static_cast<uint32_t>(b), static_cast<uint32_t>(KL));
     __syncthreads();
+    // common prefixes of the drafts, by the threads that have least to do with the table (the last first)
+    for (int idx = kDecideThreads - 1 - tid; idx < K * K; idx += kDecideThreads) {
+        const int k1 = idx / K, k2 = idx % K;
+        int n = 0;
+        while (n < L && tok[k1 * L + n] == tok[k2 * L + n]) ++n;
+        cpl[idx] = static_cast<unsigned char>(n);
+    }
     // One entry of the acceptance table.  With may_mark (two-pass schedule, first visit): a row whose s and g cancel
     // so far that h needs E = nu^2 (s - g) summed term by term (the kernels' two tests; rows under pending
     // modifications keep the plain sum) is marked instead and true is returned; its entry is made after the
     // workgroups of the prefix have summed E together.
     auto table_entry = [&](int idx, bool may_mark) -> bool {
-        const double e = philox_uniform(seed, offset, static_cast<uint32_t>(b), static_cast<uint32_t>(idx));
-        if (idx == KL) { *u_final_out = e; return false; }
+        const double e = static_cast<double>(et[idx]);
         const int k = idx / L, i = idx % L + 1;
         const double s = l2nu[idx];                         // parked by this thread above
         double log2nu = 0.0, log2P = 0.0;
@@ -233,26 +251,21 @@ __device__ __forceinline__ void decide_prefix(const DecideIO &io, int b, int K, 
         }
         return false;
     };
+    const bool e_coop = io.e_coop != 0;
     unsigned marked = 0u;                                   // bit n: the entry of this thread's n-th visit was marked
     {
         int n = 0;
-        for (int idx = tid; idx <= KL; idx += kDecideThreads, ++n)
-            if (table_entry(idx, io.e_coop != 0)) marked |= 1u << n;
+        for (int idx = tid; idx < KL; idx += kDecideThreads, ++n)
+            if (table_entry(idx, e_coop)) marked |= 1u << n;
     }
-    if (io.e_coop) {                                        // (uniform)
+    if (e_coop) {                                           // (uniform)
         static_assert((kMaxDrafts * 64 + kDecideThreads) / kDecideThreads <= 32, "one bit per visit (K <= 64, L < 64)");
         if (__syncthreads_or(marked != 0u)) {
             excess_sums(tq, tp, lq, lp, ex);
             int n = 0;
-            for (int idx = tid; idx <= KL; idx += kDecideThreads, ++n)
+            for (int idx = tid; idx < KL; idx += kDecideThreads, ++n)
                 if (marked >> n & 1u) table_entry(idx, false);
         }
-    }
-    for (int idx = tid; idx < K * K; idx += kDecideThreads) {
-        const int k1 = idx / K, k2 = idx % K;
-        int n = 0;
-        while (n < L && tok[k1 * L + n] == tok[k2 * L + n]) ++n;
-        cpl[idx] = static_cast<unsigned char>(n);
     }
     __syncthreads();
     if (tid < kWave) {
@@ -272,11 +285,18 @@ __device__ __forceinline__ void decide_prefix(const DecideIO &io, int b, int K, 
     // longest accepted one becomes tau; the failed ones join H; a full-length acceptance ends
     // the scan.
     const unsigned long long upto_L = (2ull << L) - 1ull;                      // bits 0..L
+    int cpl_next = 0;                                      // (read one draft ahead)
+    unsigned long long acc_next = acc_bits[0];
     for (int k = 0; k < K && !done; ++k) {
-        const int my_cpl = (lane < k) ? cpl[k * K + lane] : 0;
+        const int my_cpl = cpl_next;
+        const unsigned long long acc_raw = acc_next;
+        if (k + 1 < K) {
+            cpl_next = lane <= k ? cpl[(k + 1) * K + lane] : 0;
+            acc_next = acc_bits[k + 1];
+        }
         const unsigned long long in_H =
             wave_or64((lane < k) ? (rejected & ((2ull << my_cpl) - 1ull)) : 0ull);   // lengths <= common prefix
-        const unsigned long long acc_k = uniform_u64(acc_bits[k]);
+        const unsigned long long acc_k = uniform_u64(acc_raw);
         const unsigned long long range = upto_L & ~((2ull << tau) - 1ull);      // lengths tau+1 .. L
         const unsigned long long tested = range & ~in_H, skipped = range & in_H;
         const unsigned long long won = tested & acc_k;
@@ -462,38 +482,64 @@ __device__ __forceinline__ void decide_kseq(const T *target, const T *draft, con
 
 // ------------------------------------------------------------ final token
 
-// The 8 logits [e0, e0+8) of a row; entries at or beyond V read as -inf.
-template <typename T, bool VEC>
-__device__ __forceinline__ void load8(const T *row, long long e0, int V, float (&z)[8])
+// A lane's 8 entries of a segment of one row, as loaded (16-byte loads at any address; nothing is unpacked before it is
+// needed, so that the loads of several segments and of both rows travel together).
+template <typename T> struct SegVec { U4 v[8 / Elem<T>::kPerVec]; };
+
+// Entries [e0, e0 + 8) of a row of V; a lane beyond the row's end reads its first entries instead (seg_unpack masks
+// them), and only the one lane that straddles the end goes entry by entry, later.
+template <typename T>
+__device__ __forceinline__ SegVec<T> seg_load(const T *row, long long e0, int V)
 {
     constexpr int PV = Elem<T>::kPerVec;
-    if (VEC && e0 + 8 <= V) {
+    SegVec<T> r;
+    if (V < 8) {                                            // uniform
 #pragma unroll
-        for (int v = 0; v < 8 / PV; ++v) {
-            float t[PV];
-            Elem<T>::unpack(load16(row + e0 + v * PV), t);
+        for (int i = 0; i < 8 / PV; ++i) r.v[i] = U4{0, 0, 0, 0};
+        return r;
+    }
+    const long long at = e0 + 8 <= V ? e0 : 0;
 #pragma unroll
-            for (int j = 0; j < PV; ++j) z[v * PV + j] = t[j];
-        }
-    } else {
+    for (int i = 0; i < 8 / PV; ++i) r.v[i] = load16_any(row + at + i * PV);
+    return r;
+}
+
+// The entries as floats; those at or beyond V are `fill`.
+template <typename T>
+__device__ __forceinline__ void seg_unpack(const SegVec<T> &r, const T *row, long long e0, int V, float fill, float (&z)[8])
+{
+    constexpr int PV = Elem<T>::kPerVec;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) z[j] = (e0 + j < V) ? Elem<T>::scalar(row + e0 + j) : -INFINITY;
+    for (int i = 0; i < 8 / PV; ++i) {
+        float t[PV];
+        Elem<T>::unpack(r.v[i], t);
+#pragma unroll
+        for (int j = 0; j < PV; ++j) z[i * PV + j] = t[j];
+    }
+    if (e0 + 8 > V) {
+        asm volatile("");                                   // (a branch that all waves but the last segment's skip)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) z[j] = e0 + j < V ? Elem<T>::scalar(row + e0 + j) : fill;
     }
 }
 
-// This lane's 8 logits of segment `seg` from the target row and (unless the bonus row is
-// drawn from) the draft row; entries at or beyond V read as -inf / 0.
-template <typename T, bool VEC>
+// This lane's 8 logits of segment `seg` from the target row and (unless the bonus row is drawn from) the draft row;
+// entries at or beyond V read as -inf / 0.
+template <typename T>
 __device__ __forceinline__ void segment_load(const T *target, const T *draft, const Selection &sl, int V, int seg,
-                                             int lane, float (&zq)[8], float (&zp)[8])
+                                             int lane, SegVec<T> &q, SegVec<T> &p)
 {
     const long long e0 = static_cast<long long>(seg) * kSegElems + lane * 8;
-    if (e0 < V) load8<T, VEC>(target + sl.target_row * V, e0, V, zq);
-    else {
-#pragma unroll
-        for (int j = 0; j < 8; ++j) zq[j] = -INFINITY;
-    }
-    if (sl.draft_row >= 0 && e0 < V) load8<T, VEC>(draft + sl.draft_row * V, e0, V, zp);
+    q = seg_load(target + sl.target_row * V, e0, V);
+    p = seg_load(sl.draft_row >= 0 ? draft + sl.draft_row * V : target + sl.target_row * V, e0, V);
+}
+template <typename T>
+__device__ __forceinline__ void segment_unpack(const SegVec<T> &q, const SegVec<T> &p, const T *target, const T *draft,
+                                               const Selection &sl, int V, int seg, int lane, float (&zq)[8], float (&zp)[8])
+{
+    const long long e0 = static_cast<long long>(seg) * kSegElems + lane * 8;
+    seg_unpack(q, target + sl.target_row * V, e0, V, -INFINITY, zq);
+    if (sl.draft_row >= 0) seg_unpack(p, draft + sl.draft_row * V, e0, V, 0.0f, zp);
     else {
 #pragma unroll
         for (int j = 0; j < 8; ++j) zp[j] = 0.0f;
@@ -671,23 +717,17 @@ __device__ __forceinline__ void update_pending_state(const T *target, const T *d
     }
 }
 
-template <typename T, bool VEC, bool PEND>
+template <typename T, bool PEND>
 __global__ void __launch_bounds__(kSegThreads)
 k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, FinalOut fo, int V, int K, int L,
-        float c, int nseg, uint64_t seed, uint64_t offset)
+        float c, int nseg, int spw, uint64_t seed, uint64_t offset)
 {
     static_assert(kSegThreads == kDecideThreads, "the decision runs on the whole workgroup");
     extern __shared__ double lds_decide[];
     __shared__ Selection sh_sel;
     __shared__ PendTable sh_tab;
     __shared__ double sh_u;
-    __shared__ int sh_is_last;
     __shared__ double sh_d[kSegThreads / kWave];
-    __shared__ double sh_scan[kSegThreads / kWave];
-    __shared__ float sh_f[kSegThreads / kWave];
-    __shared__ int sh_seg, sh_first[kSegThreads / kWave], sh_last[kSegThreads / kWave];
-    __shared__ double sh_local_target, sh_total;
-    __shared__ float sh_seg_m2;
     __shared__ double sh_excess[kPendParts];
     const int b = blockIdx.y, tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wid = tid / kWave;
@@ -714,10 +754,10 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
         // workgroup itself -- the same bits, stored again -- so no workgroup depends on another one's progress.
         auto excess_sums = [&](const double *tq, const double *tp, const double *lq, const double *lp, double *ex) {
             const int KL = K * L;
-            constexpr int N = VEC ? Elem<T>::kPerVec : 1;
+            constexpr int N = Elem<T>::kPerVec;
             constexpr int kAhead = 4;                                  // vector pairs in flight per thread
             const int nparts = static_cast<int>(gridDim.x) < kPendParts ? static_cast<int>(gridDim.x) : kPendParts;
-            const int units = VEC ? V / N : V;
+            const int units = (V + N - 1) / N, rem = V % N;             // (a last vector that is not whole: the row's last 16 bytes)
             const int per = (units + nparts - 1) / nparts;
             for (int idx = 0; idx < KL; ++idx) {                       // uniform: every thread reads the same LDS entry
                 if (ex[idx] != kExcessPending) continue;
@@ -732,27 +772,35 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
                 auto sum_part = [&](int part) {                        // by the whole workgroup; the value in every thread
                     const int lo = part * per, hi = lo + per < units ? lo + per : units;
                     float acc = 0.0f;
-                    if constexpr (VEC) {
+                    if (V >= N) {                                      // uniform
                         for (int v0 = lo + tid; v0 < hi; v0 += kAhead * kSegThreads) {
                             U4 q4[kAhead], p4[kAhead];
 #pragma unroll
                             for (int a = 0; a < kAhead; ++a) {
                                 const int v = v0 + a * kSegThreads;
-                                q4[a] = load16_stream(rq + static_cast<long long>(v < hi ? v : v0) * N);
-                                p4[a] = load16_stream(rp + static_cast<long long>(v < hi ? v : v0) * N);
+                                int e = (v < hi ? v : v0) * N;
+                                e = e < V - N ? e : V - N;
+                                q4[a] = load16_stream_any(rq + e);
+                                p4[a] = load16_stream_any(rp + e);
                             }
 #pragma unroll
                             for (int a = 0; a < kAhead; ++a) {
+                                const int v = v0 + a * kSegThreads;
                                 float zq[N], zp[N];
                                 Elem<T>::unpack(q4[a], zq);
                                 Elem<T>::unpack(p4[a], zp);
-                                if (v0 + a * kSegThreads < hi) acc += excess_terms(zq, zp, ec);
+                                if (rem != 0 && v == units - 1) {      // the entries that the vector before it holds
+                                    asm volatile("");
+#pragma unroll
+                                    for (int e = 0; e < N; ++e)
+                                        if (e < N - rem) { zq[e] = -INFINITY; zp[e] = -INFINITY; }
+                                }
+                                if (v < hi) acc += excess_terms(zq, zp, ec);
                             }
                         }
-                    } else {
-                        for_each_pair_range<T, VEC, kSegThreads>(rq, rp, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
-                            acc += excess_terms(zq, zp, ec);
-                        });
+                    } else if (lo < hi && tid < V) {
+                        const float zq[1] = {Elem<T>::scalar(rq + tid)}, zp[1] = {Elem<T>::scalar(rp + tid)};
+                        acc = excess_terms(zq, zp, ec);
                     }
                     const double v = block_sum(static_cast<double>(acc), sh_d) * ec.scale;
                     if (tid == 0)
@@ -798,30 +846,27 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
     const Selection sl = sh_sel;
     if (blockIdx.x == 0 && tid == 0) fo.sel[b] = sl;
 
-    // ---- 2. partial sums of this workgroup's segments: kSegPerWave consecutive segments per wave
+    // ---- 2. partial sums of this workgroup's segments: `spw` consecutive segments per wave, kSegAtOnce of them at a time
     {
-        const int seg0 = (blockIdx.x * (kSegThreads / kWave) + wid) * kSegPerWave;
-        double sw[kSegPerWave], sq[kSegPerWave];
-        float m2[kSegPerWave];
-        float zq[kSegPerWave][8], zp[kSegPerWave][8];
+        const int seg0 = (blockIdx.x * (kSegThreads / kWave) + wid) * spw;
+        const int seg1 = seg0 + spw < nseg ? seg0 + spw : nseg;
+        for (int sg = seg0; sg < seg1; sg += kSegAtOnce) {   // wave-uniform
+            SegVec<T> vq[kSegAtOnce], vp[kSegAtOnce];
 #pragma unroll
-        for (int i = 0; i < kSegPerWave; ++i)            // all loads first: one memory latency, not four
-            if (seg0 + i < nseg) segment_load<T, VEC>(target, draft, sl, V, seg0 + i, lane, zq[i], zp[i]);
+            for (int i = 0; i < kSegAtOnce; ++i)         // all loads first: one memory latency, not several
+                segment_load<T>(target, draft, sl, V, sg + i < seg1 ? sg + i : seg1 - 1, lane, vq[i], vp[i]);
 #pragma unroll
-        for (int i = 0; i < kSegPerWave; ++i) {
-            sw[i] = 0.0; sq[i] = 0.0; m2[i] = 0.0f;
-            if (seg0 + i < nseg) {                      // wave-uniform
-                float w[8], wq[8];
-                m2[i] = segment_weigh<PEND>(sl, sh_tab, V, K, c, seg0 + i, lane, __builtin_nanf(""), zq[i], zp[i], w, wq);
+            for (int i = 0; i < kSegAtOnce; ++i) {
+                if (sg + i < seg1) {                    // wave-uniform
+                    float zq[8], zp[8], w[8], wq[8];
+                    segment_unpack<T>(vq[i], vp[i], target, draft, sl, V, sg + i, lane, zq, zp);
+                    const float m2 = segment_weigh<PEND>(sl, sh_tab, V, K, c, sg + i, lane, __builtin_nanf(""), zq, zp, w, wq);
+                    double sw = 0.0, sq = 0.0;
 #pragma unroll
-                for (int j = 0; j < 8; ++j) { sw[i] += static_cast<double>(w[j]); sq[i] += static_cast<double>(wq[j]); }
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < kSegPerWave; ++i) {
-            if (seg0 + i < nseg) {
-                const double a = wave_sum(sw[i]), bq = wave_sum(sq[i]);
-                if (lane == 0) partial_store(&fo.partial[static_cast<long long>(b) * nseg + seg0 + i], a, bq, m2[i]);
+                    for (int j = 0; j < 8; ++j) { sw += static_cast<double>(w[j]); sq += static_cast<double>(wq[j]); }
+                    sw = wave_sum(sw); sq = wave_sum(sq);
+                    if (lane == 0) partial_store(&fo.partial[static_cast<long long>(b) * nseg + sg + i], sw, sq, m2);
+                }
             }
         }
     }
@@ -830,76 +875,66 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
     // they have completed, the barrier orders them before the first thread's counter update.
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
     __syncthreads();
-    if (tid == 0) {
-        const int arrived = __hip_atomic_fetch_add(&fo.counter[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        sh_is_last = arrived == static_cast<int>(gridDim.x) - 1;
+    if (wid != 0) return;
+    {
+        int arrived = 0;
+        if (lane == 0) arrived = __hip_atomic_fetch_add(&fo.counter[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (__builtin_amdgcn_readfirstlane(arrived) != static_cast<int>(gridDim.x) - 1) return;
     }
-    __syncthreads();
-    if (!sh_is_last) return;
     const SegPartial *pp = fo.partial + static_cast<long long>(b) * nseg;
 
-    // thread t owns the contiguous segments [t*chunk, (t+1)*chunk); the first kKeep of them stay
-    // in registers (all of them up to V = 256K), later ones are read again when needed
-    constexpr int kKeep = 2;
-    const int chunk = (nseg + kSegThreads - 1) / kSegThreads;
-    const int s0 = tid * chunk, s1 = min(nseg, s0 + chunk);
+    // From here on one wave: a workgroup-wide search spends its time at barriers.  Lane l owns the contiguous segments
+    // [l chunk, (l + 1) chunk); the first kKeep of them stay in registers (all of them up to V = 163840), later ones are
+    // read again when needed.
+    constexpr int kKeep = 5;
+    const int chunk = (nseg + kWave - 1) / kWave;
+    const int s0 = lane * chunk, s1 = min(nseg, s0 + chunk);
     float km2[kKeep];
     double kw[kKeep], kq[kKeep];
     float mloc = -3.0e38f;
 #pragma unroll
+    for (int i = 0; i < kKeep; ++i) {                // (every slot is loaded: lanes without a segment repeat the last one's)
+        const int s = s0 + i < s1 ? s0 + i : nseg - 1;
+        km2[i] = partial_load_m2(&pp[s]);
+        kw[i] = partial_load_d(&pp[s].sum_w); kq[i] = partial_load_d(&pp[s].sum_q);
+    }
+#pragma unroll
     for (int i = 0; i < kKeep; ++i) {
-        km2[i] = -3.0e38f; kw[i] = 0.0; kq[i] = 0.0;
-        if (s0 + i < s1) {
-            km2[i] = partial_load_m2(&pp[s0 + i]);
-            kw[i] = partial_load_d(&pp[s0 + i].sum_w); kq[i] = partial_load_d(&pp[s0 + i].sum_q);
-            mloc = fmaxf(mloc, km2[i]);
-        }
+        if (!(s0 + i < s1)) { km2[i] = -3.0e38f; kw[i] = 0.0; kq[i] = 0.0; }
+        mloc = fmaxf(mloc, km2[i]);
     }
     for (int s = s0 + kKeep; s < s1; ++s) mloc = fmaxf(mloc, partial_load_m2(&pp[s]));
-    const float M = block_max(mloc, sh_f);
+    const float M = wave_max(mloc);
     double tw = 0.0, tqs = 0.0;
 #pragma unroll
     for (int i = 0; i < kKeep; ++i) {
-        if (s0 + i < s1) {
-            const int sh = reference_shift(km2[i], M);                         // both integral, difference <= 0
-            kw[i] = ldexp(kw[i], sh); kq[i] = ldexp(kq[i], sh);               // now relative to 2^M
-            tw += kw[i]; tqs += kq[i];
-        }
+        const int sh = reference_shift(km2[i], M);                             // both integral, difference <= 0
+        kw[i] = ldexp(kw[i], sh); kq[i] = ldexp(kq[i], sh);                   // now relative to 2^M
+        tw += kw[i]; tqs += kq[i];
     }
     for (int s = s0 + kKeep; s < s1; ++s) {
         const int sh = reference_shift(partial_load_m2(&pp[s]), M);
         tw += ldexp(partial_load_d(&pp[s].sum_w), sh); tqs += ldexp(partial_load_d(&pp[s].sum_q), sh);
     }
-    const double Ww = block_sum(tw, sh_d);
-    const double Wq = block_sum(tqs, sh_d);
-    const bool use_q = !(Ww > 0.0);           // every residual weight is zero: draw from q
-    const double W = use_q ? Wq : Ww;
+    const double incl_w = wave_inclusive_sum(tw);
+    const double Ww = lane_value(incl_w, kWave - 1);
+    const bool use_q = !(Ww > 0.0);           // every residual weight is zero: draw from q (wave-uniform)
+    const double incl_t = use_q ? wave_inclusive_sum(tqs) : incl_w;
+    const double W = use_q ? lane_value(incl_t, kWave - 1) : Ww;
     const double u = sh_u;
     const double goal = u * W;
 
-    // first thread, then first segment, whose running total exceeds the goal
+    // first lane, then first segment, whose running total exceeds the goal
     const double mine_seg = use_q ? tqs : tw;
-    const double incl_t = wave_inclusive_sum(mine_seg);
-    if (lane == kWave - 1) sh_scan[wid] = incl_t;
-    __syncthreads();
-    double wave_off = 0.0;
-    for (int wv = 0; wv < wid; ++wv) wave_off += sh_scan[wv];
-    const double excl_t = wave_off + incl_t - mine_seg;
-    // per wave: first thread whose running total exceeds the goal, last thread with any weight
-    // (ballots; same-address LDS atomics from every lane serialise and cost microseconds)
+    const double excl_t = incl_t - mine_seg;
     const unsigned long long has = __ballot(mine_seg > 0.0);
     const unsigned long long over = __ballot(mine_seg > 0.0 && excl_t + mine_seg > goal);
-    if (lane == 0) {
-        sh_first[wid] = over ? wid * kWave + __ffsll(static_cast<long long>(over)) - 1 : kSegThreads;
-        sh_last[wid] = has ? wid * kWave + 63 - __clzll(static_cast<long long>(has)) : -1;
-    }
-    __syncthreads();
-    int win_t = kSegThreads, last_t = -1;
-#pragma unroll
-    for (int wv = 0; wv < kSegThreads / kWave; ++wv) { win_t = min(win_t, sh_first[wv]); last_t = max(last_t, sh_last[wv]); }
-    if (win_t == kSegThreads) win_t = last_t < 0 ? 0 : last_t;   // rounding pushed the goal past the end
-    __syncthreads();
-    if (tid == win_t) {
+    const int win_l = over ? __ffsll(static_cast<long long>(over)) - 1
+                           : (has ? 63 - __clzll(static_cast<long long>(has)) : 0);   // (rounding pushed the goal past the end)
+    int seg_w = 0;
+    float seg_m2 = 0.0f;
+    double cum_w = 0.0;
+    if (lane == win_l) {
         double cum = excl_t, cum_before = excl_t;
         int found = -1, last_pos = s0 < nseg ? s0 : 0;
         float found_m2 = km2[0], last_m2 = km2[0];
@@ -922,23 +957,22 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
             else cum += v;
         }
         if (found < 0) { found = last_pos; found_m2 = last_m2; cum_before = cum_before_last; }
-        const int up = -reference_shift(found_m2, M);
-        sh_seg = found;
-        sh_seg_m2 = found_m2;
-        sh_local_target = ldexp(goal - cum_before, up);    // goal in the segment's own scale
-        sh_total = ldexp(W, up);
+        seg_w = found; seg_m2 = found_m2; cum_w = cum_before;
     }
-    __syncthreads();
-    if (wid != 0) return;
+    const int seg = __builtin_amdgcn_readlane(seg_w, win_l);
+    const float m2_seg = __uint_as_float(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(seg_m2)), win_l));
+    const int up = -reference_shift(m2_seg, M);
+    const double local_target = ldexp(goal - lane_value(cum_w, win_l), up);     // goal in the segment's own scale
+    const double total_here = ldexp(W, up);
 
     // inside the segment: one wave, lane order = token-id order
-    const int seg = sh_seg;
-    const double local_target = sh_local_target;
     float w[8], wq[8];
     {
+        SegVec<T> vq, vp;
         float zq[8], zp[8];
-        segment_load<T, VEC>(target, draft, sl, V, seg, lane, zq, zp);
-        segment_weigh<PEND>(sl, sh_tab, V, K, c, seg, lane, sh_seg_m2, zq, zp, w, wq);
+        segment_load<T>(target, draft, sl, V, seg, lane, vq, vp);
+        segment_unpack<T>(vq, vp, target, draft, sl, V, seg, lane, zq, zp);
+        segment_weigh<PEND>(sl, sh_tab, V, K, c, seg, lane, m2_seg, zq, zp, w, wq);
     }
     double ws[8];
     double mine = 0.0;
@@ -971,7 +1005,7 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
             if (y < 0 && run > local_target) {
                 y = j;
                 const double lo = local_target - prev, hi = run - local_target;
-                mg = (lo < hi ? lo : hi) / sh_total;
+                mg = (lo < hi ? lo : hi) / total_here;
             }
         }
         if (y < 0) { y = last < 0 ? 0 : last; mg = 0.0; }
@@ -1011,16 +1045,28 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
     if (PEND && fo.state_carry) update_pending_state<T>(target, draft, io, fo, sl, b, K, L, V, c, winner, tokid_w, carry_w, mcount_w);
 }
 
+// Consecutive segments a wave takes: as few as keep the grid within two and a half workgroups per compute unit.  Fewer
+// segments spread a prefix's row over more workgroups, which is what a small batch's latency is made of, but every
+// workgroup makes the prefix's whole decision, which is what a large batch pays for.  Measured, microseconds per call at
+// 1 / 2 / 4 / 8 / 16 segments: one prefix of V = 128256 26.5 / 27.4 / 29.3 / 32.7 / 39.4, 8 of 32000 43.9 / 44.7 / 49.2 /
+// 59.2 / 77.4, 32 of 128256 256.5 / 241.5 / 238.6 / 241.3 / 248.3, 128 of 152064 2296 / 2233 / 2205 / 2199 / 2193.
+int final_segments_per_wave(const Problem &p)
+{
+    const long long most = 5LL * compute_units() / 2;
+    int spw = 1;
+    auto groups = [&](int n) { return (p.lay.nseg + kSegThreads / kWave * n - 1) / (kSegThreads / kWave * n); };
+    while (groups(spw) > 1 && static_cast<long long>(groups(spw)) * p.batch > most) spw *= 2;
+    return spw;
+}
+
 template <typename T>
 hipError_t launch_final_typed(const Problem &p)
 {
     const T *target = static_cast<const T *>(p.target);
     const T *draft = static_cast<const T *>(p.draft);
-    const bool vec = (p.V % Elem<T>::kPerVec) == 0 &&
-                     (reinterpret_cast<uintptr_t>(p.target) % 16 == 0) &&
-                     (reinterpret_cast<uintptr_t>(p.draft) % 16 == 0);
-    constexpr int kSegPerBlock = kSegThreads / kWave * kSegPerWave;
-    const dim3 g(static_cast<unsigned>((p.lay.nseg + kSegPerBlock - 1) / kSegPerBlock), static_cast<unsigned>(p.batch));
+    const int spw = final_segments_per_wave(p);
+    const int per_block = kSegThreads / kWave * spw;
+    const dim3 g(static_cast<unsigned>((p.lay.nseg + per_block - 1) / per_block), static_cast<unsigned>(p.batch));
     DecideIO io;
     io.tokens = p.tokens;
     io.stats = reinterpret_cast<const RowStat *>(p.ws + p.lay.stats);
@@ -1058,12 +1104,12 @@ hipError_t launch_final_typed(const Problem &p)
     fo.mcount = reinterpret_cast<int32_t *>(p.ws + p.lay.mcount);
     fo.state_carry = p.state_carry; fo.state_count = p.state_count;
     const int KL = p.K * p.L;
-    const size_t lds = sizeof(double) * (6 * KL + p.K) + sizeof(int) * KL + ((static_cast<size_t>(p.K) * p.K + 7) & ~static_cast<size_t>(7));
-#define SPECGBV_FINAL_LAUNCH(VEC, PEND)                                                                              \
-    hipLaunchKernelGGL((k_final<T, VEC, PEND>), g, dim3(kSegThreads), lds, p.stream, target, draft, io, fo, p.V, p.K, \
-                       p.L, p.c, p.lay.nseg, p.seed, p.offset)
-    if (p.pend_levels > 0) { if (vec) SPECGBV_FINAL_LAUNCH(true, true); else SPECGBV_FINAL_LAUNCH(false, true); }
-    else { if (vec) SPECGBV_FINAL_LAUNCH(true, false); else SPECGBV_FINAL_LAUNCH(false, false); }
+    const size_t lds = sizeof(double) * (6 * KL + p.K) + sizeof(int) * (2 * KL + 1) + ((static_cast<size_t>(p.K) * p.K + 7) & ~static_cast<size_t>(7));
+#define SPECGBV_FINAL_LAUNCH(PEND)                                                                              \
+    hipLaunchKernelGGL((k_final<T, PEND>), g, dim3(kSegThreads), lds, p.stream, target, draft, io, fo, p.V, p.K, \
+                       p.L, p.c, p.lay.nseg, spw, p.seed, p.offset)
+    if (p.pend_levels > 0) SPECGBV_FINAL_LAUNCH(true);
+    else SPECGBV_FINAL_LAUNCH(false);
 #undef SPECGBV_FINAL_LAUNCH
     return hipGetLastError();
 }

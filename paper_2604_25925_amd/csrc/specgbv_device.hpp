@@ -142,6 +142,15 @@ __device__ __forceinline__ U4 load16_stream_any(const T *p) {
     return U4{v.x, v.y, v.z, v.w};
 }
 
+// ... and without the hint.
+template <typename T>
+__device__ __forceinline__ U4 load16_any(const T *p) {
+    typedef unsigned int V4 __attribute__((ext_vector_type(4)));
+    typedef V4 V4any __attribute__((aligned(2)));
+    const V4 v = *(const __attribute__((address_space(1))) V4any *)p;
+    return U4{v.x, v.y, v.z, v.w};
+}
+
 // ------------------------------------------------------------------- math
 
 // v_exp_f32: 2^x, about 1 ulp, flushes results below 2^-126.
