@@ -31,66 +31,121 @@ constexpr bool kKseqKeep = true;
 // small (G where the models hardly overlap, S where they nearly coincide) whatever the accuracy of the row's normaliser.
 struct KseqSums { double G, S, Dr; };
 
-// One sweep over the row pair at scale rho.  C1 = log2 Z_p - log2 Z_q; weights relative to 2^shift_q.
-template <typename T, bool VEC>
-__device__ __forceinline__ KseqSums kseq_sweep(const T *rq, const T *rp, int V, float c, float shift_q, double C1,
-                                               double rho, double *sh_d)
+// Three workgroup-wide sums with one barrier: sh holds 2 * 3 * (waves) doubles, `turn` alternates between its halves.
+__device__ __forceinline__ KseqSums kseq_block_sums(double G, double S, double Dr, double *sh, int turn)
 {
-    constexpr int N = VEC ? Elem<T>::kPerVec : 1;
-    const RatioConst rc(C1 - log2(rho));                  // rho p / q = 2^(c (z_p - z_q) - C2)
-    const float kappa = -rc.neg_kappa;
-    // summed as min{rho p, q} (not as max{q - rho p, 0} = q - min): where the two models hardly overlap the sum is
-    // tiny and the equation for rho is decided by its leading digits
-    float G = 0.0f, S = 0.0f, Dr = 0.0f;
-    for_each_pair<T, VEC, kKseqThreads, kKseqKeep>(rq, rp, V, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+    constexpr int kWaves = kKseqThreads / kWave;
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x / kWave;
+    double *at = sh + turn * 3 * kWaves;
+    G = wave_sum(G); S = wave_sum(S); Dr = wave_sum(Dr);
+    if (lane == 0) { at[wid] = G; at[kWaves + wid] = S; at[2 * kWaves + wid] = Dr; }
+    __syncthreads();
+    KseqSums out{0.0, 0.0, 0.0};
 #pragma unroll
-        for (int j = 0; j < N; ++j) {
-            const float r = exp2_fast(fmaf(zp[j] - zq[j], c, -rc.C2_hi)) * kappa;        // rho p / q
-            const float e = exp2_fast(fmaf(zq[j], c, -shift_q));
-            const bool open = r < 1.0f;                                                   // rho p < q
-            G = fmaf(e, open ? r : 1.0f, G);
-            S = fmaf(e, open ? 1.0f - r : 0.0f, S);
-            Dr += open ? e * r : 0.0f;
-        }
-    });
-    KseqSums out;
-    out.G = block_sum(static_cast<double>(G), sh_d);
-    out.S = block_sum(static_cast<double>(S), sh_d);
-    out.Dr = block_sum(static_cast<double>(Dr), sh_d);
+    for (int w = 0; w < kWaves; ++w) { out.G += at[w]; out.S += at[kWaves + w]; out.Dr += at[2 * kWaves + w]; }
     const double tot = out.G + out.S;                      // = sum_x q in the sums' own units
     if (tot > 0.0) { out.G /= tot; out.S /= tot; out.Dr /= tot; }
     return out;
 }
 
-// grid batch * ndrafts * L: workgroup (b, k, r) takes row pair r of draft k of prefix b: its statistics, the number
-// n of drafts (among the first ndrafts) that share the draft's first r tokens, and the root rho for k = n.
+// The root: f(rho) = G(rho) - 1 + (1 - beta)^n, beta = G / rho, is non-positive at 1, non-negative at n, increasing.  It is
+// evaluated as G - beta sum_{j<n} (1 - beta)^j, which keeps its leading digits when G is tiny, or as (1 - beta)^n - S, which
+// keeps them where S is.  Newton from the left end, kept inside the bracket by bisection, until the step is below 2e-7 rho
+// (or f is below the noise of the float32 sums); every quantity is workgroup-uniform, and rho is a float32 value, so that
+// the sweeps evaluate at exactly the rho that is returned.  sweep(rho, turn): KseqSums.
+struct KseqRoot { double rho, beta; };
+template <typename Sweep>
+__device__ __forceinline__ KseqRoot kseq_root(int n, Sweep sweep)
+{
+    double rho = 1.0, lo = 1.0, hi = static_cast<double>(n), beta = 0.0;
+    for (int it = 0;; ++it) {
+        const KseqSums sm = sweep(rho, it & 1);
+        beta = sm.G / rho;
+        if (n <= 1) break;                                 // one candidate: rho = 1 (Section 3.1)
+        const double b1 = beta < 1.0 ? beta : 1.0, A = 1.0 - b1;
+        double geo = 1.0, pw1 = 1.0;                       // sum_{j<n} A^j and A^(n-1)
+        for (int j = 1; j < n; ++j) { pw1 *= A; geo += pw1; }
+        const double f = b1 > 0.5 ? pw1 * A - sm.S : sm.G - b1 * geo;
+        if (hi - lo <= 2.0e-7 * rho || it >= 40) break;    // (rho, beta): the pair just evaluated
+        if (f >= 0.0) hi = rho; else lo = rho;
+        const double D = sm.Dr / rho;                      // d(rho beta)/d rho = mass of p where rho p < q
+        const double fp = D - static_cast<double>(n) * pw1 * (D - beta) / rho;
+        double nxt = fp > 0.0 ? rho - f / fp : 0.5 * (lo + hi);
+        const bool inside = nxt > lo && nxt < hi;
+        if (!inside) nxt = 0.5 * (lo + hi);
+        const double step = nxt - rho;
+        if (fabs(f) <= 1.0e-7 * fmin(sm.G, sm.S) || (fabs(step) <= 2.0e-7 * rho && it > 0)) {
+            if (inside && fabs(step) <= 1.0e-5 * rho) {    // the last, short step is taken along the tangent of G
+                beta = (sm.G + D * step) / nxt;
+                rho = nxt;
+            }
+            break;
+        }
+        nxt = static_cast<double>(static_cast<float>(nxt));
+        if (nxt == rho) break;
+        rho = nxt;
+    }
+    return KseqRoot{rho, beta};
+}
+
+// What a workgroup of either kernel works on: grid batch * ndrafts * L, the row index slowest (rows 0, which all drafts
+// share and which take the most steps, come first and the others fill in behind them): row pair r of draft k of prefix b,
+// and the number n of drafts (among the first ndrafts) that share the draft's first r tokens.
+struct KseqPair { long long bk, pair; int r, k; long long b; };
+__device__ __forceinline__ KseqPair kseq_pair(int K, int L, int ndrafts)
+{
+    KseqPair w;
+    const unsigned chains = gridDim.x / static_cast<unsigned>(L), at = blockIdx.x % chains;
+    w.r = static_cast<int>(blockIdx.x / chains);
+    w.k = static_cast<int>(at % static_cast<unsigned>(ndrafts));
+    w.b = at / static_cast<unsigned>(ndrafts);
+    w.bk = w.b * K + w.k;
+    w.pair = w.bk * L + w.r;
+    return w;
+}
+__device__ __forceinline__ void kseq_begin(const KseqPair &w, const int32_t *tokens, int K, int L, int ndrafts, int32_t *final_counter, int *sh_n)
+{
+    const int tid = threadIdx.x;
+    if (tid == 0) {
+        *sh_n = 0;
+        if (w.k == 0 && w.r == 0) final_counter[w.b] = 0;  // arrival counter of the final-token kernel
+    }
+    __syncthreads();
+    if (tid < ndrafts) {
+        bool same = true;
+        for (int j = 0; j < w.r; ++j) same = same && tokens[(w.b * K + tid) * L + j] == tokens[w.bk * L + j];
+        if (same) atomicAdd(sh_n, 1);
+    }
+}
+template <typename T>
+__device__ __forceinline__ void kseq_store_stats(const KseqPair &w, const T *rq, const T *rp, const int32_t *tokens, int V, double lse2_q,
+                                                 double lse2_p, float c, double c_rel, RowStat *stats)
+{
+    int tok = tokens[w.pair];
+    tok = tok < 0 ? 0 : (tok >= V ? V - 1 : tok);
+    RowStat st;
+    st.lse2_q = lse2_q; st.lse2_p = lse2_p;
+    st.tok2_q = token_scaled(static_cast<double>(Elem<T>::scalar(rq + tok)) * static_cast<double>(c), lse2_q, c_rel);
+    st.tok2_p = token_scaled(static_cast<double>(Elem<T>::scalar(rp + tok)) * static_cast<double>(c), lse2_p, c_rel);
+    stats[w.pair] = st;
+}
+
+// Rows from memory, one sweep per step (any length and address): those that do not fit a workgroup's registers.  With the
+// row index slowest and one barrier per step, 32 x 8 drafts of 8 at V = 128256 take 452 us a call, 920 before.
 template <typename T, bool VEC>
 __global__ void __launch_bounds__(kKseqThreads)
 k_kseq_rows(const T *__restrict__ target, const T *__restrict__ draft, const int32_t *__restrict__ tokens, int K, int L,
             int V, int ndrafts, float c, double c_rel, RowStat *__restrict__ stats, double *__restrict__ rho_out,
             double *__restrict__ beta_out, int32_t *__restrict__ final_counter)
 {
-    __shared__ double sh_d[kKseqThreads / kWave];
+    __shared__ double sh_d[2 * 3 * (kKseqThreads / kWave)];
     __shared__ float sh_f[kKseqThreads / kWave];
     __shared__ int sh_n;
-    const int r = static_cast<int>(blockIdx.x % L);
-    const long long bkd = blockIdx.x / L;
-    const int k = static_cast<int>(bkd % ndrafts);
-    const long long b = bkd / ndrafts;
-    const long long bk = b * K + k, pair = bk * L + r;
     const int tid = threadIdx.x;
-    if (tid == 0) {
-        sh_n = 0;
-        if (k == 0 && r == 0) final_counter[b] = 0;       // arrival counter of the final-token kernel
-    }
-    __syncthreads();
-    if (tid < ndrafts) {
-        bool same = true;
-        for (int j = 0; j < r; ++j) same = same && tokens[(b * K + tid) * L + j] == tokens[bk * L + j];
-        if (same) atomicAdd(&sh_n, 1);
-    }
-    const T *rq = target + (bk * (L + 1) + r) * static_cast<long long>(V);
-    const T *rp = draft + pair * static_cast<long long>(V);
+    const KseqPair w = kseq_pair(K, L, ndrafts);
+    kseq_begin(w, tokens, K, L, ndrafts, final_counter, &sh_n);
+    const T *rq = target + (w.bk * (L + 1) + w.r) * static_cast<long long>(V);
+    const T *rp = draft + w.pair * static_cast<long long>(V);
     constexpr int N = VEC ? Elem<T>::kPerVec : 1;
     RunningSum aq, ap;
     for_each_pair<T, VEC, kKseqThreads, kKseqKeep>(rq, rp, V, [&](int, const float (&zq)[N], const float (&zp)[N]) {
@@ -102,43 +157,132 @@ k_kseq_rows(const T *__restrict__ target, const T *__restrict__ draft, const int
     const float Mp = block_max(ap.m2, sh_f);
     const double Zp = block_sum(ap.Z > 0.0f ? static_cast<double>(ap.Z) * exp2(static_cast<double>(ap.m2) - static_cast<double>(Mp)) : 0.0, sh_d);
     const double lse2_q = static_cast<double>(Mq) + log2(Zq), lse2_p = static_cast<double>(Mp) + log2(Zp);
-    if (tid == 0) {
-        int tok = tokens[pair];
-        tok = tok < 0 ? 0 : (tok >= V ? V - 1 : tok);
-        RowStat st;
-        st.lse2_q = lse2_q; st.lse2_p = lse2_p;
-        st.tok2_q = token_scaled(static_cast<double>(Elem<T>::scalar(rq + tok)) * static_cast<double>(c), lse2_q, c_rel);
-        st.tok2_p = token_scaled(static_cast<double>(Elem<T>::scalar(rp + tok)) * static_cast<double>(c), lse2_p, c_rel);
-        stats[pair] = st;
-    }
+    if (tid == 0) kseq_store_stats(w, rq, rp, tokens, V, lse2_q, lse2_p, c, c_rel, stats);
     const int n = sh_n;                                    // (the block sums above contain the barriers that publish it)
     const float shift_q = rintf(static_cast<float>(lse2_q));
     const double C1 = lse2_p - lse2_q;
+    __syncthreads();                                       // (the last block sum has been read)
+    const KseqRoot root = kseq_root(n, [&](double rho, int turn) {
+        const RatioConst rc(C1 - log2(rho));               // rho p / q = 2^(c (z_p - z_q) - C2)
+        const float kappa = -rc.neg_kappa;
+        // summed as min{rho p, q} (not as max{q - rho p, 0} = q - min): where the two models hardly overlap the sum is
+        // tiny and the equation for rho is decided by its leading digits
+        float G = 0.0f, S = 0.0f, Dr = 0.0f;
+        for_each_pair<T, VEC, kKseqThreads, kKseqKeep>(rq, rp, V, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) {
+                const float r = exp2_fast(fmaf(zp[j] - zq[j], c, -rc.C2_hi)) * kappa;        // rho p / q
+                const float e = exp2_fast(fmaf(zq[j], c, -shift_q));
+                const bool open = r < 1.0f;                                                   // rho p < q
+                G = fmaf(e, open ? r : 1.0f, G);
+                S = fmaf(e, open ? 1.0f - r : 0.0f, S);
+                Dr += open ? e * r : 0.0f;
+            }
+        });
+        return kseq_block_sums(static_cast<double>(G), static_cast<double>(S), static_cast<double>(Dr), sh_d, turn);
+    });
+    if (tid == 0) { rho_out[w.pair] = root.rho; beta_out[w.pair] = root.beta; }
+}
 
-    // f(rho) = G(rho) - 1 + (1 - beta)^n, beta = G / rho: non-positive at 1, non-negative at n, increasing.  It is
-    // evaluated as G + expm1(n log1p(-beta)), which keeps its leading digits when G is tiny.  Newton from the left end,
-    // kept inside the bracket by bisection, until the step is below 2e-7 rho (or f is below the noise of the float32
-    // sums); every quantity is workgroup-uniform.
-    double rho = 1.0, lo = 1.0, hi = static_cast<double>(n), beta = 0.0;
-    for (int it = 0;; ++it) {
-        const KseqSums sm = kseq_sweep<T, VEC>(rq, rp, V, c, shift_q, C1, rho, sh_d);
-        beta = sm.G / rho;
-        if (n <= 1) break;                                 // one candidate: rho = 1 (Section 3.1)
-        const double b1 = beta < 1.0 ? beta : 1.0;
-        // (1 - beta)^n - S, or G + [(1 - beta)^n - 1]: the same number, each form exact where the other cancels
-        const double f = b1 > 0.5 ? exp(static_cast<double>(n) * log1p(-b1 < -1.0 ? -1.0 : -b1)) - sm.S
-                                  : sm.G + expm1(static_cast<double>(n) * log1p(-b1));
-        if (fabs(f) <= 1.0e-7 * fmin(sm.G, sm.S) || hi - lo <= 2.0e-7 * rho || it >= 40) break;   // (rho, beta): the pair just evaluated
-        if (f >= 0.0) hi = rho; else lo = rho;
-        const double D = sm.Dr / rho;                      // d(rho beta)/d rho = mass of p where rho p < q
-        const double pw1 = b1 < 1.0 ? exp(static_cast<double>(n - 1) * log1p(-b1)) : 0.0;
-        const double fp = D - static_cast<double>(n) * pw1 * (D - beta) / rho;
-        double nxt = fp > 0.0 ? rho - f / fp : 0.5 * (lo + hi);
-        if (!(nxt > lo && nxt < hi)) nxt = 0.5 * (lo + hi);
-        if (fabs(nxt - rho) <= 2.0e-7 * rho && it > 0) break;
-        rho = nxt;
+// Rows of at most NS * kKseqThreads vectors, read once: after the statistics a thread keeps of its entries the weights
+// e = q[x] and the ratios p[x] / q[x], and a step is nine instructions per entry, without an exponential and without
+// memory.  One workgroup has the compute unit's registers to itself (64 entries per thread); what bounds it is a row's
+// own chain: load, statistics, and a step's sweep and barrier for each of five steps in the rows 0 (most others have a
+// single candidate and one step).  Before, a workgroup streamed its row pair alone for every step, 27 us each at
+// V = 32000 float32: 32 x 4 drafts of 8 took 206 us a call, 99 now; 64 x 8 in bfloat16 634, 280 now.
+template <typename T, int NS>
+__global__ void __launch_bounds__(kKseqThreads, 2)
+k_kseq_onchip(const T *__restrict__ target, const T *__restrict__ draft, const int32_t *__restrict__ tokens, int K, int L,
+              int V, int ndrafts, float c, double c_rel, RowStat *__restrict__ stats, double *__restrict__ rho_out,
+              double *__restrict__ beta_out, int32_t *__restrict__ final_counter)
+{
+    constexpr int PV = Elem<T>::kPerVec, NE = NS * PV;
+    __shared__ double sh_d[2 * 3 * (kKseqThreads / kWave)];
+    __shared__ float sh_f[kKseqThreads / kWave];
+    __shared__ int sh_n;
+    const int tid = threadIdx.x;
+    const KseqPair w = kseq_pair(K, L, ndrafts);
+    const T *rq = target + (w.bk * (L + 1) + w.r) * static_cast<long long>(V);
+    const T *rp = draft + w.pair * static_cast<long long>(V);
+    const int nv = (V + PV - 1) / PV, before = (PV - V % PV) % PV;      // entries of the last vector that the one before it holds
+    U4 q[NS], p[NS];
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {                         // (no branch: a load under one is waited for where the branch ends)
+        const int v = j * kKseqThreads + tid;
+        int e = (v < nv ? v : nv - 1) * PV;
+        e = e < V - PV ? e : V - PV;
+        q[j] = load16_stream_any(rq + e);
+        p[j] = load16_stream_any(rp + e);
     }
-    if (tid == 0) { rho_out[pair] = rho; beta_out[pair] = beta; }
+    kseq_begin(w, tokens, K, L, ndrafts, final_counter, &sh_n);
+    // entries of slot j: those beyond the row, or held by the vector before, become -inf
+    auto unpack = [&](int j, float (&zq)[PV], float (&zp)[PV]) {
+        Elem<T>::unpack(q[j], zq);
+        Elem<T>::unpack(p[j], zp);
+        if ((j + 1) * kKseqThreads >= nv) {                // uniform
+            const int v = j * kKseqThreads + tid, cut = v >= nv ? PV : (v == nv - 1 ? before : 0);
+#pragma unroll
+            for (int e = 0; e < PV; ++e)
+                if (e < cut) { zq[e] = -__builtin_inff(); zp[e] = -__builtin_inff(); }
+        }
+    };
+    float mq = -3.0e38f, mp = -3.0e38f;
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        float zq[PV], zp[PV];
+        Elem<T>::unpack(q[j], zq);                         // (an entry read twice changes no maximum)
+        Elem<T>::unpack(p[j], zp);
+#pragma unroll
+        for (int e = 0; e < PV; ++e) { mq = fmaxf(mq, zq[e]); mp = fmaxf(mp, zp[e]); }
+        asm volatile("" : "+v"(q[j].x), "+v"(q[j].y), "+v"(q[j].z), "+v"(q[j].w), "+v"(mq));
+        asm volatile("" : "+v"(p[j].x), "+v"(p[j].y), "+v"(p[j].z), "+v"(p[j].w), "+v"(mp));
+    }
+    const float Mq = block_max(mq * c, sh_f), Mp = block_max(mp * c, sh_f);
+    float aq = 0.0f, ap = 0.0f;
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        float zq[PV], zp[PV];
+        unpack(j, zq, zp);
+        float a = 0.0f, b2 = 0.0f;
+#pragma unroll
+        for (int e = 0; e < PV; ++e) { a += exp2_fast(fmaf(zq[e], c, -Mq)); b2 += exp2_fast(fmaf(zp[e], c, -Mp)); }
+        aq += a; ap += b2;
+        asm volatile("" : "+v"(q[j].x), "+v"(q[j].y), "+v"(q[j].z), "+v"(q[j].w), "+v"(aq));
+        asm volatile("" : "+v"(p[j].x), "+v"(p[j].y), "+v"(p[j].z), "+v"(p[j].w), "+v"(ap));
+    }
+    const double Zq = block_sum(static_cast<double>(aq), sh_d), Zp = block_sum(static_cast<double>(ap), sh_d);
+    const double lse2_q = static_cast<double>(Mq) + log2(Zq), lse2_p = static_cast<double>(Mp) + log2(Zp);
+    if (tid == 0) kseq_store_stats(w, rq, rp, tokens, V, lse2_q, lse2_p, c, c_rel, stats);
+    const int n = __builtin_amdgcn_readfirstlane(sh_n);    // (the block sums above contain the barriers that publish it)
+    const float shift_q = rintf(static_cast<float>(lse2_q));
+    const RatioConst rc(lse2_p - lse2_q);
+    const float kappa = -rc.neg_kappa;
+    float ew[NE], rw[NE];
+#pragma unroll
+    for (int j = 0; j < NS; ++j) {
+        float zq[PV], zp[PV];
+        unpack(j, zq, zp);
+#pragma unroll
+        for (int e = 0; e < PV; ++e) {
+            ew[j * PV + e] = exp2_fast(fmaf(zq[e], c, -shift_q));
+            rw[j * PV + e] = exp2_fast(fmaf(zp[e] - zq[e], c, -rc.C2_hi)) * kappa;     // (masked entries: weight 0, whatever the ratio)
+        }
+    }
+    __syncthreads();                                       // (the last block sum has been read)
+    const KseqRoot root = kseq_root(n, [&](double rho, int turn) {
+        const float rf = static_cast<float>(rho);
+        float C = 0.0f, S = 0.0f, Dr = 0.0f;               // C: mass of q where rho p >= q
+#pragma unroll
+        for (int e = 0; e < NE; ++e) {
+            const float s = fmaf(-rf, rw[e], 1.0f);
+            const bool open = s > 0.0f;                    // rho p < q, the same for all three sums
+            Dr = fmaf(ew[e], open ? rf * rw[e] : 0.0f, Dr);
+            S = fmaf(ew[e], fmaxf(s, 0.0f), S);
+            C += open ? 0.0f : ew[e];
+        }
+        return kseq_block_sums(static_cast<double>(C) + static_cast<double>(Dr), static_cast<double>(S), static_cast<double>(Dr), sh_d, turn);
+    });
+    if (tid == 0) { rho_out[w.pair] = root.rho; beta_out[w.pair] = root.beta; }
 }
 
 template <typename T>
@@ -153,12 +297,20 @@ hipError_t launch_kseq_typed(const Problem &p, int ndrafts)
     double *rho = reinterpret_cast<double *>(p.ws + p.lay.s);
     double *beta = reinterpret_cast<double *>(p.ws + p.lay.excess);
     int32_t *counter = reinterpret_cast<int32_t *>(p.ws + p.lay.counter);
-    if (vec)
+    constexpr int PV = Elem<T>::kPerVec;
+    const int nv = (p.V + PV - 1) / PV;
+#define SPECGBV_KSEQ_ONCHIP(NS)                                                                                       \
+    hipLaunchKernelGGL((k_kseq_onchip<T, NS>), grid, dim3(kKseqThreads), 0, p.stream, target, draft, p.tokens, p.K, p.L, \
+                       p.V, ndrafts, p.c, p.c_rel, stats, rho, beta, counter)
+    if (p.V >= PV && nv <= 16 / PV * kKseqThreads) SPECGBV_KSEQ_ONCHIP(16 / PV);         // 16 entries per thread
+    else if (p.V >= PV && nv <= 64 / PV * kKseqThreads) SPECGBV_KSEQ_ONCHIP(64 / PV);    // 64
+    else if (vec)
         hipLaunchKernelGGL((k_kseq_rows<T, true>), grid, dim3(kKseqThreads), 0, p.stream, target, draft, p.tokens, p.K, p.L,
                            p.V, ndrafts, p.c, p.c_rel, stats, rho, beta, counter);
     else
         hipLaunchKernelGGL((k_kseq_rows<T, false>), grid, dim3(kKseqThreads), 0, p.stream, target, draft, p.tokens, p.K, p.L,
                            p.V, ndrafts, p.c, p.c_rel, stats, rho, beta, counter);
+#undef SPECGBV_KSEQ_ONCHIP
     return hipGetLastError();
 }
 
