@@ -124,7 +124,7 @@ struct DecideIO {
 // *sel_out (shared memory) and is visible to every thread on return.  Only a workgroup with
 // write = true stores outputs and intermediates.  *u_final_out (shared memory) receives the uniform
 // of the final token (Philox slot K*L), drawn here so that the generator is instantiated once.
-// excess_sums(tq, tp, lq, lp, ex): called by all threads (behind a barrier) when io.e_coop is set and some entry of
+// excess_sums(tq, tp, lq, lp, ex, list): called by all threads (behind a barrier) when io.e_coop is set and some entry of
 // ex has been marked kExcessPending by the acceptance table's loop below; it replaces every marked entry by the
 // row's E = nu^2 (s - g) and ends with a barrier.
 template <typename Hook>
@@ -145,7 +145,8 @@ __device__ __forceinline__ void decide_prefix(const DecideIO &io, int b, int K, 
     unsigned long long *acc_bits = reinterpret_cast<unsigned long long *>(lds + 6 * KL);   // [K] bit i: eta_{k,i} < h_{k,i}
     int *tok = reinterpret_cast<int *>(acc_bits + K);       // [K*L]
     float *et = reinterpret_cast<float *>(tok + KL);        // [K*L + 1] the uniforms (24 bits: exact in float32)
-    unsigned char *cpl = reinterpret_cast<unsigned char *>(et + KL + 1);   // [K*K] common prefix lengths (at most L <= 62)
+    int *list = reinterpret_cast<int *>(et + KL + 1);       // [K*L] scratch of excess_sums
+    unsigned char *cpl = reinterpret_cast<unsigned char *>(list + KL);   // [K*K] common prefix lengths (at most L <= 62)
     const int tid = threadIdx.x;
     const long long base = static_cast<long long>(b) * KL;
     constexpr double kLn2 = 0.693147180559945309417;
@@ -261,7 +262,7 @@ __device__ __forceinline__ void decide_prefix(const DecideIO &io, int b, int K, 
     if (e_coop) {                                           // (uniform)
         static_assert((kMaxDrafts * 64 + kDecideThreads) / kDecideThreads <= 32, "one bit per visit (K <= 64, L < 64)");
         if (__syncthreads_or(marked != 0u)) {
-            excess_sums(tq, tp, lq, lp, ex);
+            excess_sums(tq, tp, lq, lp, ex, list);
             int n = 0;
             for (int idx = tid; idx < KL; idx += kDecideThreads, ++n)
                 if (marked >> n & 1u) table_entry(idx, false);
@@ -728,7 +729,8 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
     __shared__ PendTable sh_tab;
     __shared__ double sh_u;
     __shared__ double sh_d[kSegThreads / kWave];
-    __shared__ double sh_excess[kPendParts];
+    __shared__ double sh_excess[kSegThreads];
+    __shared__ int sh_nmark;
     const int b = blockIdx.y, tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wid = tid / kWave;
     int32_t *__restrict__ out_tokens = io.out_tokens;
@@ -747,20 +749,33 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
         // under the pending modifications, if there are any, so nu is the one the decision uses.  Every workgroup of the
         // prefix applies the kernels' two tests to every row while it makes the acceptance table (the same values, so
         // the same rows), and for the rare row that fails them the workgroups sum E together, straight from memory (this
-        // function, called only then): one part per workgroup (at most
-        // kPendParts), left in the workspace with a device-scope store; every workgroup needs all parts (each runs the
-        // decision itself) and polls for the ones it has not summed.  The wait is bounded: a part that has not
+        // function, called only then): the (row, part) units of all such rows, at most kPendParts parts each, are dealt out
+        // to the workgroups and left in the workspace with device-scope stores; every workgroup needs all parts (each runs
+        // the decision itself) and polls for them, a part per thread.  (Row after row, with a wait for every row, took 8 - 9 us
+        // a row: 8 x 4 drafts of 5 at V = 32000 with two such rows 22 us in this kernel, 19.6 now; with pending modifications 8 x 4 of 8 at V = 128256 43 us, 27 now.)  The wait is bounded: a part that has not
         // arrived after io.e_polls looks (its workgroup has not been scheduled yet, say) is summed by the waiting
         // workgroup itself -- the same bits, stored again -- so no workgroup depends on another one's progress.
-        auto excess_sums = [&](const double *tq, const double *tp, const double *lq, const double *lp, double *ex) {
+        auto excess_sums = [&](const double *tq, const double *tp, const double *lq, const double *lp, double *ex, int *list) {
             const int KL = K * L;
             constexpr int N = Elem<T>::kPerVec;
             constexpr int kAhead = 4;                                  // vector pairs in flight per thread
             const int nparts = static_cast<int>(gridDim.x) < kPendParts ? static_cast<int>(gridDim.x) : kPendParts;
             const int units = (V + N - 1) / N, rem = V % N;             // (a last vector that is not whole: the row's last 16 bytes)
             const int per = (units + nparts - 1) / nparts;
-            for (int idx = 0; idx < KL; ++idx) {                       // uniform: every thread reads the same LDS entry
-                if (ex[idx] != kExcessPending) continue;
+            if (tid < kWave) {                                         // the marked rows, in order
+                int n = 0;
+                for (int c0 = 0; c0 < KL; c0 += kWave) {
+                    const bool m = c0 + lane < KL && ex[c0 + lane] == kExcessPending;
+                    const unsigned long long mask = __ballot(m);
+                    if (m) list[n + __popcll(mask & ((1ull << lane) - 1ull))] = c0 + lane;
+                    n += __popcll(mask);
+                }
+                if (lane == 0) sh_nmark = n;
+            }
+            __syncthreads();
+            const int nmark = __builtin_amdgcn_readfirstlane(sh_nmark);
+            auto unit_sum = [&](int u) {                               // part u % nparts of marked row u / nparts, by the whole workgroup
+                const int idx = __builtin_amdgcn_readfirstlane(list[u / nparts]), part = u % nparts;
                 const int k = idx / L, i = idx % L + 1;
                 const long long bk = static_cast<long long>(b) * K + k, pair = bk * L + i;
                 double log2nu = 0.0;
@@ -768,75 +783,74 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
                 const ExcessConst ec = make_excess_const(lq[k * L + i], lp[k * L + i], log2nu, K, c);
                 const T *rq = target + (bk * (L + 1) + i) * static_cast<long long>(V);
                 const T *rp = draft + pair * static_cast<long long>(V);
-                double *parts = io.e_part_rw + pair * kPendParts;
-                auto sum_part = [&](int part) {                        // by the whole workgroup; the value in every thread
-                    const int lo = part * per, hi = lo + per < units ? lo + per : units;
-                    float acc = 0.0f;
-                    if (V >= N) {                                      // uniform
-                        for (int v0 = lo + tid; v0 < hi; v0 += kAhead * kSegThreads) {
-                            U4 q4[kAhead], p4[kAhead];
+                const int lo = part * per, hi = lo + per < units ? lo + per : units;
+                float acc = 0.0f;
+                if (V >= N) {                                      // uniform
+                    for (int v0 = lo + tid; v0 < hi; v0 += kAhead * kSegThreads) {
+                        U4 q4[kAhead], p4[kAhead];
 #pragma unroll
-                            for (int a = 0; a < kAhead; ++a) {
-                                const int v = v0 + a * kSegThreads;
-                                int e = (v < hi ? v : v0) * N;
-                                e = e < V - N ? e : V - N;
-                                q4[a] = load16_stream_any(rq + e);
-                                p4[a] = load16_stream_any(rp + e);
-                            }
-#pragma unroll
-                            for (int a = 0; a < kAhead; ++a) {
-                                const int v = v0 + a * kSegThreads;
-                                float zq[N], zp[N];
-                                Elem<T>::unpack(q4[a], zq);
-                                Elem<T>::unpack(p4[a], zp);
-                                if (rem != 0 && v == units - 1) {      // the entries that the vector before it holds
-                                    asm volatile("");
-#pragma unroll
-                                    for (int e = 0; e < N; ++e)
-                                        if (e < N - rem) { zq[e] = -INFINITY; zp[e] = -INFINITY; }
-                                }
-                                if (v < hi) acc += excess_terms(zq, zp, ec);
-                            }
+                        for (int a = 0; a < kAhead; ++a) {
+                            const int v = v0 + a * kSegThreads;
+                            int e = (v < hi ? v : v0) * N;
+                            e = e < V - N ? e : V - N;
+                            q4[a] = load16_stream_any(rq + e);
+                            p4[a] = load16_stream_any(rp + e);
                         }
-                    } else if (lo < hi && tid < V) {
-                        const float zq[1] = {Elem<T>::scalar(rq + tid)}, zp[1] = {Elem<T>::scalar(rp + tid)};
-                        acc = excess_terms(zq, zp, ec);
+#pragma unroll
+                        for (int a = 0; a < kAhead; ++a) {
+                            const int v = v0 + a * kSegThreads;
+                            float zq[N], zp[N];
+                            Elem<T>::unpack(q4[a], zq);
+                            Elem<T>::unpack(p4[a], zp);
+                            if (rem != 0 && v == units - 1) {      // the entries that the vector before it holds
+                                asm volatile("");
+#pragma unroll
+                                for (int e = 0; e < N; ++e)
+                                    if (e < N - rem) { zq[e] = -INFINITY; zp[e] = -INFINITY; }
+                            }
+                            if (v < hi) acc += excess_terms(zq, zp, ec);
+                        }
                     }
-                    const double v = block_sum(static_cast<double>(acc), sh_d) * ec.scale;
-                    if (tid == 0)
-                        __hip_atomic_store(reinterpret_cast<unsigned long long *>(parts + part),
-                                           static_cast<unsigned long long>(__double_as_longlong(v)), __ATOMIC_RELAXED,
-                                           __HIP_MEMORY_SCOPE_AGENT);
-                    return v;
-                };
-                __syncthreads();                                       // (sh_excess of the previous row has been read)
-                {
-                    const int mine = static_cast<int>(blockIdx.x);     // (workgroups beyond kPendParts only wait)
-                    const double v = mine < nparts ? sum_part(mine) : -1.0;
-                    if (tid < kPendParts) sh_excess[tid] = tid == mine ? v : -1.0;
+                } else if (lo < hi && tid < V) {
+                    const float zq[1] = {Elem<T>::scalar(rq + tid)}, zp[1] = {Elem<T>::scalar(rp + tid)};
+                    acc = excess_terms(zq, zp, ec);
                 }
-                __syncthreads();
-                if (tid < nparts && sh_excess[tid] == -1.0) {
-                    double v = -1.0;
+                const double v = block_sum(static_cast<double>(acc), sh_d) * ec.scale;
+                if (tid == 0)
+                    __hip_atomic_store(reinterpret_cast<unsigned long long *>(io.e_part_rw + pair * kPendParts + part),
+                                       static_cast<unsigned long long>(__double_as_longlong(v)), __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_AGENT);
+                return v;                                              // (in every thread)
+            };
+            for (int u = static_cast<int>(blockIdx.x); u < nmark * nparts; u += static_cast<int>(gridDim.x)) unit_sum(u);
+            constexpr int kRowsAtOnce = kSegThreads / kPendParts;
+            for (int r0 = 0; r0 < nmark; r0 += kRowsAtOnce) {          // uniform: a part per thread
+                const int nu = (nmark - r0 < kRowsAtOnce ? nmark - r0 : kRowsAtOnce) * nparts;
+                double v = 0.0;
+                if (tid < nu) {
+                    const int idx = list[r0 + tid / nparts], k = idx / L, i = idx % L + 1;
+                    const double *src = io.e_part_rw + ((static_cast<long long>(b) * K + k) * L + i) * kPendParts + tid % nparts;
+                    v = -1.0;
                     for (int look = 0; look < io.e_polls && v == -1.0; ++look) {
-                        v = partial_load_d(parts + tid);
-                        if (v == -1.0) __builtin_amdgcn_s_sleep(8);
+                        v = partial_load_d(src);
+                        if (v == -1.0) __builtin_amdgcn_s_sleep(2);
                     }
                     sh_excess[tid] = v;
                 }
-                __syncthreads();
-                for (int part = 0; part < nparts; ++part) {            // uniform; normally none is missing
-                    if (sh_excess[part] == -1.0) {
-                        const double v = sum_part(part);
-                        __syncthreads();
-                        if (tid == 0) sh_excess[part] = v;
-                        __syncthreads();
+                if (__syncthreads_or(v == -1.0)) {                     // normally none is missing
+                    for (int w = 0; w < nu; ++w) {
+                        if (sh_excess[w] == -1.0) {                    // uniform
+                            const double own = unit_sum(r0 * nparts + w);
+                            __syncthreads();
+                            if (tid == 0) sh_excess[w] = own;
+                            __syncthreads();
+                        }
                     }
                 }
-                if (tid == 0) {
+                if (tid < nu / nparts) {
                     double e = 0.0;
-                    for (int part = 0; part < nparts; ++part) e += sh_excess[part];          // in part order
-                    ex[idx] = e;
+                    for (int part = 0; part < nparts; ++part) e += sh_excess[tid * nparts + part];       // in part order
+                    ex[list[r0 + tid]] = e;
                 }
                 __syncthreads();
             }
@@ -1104,7 +1118,7 @@ hipError_t launch_final_typed(const Problem &p)
     fo.mcount = reinterpret_cast<int32_t *>(p.ws + p.lay.mcount);
     fo.state_carry = p.state_carry; fo.state_count = p.state_count;
     const int KL = p.K * p.L;
-    const size_t lds = sizeof(double) * (6 * KL + p.K) + sizeof(int) * (2 * KL + 1) + ((static_cast<size_t>(p.K) * p.K + 7) & ~static_cast<size_t>(7));
+    const size_t lds = sizeof(double) * (6 * KL + p.K) + sizeof(int) * (3 * KL + 1) + ((static_cast<size_t>(p.K) * p.K + 7) & ~static_cast<size_t>(7));
 #define SPECGBV_FINAL_LAUNCH(PEND)                                                                              \
     hipLaunchKernelGGL((k_final<T, PEND>), g, dim3(kSegThreads), lds, p.stream, target, draft, io, fo, p.V, p.K, \
                        p.L, p.c, p.lay.nseg, spw, p.seed, p.offset)
