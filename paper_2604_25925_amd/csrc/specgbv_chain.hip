@@ -1161,7 +1161,7 @@ bool chain_supports_pending(const Problem &p)
 //   one row of a chain:  3 + 1.44e-3 per vector (bfloat16: 8.8 / 15.5 / 26 at 4000 / 8000 / 16032 vectors),
 //                        2 + 0.85e-3 per vector (float32), but not faster than 6.3 TB/s over all chains;
 //   two chains per compute unit (short rows): 1.75 times the time of one;
-//   rows schedule:       8.8e-6 per vector of a row pair (7.7 - 9.4), e.g. bfloat16, V = 128256: 156 / 220 / 295 at
+//   rows schedule:       9.4e-6 per vector of a row pair (8 - 10), e.g. bfloat16, V = 128256: 165 / 235 / 310 at
 //                        128 / 192 / 256 drafts against 200 / 210 / 215 on the chain schedule; V = 32000, 320 drafts: 97
 //                        against 113, 512 drafts: 156 against 122.
 bool chain_preferred(const Problem &p)
@@ -1179,7 +1179,7 @@ bool chain_preferred(const Problem &p)
         t_chain = one * (1.75 * static_cast<double>(chains / (2 * units)) + (left == 0 ? 0.0 : (left <= units ? 1.0 : 1.75)));
     } else t_chain = one * static_cast<double>((chains + units - 1) / units);
     t_chain = fmax(t_chain, rows * nv * 32.0 / 6.3e6);                        // (bytes over bytes per microsecond)
-    return t_chain < rows * nv * 8.8e-6 * scale;
+    return t_chain < rows * nv * 9.4e-6 * scale;
 }
 
 hipError_t launch_chain_main(const Problem &p)
