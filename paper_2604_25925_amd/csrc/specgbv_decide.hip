@@ -85,15 +85,6 @@ __device__ double clamp01(double h)
     return h < 1.0 ? h : 1.0;
 }
 
-// A double of lane `src` (wave-uniform) in every lane.
-__device__ __forceinline__ double lane_value(double v, int src)
-{
-    const long long bits = __double_as_longlong(v);
-    const unsigned lo = __builtin_amdgcn_readlane(static_cast<int>(bits), src);
-    const unsigned hi = __builtin_amdgcn_readlane(static_cast<int>(bits >> 32), src);
-    return __longlong_as_double(static_cast<long long>((static_cast<unsigned long long>(hi) << 32) | lo));
-}
-
 struct DecideIO {
     const int32_t *tokens;
     const RowStat *stats;
@@ -483,64 +474,22 @@ __device__ __forceinline__ void decide_kseq(const T *target, const T *draft, con
 
 // ------------------------------------------------------------ final token
 
-// A lane's 8 entries of a segment of one row, as loaded (16-byte loads at any address; nothing is unpacked before it is
-// needed, so that the loads of several segments and of both rows travel together).
-template <typename T> struct SegVec { U4 v[8 / Elem<T>::kPerVec]; };
-
-// Entries [e0, e0 + 8) of a row of V; a lane beyond the row's end reads its first entries instead (seg_unpack masks
-// them), and only the one lane that straddles the end goes entry by entry, later.
-template <typename T>
-__device__ __forceinline__ SegVec<T> seg_load(const T *row, long long e0, int V)
-{
-    constexpr int PV = Elem<T>::kPerVec;
-    SegVec<T> r;
-    if (V < 8) {                                            // uniform
-#pragma unroll
-        for (int i = 0; i < 8 / PV; ++i) r.v[i] = U4{0, 0, 0, 0};
-        return r;
-    }
-    const long long at = e0 + 8 <= V ? e0 : 0;
-#pragma unroll
-    for (int i = 0; i < 8 / PV; ++i) r.v[i] = load16_any(row + at + i * PV);
-    return r;
-}
-
-// The entries as floats; those at or beyond V are `fill`.
-template <typename T>
-__device__ __forceinline__ void seg_unpack(const SegVec<T> &r, const T *row, long long e0, int V, float fill, float (&z)[8])
-{
-    constexpr int PV = Elem<T>::kPerVec;
-#pragma unroll
-    for (int i = 0; i < 8 / PV; ++i) {
-        float t[PV];
-        Elem<T>::unpack(r.v[i], t);
-#pragma unroll
-        for (int j = 0; j < PV; ++j) z[i * PV + j] = t[j];
-    }
-    if (e0 + 8 > V) {
-        asm volatile("");                                   // (a branch that all waves but the last segment's skip)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) z[j] = e0 + j < V ? Elem<T>::scalar(row + e0 + j) : fill;
-    }
-}
-
 // This lane's 8 logits of segment `seg` from the target row and (unless the bonus row is drawn from) the draft row;
 // entries at or beyond V read as -inf / 0.
 template <typename T>
 __device__ __forceinline__ void segment_load(const T *target, const T *draft, const Selection &sl, int V, int seg,
                                              int lane, SegVec<T> &q, SegVec<T> &p)
 {
-    const long long e0 = static_cast<long long>(seg) * kSegElems + lane * 8;
-    q = seg_load(target + sl.target_row * V, e0, V);
-    p = seg_load(sl.draft_row >= 0 ? draft + sl.draft_row * V : target + sl.target_row * V, e0, V);
+    static_assert(kSegElems == kWave * 8, "eight entries per lane");
+    q = seg_load(target + sl.target_row * V, seg, lane, V);
+    p = seg_load(sl.draft_row >= 0 ? draft + sl.draft_row * V : target + sl.target_row * V, seg, lane, V);
 }
 template <typename T>
 __device__ __forceinline__ void segment_unpack(const SegVec<T> &q, const SegVec<T> &p, const T *target, const T *draft,
                                                const Selection &sl, int V, int seg, int lane, float (&zq)[8], float (&zp)[8])
 {
-    const long long e0 = static_cast<long long>(seg) * kSegElems + lane * 8;
-    seg_unpack(q, target + sl.target_row * V, e0, V, -INFINITY, zq);
-    if (sl.draft_row >= 0) seg_unpack(p, draft + sl.draft_row * V, e0, V, 0.0f, zp);
+    seg_unpack(q, target + sl.target_row * V, seg, lane, V, -INFINITY, zq);
+    if (sl.draft_row >= 0) seg_unpack(p, draft + sl.draft_row * V, seg, lane, V, 0.0f, zp);
     else {
 #pragma unroll
         for (int j = 0; j < 8; ++j) zp[j] = 0.0f;
@@ -732,7 +681,7 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
     __shared__ double sh_excess[kSegThreads];
     __shared__ int sh_nmark;
     const int b = blockIdx.y, tid = threadIdx.x;
-    const int lane = tid & (kWave - 1), wid = tid / kWave;
+    const int lane = tid & (kWave - 1), wid = __builtin_amdgcn_readfirstlane(tid / kWave);    // (scalar: so are the segments' addresses)
     int32_t *__restrict__ out_tokens = io.out_tokens;
     double *__restrict__ res_norm = fo.res_norm, *__restrict__ u_final = fo.u_final, *__restrict__ margin_out = fo.margin;
     int32_t *__restrict__ fallback_out = fo.fallback, *__restrict__ mcount_out = fo.mcount;

@@ -151,6 +151,14 @@ __device__ __forceinline__ U4 load16_any(const T *p) {
     return U4{v.x, v.y, v.z, v.w};
 }
 
+// Eight masked entries (-inf, of weight zero in every sum), for lanes that have nothing to load: selecting an address
+// costs less than a branch around a load, which is waited for where the branch ends.
+static __device__ const uint32_t g_masked_f32[8] __attribute__((aligned(16))) = {0xFF800000u, 0xFF800000u, 0xFF800000u, 0xFF800000u, 0xFF800000u, 0xFF800000u, 0xFF800000u, 0xFF800000u};
+static __device__ const uint32_t g_masked_bf16[4] __attribute__((aligned(16))) = {0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u};
+template <typename T> __device__ __forceinline__ const T *masked_vector();
+template <> __device__ __forceinline__ const float *masked_vector<float>() { return reinterpret_cast<const float *>(g_masked_f32); }
+template <> __device__ __forceinline__ const uint16_t *masked_vector<uint16_t>() { return reinterpret_cast<const uint16_t *>(g_masked_bf16); }
+
 // ------------------------------------------------------------------- math
 
 // v_exp_f32: 2^x, about 1 ulp, flushes results below 2^-126.
@@ -743,6 +751,60 @@ __device__ __forceinline__ float block_max(float v, float *scratch) {
     float r = scratch[0];
     for (int w = 1; w < nw; ++w) r = fmaxf(r, scratch[w]);
     return r;
+}
+
+// A double of lane `src` (wave-uniform) in every lane.
+__device__ __forceinline__ double lane_value(double v, int src)
+{
+    const long long bits = __double_as_longlong(v);
+    const unsigned lo = __builtin_amdgcn_readlane(static_cast<int>(bits), src);
+    const unsigned hi = __builtin_amdgcn_readlane(static_cast<int>(bits >> 32), src);
+    return __longlong_as_double(static_cast<long long>((static_cast<unsigned long long>(hi) << 32) | lo));
+}
+
+// ---------------------------------------------------------------- segments
+
+// A lane's 8 entries of a segment of one row, as loaded (16-byte loads at any address; nothing is unpacked before it is
+// needed, so that the loads of several segments and of both rows travel together).
+template <typename T> struct SegVec { U4 v[8 / Elem<T>::kPerVec]; };
+
+// Entries [512 seg + 8 lane, ... + 8) of a row of V; a lane that reaches beyond the row's end reads its last eight entries
+// instead, and seg_unpack goes entry by entry there, later.
+template <typename T>
+__device__ __forceinline__ SegVec<T> seg_load(const T *row, int seg, int lane, int V)
+{
+    constexpr int PV = Elem<T>::kPerVec;
+    SegVec<T> r;
+    const bool some = V >= 8;                               // (uniform; a shorter row is unpacked entry by entry)
+    const T *base = some ? row + static_cast<long long>(seg) * (kWave * 8) : masked_vector<T>();
+    const int left = some ? V - 8 - seg * (kWave * 8) : 0;  // (may be negative, down to 8 - 512)
+    const int at = lane * 8 < left ? lane * 8 : left;
+#pragma unroll
+    for (int i = 0; i < 8 / PV; ++i) r.v[i] = load16_any(base + at + i * PV);
+    return r;
+}
+
+// The entries as floats; those at or beyond V are `fill`.
+template <typename T>
+__device__ __forceinline__ void seg_unpack(const SegVec<T> &r, const T *row, int seg, int lane, int V, float fill, float (&z)[8])
+{
+    constexpr int PV = Elem<T>::kPerVec;
+#pragma unroll
+    for (int i = 0; i < 8 / PV; ++i) {
+        float t[PV];
+        Elem<T>::unpack(r.v[i], t);
+#pragma unroll
+        for (int j = 0; j < PV; ++j) z[i * PV + j] = t[j];
+    }
+    const int left = V - seg * (kWave * 8);                 // entries of the row from this segment on
+    if (left < kWave * 8) {                                 // uniform: the row's last segment, not whole
+        asm volatile("");
+        if (lane * 8 + 8 > left) {
+            const T *base = row + static_cast<long long>(seg) * (kWave * 8);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) z[j] = lane * 8 + j < left ? Elem<T>::scalar(base + lane * 8 + j) : fill;
+        }
+    }
 }
 
 // ------------------------------------------------------------------ Philox

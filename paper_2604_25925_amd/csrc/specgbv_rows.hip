@@ -53,13 +53,6 @@ k_rows_begin(unsigned long long *__restrict__ words, long long nwords, int P, in
     for (long long i = at; i < batch; i += step) final_counter[i] = 0;
 }
 
-// What lanes past a part's end load: masked entries, of weight zero in every sum.
-__device__ const float4 g_masked_f32 = {-__builtin_inff(), -__builtin_inff(), -__builtin_inff(), -__builtin_inff()};
-__device__ const uint4 g_masked_bf16 = {0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u, 0xFF80FF80u};
-template <typename T> __device__ __forceinline__ const T *masked_vector();
-template <> __device__ __forceinline__ const float *masked_vector<float>() { return reinterpret_cast<const float *>(&g_masked_f32); }
-template <> __device__ __forceinline__ const uint16_t *masked_vector<uint16_t>() { return reinterpret_cast<const uint16_t *>(&g_masked_bf16); }
-
 // This thread's vectors of units [lo, lo + n) of a row pair, n <= NS * TH.  Every slot is loaded, without a
 // branch (a load under one is waited for where the branch ends): lanes and slots past the part's end read masked
 // entries, so that the sweeps need not look at the lane, and a row's last vector that is not whole is loaded from the
