@@ -834,9 +834,9 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
         }
     }
     // ---- 3. the last workgroup of the prefix to get here locates the token.  The partial
-    // stores above are device-scope accesses; the workgroup-scope release fence waits until
-    // they have completed, the barrier orders them before the first thread's counter update.
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    // stores above are device-scope accesses; every wave waits until its own have been performed,
+    // the barrier orders them before the first thread's counter update.
+    wait_for_stores();
     __syncthreads();
     if (wid != 0) return;
     {

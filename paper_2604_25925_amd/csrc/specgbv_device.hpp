@@ -644,6 +644,11 @@ __device__ __forceinline__ float integral_reference(float m, float c) { return c
 // below 2^-4000 every partial sum is 0 in float64 anyway.
 __device__ __forceinline__ int reference_shift(float from, float to) { return static_cast<int>(fmaxf(from - to, -4000.0f)); }
 
+// Until this wave's device-scope stores have been performed where other workgroups' device-scope loads see them.  A
+// workgroup-scope release fence does not wait for that (nor does a barrier): within a compute unit stores need no wait
+// to be seen, so the compiler leaves it out, and a counter advanced behind them can overtake them.
+__device__ __forceinline__ void wait_for_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // ------------------------------------------------------------- reductions
 
 // Wave-wide reductions with data-parallel-primitive moves instead of LDS permutes: shifts by

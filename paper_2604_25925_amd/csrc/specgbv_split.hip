@@ -387,13 +387,13 @@ k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, int K, in
     }
     double S = block_sum(static_cast<double>(acc), sh_d);                 // relative to 2^shift_q
     if (P > 1) {
-        // the store is a device-scope access; the workgroup-scope release fence waits until it has completed,
-        // so the counter update that follows (same thread) cannot be seen before it
+        // the store is a device-scope access; the wait lasts until it has been performed, so the counter update that
+        // follows (same thread) cannot be seen before it
         if (threadIdx.x == 0) {
             __hip_atomic_store(reinterpret_cast<unsigned long long *>(part_buf + pair * kPendParts + part),
                                static_cast<unsigned long long>(__double_as_longlong(S)), __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+            wait_for_stores();
             const int arrived = __hip_atomic_fetch_add(&arrive[pair], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             sh_last = arrived == P - 1;
         }
