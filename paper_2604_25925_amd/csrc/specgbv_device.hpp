@@ -117,11 +117,7 @@ template <> struct Elem<uint16_t> {
     __device__ static __forceinline__ float from_bits(uint32_t b) { return __uint_as_float(b << 16); }
 };
 
-__device__ __forceinline__ U4 load16(const void *p) {
-    return *reinterpret_cast<const U4 *>(p);
-}
-
-// The same with the non-temporal hint, for logits that are streamed once per kernel: they are not kept in the
+// 16-byte load with the non-temporal hint, for logits that are streamed once per kernel: they are not kept in the
 // cache levels in front of HBM, which on this chip raises the streaming rate noticeably (measured on the chain
 // kernel: float32 rows 69 % -> 76 % of the HBM peak).
 __device__ __forceinline__ U4 load16_stream(const void *p) {
@@ -494,30 +490,65 @@ __device__ __forceinline__ double pend_token_adjust(const PendRow *pend, long lo
 
 // ------------------------------------------------------- row-pair streaming
 
+// Vectors of a row of V entries: the last one may not be whole.  Rows may start at any address.
+template <typename T>
+__device__ __host__ __forceinline__ int row_vectors(int V) { return (V + Elem<T>::kPerVec - 1) / Elem<T>::kPerVec; }
+
+// Vector v of a row of V >= kPerVec entries starts at this entry: a last vector that is not whole is the row's last 16
+// bytes, which repeat entries of the vector before it (mask_repeated).
+template <typename T>
+__device__ __forceinline__ int vector_entry(int v, int V)
+{
+    const int e = v * Elem<T>::kPerVec, last = V - Elem<T>::kPerVec;
+    return e < last ? e : last;
+}
+
+// The entries of vector v that belong to the vector before it become -inf (of weight zero in every sum).
+template <typename T, int N>
+__device__ __forceinline__ void mask_repeated(float (&z)[N], int v, int V)
+{
+    if ((V & (N - 1)) != 0) {                            // uniform
+        asm volatile("");
+        const int over = (v + 1) * N - V;                // > 0 in the last vector
+        if (over > 0) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) z[j] = j < over ? -__builtin_inff() : z[j];
+        }
+    }
+}
+
 // f(first entry index, z_q[N], z_p[N]) for the entries of a (target, draft) row pair in the unit range [lo, hi),
-// N = 8 or 4 entries of one 16-byte vector (VEC; a unit is a vector) or 1 (a unit is an entry); the workgroup's
-// THREADS threads stride over the range, each keeping the loads of two vectors of either row in flight.
+// N = 8 or 4 entries of one 16-byte vector (VEC, V >= N; a unit is a vector) or 1 (a unit is an entry); the workgroup's
+// THREADS threads stride over the range, each keeping the loads of two vectors of either row in flight.  (16-byte loads at any
+// address: entry by entry, rows of 32003 bfloat16 entries took 149 us a call under two pending levels, 16 x 4 drafts of 6,
+// and 93 now; 32000 take 94.)
 // KEEP: the rows are read again soon (by the same workgroup), so they are loaded without the non-temporal hint.
-template <typename T, bool VEC, int THREADS, bool KEEP = false, typename F>
-__device__ __forceinline__ void for_each_pair_range(const T *rq, const T *rp, int lo, int hi, F f)
+// REPEAT: entries of the vector before a last one that is not whole come again, with their values (for stores); else
+// they come as -inf in both rows (for sums).
+template <typename T, bool VEC, int THREADS, bool KEEP = false, bool REPEAT = false, typename F>
+__device__ __forceinline__ void for_each_pair_range(const T *rq, const T *rp, int V, int lo, int hi, F f)
 {
     constexpr int PV = Elem<T>::kPerVec;
-    auto ld = [](const T *p) { return KEEP ? load16(p) : load16_stream(p); };
+    auto ld = [](const T *p) { return KEEP ? load16_any(p) : load16_stream_any(p); };
     if constexpr (VEC) {
+        auto one = [&](const U4 &q, const U4 &p, int v, int e) {
+            float zq[PV], zp[PV];
+            Elem<T>::unpack(q, zq);
+            Elem<T>::unpack(p, zp);
+            if constexpr (!REPEAT) { mask_repeated<T>(zq, v, V); mask_repeated<T>(zp, v, V); }
+            f(e, zq, zp);
+        };
         int v = lo + static_cast<int>(threadIdx.x);
         for (; v + THREADS < hi; v += 2 * THREADS) {             // four loads in flight per thread
-            const U4 q0 = ld(rq + static_cast<long long>(v) * PV), p0 = ld(rp + static_cast<long long>(v) * PV);
-            const U4 q1 = ld(rq + static_cast<long long>(v + THREADS) * PV);
-            const U4 p1 = ld(rp + static_cast<long long>(v + THREADS) * PV);
-            float zq[PV], zp[PV];
-            Elem<T>::unpack(q0, zq); Elem<T>::unpack(p0, zp); f(v * PV, zq, zp);
-            Elem<T>::unpack(q1, zq); Elem<T>::unpack(p1, zp); f((v + THREADS) * PV, zq, zp);
+            const int e0 = vector_entry<T>(v, V), e1 = vector_entry<T>(v + THREADS, V);
+            const U4 q0 = ld(rq + e0), p0 = ld(rp + e0), q1 = ld(rq + e1), p1 = ld(rp + e1);
+            one(q0, p0, v, e0);
+            one(q1, p1, v + THREADS, e1);
         }
         if (v < hi) {
-            float zq[PV], zp[PV];
-            Elem<T>::unpack(ld(rq + static_cast<long long>(v) * PV), zq);
-            Elem<T>::unpack(ld(rp + static_cast<long long>(v) * PV), zp);
-            f(v * PV, zq, zp);
+            const int e = vector_entry<T>(v, V);
+            const U4 q = ld(rq + e), p = ld(rp + e);
+            one(q, p, v, e);
         }
     } else {
         for (int x = lo + static_cast<int>(threadIdx.x); x < hi; x += THREADS) {
@@ -528,12 +559,11 @@ __device__ __forceinline__ void for_each_pair_range(const T *rq, const T *rp, in
 }
 
 // The whole row pair.
-template <typename T, bool VEC, int THREADS, bool KEEP = false, typename F>
+template <typename T, bool VEC, int THREADS, bool KEEP = false, bool REPEAT = false, typename F>
 __device__ __forceinline__ void for_each_pair(const T *rq, const T *rp, int V, F f)
 {
-    for_each_pair_range<T, VEC, THREADS, KEEP>(rq, rp, 0, VEC ? V / Elem<T>::kPerVec : V, f);
+    for_each_pair_range<T, VEC, THREADS, KEEP, REPEAT>(rq, rp, V, 0, VEC ? row_vectors<T>(V) : V, f);
 }
-
 
 // ------------------------------------------------------------ running sum
 

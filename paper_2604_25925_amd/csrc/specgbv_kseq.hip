@@ -290,8 +290,7 @@ hipError_t launch_kseq_typed(const Problem &p, int ndrafts)
 {
     const T *target = static_cast<const T *>(p.target);
     const T *draft = static_cast<const T *>(p.draft);
-    const bool vec = (p.V % Elem<T>::kPerVec) == 0 && (reinterpret_cast<uintptr_t>(p.target) % 16 == 0) &&
-                     (reinterpret_cast<uintptr_t>(p.draft) % 16 == 0);
+    const bool vec = p.V >= Elem<T>::kPerVec;
     const dim3 grid(static_cast<unsigned>(static_cast<long long>(p.batch) * ndrafts * p.L));
     RowStat *stats = reinterpret_cast<RowStat *>(p.ws + p.lay.stats);
     double *rho = reinterpret_cast<double *>(p.ws + p.lay.s);

@@ -68,20 +68,21 @@ k_mod_stats(const T *__restrict__ target, const T *__restrict__ draft, const int
     constexpr int PV = Elem<T>::kPerVec;
     RunningSum acc;
     if (VEC) {
-        const int nvec = V / PV;
+        const int nvec = row_vectors<T>(V);
+        auto add = [&](const U4 &raw, int v) {
+            float z[PV];
+            Elem<T>::unpack(raw, z);
+            mask_repeated<T>(z, v, V);
+            acc.add(z, c);
+        };
         int v = threadIdx.x;
         for (; v + kModThreads < nvec; v += 2 * kModThreads) {          // two loads in flight per thread
-            const U4 a = load16_stream(z_row + static_cast<long long>(v) * PV);
-            const U4 b = load16_stream(z_row + static_cast<long long>(v + kModThreads) * PV);
-            float z[PV];
-            Elem<T>::unpack(a, z); acc.add(z, c);
-            Elem<T>::unpack(b, z); acc.add(z, c);
+            const U4 a = load16_stream_any(z_row + vector_entry<T>(v, V));
+            const U4 b = load16_stream_any(z_row + vector_entry<T>(v + kModThreads, V));
+            add(a, v);
+            add(b, v + kModThreads);
         }
-        if (v < nvec) {
-            float z[PV];
-            Elem<T>::unpack(load16_stream(z_row + static_cast<long long>(v) * PV), z);
-            acc.add(z, c);
-        }
+        if (v < nvec) add(load16_stream_any(z_row + vector_entry<T>(v, V)), v);
     } else {
         for (int x = threadIdx.x; x < V; x += kModThreads) {
             const float z[1] = {Elem<T>::scalar(z_row + x)};
@@ -105,13 +106,21 @@ k_mod_stats(const T *__restrict__ target, const T *__restrict__ draft, const int
 
 constexpr int kRowSlots = 40;          // vectors per thread k_mod_row keeps: rows up to 163840 bfloat16 / 81920 float32 entries
 
+// Four floats to an address that needs the alignment of one only.
+__device__ __forceinline__ void store16_any(float *dst, float a, float b, float c, float d)
+{
+    typedef float F4 __attribute__((ext_vector_type(4)));
+    typedef F4 F4any __attribute__((aligned(4)));
+    *(__attribute__((address_space(1))) F4any *)dst = F4{a, b, c, d};
+}
+
 // 8 (or 4) consecutive floats of an output row
 template <int N>
 __device__ __forceinline__ void store_vals(float *dst, const float (&v)[N])
 {
     if (N % 4 == 0) {
 #pragma unroll
-        for (int j = 0; j < N; j += 4) *reinterpret_cast<float4 *>(dst + j) = make_float4(v[j], v[j + 1], v[j + 2], v[j + 3]);
+        for (int j = 0; j < N; j += 4) store16_any(dst + j, v[j], v[j + 1], v[j + 2], v[j + 3]);
     } else {
 #pragma unroll
         for (int j = 0; j < N; ++j) dst[j] = v[j];
@@ -140,14 +149,14 @@ k_mod_row(const T *__restrict__ target, const T *__restrict__ draft, const int32
     const int r = static_cast<int>(row % (is_draft ? M : rows_t));
     const long long bk = row / (is_draft ? M : rows_t);
     constexpr int PV = Elem<T>::kPerVec;
-    const int nvec = V / PV;                               // host: nvec <= kRowSlots * kModThreads
+    const int nvec = row_vectors<T>(V);                    // host: nvec <= kRowSlots * kModThreads
     const int tid = threadIdx.x;
     U4 v[kRowSlots];
 #pragma unroll
     for (int j = 0; j < kRowSlots; ++j) {
         const int idx = j * kModThreads + tid;
         if (j * kModThreads < nvec)                        // (uniform: slots the row does not reach issue nothing)
-            v[j] = load16_stream(z_row + static_cast<long long>(idx < nvec ? idx : nvec - 1) * PV);
+            v[j] = load16_stream_any(z_row + vector_entry<T>(idx < nvec ? idx : nvec - 1, V));
         else
             v[j] = U4{0, 0, 0, 0};
     }
@@ -157,6 +166,7 @@ k_mod_row(const T *__restrict__ target, const T *__restrict__ draft, const int32
         if (j * kModThreads + tid < nvec) {
             float z[PV];
             Elem<T>::unpack(v[j], z);
+            mask_repeated<T>(z, j * kModThreads + tid, V);
             acc.add(z, c);
         }
     }
@@ -189,7 +199,7 @@ k_mod_row(const T *__restrict__ target, const T *__restrict__ draft, const int32
             Elem<T>::unpack(v[j], z);
 #pragma unroll
             for (int e = 0; e < PV; ++e) a[e] = (fmaf(z[e], c, -h) - dlt) * kLn2f;
-            store_vals(out + static_cast<long long>(idx) * PV, a);
+            store_vals(out + vector_entry<T>(idx, V), a);          // (repeated entries: the same values again)
         }
     }
 }
@@ -283,7 +293,7 @@ k_mod_write(const T *__restrict__ target, const T *__restrict__ draft, int K, in
         const RatioConst rc(sp.lse2 - sq.lse2 + mod_log2nu(tstat, dstat, bk, rows_t, M, r, carry_log_nu[b]));
         const float log2W = static_cast<float>(log2(norm[drow]) + sq.lse2 - static_cast<double>(hq));   // relative to 2^hq
         const float Kf = static_cast<float>(K);
-        for_each_pair<T, VEC, kModThreads>(rq, rp, V, [&](int x, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair<T, VEC, kModThreads, false, true>(rq, rp, V, [&](int x, const float (&zq)[N], const float (&zp)[N]) {
             float a[N], bb[N];
 #pragma unroll
             for (int j = 0; j < N; ++j) {
@@ -294,7 +304,7 @@ k_mod_write(const T *__restrict__ target, const T *__restrict__ draft, int K, in
             if (op) store_vals(op + x, bb);
         });
     } else {
-        for_each_pair<T, VEC, kModThreads>(rq, rp, V, [&](int x, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair<T, VEC, kModThreads, false, true>(rq, rp, V, [&](int x, const float (&zq)[N], const float (&zp)[N]) {
             float a[N], bb[N];
 #pragma unroll
             for (int j = 0; j < N; ++j) {
@@ -318,14 +328,12 @@ hipError_t launch_modify_typed(const void *target_v, const void *draft_v, const 
     ModStat *tstat = reinterpret_cast<ModStat *>(ws + lay.tstat), *dstat = reinterpret_cast<ModStat *>(ws + lay.dstat);
     double *norm = norm_out ? norm_out : reinterpret_cast<double *>(ws + lay.norm);
     int32_t *fb = fallback_out ? fallback_out : reinterpret_cast<int32_t *>(ws + lay.fb);
-    const bool vec = (V % Elem<T>::kPerVec) == 0 && reinterpret_cast<uintptr_t>(target_v) % 16 == 0 &&
-                     reinterpret_cast<uintptr_t>(draft_v) % 16 == 0 && reinterpret_cast<uintptr_t>(out_logq) % 16 == 0 &&
-                     reinterpret_cast<uintptr_t>(out_logp) % 16 == 0;
+    const bool vec = V >= Elem<T>::kPerVec;
     const long long bk = static_cast<long long>(batch) * K;
     const long long n_t = bk * (M + bonus), n_d = bk * M;
     const dim3 blk(kModThreads);
     // rows short enough to stay in a workgroup's registers are read once unless a modification is pending for them
-    const bool rows_fit = vec && V / Elem<T>::kPerVec <= kRowSlots * kModThreads;
+    const bool rows_fit = vec && row_vectors<T>(V) <= kRowSlots * kModThreads;
 #define SPECGBV_MOD_LAUNCH(VEC)                                                                                   \
     do {                                                                                                          \
         if (rows_fit)                                                                                             \
@@ -374,12 +382,10 @@ k_carry_rows(const T *__restrict__ rows_q, const T *__restrict__ rows_p, const i
     constexpr int PV = Elem<T>::kPerVec;
     RunningSum aq, ap;
     if constexpr (VEC) {
-        const int nvec = V / PV;
-        for (int v = threadIdx.x; v < nvec; v += kModThreads) {
-            float z[PV];
-            Elem<T>::unpack(load16_stream(rq + static_cast<long long>(v) * PV), z); aq.add(z, c);
-            Elem<T>::unpack(load16_stream(rp + static_cast<long long>(v) * PV), z); ap.add(z, c);
-        }
+        for_each_pair<T, VEC, kModThreads>(rq, rp, V, [&](int, const float (&zq)[PV], const float (&zp)[PV]) {
+            aq.add(zq, c);
+            ap.add(zp, c);
+        });
     } else {
         for (int x = threadIdx.x; x < V; x += kModThreads) {
             const float zq[1] = {Elem<T>::scalar(rq + x)}, zp[1] = {Elem<T>::scalar(rp + x)};
@@ -419,8 +425,7 @@ hipError_t launch_carry_typed(const void *rows_q, const void *rows_p, const int3
                               const int32_t *accepted_idx, const int32_t *out_tokens, int K, int M, int bonus, int V,
                               int batch, float c, double *carry, int32_t *count, double *delta, hipStream_t stream)
 {
-    const bool vec = (V % Elem<T>::kPerVec) == 0 && reinterpret_cast<uintptr_t>(rows_q) % 16 == 0 &&
-                     reinterpret_cast<uintptr_t>(rows_p) % 16 == 0;
+    const bool vec = V >= Elem<T>::kPerVec;
     const dim3 g(static_cast<unsigned>(M), static_cast<unsigned>(batch));
     if (vec)
         hipLaunchKernelGGL((k_carry_rows<T, true>), g, dim3(kModThreads), 0, stream, static_cast<const T *>(rows_q),

@@ -17,8 +17,8 @@
 // k_ot_sum_parts instead: every row is cut into
 // parts, combined in part order by the consumers.
 //
-// Any V and any alignment is accepted (rows whose byte length is not a multiple of 16
-// take the scalar-load path).  This schedule reads every row pair twice; it is the
+// Any V and any alignment is accepted (16-byte loads need no alignment on this hardware; only rows shorter than a vector
+// go entry by entry).  This schedule reads every row pair twice; it is the
 // general fallback and the reference schedule for the on-chip "chain" kernel.
 #include "specgbv_internal.hpp"
 
@@ -56,6 +56,20 @@ __device__ __forceinline__ void pend_offsets(const int32_t *count_l, int K, int 
     if (tid == kStatThreads - 1) off_l[batch] = static_cast<int32_t>(before);     // the last thread's end is the total
 }
 
+constexpr int kAhead = 4;            // loads a thread of k_row_stats keeps in flight
+
+// Vector v of a row into its running sum, without the drafted token and without entries the vector before holds.
+template <typename T>
+__device__ __forceinline__ void add_vector(RunningSum &acc, const U4 &raw, int v, int tok, int V, float c)
+{
+    constexpr int PV = Elem<T>::kPerVec;
+    float z[PV];
+    Elem<T>::unpack(raw, z);
+    mask_repeated<T>(z, v, V);
+    leave_out(z, v == tok / PV, tok - vector_entry<T>(v, V));
+    acc.add(z, c);
+}
+
 // grid (row pairs + pending levels, 2): blocks (pair, 0 / 1) reduce the target / draft row of the pair; with
 // pending modifications blocks (pairs + l, 0) compute level l's offsets (pend_offsets) and the row blocks clear
 // the arrival counters of the level passes.
@@ -87,18 +101,23 @@ k_row_stats(const T *__restrict__ target, const T *__restrict__ draft,
     }
     const T *row = is_draft ? draft + (bk * L + r) * static_cast<long long>(V)
                             : target + (bk * (L + 1) + r) * static_cast<long long>(V);
-    constexpr int PV = Elem<T>::kPerVec;
     const int tok_raw = token_index_queued(tokens, pair);
     RunningSum acc;                               // the drafted token is left out (leave_out)
     if (VEC) {
-        const int nvec = V / PV;
-        for (int i = threadIdx.x; i < nvec; i += kStatThreads) {
-            const U4 v = load16_stream(row + static_cast<long long>(i) * PV);
+        const int nvec = row_vectors<T>(V);
+        for (int i = threadIdx.x; i < nvec; i += kAhead * kStatThreads) {
+            U4 v[kAhead];
+#pragma unroll
+            for (int a = 0; a < kAhead; ++a) {            // (no branch around a load: past the end the last vector again)
+                const int at = i + a * kStatThreads;
+                v[a] = load16_stream_any(row + vector_entry<T>(at < nvec ? at : nvec - 1, V));
+            }
             const int tok = token_index_used(tok_raw, V);
-            float z[PV];
-            Elem<T>::unpack(v, z);
-            leave_out(z, i == tok / PV, tok % PV);
-            acc.add(z, c);
+#pragma unroll
+            for (int a = 0; a < kAhead; ++a) {
+                const int at = i + a * kStatThreads;
+                if (at < nvec) add_vector<T>(acc, v[a], at, tok, V, c);
+            }
         }
     } else {
         for (int x = threadIdx.x; x < V; x += kStatThreads) {
@@ -145,7 +164,7 @@ k_row_stats_parts(const T *__restrict__ target, const T *__restrict__ draft, con
     const T *row = is_draft ? draft + (bk * L + r) * static_cast<long long>(V)
                             : target + (bk * (L + 1) + r) * static_cast<long long>(V);
     constexpr int PV = Elem<T>::kPerVec;
-    const int units = VEC ? V / PV : V;
+    const int units = VEC ? row_vectors<T>(V) : V;
     const int per = (units + P - 1) / P;
     const int lo = part * per, hi = lo + per < units ? lo + per : units;
     const int tok_raw = token_index_queued(tokens, pair);
@@ -153,20 +172,15 @@ k_row_stats_parts(const T *__restrict__ target, const T *__restrict__ draft, con
     if (VEC) {
         int i = lo + static_cast<int>(threadIdx.x);
         for (; i + kStatThreads < hi; i += 2 * kStatThreads) {            // two loads in flight per thread
-            const U4 a = load16_stream(row + static_cast<long long>(i) * PV);
-            const U4 b2 = load16_stream(row + static_cast<long long>(i + kStatThreads) * PV);
+            const U4 a = load16_stream_any(row + vector_entry<T>(i, V));
+            const U4 b2 = load16_stream_any(row + vector_entry<T>(i + kStatThreads, V));
             const int tk = token_index_used(tok_raw, V);
-            float z[PV];
-            Elem<T>::unpack(a, z); leave_out(z, i == tk / PV, tk % PV); acc.add(z, c);
-            Elem<T>::unpack(b2, z); leave_out(z, i + kStatThreads == tk / PV, tk % PV); acc.add(z, c);
+            add_vector<T>(acc, a, i, tk, V, c);
+            add_vector<T>(acc, b2, i + kStatThreads, tk, V, c);
         }
         if (i < hi) {
-            const U4 a = load16_stream(row + static_cast<long long>(i) * PV);
-            const int tk = token_index_used(tok_raw, V);
-            float z[PV];
-            Elem<T>::unpack(a, z);
-            leave_out(z, i == tk / PV, tk % PV);
-            acc.add(z, c);
+            const U4 a = load16_stream_any(row + vector_entry<T>(i, V));
+            add_vector<T>(acc, a, i, token_index_used(tok_raw, V), V, c);
         }
     } else {
         for (int x = lo + static_cast<int>(threadIdx.x); x < hi; x += kStatThreads) {
@@ -276,19 +290,19 @@ k_ot_sum_parts(const T *__restrict__ target, const T *__restrict__ draft, const 
     const T *rp = draft + pair * static_cast<long long>(V);
     constexpr int N = VEC ? Elem<T>::kPerVec : 1;
     const RatioConst rc(ratio_const(st.lse2_p, st.lse2_q, log2nu, c_rel) - sumN);
-    const int units = VEC ? V / N : V;
+    const int units = VEC ? row_vectors<T>(V) : V;
     const int per = (units + P - 1) / P;
     const int lo = part * per, hi = lo + per < units ? lo + per : units;
     float acc = 0.0f;
     if (PEND && sh_tab.n > 0) {                   // uniform over the workgroup
-        for_each_pair_range<T, VEC, kStatThreads>(rq, rp, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_range<T, VEC, kStatThreads>(rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             pending_weights(zq, zp, c, shift_q, sh_tab, rc, K, wq, w);
 #pragma unroll
             for (int j = 0; j < N; ++j) acc += w[j];
         });
     } else {
-        for_each_pair_range<T, VEC, kStatThreads>(rq, rp, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_range<T, VEC, kStatThreads>(rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
 #pragma unroll
@@ -297,7 +311,7 @@ k_ot_sum_parts(const T *__restrict__ target, const T *__restrict__ draft, const 
     }
     double total = block_sum(static_cast<double>(acc), sh_d);
     if (threadIdx.x == 0 && !(PEND && sh_tab.n > 0))
-        total = with_token_term<T>(total, st, log2nu, rq, rp, tokens + pair, V, lo * N, hi * N, c, shift_q, rc, K);
+        total = with_token_term<T>(total, st, log2nu, rq, rp, tokens + pair, V, lo * N, hi * N < V ? hi * N : V, c, shift_q, rc, K);
     // (whether the row's s and g nearly cancel, so that Eq. (hik) needs nu^2 (s - g) summed term by term, only the sum
     // over all parts can tell: the final-token kernel looks at it)
     if (threadIdx.x == 0) s_part[pair * kPendParts + part] = total * exp2(static_cast<double>(shift_q) - st.lse2_q - sumN);
@@ -366,19 +380,19 @@ k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, int K, in
     const T *rq = target + (bk * (L + 1) + r) * static_cast<long long>(V);
     const T *rp = draft + pair * static_cast<long long>(V);
     constexpr int N = VEC ? Elem<T>::kPerVec : 1;
-    const int units = VEC ? V / N : V;
+    const int units = VEC ? row_vectors<T>(V) : V;
     const int per = (units + P - 1) / P;
     const int lo = part * per, hi = lo + per < units ? lo + per : units;
     float acc = 0.0f;
     if (sh_tab.n == 0) {
-        for_each_pair_range<T, VEC, kStatThreads>(rq, rp, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_range<T, VEC, kStatThreads>(rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
 #pragma unroll
             for (int jj = 0; jj < N; ++jj) acc += w[jj];
         });
     } else {
-        for_each_pair_range<T, VEC, kStatThreads>(rq, rp, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_range<T, VEC, kStatThreads>(rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             pending_weights(zq, zp, c, shift_q, sh_tab, rc, K, wq, w);
 #pragma unroll
@@ -504,9 +518,7 @@ hipError_t launch_typed(const Problem &p)
     double *s = reinterpret_cast<double *>(p.ws + p.lay.s);
     int32_t *counter = reinterpret_cast<int32_t *>(p.ws + p.lay.counter);
     const long long pairs = static_cast<long long>(p.batch) * p.K * p.L;
-    const bool vec = (p.V % Elem<T>::kPerVec) == 0 &&
-                     (reinterpret_cast<uintptr_t>(p.target) % 16 == 0) &&
-                     (reinterpret_cast<uintptr_t>(p.draft) % 16 == 0);
+    const bool vec = p.V >= Elem<T>::kPerVec;
     int32_t *pend_off = reinterpret_cast<int32_t *>(p.ws + p.lay.pend_off);
     int32_t *pend_cnt = p.pend_levels > 0 ? reinterpret_cast<int32_t *>(p.ws + p.lay.pend_cnt) : nullptr;
     double *pend_part = reinterpret_cast<double *>(p.ws + p.lay.pend_part);

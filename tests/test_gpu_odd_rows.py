@@ -1,0 +1,38 @@
+"""Rows that are not a multiple of the 16-byte vector on the two-pass schedule, in Algorithm 2 and under pending
+modifications: every remainder, rows of one vector and less (needs an MI355X: run with -m gpu)."""
+import numpy as np
+import pytest
+
+from parity_util import check_case
+from specgbv_synth import Workload, make_inputs
+from test_gpu_modification import _check_modify
+from test_gpu_pending import check_pending
+
+pytestmark = pytest.mark.gpu
+
+SHAPES = [(V, "bf16") for V in (5, 8, 9, 15, 4097, 4103, 8198)] + [(V, "f32") for V in (3, 4, 5, 7, 2049, 4094, 8199)]
+
+
+def _inputs(B, K, L, V, dtype):
+    t, d, tok = make_inputs(Workload("odd", B, K, L, V, dtype, 2.0, 0.8, head=min(8, V // 2), temperature=0.9), seed=3 + V)
+    tok[:, 0, -1] = V - 1                                  # a drafted token in the vector that is not whole
+    return t, d, tok
+
+
+@pytest.mark.parametrize("V,dtype", SHAPES)
+def test_two_pass(V, dtype):
+    t, d, tok = _inputs(3, 2, 3, V, dtype)
+    check_case(t, d, tok, 0.9, 4, 1, "split", "odd rows split %d %s" % (V, dtype))
+
+
+@pytest.mark.parametrize("V,dtype", SHAPES)
+def test_modify(V, dtype):
+    t, d, tok = _inputs(2, 3, 3, V, dtype)
+    _check_modify(np.ascontiguousarray(t[:, :, :3]), d, tok, 0.9, np.array([0.2, -0.4]), np.array([2, 1], np.int32), "odd rows modify %d %s" % (V, dtype))
+
+
+@pytest.mark.parametrize("V,dtype", [s for s in SHAPES if s[0] > 100])
+def test_pending(V, dtype):
+    t, d, tok = _inputs(6, 2, 4, V, dtype)
+    rng = np.random.default_rng(V)
+    check_pending(t, d, tok, 0.9, 4, 1, rng.normal(0, 0.5, 6), rng.integers(0, 4, 6).astype(np.int32), "odd rows pending %d %s" % (V, dtype))
