@@ -290,7 +290,7 @@ hipError_t launch_kseq_typed(const Problem &p, int ndrafts)
 {
     const T *target = static_cast<const T *>(p.target);
     const T *draft = static_cast<const T *>(p.draft);
-    const bool vec = p.V >= Elem<T>::kPerVec;
+    const bool vec = read_by_vectors<T>(p.V);
     const dim3 grid(static_cast<unsigned>(static_cast<long long>(p.batch) * ndrafts * p.L));
     RowStat *stats = reinterpret_cast<RowStat *>(p.ws + p.lay.stats);
     double *rho = reinterpret_cast<double *>(p.ws + p.lay.s);

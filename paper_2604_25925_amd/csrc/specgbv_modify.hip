@@ -328,7 +328,7 @@ hipError_t launch_modify_typed(const void *target_v, const void *draft_v, const 
     ModStat *tstat = reinterpret_cast<ModStat *>(ws + lay.tstat), *dstat = reinterpret_cast<ModStat *>(ws + lay.dstat);
     double *norm = norm_out ? norm_out : reinterpret_cast<double *>(ws + lay.norm);
     int32_t *fb = fallback_out ? fallback_out : reinterpret_cast<int32_t *>(ws + lay.fb);
-    const bool vec = V >= Elem<T>::kPerVec;
+    const bool vec = read_by_vectors<T>(V);
     const long long bk = static_cast<long long>(batch) * K;
     const long long n_t = bk * (M + bonus), n_d = bk * M;
     const dim3 blk(kModThreads);
@@ -425,7 +425,7 @@ hipError_t launch_carry_typed(const void *rows_q, const void *rows_p, const int3
                               const int32_t *accepted_idx, const int32_t *out_tokens, int K, int M, int bonus, int V,
                               int batch, float c, double *carry, int32_t *count, double *delta, hipStream_t stream)
 {
-    const bool vec = V >= Elem<T>::kPerVec;
+    const bool vec = read_by_vectors<T>(V);
     const dim3 g(static_cast<unsigned>(M), static_cast<unsigned>(batch));
     if (vec)
         hipLaunchKernelGGL((k_carry_rows<T, true>), g, dim3(kModThreads), 0, stream, static_cast<const T *>(rows_q),

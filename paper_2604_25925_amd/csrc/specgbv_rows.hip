@@ -427,6 +427,7 @@ int rows_schedule_parts(const Problem &p)
     const long long pairs = static_cast<long long>(p.batch) * p.K * p.L;
     if (p.V < pv || p.L >= kRowsMaxL) return 0;
     const int nv = (p.V + pv - 1) / pv;
+    if (!(p.dtype == 1 ? read_by_vectors<uint16_t>(p.V) : read_by_vectors<float>(p.V))) return 0;   // (two-pass, for accuracy)
     // a handful of rows shorter than one load per thread: the two-pass kernels, which need no marks to wait on (V = 1000,
     // 8 float32 row pairs: 19.0 us a call against 20.0; from 200 row pairs on, or with longer rows, this schedule is ahead)
     if (nv < 512 && pairs * 2 <= compute_units()) return 0;

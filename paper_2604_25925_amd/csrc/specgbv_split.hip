@@ -518,7 +518,7 @@ hipError_t launch_typed(const Problem &p)
     double *s = reinterpret_cast<double *>(p.ws + p.lay.s);
     int32_t *counter = reinterpret_cast<int32_t *>(p.ws + p.lay.counter);
     const long long pairs = static_cast<long long>(p.batch) * p.K * p.L;
-    const bool vec = p.V >= Elem<T>::kPerVec;
+    const bool vec = read_by_vectors<T>(p.V);
     int32_t *pend_off = reinterpret_cast<int32_t *>(p.ws + p.lay.pend_off);
     int32_t *pend_cnt = p.pend_levels > 0 ? reinterpret_cast<int32_t *>(p.ws + p.lay.pend_cnt) : nullptr;
     double *pend_part = reinterpret_cast<double *>(p.ws + p.lay.pend_part);

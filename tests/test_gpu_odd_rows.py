@@ -36,3 +36,11 @@ def test_pending(V, dtype):
     t, d, tok = _inputs(6, 2, 4, V, dtype)
     rng = np.random.default_rng(V)
     check_pending(t, d, tok, 0.9, 4, 1, rng.normal(0, 0.5, 6), rng.integers(0, 4, 6).astype(np.int32), "odd rows pending %d %s" % (V, dtype))
+
+
+@pytest.mark.parametrize("algo", ["auto", "split"])
+def test_many_drafts_of_short_odd_rows(algo):
+    """600 prompts: among so many rows some have nearly equal sums in Eq. (hik), and h then takes ln nu to 2e-7."""
+    t, d, tok = make_inputs(Workload("short", 600, 2, 3, 100, "bf16", 2.5, 0.9, head=20, temperature=0.8), seed=5)
+    tok[:, 0, -1] = 99
+    check_case(t, d, tok, 0.8, 3, 1, algo, "odd rows, 600 prompts")
