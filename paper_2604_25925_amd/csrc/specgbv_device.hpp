@@ -597,6 +597,40 @@ struct RunningSum {
     }
 };
 
+// 2^x for the terms of a sum in float64, relative error 2e-10: a polynomial of the eighth degree.
+__device__ __forceinline__ double exp2_term(double x)
+{
+    const double n = rint(x), f = (x - n) * 0.693147180559945309417;         // |f| <= 0.3466
+    double p = 1.0 / 40320.0;
+    p = fma(p, f, 1.0 / 5040.0);
+    p = fma(p, f, 1.0 / 720.0);
+    p = fma(p, f, 1.0 / 120.0);
+    p = fma(p, f, 1.0 / 24.0);
+    p = fma(p, f, 1.0 / 6.0);
+    p = fma(p, f, 0.5);
+    p = fma(p, f, 1.0);
+    p = fma(p, f, 1.0);
+    return x < -1000.0 ? 0.0 : ldexp(p, static_cast<int>(n));
+}
+
+// RunningSum with its terms and their sum in float64, for lanes that add up several vectors of a row of few entries.
+struct RunningSum64 {
+    float m2 = -3.0e38f;
+    double Z = 0.0;
+    template <int N>
+    __device__ __forceinline__ void add(const float (&z)[N], float c) {
+        float vm = z[0];
+#pragma unroll
+        for (int j = 1; j < N; ++j) vm = fmaxf(vm, z[j]);
+        const float n2 = fmaxf(m2, vm * c);
+        double a = Z * exp2_term(static_cast<double>(m2) - static_cast<double>(n2));
+#pragma unroll
+        for (int j = 0; j < N; ++j) a += exp2_term(fma(static_cast<double>(z[j]), static_cast<double>(c), -static_cast<double>(n2)));
+        Z = a;
+        m2 = n2;
+    }
+};
+
 // The drafted token is left out of a row's float32 sums: `here` says that the vector z holds it, as entry `elem`, and
 // its weight becomes 2^(-inf) = 0.  Its weight is added in float64 where the row's partial sums meet (with_token).
 // A row whose mass sits on its drafted token (probability 0.9999 and beyond: low temperatures) then keeps the mass of

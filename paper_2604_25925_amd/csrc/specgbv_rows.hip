@@ -386,12 +386,128 @@ k_rows(const T *__restrict__ target, const T *__restrict__ draft, RowsArgs ar)
     }
 }
 
+// Short rows (short_rows): one workgroup per draft, one wave per row pair, both sweeps in one launch.
+// A row is a few loads per lane here, and what such a call takes is launches and barriers: K = 2, L = 4, V = 1000 float32
+// took 4.3 + 3.6 us in two kernels and the gap between them (19.1 us a call), and takes 17.5 us a call.
+constexpr int kShortRows = 16;                         // waves of a workgroup, and rows of a draft
+
+// The range of k_short_rows.  Its terms of sweep 1 are summed in float64 (a lane adds up to 32 entries of a row, and in
+// float32 the error of ln nu would be 3e-7 where the other schedules' lanes, with fewer entries each, have 1.2e-7).  With
+// few drafts the time of one row counts: one prompt, L = 8, bfloat16, a call takes 18.0 us with V = 1024 and 22.8 with
+// V = 2048, on the other schedules 19.0 and 19.5.  With a draft for every compute unit, the workgroups and barriers per
+// row count: 64 x 4 drafts of 8, V = 2048, 32.5 us and 46.5, 500 x 8 of 16 355 and 820; 40 x 2 of 16 still 37.3 and 35.0.
+bool short_rows(const Problem &p)
+{
+    const long long drafts = static_cast<long long>(p.batch) * p.K;
+    return (p.V <= 1024 && p.L <= 8) || (p.V <= 2048 && p.L <= kShortRows && drafts >= compute_units());
+}
+
+template <typename T>
+__global__ void __launch_bounds__(kShortRows * kWave)
+k_short_rows(const T *__restrict__ target, const T *__restrict__ draft, const int32_t *__restrict__ tokens, int K, int L, int V,
+             float c, double c_rel, RowStat *__restrict__ stats, double *__restrict__ s_out, double *__restrict__ e_out,
+             int32_t *__restrict__ final_counter)
+{
+    __shared__ double sh_lse[2 * kShortRows], sh_tok[2 * kShortRows];
+    constexpr int PV = Elem<T>::kPerVec;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), r = __builtin_amdgcn_readfirstlane(tid / kWave);   // wave r: row pair r
+    const int nv = row_vectors<T>(V);
+    const long long bk = blockIdx.x;
+    if (tid == 0 && bk % K == 0) final_counter[bk / K] = 0;              // arrival counter of the final-token kernel
+    const T *const rq = target + (bk * (L + 1) + r) * static_cast<long long>(V);
+    const T *const rp = draft + (bk * L + r) * static_cast<long long>(V);
+    // f(v, z_q, z_p) for this lane's vectors of the row pair
+    auto sweep = [&](auto f) {
+        for (int v = lane; v < nv; v += 2 * kWave) {
+            const int w = v + kWave < nv ? v + kWave : v;                // (no branch around a load)
+            const U4 q0 = load16_stream_any(rq + vector_entry<T>(v, V)), p0 = load16_stream_any(rp + vector_entry<T>(v, V));
+            const U4 q1 = load16_stream_any(rq + vector_entry<T>(w, V)), p1 = load16_stream_any(rp + vector_entry<T>(w, V));
+            float zq[PV], zp[PV];
+            Elem<T>::unpack(q0, zq); Elem<T>::unpack(p0, zp);
+            mask_repeated<T>(zq, v, V); mask_repeated<T>(zp, v, V);
+            f(v, zq, zp);
+            if (w != v) {
+                Elem<T>::unpack(q1, zq); Elem<T>::unpack(p1, zp);
+                mask_repeated<T>(zq, w, V); mask_repeated<T>(zp, w, V);
+                f(w, zq, zp);
+            }
+        }
+    };
+    int tok = tokens[bk * L + r];
+    tok = tok < 0 ? 0 : (tok >= V ? V - 1 : tok);
+    const float ztok = Elem<T>::scalar((lane & 1) ? rp + tok : rq + tok);
+    RunningSum64 aq, ap;                               // the drafted token is left out (leave_out)
+    const int tok_v = tok / PV, tok_e = tok - vector_entry<T>(tok / PV, V);
+    sweep([&](int v, float (&zq)[PV], float (&zp)[PV]) {
+        leave_out(zq, v == tok_v, tok_e);
+        leave_out(zp, v == tok_v, tok_e);
+        aq.add(zq, c);
+        ap.add(zp, c);
+    });
+    const float Mq = wave_max(aq.m2), Mp = wave_max(ap.m2);
+    const double Zq = wave_sum(aq.Z > 0.0 ? aq.Z * exp2_small(static_cast<double>(aq.m2) - static_cast<double>(Mq)) : 0.0);
+    const double Zp = wave_sum(ap.Z > 0.0 ? ap.Z * exp2_small(static_cast<double>(ap.m2) - static_cast<double>(Mp)) : 0.0);
+    {                                                  // even lanes: the target's row, odd lanes: the draft's
+        const double Z0 = (lane & 1) ? Zp : Zq, ref = static_cast<double>((lane & 1) ? Mp : Mq);
+        const double t = static_cast<double>(ztok) * static_cast<double>(c);
+        const double top = Z0 > 0.0 ? fmax(ref, t) : t;
+        const double Z = (Z0 > 0.0 ? Z0 * exp2_small(ref - top) : 0.0) + (t - top == 0.0 ? 1.0 : exp2_small(t - top));
+        const double lse = top + rows_log2(Z);
+        if (lane < 2) { sh_lse[2 * r + lane] = lse; sh_tok[2 * r + lane] = token_scaled(t, lse, c_rel); }
+    }
+    __syncthreads();
+    RowStat st;
+    st.lse2_q = sh_lse[2 * r]; st.lse2_p = sh_lse[2 * r + 1];
+    st.tok2_q = sh_tok[2 * r]; st.tok2_p = sh_tok[2 * r + 1];
+    if (lane == 0) stats[bk * L + r] = st;
+    if (r == 0) return;
+    const int j = lane < r ? lane : 0;                 // lane j: row j of the rows before this one
+    const double lp = lane < r ? sh_tok[2 * j + 1] - sh_lse[2 * j + 1] : 0.0;
+    const double log2P = wave_sum(lp);
+    const double log2nu = wave_sum(lane < r ? sh_tok[2 * j] - sh_lse[2 * j] - lp : 0.0);
+    const float shift_q = static_cast<float>(st.lse2_q);
+    const RatioConst rc(ratio_const(st.lse2_p, st.lse2_q, log2nu, c_rel));
+    double acc = 0.0;
+    sweep([&](int, float (&zq)[PV], float (&zp)[PV]) {
+        float wq[PV], w[PV];
+        ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
+#pragma unroll
+        for (int e = 0; e < PV; ++e) acc += static_cast<double>(w[e]);
+    });
+    const double total = with_token_term<T>(wave_sum(acc), st, log2nu, rq, rp, tokens + (bk * L + r), V, 0, V,
+                                            c, shift_q, rc, K);
+    const double s = total * exp2_small(static_cast<double>(shift_q) - st.lse2_q);
+    double e = -1.0;
+    // where s and g nearly cancel, Eq. (hik) needs nu^2 (s - g) summed term by term (see excess_wanted; wave-uniform)
+    if (excess_wanted(static_cast<float>(log2nu), static_cast<float>(s), K) && excess_needed(log2nu, log2P, s, K)) {
+        const ExcessConst ec = make_excess_const(st.lse2_q, st.lse2_p, log2nu, K, c);
+        double ex = 0.0;
+        sweep([&](int, float (&zq)[PV], float (&zp)[PV]) {
+#pragma unroll
+            for (int x = 0; x < PV; ++x) {
+                const float q1[1] = {zq[x]}, p1[1] = {zp[x]};
+                ex += static_cast<double>(excess_terms(q1, p1, ec));
+            }
+        });
+        e = wave_sum(ex) * ec.scale;
+    }
+    if (lane == 0) { s_out[bk * L + r] = s; e_out[bk * L + r] = e; }
+}
+
 template <typename T>
 hipError_t launch_rows_typed(const Problem &p)
 {
     constexpr int PV = Elem<T>::kPerVec;
     const long long pairs = static_cast<long long>(p.batch) * p.K * p.L;
     const int P = p.rows_parts;
+    if (short_rows(p)) {
+        hipLaunchKernelGGL((k_short_rows<T>), dim3(static_cast<unsigned>(p.batch) * static_cast<unsigned>(p.K)),
+                           dim3(static_cast<unsigned>(p.L) * kWave), 0, p.stream,
+                           static_cast<const T *>(p.target), static_cast<const T *>(p.draft), p.tokens, p.K, p.L, p.V, p.c, p.c_rel,
+                           reinterpret_cast<RowStat *>(p.ws + p.lay.stats), reinterpret_cast<double *>(p.ws + p.lay.s),
+                           reinterpret_cast<double *>(p.ws + p.lay.excess), reinterpret_cast<int32_t *>(p.ws + p.lay.counter));
+        return hipGetLastError();
+    }
     RowsArgs ar;
     ar.tokens = p.tokens;
     ar.words = reinterpret_cast<unsigned long long *>(p.ws + p.lay.stat_part);
@@ -427,8 +543,9 @@ int rows_schedule_parts(const Problem &p)
     const long long pairs = static_cast<long long>(p.batch) * p.K * p.L;
     if (p.V < pv || p.L >= kRowsMaxL) return 0;
     const int nv = (p.V + pv - 1) / pv;
+    if (short_rows(p)) return 1;                           // (k_short_rows: whole rows)
     if (!(p.dtype == 1 ? read_by_vectors<uint16_t>(p.V) : read_by_vectors<float>(p.V))) return 0;   // (two-pass, for accuracy)
-    // a handful of rows shorter than one load per thread: the two-pass kernels, which need no marks to wait on (V = 1000,
+    // few row pairs shorter than one load per thread: the two-pass kernels, which need no marks to wait on (V = 1000,
     // 8 float32 row pairs: 19.0 us a call against 20.0; from 200 row pairs on, or with longer rows, this schedule is ahead)
     if (nv < 512 && pairs * 2 <= compute_units()) return 0;
     static_assert((kRowParts & (kRowParts - 1)) == 0, "a power of two");
