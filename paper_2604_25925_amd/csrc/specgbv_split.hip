@@ -17,9 +17,9 @@
 // k_ot_sum_parts instead: every row is cut into
 // parts, combined in part order by the consumers.
 //
-// Any V and any alignment is accepted (16-byte loads need no alignment on this hardware; only rows shorter than a vector
-// go entry by entry).  This schedule reads every row pair twice; it is the
-// general fallback and the reference schedule for the on-chip "chain" kernel.
+// Any V and any alignment is accepted (16-byte loads need no alignment on this hardware; short rows that are not a
+// multiple of the vector go entry by entry, see read_by_vectors).  This schedule reads every row pair twice; it serves
+// pending modifications, a few short rows, and callers who ask for it, the reference for the schedules that read once.
 #include "specgbv_internal.hpp"
 
 namespace specgbv {
