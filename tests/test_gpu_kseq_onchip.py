@@ -16,3 +16,11 @@ pytestmark = pytest.mark.gpu
 def test_tiles(B, K, L, V, dtype):
     t, d, tok = make_inputs(Workload("kseq", B, K, L, V, dtype, 2.5, 0.8, head=min(8, V // 2), temperature=0.8), seed=3)
     check(t, d, tok, 0.8, 3, 1, None, "K-SEQ tiles %s" % ((B, K, L, V, dtype),), rho_tol=3.0)
+
+
+@pytest.mark.parametrize("B,L,V,sigma_d,T,seed", [(64, 4, 301, 1.0, 0.4, 5), (64, 3, 100, 0.25, 0.3, 1)])
+def test_roots_behind_a_change_of_slope(B, L, V, sigma_d, T, seed):
+    """Low temperatures: one entry holds nearly all mass, and the equation for rho turns flat by orders of magnitude as
+    rho p passes q there, so that a short Newton step in front of that point says nothing about the root."""
+    t, d, tok = make_inputs(Workload("kink", B, 4, L, V, "bf16", 3.0, sigma_d, head=min(50, V // 4), temperature=T), seed=seed)
+    check(t, d, tok, T, 1, 1, None, "K-SEQ roots behind a change of slope V=%d" % V)
