@@ -238,31 +238,40 @@ k_kseq_onchip(const T *__restrict__ target, const T *__restrict__ draft, const i
                 if (e < cut) { zq[e] = -__builtin_inff(); zp[e] = -__builtin_inff(); }
         }
     };
-    float mq = -3.0e38f, mp = -3.0e38f;
+    // Statistics: a running reference per lane, as in k_kseq_rows.  A row that is not a multiple of the vector and gives no
+    // lane more than one is summed in float64: entry by entry a lane would add up two of them at most, and eight terms
+    // relative to one reference cost accuracy there (ln-normalisers at V = 100 bfloat16, T = 0.8: relative to one reference
+    // for the whole row in float32 5.3e-8 rms and 2.6e-7 at most, entry by entry 2e-8 and 6e-8, in float64 4e-11 at most).
+    float m2q = -3.0e38f, m2p = -3.0e38f;
+    double zsum_q = 0.0, zsum_p = 0.0;
+    if (read_by_vectors<T>(V)) {                           // uniform
+        RunningSum aq, ap;
 #pragma unroll
-    for (int j = 0; j < NS; ++j) {
+        for (int j = 0; j < NS; ++j) {
+            if (j * kKseqThreads < nv) {                   // uniform
+                float zq[PV], zp[PV];
+                unpack(j, zq, zp);
+                aq.add(zq, c);
+                ap.add(zp, c);
+            }
+            // (opaque touches: the unpacked floats are not kept for the sweeps)
+            asm volatile("" : "+v"(q[j].x), "+v"(q[j].y), "+v"(q[j].z), "+v"(q[j].w), "+v"(aq.Z));
+            asm volatile("" : "+v"(p[j].x), "+v"(p[j].y), "+v"(p[j].z), "+v"(p[j].w), "+v"(ap.Z));
+        }
+        m2q = aq.m2; m2p = ap.m2;
+        zsum_q = static_cast<double>(aq.Z); zsum_p = static_cast<double>(ap.Z);
+    } else {                                               // (nv <= kKseqThreads: slot 0 holds the row)
+        RunningSum64 aq, ap;
         float zq[PV], zp[PV];
-        Elem<T>::unpack(q[j], zq);                         // (an entry read twice changes no maximum)
-        Elem<T>::unpack(p[j], zp);
-#pragma unroll
-        for (int e = 0; e < PV; ++e) { mq = fmaxf(mq, zq[e]); mp = fmaxf(mp, zp[e]); }
-        asm volatile("" : "+v"(q[j].x), "+v"(q[j].y), "+v"(q[j].z), "+v"(q[j].w), "+v"(mq));
-        asm volatile("" : "+v"(p[j].x), "+v"(p[j].y), "+v"(p[j].z), "+v"(p[j].w), "+v"(mp));
+        unpack(0, zq, zp);
+        aq.add(zq, c);
+        ap.add(zp, c);
+        m2q = aq.m2; m2p = ap.m2;
+        zsum_q = aq.Z; zsum_p = ap.Z;
     }
-    const float Mq = block_max(mq * c, sh_f), Mp = block_max(mp * c, sh_f);
-    float aq = 0.0f, ap = 0.0f;
-#pragma unroll
-    for (int j = 0; j < NS; ++j) {
-        float zq[PV], zp[PV];
-        unpack(j, zq, zp);
-        float a = 0.0f, b2 = 0.0f;
-#pragma unroll
-        for (int e = 0; e < PV; ++e) { a += exp2_fast(fmaf(zq[e], c, -Mq)); b2 += exp2_fast(fmaf(zp[e], c, -Mp)); }
-        aq += a; ap += b2;
-        asm volatile("" : "+v"(q[j].x), "+v"(q[j].y), "+v"(q[j].z), "+v"(q[j].w), "+v"(aq));
-        asm volatile("" : "+v"(p[j].x), "+v"(p[j].y), "+v"(p[j].z), "+v"(p[j].w), "+v"(ap));
-    }
-    const double Zq = block_sum(static_cast<double>(aq), sh_d), Zp = block_sum(static_cast<double>(ap), sh_d);
+    const float Mq = block_max(m2q, sh_f), Mp = block_max(m2p, sh_f);
+    const double Zq = block_sum(zsum_q > 0.0 ? zsum_q * exp2_small(static_cast<double>(m2q) - static_cast<double>(Mq)) : 0.0, sh_d);
+    const double Zp = block_sum(zsum_p > 0.0 ? zsum_p * exp2_small(static_cast<double>(m2p) - static_cast<double>(Mp)) : 0.0, sh_d);
     const double lse2_q = static_cast<double>(Mq) + log2(Zq), lse2_p = static_cast<double>(Mp) + log2(Zp);
     if (tid == 0) kseq_store_stats(w, rq, rp, tokens, V, lse2_q, lse2_p, c, c_rel, stats);
     const int n = __builtin_amdgcn_readfirstlane(sh_n);    // (the block sums above contain the barriers that publish it)
@@ -286,7 +295,7 @@ k_kseq_onchip(const T *__restrict__ target, const T *__restrict__ draft, const i
         float C = 0.0f, S = 0.0f, Dr = 0.0f;               // C: mass of q where rho p >= q
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
-            const float r = fmaf(rf, rw[e], rl * rw[e]);   // rho p / q
+            const float r = fmaf(rf, rw[e], rl * rw[e]);   // rho p / q (where p / q overflows r may be NaN: then not open)
             const float s = 1.0f - r;
             const bool open = s > 0.0f;                    // rho p < q, the same for all three sums
             Dr = fmaf(ew[e], open ? r : 0.0f, Dr);

@@ -1,7 +1,9 @@
 """K-SEQ rows kept in registers, at the edges of their two tiles (16 and 64 entries for each of 512 threads) and with
 every remainder of a vector, against the oracle (needs an MI355X: run with -m gpu)."""
+import numpy as np
 import pytest
 
+from parity_util import to_torch
 from specgbv_synth import Workload, make_inputs
 from test_gpu_comparison import check
 
@@ -24,3 +26,26 @@ def test_roots_behind_a_change_of_slope(B, L, V, sigma_d, T, seed):
     rho p passes q there, so that a short Newton step in front of that point says nothing about the root."""
     t, d, tok = make_inputs(Workload("kink", B, 4, L, V, "bf16", 3.0, sigma_d, head=min(50, V // 4), temperature=T), seed=seed)
     check(t, d, tok, T, 1, 1, None, "K-SEQ roots behind a change of slope V=%d" % V)
+
+
+@pytest.mark.parametrize("V,dtype,T", [(13, "bf16", 0.8), (100, "bf16", 0.8), (1003, "bf16", 0.4), (4095, "bf16", 0.7),
+                                       (5, "f32", 1.0), (101, "f32", 0.8), (2047, "f32", 0.7)])
+def test_normalisers_of_short_odd_rows(V, dtype, T):
+    """Rows that are not a multiple of the vector and give no thread more than one: their normalisers are summed in float64.
+    Bound: the scaled logits' scale is float32(log2 e / T) on both sides; a term's exponential is good to 2e-10, the sum
+    and the logarithm to 1e-14: 1e-9 in ln Z.  (A float32 sum relative to one reference is off by up to 2.6e-7 here.)"""
+    import torch
+    import paper_2604_25925_amd as sg
+    B, K, L = 40, 4, 3
+    t, d, tok = make_inputs(Workload("norm", B, K, L, V, dtype, 3.0, 1.0, head=max(1, min(50, V // 4)), temperature=T), seed=5)
+    tl, dl = to_torch(t), to_torch(d)
+    ws = sg.specgbv_verify_kseq(tl, dl, to_torch(tok), T, 1, 1)[3]
+    torch.cuda.synchronize()
+    got = sg.specgbv_read_intermediates(ws, B, K, L, V, 1 if dtype == "bf16" else 0)
+    c = float(np.float32(1.4426950408889634 / float(np.float32(T))))
+    for z, name in ((tl[:, :, :L], "lse_q"), (dl, "lse_p")):
+        y = z.double().cpu() * c
+        m = y.amax(-1, keepdim=True)
+        ref = (m[..., 0] + torch.log2(torch.exp2(y - m).sum(-1))).numpy() * 0.693147180559945309417
+        err = np.abs(got[name] - ref).max()
+        assert err <= 1e-9, "%s: off by %.3g" % (name, err)
