@@ -108,46 +108,56 @@ __device__ __forceinline__ void rows_touch(U4 &v, float &acc)
 }
 
 // Sum over this wave's vectors (the drafted token's entry left out) of 2^(c z - ref), ref integral.  Every lane keeps a
-// running reference, the largest entry so far, updated once per 16 entries: the entries that make up a row's mass then
-// have small exponents, which float32 rounds little.  (A reference taken from the wave's first vectors alone saves a
-// tenth of the sweep and costs five times the error at T = 0.4: 2.7e-7 instead of 6e-8 in ln nu.)
+// running reference, the largest entry so far, updated once per vector: the entries that make up a row's mass then
+// have small exponents, which float32 rounds little, and the largest weigh exactly 1.  A workgroup of 256 threads does so for
+// either half of its slots by itself, so that as many entries share a reference as with 512.  Error of ln Z, rms, bfloat16 rows
+// of 8000 / 16000 entries at T = 0.7: 3.05e-8 / 3.1e-8, as on the two-pass schedule; updated once per 16 entries, without the
+// halves, 4.0e-8 / 4.1e-8, and no faster.  (A reference taken from the wave's first vectors alone saves a tenth of the sweep
+// and costs five times the error at T = 0.4: 2.7e-7 instead of 6e-8 in ln nu.)
 struct WaveSum { float ref; double Z; };
 struct TokenAt { int slot, elem; bool mine; };             // where the drafted token lies: slot (uniform, -1: not here), entry, this lane?
 
 template <typename T, int TH, int NS>
 __device__ __forceinline__ WaveSum rows_wave_sum(U4 (&v)[NS], const Slots<T, TH> &sl, float c, const TokenAt &tk)
 {
-    constexpr int PV = Elem<T>::kPerVec, kGroup = 16 / PV < NS ? 16 / PV : NS;
-    static_assert(NS % kGroup == 0, "whole groups of slots");
-    float m2 = -3.0e38f, Z = 0.0f;
+    constexpr int PV = Elem<T>::kPerVec, A = 512 / TH;
+    static_assert(A == 1 || A == 2, "workgroups of 256 or 512 threads");
+    float m2[A], Z[A];
 #pragma unroll
-    for (int j0 = 0; j0 < NS; j0 += kGroup) {
-        if (sl.used(j0)) {                                 // (a slot past the part's end holds masked entries)
-            float z[kGroup][PV], vm = -3.0e38f;
+    for (int x = 0; x < A; ++x) {
+        float m = -3.0e38f, zs = 0.0f;
 #pragma unroll
-            for (int g = 0; g < kGroup; ++g) {
-                rows_touch(v[j0 + g], Z);
-                sl.unpack(v[j0 + g], j0 + g, z[g]);
-                if (j0 + g == tk.slot) {                   // uniform
+        for (int j = x * (NS / A); j < (x + 1) * (NS / A); ++j) {
+            if (sl.used(j)) {
+                rows_touch(v[j], zs);
+                float z[PV], vm = -3.0e38f;
+                sl.unpack(v[j], j, z);
+                if (j == tk.slot) {                        // uniform
                     asm volatile("");
-                    leave_out(z[g], tk.mine, tk.elem);
+                    leave_out(z, tk.mine, tk.elem);
                 }
 #pragma unroll
-                for (int e = 0; e < PV; ++e) vm = fmaxf(vm, z[g][e]);
+                for (int e = 0; e < PV; ++e) vm = fmaxf(vm, z[e]);
+                const float n2 = fmaxf(m, vm * c);
+                float a = 0.0f;
+#pragma unroll
+                for (int e = 0; e < PV; ++e) a += exp2_fast(fmaf(z[e], c, -n2));
+                zs = fmaf(zs, exp2_fast(m - n2), a);
+                m = n2;
             }
-            const float n2 = fmaxf(m2, vm * c);
-            float a = 0.0f;
-#pragma unroll
-            for (int g = 0; g < kGroup; ++g)
-#pragma unroll
-                for (int e = 0; e < PV; ++e) a += exp2_fast(fmaf(z[g][e], c, -n2));
-            Z = fmaf(Z, exp2_fast(m2 - n2), a);
-            m2 = n2;
         }
+        m2[x] = m; Z[x] = zs;
     }
+    float top = m2[0];
+#pragma unroll
+    for (int x = 1; x < A; ++x) top = fmaxf(top, m2[x]);
     WaveSum s;
-    s.ref = ceilf(fmaxf(wave_max(m2), -3.0e38f));
-    s.Z = wave_sum(Z > 0.0f ? static_cast<double>(Z) * exp2_small(static_cast<double>(m2) - static_cast<double>(s.ref)) : 0.0);
+    s.ref = ceilf(fmaxf(wave_max(top), -3.0e38f));
+    double lane = 0.0;
+#pragma unroll
+    for (int x = 0; x < A; ++x)
+        lane += Z[x] > 0.0f ? static_cast<double>(Z[x]) * exp2_small(static_cast<double>(m2[x]) - static_cast<double>(s.ref)) : 0.0;
+    s.Z = wave_sum(lane);
     return s;
 }
 
@@ -529,6 +539,7 @@ hipError_t launch_rows_typed(const Problem &p)
     const dim3 grid(static_cast<unsigned>(pairs * P));
 #define SPECGBV_ROWS_LAUNCH(TH, NS) hipLaunchKernelGGL((k_rows<T, TH, NS>), grid, dim3(TH), 0, p.stream, target, draft, ar)
     if (per <= 1024) SPECGBV_ROWS_LAUNCH(512, 2);
+    else if (per <= 1536) SPECGBV_ROWS_LAUNCH(256, 6);
     else if (per <= 2048) SPECGBV_ROWS_LAUNCH(256, 8);
     else SPECGBV_ROWS_LAUNCH(512, 8);
 #undef SPECGBV_ROWS_LAUNCH
@@ -553,7 +564,9 @@ int rows_schedule_parts(const Problem &p)
     // Two tiles: one workgroup of 512 threads for a row of up to 4096 vectors (its overheads once per row: V = 32000
     // bfloat16, 128 drafts of 8: 78 us a call, 93 in two parts), but four workgroups of 256 per compute unit, with parts
     // of up to 2048 vectors, for longer rows, whose parts must not wait for one another in step (V = 128256: 187 in eight
-    // parts, 213 in four; 8 x 4 drafts of 5, V = 32000 float32: 35.8 in four, 38.6 in two).
+    // parts, 213 in four; 8 x 4 drafts of 5, V = 32000 float32: 35.8 in four, 38.6 in two).  Parts of up to 1536 vectors take
+    // a tile of their own, whose halves are the same for every lane (8 x 4 drafts of 8, V = 70001 float32: 84.1, 85.3 in the
+    // tile of 2048).
     const int most = nv <= 4096 ? 4096 : 2048;
     while (P < kRowParts && (nv + P - 1) / P > most) P *= 2;
     if ((nv + P - 1) / P > 4096) return 0;

@@ -28,6 +28,9 @@ def _inputs(B, K, L, V, dtype, T=0.8, seed=5, sigma=2.5):
     (1, 1, 2, 4096, "bf16"), (1, 3, 3, 65543, "bf16"), (1, 2, 4, 300007, "bf16"), (2, 1, 2, 262145, "f32"),
     # a single row per draft (no Eq. (hik) sum at all), and the longest drafts
     (140, 1, 1, 1003, "bf16"), (1, 3, 62, 2051, "f32"),
+    # whole rows in the tiles of 1024, 1536, 2048 and 4096 vectors (288 row pairs: one part each)
+    (9, 4, 8, 8192, "bf16"), (9, 4, 8, 8193, "bf16"), (9, 4, 8, 12288, "bf16"), (9, 4, 8, 12289, "bf16"),
+    (9, 4, 8, 16384, "bf16"), (9, 4, 8, 16391, "bf16"), (9, 4, 8, 6143, "f32"), (9, 4, 8, 6145, "f32"),
 ])
 def test_rows_at_the_edges_of_tiles_and_parts(B, K, L, V, dtype):
     t, d, tok = _inputs(B, K, L, V, dtype)
@@ -70,3 +73,26 @@ def test_bounded_wait_falls_back_to_the_waiting_workgroups_own_statistics(B, K, 
 @pytest.mark.parametrize("V,dtype,B,K,L", [(9001, "bf16", 20, 2, 5), (16387, "f32", 12, 3, 4), (131077, "bf16", 2, 2, 4)])
 def test_rows_that_need_the_cancellation_free_sum(V, dtype, B, K, L):
     peaked.test_block_ratio_runs_away("auto", dtype, V, B, K, L)
+
+
+@pytest.mark.parametrize("V,T", [(8000, 0.7), (9001, 0.4), (16000, 0.7)])
+def test_normalisers_are_as_accurate_as_on_the_two_pass_schedule(V, T):
+    """Rms error of the ln-normalisers of 1024 rows against float64.  No more entries share a reference than on the two-pass
+    schedule, so the errors have the same size; a tenth is left for the scatter of an rms over 1024 rows (3 %), and where the
+    two-pass kernels add up other entries together."""
+    import torch
+    from parity_util import run_gpu, to_torch
+    from specgbv_synth import f32_to_bf16_bits
+    B, K, L = 32, 4, 4
+    rng = np.random.default_rng(V)
+    t = f32_to_bf16_bits(rng.normal(0, 3, (B, K, L + 1, V)).astype(np.float32))
+    d = f32_to_bf16_bits(rng.normal(0, 3, (B, K, L, V)).astype(np.float32))
+    tok = rng.integers(0, V, (B, K, L)).astype(np.int32)
+    c = float(np.float32(1.4426950408889634 / float(np.float32(T)))) * 0.693147180559945309417
+    ref = [torch.logsumexp(to_torch(np.ascontiguousarray(z)).double() * c, -1).cpu().numpy() for z in (t[:, :, :L], d)]
+    rms = {}
+    for algo in ("auto", "split"):
+        g = run_gpu(t, d, tok, T, 1, 1, algo)
+        rms[algo] = float(np.sqrt(np.mean([np.square(g["lse_q"] - ref[0]), np.square(g["lse_p"] - ref[1])])))
+    print("[normalisers] V=%d T=%g: rms %r" % (V, T, rms), flush=True)
+    assert rms["auto"] <= 1.1 * rms["split"]
