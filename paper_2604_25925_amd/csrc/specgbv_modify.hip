@@ -317,6 +317,14 @@ k_mod_write(const T *__restrict__ target, const T *__restrict__ draft, int K, in
     }
 }
 
+// Whether n floats at `out` share memory with m logits at `in`.
+template <typename T>
+bool overlap(const float *out, long long n, const T *in, long long m)
+{
+    const uintptr_t o = reinterpret_cast<uintptr_t>(out), i = reinterpret_cast<uintptr_t>(in);
+    return out && o < i + static_cast<uintptr_t>(m) * sizeof(T) && i < o + static_cast<uintptr_t>(n) * sizeof(float);
+}
+
 template <typename T>
 hipError_t launch_modify_typed(const void *target_v, const void *draft_v, const int32_t *tokens, int K, int M,
                                int bonus, int V, int batch, float c, const double *carry, const int32_t *count,
@@ -328,12 +336,17 @@ hipError_t launch_modify_typed(const void *target_v, const void *draft_v, const 
     ModStat *tstat = reinterpret_cast<ModStat *>(ws + lay.tstat), *dstat = reinterpret_cast<ModStat *>(ws + lay.dstat);
     double *norm = norm_out ? norm_out : reinterpret_cast<double *>(ws + lay.norm);
     int32_t *fb = fallback_out ? fallback_out : reinterpret_cast<int32_t *>(ws + lay.fb);
-    const bool vec = read_by_vectors<T>(V);
     const long long bk = static_cast<long long>(batch) * K;
     const long long n_t = bk * (M + bonus), n_d = bk * M;
     const dim3 blk(kModThreads);
+    // Results that replace their inputs (a level applied on top of another one, in its buffers): no row is written before the
+    // last kernel, which then has every entry read and written by one thread.  By vectors that holds unless the last one
+    // repeats entries of the vector before it, which another thread may have written.
+    const bool in_place = overlap(out_logq, n_t * V, target, n_t * V) || overlap(out_logq, n_t * V, draft, n_d * V) ||
+                          overlap(out_logp, n_d * V, target, n_t * V) || overlap(out_logp, n_d * V, draft, n_d * V);
+    const bool vec = read_by_vectors<T>(V) && !(in_place && V % Elem<T>::kPerVec != 0);
     // rows short enough to stay in a workgroup's registers are read once unless a modification is pending for them
-    const bool rows_fit = vec && row_vectors<T>(V) <= kRowSlots * kModThreads;
+    const bool rows_fit = vec && !in_place && row_vectors<T>(V) <= kRowSlots * kModThreads;
 #define SPECGBV_MOD_LAUNCH(VEC)                                                                                   \
     do {                                                                                                          \
         if (rows_fit)                                                                                             \

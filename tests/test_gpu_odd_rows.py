@@ -44,3 +44,27 @@ def test_many_drafts_of_short_odd_rows(algo):
     t, d, tok = make_inputs(Workload("short", 600, 2, 3, 100, "bf16", 2.5, 0.9, head=20, temperature=0.8), seed=5)
     tok[:, 0, -1] = 99
     check_case(t, d, tok, 0.8, 3, 1, algo, "odd rows, 600 prompts")
+
+
+@pytest.mark.parametrize("V", [515, 2048, 2051, 4099, 8192])
+@pytest.mark.parametrize("T", [1.0, 0.7])
+def test_modify_in_place(V, T):
+    """Float32 results in the buffers of their inputs against results in buffers of their own.  Where the two take kernels that
+    add up in another order, a normaliser moves by 1e-6 at most (512 float32 partial sums of up to 2^5 entries), and with it
+    the probabilities, relatively; they are compared, not their logarithms, which have a pole where a weight is zero."""
+    import torch
+    import paper_2604_25925_amd as sg
+    from parity_util import to_torch
+    B, K, M = 6, 3, 3
+    t, d, tok = make_inputs(Workload("place", B, K, M, V, "f32", 2.0, 0.8, head=8, temperature=T), seed=V)
+    tl, dl, tk = to_torch(t), to_torch(d), to_torch(tok)
+    carry = torch.from_numpy(np.linspace(-0.5, 0.5, B)).cuda()
+    count = torch.from_numpy(np.array([0, 1, 2, 3, 3, 2], np.int32)).cuda()
+    own = sg.specgbv_modify_target(tl, dl, tk, T, carry, count, want_logp=True, want_norm=True)
+    tp, dp = tl.clone(), dl.clone()
+    here = sg.specgbv_modify_target(tp, dp, tk, T, carry, count, want_logp=True, want_norm=True, out={"logq": tp, "logp": dp})
+    torch.cuda.synchronize()
+    assert torch.equal(own["fallback"], here["fallback"])
+    assert torch.allclose(own["norm"], here["norm"], rtol=1e-6, atol=1e-9)
+    for k in ("logq", "logp"):
+        assert torch.allclose(own[k].double().exp(), here[k].double().exp(), rtol=1e-5, atol=1e-8), k
