@@ -1067,6 +1067,7 @@ hipError_t launch_final_typed(const Problem &p)
     fo.mcount = reinterpret_cast<int32_t *>(p.ws + p.lay.mcount);
     fo.state_carry = p.state_carry; fo.state_count = p.state_count;
     const int KL = p.K * p.L;
+    // (66 KB at the largest accepted K L = 1024, K = 64, and 2.4 KB static: within the 160 KB a workgroup may have)
     const size_t lds = sizeof(double) * (6 * KL + p.K) + sizeof(int) * (3 * KL + 1) + ((static_cast<size_t>(p.K) * p.K + 7) & ~static_cast<size_t>(7));
 #define SPECGBV_FINAL_LAUNCH(PEND)                                                                              \
     hipLaunchKernelGGL((k_final<T, PEND>), g, dim3(kSegThreads), lds, p.stream, target, draft, io, fo, p.V, p.K, \
