@@ -667,7 +667,9 @@ __device__ __forceinline__ void update_pending_state(const T *target, const T *d
     }
 }
 
-template <typename T, bool PEND>
+constexpr int kKeep = 5;                     // segments per lane that the search for the token keeps in registers
+
+template <typename T, bool PEND, bool FAR>
 __global__ void __launch_bounds__(kSegThreads)
 k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, FinalOut fo, int V, int K, int L,
         float c, int nseg, int spw, uint64_t seed, uint64_t offset)
@@ -680,6 +682,8 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
     __shared__ double sh_d[kSegThreads / kWave];
     __shared__ double sh_excess[kSegThreads];
     __shared__ int sh_nmark;
+    __shared__ double sh_far_q[FAR ? kSegThreads : 1];
+    __shared__ float sh_far_m[FAR ? kSegThreads : 1];
     const int b = blockIdx.y, tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wid = __builtin_amdgcn_readfirstlane(tid / kWave);    // (scalar: so are the segments' addresses)
     int32_t *__restrict__ out_tokens = io.out_tokens;
@@ -838,35 +842,81 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
     // the barrier orders them before the first thread's counter update.
     wait_for_stores();
     __syncthreads();
-    if (wid != 0) return;
-    {
+    const SegPartial *pp = fo.partial + static_cast<long long>(b) * nseg;
+    // The search is one wave's: a workgroup-wide one spends its time at barriers.  Lane l owns the contiguous segments
+    // [l chunk, (l + 1) chunk), which stay in its registers up to V = kKeep * 64 * 512 = 163840.  Of longer rows (FAR) every
+    // thread of the workgroup sums a quarter of a lane's chunk, kFar segments at a time, and once the lane is known the wave
+    // looks at all its segments at once.  (By one wave, segment by segment beyond kKeep, they cost a memory latency each,
+    // three times: one prefix of V = 1000000 float32 66 us a call, 54 now, 3000000 bfloat16 124, 101 now.  An instance of its
+    // own, because the shorter rows' kernel took 2 % longer with this code in it.)
+    constexpr int kFar = 4;
+    const int quarter = (nseg + kSegThreads - 1) / kSegThreads;
+    const int chunk = FAR ? quarter * (kSegThreads / kWave) : (nseg + kWave - 1) / kWave;
+    const int s0 = lane * chunk, s1 = min(nseg, s0 + chunk);
+    if constexpr (FAR) {
+        if (tid == 0)
+            sh_nmark = __hip_atomic_fetch_add(&fo.counter[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == static_cast<int>(gridDim.x) - 1;
+        __syncthreads();
+        if (!sh_nmark) return;
+        const int t0 = tid * quarter;
+        float m = -3.0e38f;
+        double tw = 0.0, tq = 0.0;                   // relative to 2^m
+        for (int o = 0; o < quarter; o += kFar) {    // uniform
+            float fm[kFar];
+            double fw[kFar], fq[kFar];
+#pragma unroll
+            for (int i = 0; i < kFar; ++i) {         // (no branch around a load)
+                const int s = t0 + o + i < nseg ? t0 + o + i : nseg - 1;
+                fm[i] = partial_load_m2(&pp[s]);
+                fw[i] = partial_load_d(&pp[s].sum_w); fq[i] = partial_load_d(&pp[s].sum_q);
+            }
+            float n = m;
+#pragma unroll
+            for (int i = 0; i < kFar; ++i) {
+                if (!(o + i < quarter && t0 + o + i < nseg)) { fm[i] = -3.0e38f; fw[i] = 0.0; fq[i] = 0.0; }
+                n = fmaxf(n, fm[i]);
+            }
+            tw = ldexp(tw, reference_shift(m, n)); tq = ldexp(tq, reference_shift(m, n));
+#pragma unroll
+            for (int i = 0; i < kFar; ++i) {
+                tw += ldexp(fw[i], reference_shift(fm[i], n)); tq += ldexp(fq[i], reference_shift(fm[i], n));
+            }
+            m = n;
+        }
+        sh_excess[tid] = tw; sh_far_q[tid] = tq; sh_far_m[tid] = m;
+        __syncthreads();
+        if (wid != 0) return;
+    } else {
+        if (wid != 0) return;
         int arrived = 0;
         if (lane == 0) arrived = __hip_atomic_fetch_add(&fo.counter[b], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (__builtin_amdgcn_readfirstlane(arrived) != static_cast<int>(gridDim.x) - 1) return;
     }
-    const SegPartial *pp = fo.partial + static_cast<long long>(b) * nseg;
-
-    // From here on one wave: a workgroup-wide search spends its time at barriers.  Lane l owns the contiguous segments
-    // [l chunk, (l + 1) chunk); the first kKeep of them stay in registers (all of them up to V = 163840), later ones are
-    // read again when needed.
-    constexpr int kKeep = 5;
-    const int chunk = (nseg + kWave - 1) / kWave;
-    const int s0 = lane * chunk, s1 = min(nseg, s0 + chunk);
     float km2[kKeep];
-    double kw[kKeep], kq[kKeep];
+    double kw[kKeep], kq[kKeep];                     // the lane's segments (FAR: its four quarters)
+    if constexpr (FAR) {
+        static_assert(kSegThreads / kWave <= kKeep, "a lane's quarters in the registers of its segments");
+#pragma unroll
+        for (int i = kSegThreads / kWave; i < kKeep; ++i) { km2[i] = -3.0e38f; kw[i] = 0.0; kq[i] = 0.0; }
+#pragma unroll
+        for (int i = 0; i < kSegThreads / kWave; ++i) {
+            const int t = lane * (kSegThreads / kWave) + i;
+            km2[i] = sh_far_m[t]; kw[i] = sh_excess[t]; kq[i] = sh_far_q[t];
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < kKeep; ++i) {            // (every slot is loaded: lanes without a segment repeat the last one's)
+            const int s = s0 + i < s1 ? s0 + i : nseg - 1;
+            km2[i] = partial_load_m2(&pp[s]);
+            kw[i] = partial_load_d(&pp[s].sum_w); kq[i] = partial_load_d(&pp[s].sum_q);
+        }
+#pragma unroll
+        for (int i = 0; i < kKeep; ++i)
+            if (!(s0 + i < s1)) { km2[i] = -3.0e38f; kw[i] = 0.0; kq[i] = 0.0; }
+    }
     float mloc = -3.0e38f;
 #pragma unroll
-    for (int i = 0; i < kKeep; ++i) {                // (every slot is loaded: lanes without a segment repeat the last one's)
-        const int s = s0 + i < s1 ? s0 + i : nseg - 1;
-        km2[i] = partial_load_m2(&pp[s]);
-        kw[i] = partial_load_d(&pp[s].sum_w); kq[i] = partial_load_d(&pp[s].sum_q);
-    }
-#pragma unroll
-    for (int i = 0; i < kKeep; ++i) {
-        if (!(s0 + i < s1)) { km2[i] = -3.0e38f; kw[i] = 0.0; kq[i] = 0.0; }
-        mloc = fmaxf(mloc, km2[i]);
-    }
-    for (int s = s0 + kKeep; s < s1; ++s) mloc = fmaxf(mloc, partial_load_m2(&pp[s]));
+    for (int i = 0; i < kKeep; ++i) mloc = fmaxf(mloc, km2[i]);
     const float M = wave_max(mloc);
     double tw = 0.0, tqs = 0.0;
 #pragma unroll
@@ -874,10 +924,6 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
         const int sh = reference_shift(km2[i], M);                             // both integral, difference <= 0
         kw[i] = ldexp(kw[i], sh); kq[i] = ldexp(kq[i], sh);                   // now relative to 2^M
         tw += kw[i]; tqs += kq[i];
-    }
-    for (int s = s0 + kKeep; s < s1; ++s) {
-        const int sh = reference_shift(partial_load_m2(&pp[s]), M);
-        tw += ldexp(partial_load_d(&pp[s].sum_w), sh); tqs += ldexp(partial_load_d(&pp[s].sum_q), sh);
     }
     const double incl_w = wave_inclusive_sum(tw);
     const double Ww = lane_value(incl_w, kWave - 1);
@@ -894,38 +940,59 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
     const unsigned long long over = __ballot(mine_seg > 0.0 && excl_t + mine_seg > goal);
     const int win_l = over ? __ffsll(static_cast<long long>(over)) - 1
                            : (has ? 63 - __clzll(static_cast<long long>(has)) : 0);   // (rounding pushed the goal past the end)
-    int seg_w = 0;
-    float seg_m2 = 0.0f;
-    double cum_w = 0.0;
-    if (lane == win_l) {
-        double cum = excl_t, cum_before = excl_t;
-        int found = -1, last_pos = s0 < nseg ? s0 : 0;
-        float found_m2 = km2[0], last_m2 = km2[0];
-        double cum_before_last = excl_t;
-        bool open = true;
+    int seg = 0;
+    float m2_seg = 0.0f;
+    double cum_seg = 0.0;                            // all three wave-uniform
+    if constexpr (!FAR) {
+        int seg_w = 0;
+        float seg_m2 = 0.0f;
+        double cum_w = 0.0;
+        if (lane == win_l) {
+            double cum = excl_t, cum_before = excl_t;
+            int found = -1, last_pos = s0 < nseg ? s0 : 0;
+            float found_m2 = km2[0], last_m2 = km2[0];
+            double cum_before_last = excl_t;
+            bool open = true;
 #pragma unroll
-        for (int i = 0; i < kKeep; ++i) {
-            if (open && s0 + i < s1) {
-                const double v = use_q ? kq[i] : kw[i];
-                if (v > 0.0) { last_pos = s0 + i; last_m2 = km2[i]; cum_before_last = cum; }
-                if (cum + v > goal) { found = s0 + i; found_m2 = km2[i]; cum_before = cum; open = false; }
-                else cum += v;
+            for (int i = 0; i < kKeep; ++i) {
+                if (open && s0 + i < s1) {
+                    const double v = use_q ? kq[i] : kw[i];
+                    if (v > 0.0) { last_pos = s0 + i; last_m2 = km2[i]; cum_before_last = cum; }
+                    if (cum + v > goal) { found = s0 + i; found_m2 = km2[i]; cum_before = cum; open = false; }
+                    else cum += v;
+                }
             }
+            if (found < 0) { found = last_pos; found_m2 = last_m2; cum_before = cum_before_last; }
+            seg_w = found; seg_m2 = found_m2; cum_w = cum_before;
         }
-        for (int s = s0 + kKeep; open && s < s1; ++s) {
+        seg = __builtin_amdgcn_readlane(seg_w, win_l);
+        m2_seg = __uint_as_float(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(seg_m2)), win_l));
+        cum_seg = lane_value(cum_w, win_l);
+    } else {
+        const int w0 = win_l * chunk, w1 = min(nseg, w0 + chunk);
+        double cum = lane_value(excl_t, win_l);
+        seg = w0 < nseg ? w0 : 0;                    // (kept where no segment has any weight)
+        m2_seg = partial_load_m2(&pp[seg]);
+        cum_seg = cum;
+        for (int at = w0; at < w1; at += kWave) {    // uniform
+            const int s = at + lane < w1 ? at + lane : w1 - 1;
             const float m2s = partial_load_m2(&pp[s]);
-            const double v = ldexp(partial_load_d(use_q ? &pp[s].sum_q : &pp[s].sum_w), reference_shift(m2s, M));
-            if (v > 0.0) { last_pos = s; last_m2 = m2s; cum_before_last = cum; }
-            if (cum + v > goal) { found = s; found_m2 = m2s; cum_before = cum; open = false; }
-            else cum += v;
+            const double raw = partial_load_d(use_q ? &pp[s].sum_q : &pp[s].sum_w);
+            const double v = at + lane < w1 ? ldexp(raw, reference_shift(m2s, M)) : 0.0;
+            const double incl = wave_inclusive_sum(v);
+            const unsigned long long some = __ballot(v > 0.0), past = __ballot(v > 0.0 && cum + incl > goal);
+            if (some) {                              // the first past the goal, else the last with any weight
+                const int l = past ? __ffsll(static_cast<long long>(past)) - 1 : 63 - __clzll(static_cast<long long>(some));
+                seg = at + l;
+                m2_seg = __uint_as_float(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(m2s)), l));
+                cum_seg = cum + (lane_value(incl, l) - lane_value(v, l));
+            }
+            if (past) break;
+            cum += lane_value(incl, kWave - 1);
         }
-        if (found < 0) { found = last_pos; found_m2 = last_m2; cum_before = cum_before_last; }
-        seg_w = found; seg_m2 = found_m2; cum_w = cum_before;
     }
-    const int seg = __builtin_amdgcn_readlane(seg_w, win_l);
-    const float m2_seg = __uint_as_float(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(seg_m2)), win_l));
     const int up = -reference_shift(m2_seg, M);
-    const double local_target = ldexp(goal - lane_value(cum_w, win_l), up);     // goal in the segment's own scale
+    const double local_target = ldexp(goal - cum_seg, up);     // goal in the segment's own scale
     const double total_here = ldexp(W, up);
 
     // inside the segment: one wave, lane order = token-id order
@@ -1013,9 +1080,13 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
 // workgroup makes the prefix's whole decision, which is what a large batch pays for.  Measured, microseconds per call at
 // 1 / 2 / 4 / 8 / 16 segments: one prefix of V = 128256 26.5 / 27.4 / 29.3 / 32.7 / 39.4, 8 of 32000 43.9 / 44.7 / 49.2 /
 // 59.2 / 77.4, 32 of 128256 256.5 / 241.5 / 238.6 / 241.3 / 248.3, 128 of 152064 2296 / 2233 / 2205 / 2199 / 2193.
+bool final_far(const Problem &p) { return p.lay.nseg > kKeep * kWave; }
+
+// Rows beyond the search's registers (final_far): one and a half workgroups per compute unit; 1 / 2 / 4 segments: one
+// prefix of V = 1000000 55.7 / 53.9 / 53.9, 4 of 600000 - / 78.0 / 75.7, one of 300000 24.8 / 24.4 / 25.5.
 int final_segments_per_wave(const Problem &p)
 {
-    const long long most = 5LL * compute_units() / 2;
+    const long long most = (final_far(p) ? 3LL : 5LL) * compute_units() / 2;
     int spw = 1;
     auto groups = [&](int n) { return (p.lay.nseg + kSegThreads / kWave * n - 1) / (kSegThreads / kWave * n); };
     while (groups(spw) > 1 && static_cast<long long>(groups(spw)) * p.batch > most) spw *= 2;
@@ -1069,11 +1140,12 @@ hipError_t launch_final_typed(const Problem &p)
     const int KL = p.K * p.L;
     // (66 KB at the largest accepted K L = 1024, K = 64, and 2.4 KB static: within the 160 KB a workgroup may have)
     const size_t lds = sizeof(double) * (6 * KL + p.K) + sizeof(int) * (3 * KL + 1) + ((static_cast<size_t>(p.K) * p.K + 7) & ~static_cast<size_t>(7));
-#define SPECGBV_FINAL_LAUNCH(PEND)                                                                              \
-    hipLaunchKernelGGL((k_final<T, PEND>), g, dim3(kSegThreads), lds, p.stream, target, draft, io, fo, p.V, p.K, \
+#define SPECGBV_FINAL_LAUNCH(PEND, FAR)                                                                         \
+    hipLaunchKernelGGL((k_final<T, PEND, FAR>), g, dim3(kSegThreads), lds, p.stream, target, draft, io, fo, p.V, p.K, \
                        p.L, p.c, p.lay.nseg, spw, p.seed, p.offset)
-    if (p.pend_levels > 0) SPECGBV_FINAL_LAUNCH(true);
-    else SPECGBV_FINAL_LAUNCH(false);
+    const bool far = final_far(p);
+    if (p.pend_levels > 0) { if (far) SPECGBV_FINAL_LAUNCH(true, true); else SPECGBV_FINAL_LAUNCH(true, false); }
+    else { if (far) SPECGBV_FINAL_LAUNCH(false, true); else SPECGBV_FINAL_LAUNCH(false, false); }
 #undef SPECGBV_FINAL_LAUNCH
     return hipGetLastError();
 }

@@ -72,7 +72,7 @@ def unannounced(lines):
     return len(adds), bad, stores
 
 
-@pytest.mark.parametrize("source,kernel,count", [("specgbv_decide.hip", "k_final", 4), ("specgbv_split.hip", "k_pend_norm", 4)])
+@pytest.mark.parametrize("source,kernel,count", [("specgbv_decide.hip", "k_final", 8), ("specgbv_split.hip", "k_pend_norm", 4)])
 def test_counter_updates_wait_for_the_stores_before_them(source, kernel, count, tmp_path):
     if not os.path.exists(hipcc()):
         pytest.skip("no hipcc")
