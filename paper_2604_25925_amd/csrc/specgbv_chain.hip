@@ -40,6 +40,7 @@ namespace {
 constexpr int kChainThreads = 512;
 constexpr int kChainWaves = kChainThreads / kWave;
 constexpr int kLdsSlots = 9;       // LDS slots of a workgroup that has its compute unit to itself
+constexpr int kOnChipVectors = (23 + kLdsSlots) * kChainThreads;   // of a row, at most: register and LDS slots
 constexpr int kPairLdsSlots = 4;   // ... and of one that shares it with a second one (rows of at most 7 + 4 slots)
 
 // t[j] <- t[j]^K.  KP > 0 fixes K at compile time; KP = 0 takes the wave-uniform K >= 1.
@@ -1155,31 +1156,38 @@ bool chain_supports_pending(const Problem &p)
     return nslots <= RS + kLdsSlots;
 }
 
-// Chain or rows?  The chain schedule's time is that of the rows a workgroup walks, whatever the number of workgroups
-// (up to one or two per compute unit); the rows schedule's goes with the number of row pairs.  Measured on 256 compute
-// units, K = L = 8, in microseconds of the streaming kernel (the call less the 30 that both spend elsewhere):
+// Chain, rows or two passes?  The chain schedule's time is that of the rows a workgroup walks, whatever the number of
+// workgroups (up to one or two per compute unit); the others' goes with the number of row pairs.  Measured on 256 compute
+// units, in microseconds of the streaming kernels (the call less the 26 - 30 that all spend elsewhere):
 //   one row of a chain:  3 + 1.44e-3 per vector (bfloat16: 8.8 / 15.5 / 26 at 4000 / 8000 / 16032 vectors),
-//                        2 + 0.85e-3 per vector (float32), but not faster than 6.3 TB/s over all chains;
+//                        2 + 0.85e-3 per vector (float32), but not faster than 6.3 TB/s over all chains; vectors that do
+//                        not fit on chip are read twice and cost 1.8e-3 and 2.6e-3 each (bfloat16, 19008 vectors: 31 a row;
+//                        float32, 25000: 40, 35000: 57);
 //   two chains per compute unit (short rows): 1.75 times the time of one;
-//   rows schedule:       9.4e-6 per vector of a row pair (8 - 10), e.g. bfloat16, V = 128256: 165 / 235 / 310 at
-//                        128 / 192 / 256 drafts against 200 / 210 / 215 on the chain schedule; V = 32000, 320 drafts: 97
-//                        against 113, 512 drafts: 156 against 122.
+//   rows schedule:       9.4e-6 (bfloat16) and 8.0e-6 (float32) per vector of a row pair, where it is taken at all;
+//   two passes:          2 + 5.8e-6 and 5.3e-6 per vector of a row pair that a pass reads ((2 L - 1) / L times).
+// E.g. (chain / rows / two passes, microseconds a call) 24 x 8 drafts of 4, V = 32768 float32: 70 / 76 / 87, bfloat16 V = 140000:
+// 140 / 190 / 159; 32 x 4 of 4, V = 140000 float32: 258 / 260 / 187, V = 25000: 59.0 / 53.6 / 53.8.
 bool chain_preferred(const Problem &p)
 {
     if (!chain_supported(p)) return false;
     const long long chains = static_cast<long long>(p.batch) * p.K, units = resident_workgroups();
     // a caller who states that rows 0 are shared gets the schedule that reads them once wherever it is near the fastest
     if (p.shared_row0 && chains * 100 >= units * 66) return true;
-    if (rows_schedule_parts(p) == 0) return chains * 100 >= units * 66;       // against the two-pass schedule: crossover at 170 of 256
-    const double nv = p.V / (p.dtype == 1 ? 8 : 4), rows = static_cast<double>(chains) * p.L, scale = 256.0 / static_cast<double>(units);
-    const double one = p.L * (p.dtype == 1 ? 3.0 + 1.44e-3 * nv : 2.0 + 0.85e-3 * nv);
+    const bool bf16 = p.dtype == 1;
+    const double nv = p.V / (bf16 ? 8 : 4), scale = 256.0 / static_cast<double>(units);
+    const double off = nv > kOnChipVectors ? nv - kOnChipVectors : 0.0, on = nv - off;
+    const double rows = static_cast<double>(chains) * p.L, reads = rows * (2.0 - 1.0 / p.L);
+    const double one = p.L * (bf16 ? 3.0 + 1.44e-3 * on + 1.8e-3 * off : 2.0 + 0.85e-3 * on + 2.6e-3 * off);
     double t_chain;
     if (chain_shares_unit(p)) {
         const long long left = chains % (2 * units);
         t_chain = one * (1.75 * static_cast<double>(chains / (2 * units)) + (left == 0 ? 0.0 : (left <= units ? 1.0 : 1.75)));
     } else t_chain = one * static_cast<double>((chains + units - 1) / units);
-    t_chain = fmax(t_chain, rows * nv * 32.0 / 6.3e6);                        // (bytes over bytes per microsecond)
-    return t_chain < rows * nv * 9.4e-6 * scale;
+    t_chain = fmax(t_chain, rows * (nv + off) * 32.0 / 6.3e6);                // (bytes over bytes per microsecond)
+    const double t_other = rows_schedule_parts(p) > 0 ? rows * nv * (bf16 ? 9.4e-6 : 8.0e-6) * scale
+                                                      : 2.0 + reads * nv * (bf16 ? 5.8e-6 : 5.3e-6) * scale;
+    return t_chain < t_other;
 }
 
 hipError_t launch_chain_main(const Problem &p)

@@ -570,7 +570,28 @@ int rows_schedule_parts(const Problem &p)
     const int most = nv <= 4096 ? 4096 : 2048;
     while (P < kRowParts && (nv + P - 1) / P > most) P *= 2;
     if ((nv + P - 1) / P > 4096) return 0;
-    while (P < kRowParts && pairs * P * 2 <= 2LL * compute_units() && nv / (P * 2) >= 512) P *= 2;
+    const long long units = compute_units();
+    while (P < kRowParts && pairs * P * 2 <= 2 * units && nv / (P * 2) >= 512) P *= 2;
+    // With more than 512 workgroups of this schedule (two per unit) the two-pass kernels, which read most rows a second time
+    // but have no workgroup wait for another, are ahead (measured at 880 shapes of 4 - 4800 row pairs, V = 1024 - 152064)
+    //   - of rows in parts, unless the parts fill their tile: a workgroup takes the compute units for 6.9 + 0.6 ns per 256
+    //     vectors in bfloat16, 6.6 + 0.2 in float32, the two passes for 3.6 and 3.0 ns per 1000 vectors and pass.  32 x 4
+    //     drafts of 4, us a call in rows / two passes: bfloat16 V = 66000 (1032 vectors per part) 85 / 70, 100000 (1563)
+    //     106 / 100, 131072 (2048) 106 / 112; float32 V = 66000 (1032) 128 / 109, 100000 (1563) 154 / 148; 128 x 1 of 5,
+    //     65536 (2048) 102 / 126; with more than 2048 per part, two workgroups per unit, 140000 (2188) 260 / 187;
+    //   - of whole rows in the tile of 4096 vectors, two workgroups per unit, in bfloat16 (32 x 8 drafts of 8, V = 24000
+    //     98.6 / 92.3; float32 20 x 8 of 6, V = 9000 46.6 / 54.3); with less than two rounds of workgroups, of either type, of
+    //     short drafts, whose rows 0 are a good part, unless the second round is nearly full (bfloat16 128 x 1 of 5,
+    //     V = 24000 49.2 / 43.6, 20 x 8 of 6 55.6 / 63.3, 100 x 2 of 5 62.3 / 65.7; 12 x 5 of 12, V = 25365 65.2 / 81.7).
+    const int per = (nv + P - 1) / P;
+    const long long wgs = pairs * P;
+    if (per > 1024 && wgs > 2 * units) {
+        if (P > 1) {
+            if (per > 2048 || per < (p.dtype == 1 ? 1750 : 1400)) return 0;
+        } else if (per > 2048) {
+            if (wgs > 4 * units ? p.dtype == 1 : p.L < 6 && wgs * 4 < 14 * units) return 0;
+        }
+    }
     return pairs * P < (1LL << 31) ? P : 0;
 }
 

@@ -2,7 +2,8 @@
 tiles end (needs an MI355X: run with -m gpu).
 
 The default takes the row schedule here: rows of at least one vector, too short or too few for the chain kernel, more
-than half as many row pairs as compute units or rows of 512 vectors and more.
+than half as many row pairs as compute units or rows of 512 vectors and more, and no more workgroups than two per compute
+unit or, beyond that, parts that fill their tile.  Cases at the edges of what it takes, which go to its neighbours, say so.
 """
 import numpy as np
 import pytest
@@ -19,18 +20,25 @@ def _inputs(B, K, L, V, dtype, T=0.8, seed=5, sigma=2.5):
 
 
 @pytest.mark.parametrize("B,K,L,V,dtype", [
-    # rows of one and two vectors, every remainder, more than half as many rows as compute units
+    # (rows of one and two vectors, which k_short_rows takes)
     (11, 3, 4, 8, "bf16"), (11, 3, 4, 9, "bf16"), (11, 3, 4, 15, "bf16"), (17, 4, 2, 4, "f32"), (17, 4, 2, 7, "f32"),
     # the edges of the three tiles (1024, 2048 and 4096 vectors) and of the parts, with and without a remainder
     (5, 4, 8, 8192, "bf16"), (5, 4, 8, 8193, "bf16"), (5, 4, 8, 16384, "bf16"), (5, 4, 8, 16391, "bf16"),
     (9, 4, 8, 32767, "bf16"), (9, 4, 8, 32768, "bf16"), (9, 4, 8, 32769, "bf16"), (9, 4, 8, 16387, "f32"),
-    # few rows: up to sixteen parts; parts that end in the middle of a slot; long rows in eight and sixteen parts
+    # few rows: up to sixteen parts; parts that end in the middle of a slot; long rows in eight and sixteen parts (the last
+    # case, one vector too long for them, goes to the two-pass kernels)
     (1, 1, 2, 4096, "bf16"), (1, 3, 3, 65543, "bf16"), (1, 2, 4, 300007, "bf16"), (2, 1, 2, 262145, "f32"),
-    # a single row per draft (no Eq. (hik) sum at all), and the longest drafts
+    # a single row per draft (no Eq. (hik) sum at all; k_short_rows), and the longest drafts
     (140, 1, 1, 1003, "bf16"), (1, 3, 62, 2051, "f32"),
     # whole rows in the tiles of 1024, 1536, 2048 and 4096 vectors (288 row pairs: one part each)
     (9, 4, 8, 8192, "bf16"), (9, 4, 8, 8193, "bf16"), (9, 4, 8, 12288, "bf16"), (9, 4, 8, 12289, "bf16"),
     (9, 4, 8, 16384, "bf16"), (9, 4, 8, 16391, "bf16"), (9, 4, 8, 6143, "f32"), (9, 4, 8, 6145, "f32"),
+    # rows of one and two vectors in drafts longer than k_short_rows takes (180 row pairs)
+    (5, 4, 9, 8, "bf16"), (5, 4, 9, 16, "bf16"), (5, 4, 9, 4, "f32"), (5, 4, 9, 8, "f32"),
+    # more workgroups than are resident, whose parts fill the tile; sixteen parts of 4096 vectors
+    (9, 4, 8, 56009, "bf16"), (9, 4, 8, 23003, "f32"), (2, 1, 2, 262141, "f32"), (4, 4, 8, 32769, "bf16"),
+    # a single row per draft, longer than k_short_rows takes
+    (140, 1, 1, 1032, "bf16"), (140, 1, 1, 4099, "bf16"),
 ])
 def test_rows_at_the_edges_of_tiles_and_parts(B, K, L, V, dtype):
     t, d, tok = _inputs(B, K, L, V, dtype)
@@ -39,8 +47,8 @@ def test_rows_at_the_edges_of_tiles_and_parts(B, K, L, V, dtype):
 
 @pytest.mark.parametrize("V,dtype", [(20003, "bf16"), (10002, "f32"), (70001, "bf16")])
 def test_first_entries_masked_or_far_below_the_rest(V, dtype):
-    """The reference exponent of a wave comes from its first vectors: here those are masked in one draft's rows and lie
-    a hundred base-2 units and more below the others in the next one's."""
+    """A lane's running reference starts without a finite entry, and is raised a hundred base-2 units and more on the way:
+    the first third of a row is masked in one draft's rows and lies that far below the rest in the next one's."""
     t, d, tok = _inputs(4, 4, 5, V, "f32", T=0.3)
     n = V // 3
     tok = np.maximum(tok, n + 1).astype(np.int32) % V
