@@ -693,8 +693,9 @@ __device__ __forceinline__ double token_term(double log2q, double log2r, int K)
 // The drafted token's term of a row's Eq. (hik) sum in float64 in place of the sweep's float32 value (see
 // token_term): called by one thread with the sum `total` (relative to 2^shift_q) of the entries [lo, hi) of the
 // row; returns total with the term exchanged if the token (*token) is among them, or total itself where the term
-// needs no second look (decided from the row's statistics: the token is not even fetched then).
-template <typename T>
+// needs no second look (decided from the row's statistics: the token is not even fetched then).  FUSED: the sweep took the
+// term's last product together with its sum, unrounded, and so it is taken out.
+template <typename T, bool FUSED = false>
 __device__ __forceinline__ double with_token_term(double total, const RowStat &st, double log2nu, const T *rq, const T *rp,
                                                   const int32_t *token, int V, int lo, int hi, float c, float shift_q,
                                                   const RatioConst &rc, int K)
@@ -707,7 +708,13 @@ __device__ __forceinline__ double with_token_term(double total, const RowStat &s
     const float zq[1] = {Elem<T>::scalar(rq + tok)}, zp[1] = {Elem<T>::scalar(rp + tok)};
     float wq[1], w[1];
     ot_weights(zq, zp, c, shift_q, rc, K, wq, w);            // the same operations as in the sweep: the same bits
-    return (total - static_cast<double>(w[0])) + token_term(log2q, log2r, K) * exp2_small(st.lse2_q - static_cast<double>(shift_q));
+    double old = static_cast<double>(w[0]);
+    if constexpr (FUSED) {
+        float t[1] = {rc.one_minus_ratio(zp[0] - zq[0], c)};
+        pow_array(t, K);
+        old = static_cast<double>(wq[0]) * static_cast<double>(t[0]);
+    }
+    return (total - old) + token_term(log2q, log2r, K) * exp2_small(st.lse2_q - static_cast<double>(shift_q));
 }
 
 // Integral reference exponent of a group of entries whose largest logit is m (partial sums taken relative to
@@ -857,7 +864,7 @@ __device__ __forceinline__ SegVec<T> seg_load(const T *row, int seg, int lane, i
     SegVec<T> r;
     const bool some = V >= 8;                               // (uniform; a shorter row is unpacked entry by entry)
     const T *base = some ? row + static_cast<long long>(seg) * (kWave * 8) : masked_vector<T>();
-    const int left = some ? V - 8 - seg * (kWave * 8) : 0;  // (may be negative, down to 8 - 512)
+    const int left = some ? V - 8 - seg * (kWave * 8) : 0;  // (may be negative, down to -7: a segment holds an entry)
     const int at = lane * 8 < left ? lane * 8 : left;
 #pragma unroll
     for (int i = 0; i < 8 / PV; ++i) r.v[i] = load16_any(base + at + i * PV);

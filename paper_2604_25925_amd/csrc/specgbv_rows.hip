@@ -373,7 +373,7 @@ k_rows(const T *__restrict__ target, const T *__restrict__ draft, RowsArgs ar)
     }
     double total = block_sum(static_cast<double>(acc), sh_Z);
     if (tid == 0) {
-        total = with_token_term<T>(total, st, log2nu, rq, rp, ar.tokens + pair, V, lo * PV, hi * PV < V ? hi * PV : V, c, shift_q, rc, K);
+        total = with_token_term<T, true>(total, st, log2nu, rq, rp, ar.tokens + pair, V, lo * PV, hi * PV < V ? hi * PV : V, c, shift_q, rc, K);
         const double s = total * exp2_small(static_cast<double>(shift_q) - st.lse2_q);
         if (P > 1) {
             ar.s_part[pair * kPendParts + part] = s;
