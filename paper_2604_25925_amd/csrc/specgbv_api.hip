@@ -210,8 +210,8 @@ specgbv_status specgbv_verify_ex(
         // chip, while a chain pays for its modified rows alone (measured: the chain is ahead only while at most
         // about three rows per draft are modified, and a batch waits for its most modified prefix).
         // Without pending modifications every row pair is read once: by the chain schedule where there are enough
-        // drafts for it, else by the rows schedule (which takes all but rows shorter than a vector or longer than
-        // its registers hold; those go the two-pass way).
+        // drafts for it, else by the rows schedule, unless two passes are faster than either or the rows schedule does
+        // not take the shape (rows shorter than a vector or longer than its registers hold).
         if (!pending) {
             use_chain = chain_preferred(p);
             if (!use_chain) p.rows_parts = rows_schedule_parts(p);

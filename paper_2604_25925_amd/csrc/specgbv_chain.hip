@@ -1037,7 +1037,8 @@ k_chain_excess(const T *__restrict__ target, const T *__restrict__ draft, int K,
     }
 }
 
-// Workgroups that can be resident at once: one per compute unit (a workgroup takes 144 KiB of LDS).
+// Workgroups that can be resident at once: one per compute unit (a workgroup takes 144 KiB of LDS; with short rows 64 KiB,
+// and chain_grid doubles the number).
 int resident_workgroups()
 {
     static int cached[64] = {};

@@ -98,7 +98,7 @@ struct DecideIO {
     double *s_store;            //              and the complete ones are stored here by the writing workgroup
     int s_parts;
     int e_parts;                // > 0: an entry kExcessPending of e_arr stands for the sum of the row's first e_parts parts
-    int e_coop;                 // != 0 (two-pass schedule): nobody has looked yet whether a row needs E; the
+    int e_coop;                 // != 0 (two-pass schedule, rows in parts): nobody has looked yet whether a row needs E; the
                                 // workgroups of the prefix find out and sum it together (e_part_rw: parts, each -1 until there)
     double *e_part_rw;
     int e_polls;                // looks a workgroup takes at a part another one sums before it sums the part itself
@@ -182,7 +182,7 @@ __device__ __forceinline__ void decide_prefix(const DecideIO &io, int b, int K, 
         while (n < L && tok[k1 * L + n] == tok[k2 * L + n]) ++n;
         cpl[idx] = static_cast<unsigned char>(n);
     }
-    // One entry of the acceptance table.  With may_mark (two-pass schedule, first visit): a row whose s and g cancel
+    // One entry of the acceptance table.  With may_mark (e_coop, first visit): a row whose s and g cancel
     // so far that h needs E = nu^2 (s - g) summed term by term (the kernels' two tests; rows under pending
     // modifications keep the plain sum) is marked instead and true is returned; its entry is made after the
     // workgroups of the prefix have summed E together.
@@ -696,7 +696,7 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
         decide_kseq<T>(target, draft, io, b, K, L, V, c, seed, offset, blockIdx.x == 0, lds_decide, &sh_sel, &sh_u, &sh_tab);
         K = 1;
     } else {
-        // Two-pass schedule: whether a row's s and g cancel so far that its E = nu^2 (s - g) has to be summed term by
+        // Two-pass schedule, and rows in parts: whether a row's s and g cancel so far that its E = nu^2 (s - g) has to be summed term by
         // term is looked at here (with small batches the sums of Eq. (hik) arrive in parts and meet here; with larger
         // ones the sum kernel's workgroup would have to take a second sweep alone).  tq holds the token probabilities
         // under the pending modifications, if there are any, so nu is the one the decision uses.  Every workgroup of the
@@ -705,7 +705,8 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
         // function, called only then): the (row, part) units of all such rows, at most kPendParts parts each, are dealt out
         // to the workgroups and left in the workspace with device-scope stores; every workgroup needs all parts (each runs
         // the decision itself) and polls for them, a part per thread.  (Row after row, with a wait for every row, took 8 - 9 us
-        // a row: 8 x 4 drafts of 5 at V = 32000 with two such rows 22 us in this kernel, 19.6 now; with pending modifications 8 x 4 of 8 at V = 128256 43 us, 27 now.)  The wait is bounded: a part that has not
+        // a row: 8 x 4 drafts of 5 at V = 32000 with two such rows 22 us in this kernel, 19.6 now; with pending modifications
+        // 8 x 4 of 8 at V = 128256 43 us, 27 now.)  The wait is bounded: a part that has not
         // arrived after io.e_polls looks (its workgroup has not been scheduled yet, say) is summed by the waiting
         // workgroup itself -- the same bits, stored again -- so no workgroup depends on another one's progress.
         auto excess_sums = [&](const double *tq, const double *tp, const double *lq, const double *lp, double *ex, int *list) {

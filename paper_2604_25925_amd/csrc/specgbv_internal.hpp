@@ -34,7 +34,8 @@ struct Workspace {
     size_t pend_off;   // int32  [kMaxPend][B+1]  per level: rows the level modifies in the prefixes before b (two-pass schedule)
     size_t pend_part;  // double [B*K*L][kPendParts]  partial normalisers of a modified row shared among workgroups
     size_t pend_cnt;   // int32  [B*K*L]  workgroups of a shared row that have stored their partial normaliser
-    size_t stat_part;  // Row0Part [B*K*L][2][kRowParts]  partial row statistics (two-pass schedule, small batches)
+    size_t stat_part;  // Row0Part [B*K*L][2][kRowParts]  partial row statistics (two-pass schedule, small batches; the rows
+                       //             schedule keeps its parts' log2-normalisers there)
     size_t row0;       // Row0Part [B][2][kRow0Parts]  partial statistics of the rows 0 a prefix's drafts share (chain schedule)
     size_t later;      // int32 [workgroups][1 + rows a workgroup sums]  chain schedule: per workgroup, the number of rows
                        //             whose Eq. (hik) sum is taken again without cancellation, then their row indices
@@ -43,7 +44,7 @@ struct Workspace {
     int nseg;
 };
 
-constexpr int kMaxChainGrid = 1024;            // workgroups of the chain kernel at most (one per compute unit)
+constexpr int kMaxChainGrid = 1024;            // workgroups of the chain kernel at most (one or two per compute unit)
 constexpr int kPendParts = 16;                 // workgroups a modified row's normaliser is shared among, at most
 constexpr int kRowParts = 16;                  // workgroups a row is shared among at most when the batch is small
 constexpr int kRow0Parts = 16;                 // slices a shared row 0 is reduced in
@@ -83,7 +84,7 @@ struct Problem {
     int s_parts;                   // > 1: the sums of Eq. (hik) are left as this many partial sums per row (small batches)
     int e_parts;                   // > 0 (chain schedule): rows marked kExcessPending have their E in this many parts
     int rows_parts;                // > 0: the rows schedule, with this many parts per row
-    int e_coop;                    // != 0 (two-pass schedule): the final-token kernel finds the rows that need E and sums it
+    int e_coop;                    // != 0 (two-pass schedule, rows in parts): the final-token kernel finds the rows that need E and sums it
     int kseq_ndrafts;              // > 0: the comparison verifier (K-SEQ rule of Section 3.2) on the first kseq_ndrafts drafts
 };
 
@@ -97,7 +98,7 @@ hipError_t launch_split_main(const Problem &p);
 int split_sum_parts(const Problem &p);
 
 // Schedule "rows": every row pair (or one of its parts, a power of two of them) in the registers of one workgroup.
-// rows_schedule_parts(): the number of parts, 0 where the schedule does not take the shape.
+// rows_schedule_parts(): the number of parts, 0 where the schedule does not take the shape or the two-pass one is ahead.
 int rows_schedule_parts(const Problem &p);
 hipError_t launch_rows_main(const Problem &p);
 
@@ -105,7 +106,7 @@ hipError_t launch_rows_main(const Problem &p);
 // the statistics sweep and the Eq. (hik) sweep.  chain_supported() says whether the shape
 // fits the kernel's static limits.
 bool chain_supported(const Problem &p);
-bool chain_preferred(const Problem &p);      // supported, and enough chains for it to beat the two-pass schedule
+bool chain_preferred(const Problem &p);      // supported, and ahead of the other schedules by their measured costs
 bool chain_supports_pending(const Problem &p);   // supported, and the whole row pair fits on chip (pending modifications)
 hipError_t launch_chain_main(const Problem &p);
 // The chain schedule's follow-up kernel: E = nu^2 (s - g) of the rows k_chain handed over (usually none).
