@@ -3,8 +3,9 @@ every remainder of a vector, against the oracle (needs an MI355X: run with -m gp
 import numpy as np
 import pytest
 
+import test_gpu_peaked_rows as peaked
 from parity_util import to_torch
-from specgbv_synth import Workload, make_inputs
+from specgbv_synth import Workload, f32_to_bf16_bits, make_inputs
 from test_gpu_comparison import check
 
 pytestmark = pytest.mark.gpu
@@ -49,3 +50,27 @@ def test_normalisers_of_short_odd_rows(V, dtype, T):
         ref = (m[..., 0] + torch.log2(torch.exp2(y - m).sum(-1))).numpy() * 0.693147180559945309417
         err = np.abs(got[name] - ref).max()
         assert err <= 1e-9, "%s: off by %.3g" % (name, err)
+
+
+@pytest.mark.parametrize("V,dtype", [(32768, "bf16"), (3001, "f32")])
+@pytest.mark.parametrize("T", [1.0, 0.4])
+def test_near_certain_drafted_tokens(V, dtype, T):
+    """Rows whose mass sits on the drafted token to within 1e-3 - 1e-6 in either model: the roots balance the other entries'."""
+    B, K, L = 5, 4, 4
+    t, d, tok = peaked._case(B, K, L, V, T, seed=31)
+    rng = np.random.default_rng(32)
+    for b in range(B):
+        eq, ep = peaked.EPS[b]
+        x0 = int(tok[b, 0, 0])
+        peaked._set_probability(t[b, 0, 0], x0, T, 1 - eq)
+        peaked._set_probability(d[b, 0, 0], x0, T, 1 - ep)
+        for k in range(K):
+            t[b, k, 0], d[b, k, 0] = t[b, 0, 0], d[b, 0, 0]
+            tok[b, k, 0] = x0 if k != 2 else int(rng.integers(0, V))
+            for r in range(1, L):
+                if k % 2 == 0:
+                    peaked._set_probability(t[b, k, r], int(tok[b, k, r]), T, 1 - eq * (r + 1))
+                    peaked._set_probability(d[b, k, r], int(tok[b, k, r]), T, 1 - ep / (r + 1))
+    if dtype == "bf16":
+        t, d = f32_to_bf16_bits(t), f32_to_bf16_bits(d)
+    check(t, d, tok, T, 3, 1, None, "K-SEQ near-certain tokens V=%d %s T=%g" % (V, dtype, T))

@@ -104,3 +104,48 @@ def test_normalisers_are_as_accurate_as_on_the_two_pass_schedule(V, T):
         rms[algo] = float(np.sqrt(np.mean([np.square(g["lse_q"] - ref[0]), np.square(g["lse_p"] - ref[1])])))
     print("[normalisers] V=%d T=%g: rms %r" % (V, T, rms), flush=True)
     assert rms["auto"] <= 1.1 * rms["split"]
+
+
+def test_two_streams_at_once():
+    """Calls of the rows schedule on two streams, each with its own workspace, beside calls that fill the GPU: whatever the
+    order in which workgroups come to run, the results have the bits of the calls made alone."""
+    import torch
+    import paper_2604_25925_amd as sg
+    from parity_util import to_torch
+    shapes = [(9, 4, 8, 9001, "bf16"), (1, 3, 8, 65543, "bf16"), (8, 4, 5, 32000, "f32")]
+    cases = []
+    for i, shape in enumerate(shapes):
+        B, K, L, V, dtype = shape
+        t, d, tok = _inputs(B, K, L, V, dtype, seed=20 + i)
+        inp = (to_torch(t), to_torch(d), to_torch(tok))
+        cases.append((shape, inp, [sg.specgbv_verify(*inp, 0.8, 3, 1) for _ in range(2)]))
+    torch.cuda.synchronize()
+
+    def read(c, n):
+        (B, K, L, V, dtype), _, runs = c
+        res = sg.specgbv_read_intermediates(runs[n][3], B, K, L, V, 1 if dtype == "bf16" else 0)
+        res.update(out=[x.cpu().numpy().copy() for x in runs[n][:3]])
+        return res
+
+    alone = [read(c, 0) for c in cases]
+    streams = [torch.cuda.Stream(), torch.cuda.Stream()]
+    big, other = torch.empty(1 << 28, dtype=torch.uint8, device="cuda"), torch.empty(1 << 28, dtype=torch.uint8, device="cuda")
+    busy = torch.cuda.Stream()
+    for _ in range(5):
+        with torch.cuda.stream(busy):
+            for _ in range(8):
+                big.copy_(other)
+        for rep in range(4):
+            for n, st in enumerate(streams):
+                with torch.cuda.stream(st):
+                    for _, inp, runs in (cases if (rep + n) % 2 else cases[::-1]):
+                        sg.specgbv_verify(*inp, 0.8, 3, 1, workspace=runs[n][3], out=runs[n][:3])
+        torch.cuda.synchronize()
+        for i, c in enumerate(cases):
+            for n in range(2):
+                got = read(c, n)
+                for key, want in alone[i].items():
+                    if key == "out":
+                        assert all(np.array_equal(a, b) for a, b in zip(want, got[key])), (c[0], n)
+                    else:
+                        assert np.array_equal(want, got[key], equal_nan=True), (c[0], n, key)
