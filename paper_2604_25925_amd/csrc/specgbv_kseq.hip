@@ -198,7 +198,7 @@ k_kseq_rows(const T *__restrict__ target, const T *__restrict__ draft, const int
 
 // Rows of at most NS * kKseqThreads vectors, read once: after the statistics a thread keeps of its entries the weights
 // e = q[x] and the ratios p[x] / q[x], and a step is ten instructions per entry, without an exponential and without
-// memory.  One workgroup has the compute unit's registers to itself (64 entries per thread); what bounds it is a row's
+// memory.  At 64 entries per thread a workgroup has the compute unit's registers to itself; what bounds it is a row's
 // own chain: load, statistics, and a step's sweep and barrier for each of five steps in the rows 0 (most others have a
 // single candidate and one step).  Before, a workgroup streamed its row pair alone for every step, 27 us each at
 // V = 32000 float32: 32 x 4 drafts of 8 took 206 us a call, 99 now; 64 x 8 in bfloat16 634, 280 now.
@@ -323,8 +323,14 @@ hipError_t launch_kseq_typed(const Problem &p, int ndrafts)
 #define SPECGBV_KSEQ_ONCHIP(NS)                                                                                       \
     hipLaunchKernelGGL((k_kseq_onchip<T, NS>), grid, dim3(kKseqThreads), 0, p.stream, target, draft, p.tokens, p.K, p.L, \
                        p.V, ndrafts, p.c, p.c_rel, stats, rho, beta, counter)
-    if (p.V >= PV && nv <= 16 / PV * kKseqThreads) SPECGBV_KSEQ_ONCHIP(16 / PV);         // 16 entries per thread
-    else if (p.V >= PV && nv <= 64 / PV * kKseqThreads) SPECGBV_KSEQ_ONCHIP(64 / PV);    // 64
+    // 16, 32 and 64 entries per thread; 64 leave room for one workgroup per compute unit, whose load, statistics and steps
+    // then follow one another with nothing beside them.  That pays where rows 0 take five steps from registers instead of
+    // memory, not for a single draft, whose rows all take one (128 drafts of 5, V = 20000 float32: 63 us from registers, 51
+    // from memory), and not for rows that 32 hold (64 x 4 drafts of 5, V = 10000 float32: 112 us with 64, 73 with 32, 83
+    // from memory; 128 drafts of 5: 54, 37, 36; at 16384: 60, 41, 44).
+    if (p.V >= PV && nv <= 16 / PV * kKseqThreads) SPECGBV_KSEQ_ONCHIP(16 / PV);
+    else if (p.V >= PV && nv <= 32 / PV * kKseqThreads) SPECGBV_KSEQ_ONCHIP(32 / PV);
+    else if (p.V >= PV && ndrafts > 1 && nv <= 64 / PV * kKseqThreads) SPECGBV_KSEQ_ONCHIP(64 / PV);
     else if (vec)
         hipLaunchKernelGGL((k_kseq_rows<T, true>), grid, dim3(kKseqThreads), 0, p.stream, target, draft, p.tokens, p.K, p.L,
                            p.V, ndrafts, p.c, p.c_rel, stats, rho, beta, counter);

@@ -1,4 +1,4 @@
-"""K-SEQ rows kept in registers, at the edges of their two tiles (16 and 64 entries for each of 512 threads) and with
+"""K-SEQ rows kept in registers, at the edges of their tiles (16, 32 and 64 entries for each of 512 threads) and with
 every remainder of a vector, against the oracle (needs an MI355X: run with -m gpu)."""
 import numpy as np
 import pytest
@@ -14,6 +14,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("B,K,L,V,dtype", [
     (3, 4, 2, 8, "bf16"), (3, 4, 2, 13, "bf16"), (3, 4, 2, 4, "f32"), (3, 4, 2, 7, "f32"), (3, 4, 2, 3, "f32"),
     (2, 4, 3, 8192, "bf16"), (2, 4, 3, 8193, "bf16"), (2, 4, 3, 8191, "f32"), (2, 4, 3, 8195, "f32"),
+    (2, 4, 3, 16384, "bf16"), (2, 4, 3, 16377, "bf16"), (2, 4, 3, 16385, "bf16"), (2, 4, 3, 16382, "f32"), (2, 4, 3, 16385, "f32"),
+    (2, 1, 3, 16384, "f32"), (2, 1, 3, 16388, "f32"), (2, 1, 3, 16385, "bf16"), (2, 1, 3, 32765, "bf16"),
     (2, 4, 3, 32768, "bf16"), (2, 4, 3, 32761, "bf16"), (2, 4, 3, 32769, "bf16"), (2, 4, 3, 32766, "f32"), (2, 4, 3, 32772, "f32"),
 ])
 def test_tiles(B, K, L, V, dtype):
