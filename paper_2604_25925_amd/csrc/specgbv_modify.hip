@@ -104,7 +104,12 @@ k_mod_stats(const T *__restrict__ target, const T *__restrict__ draft, const int
     }
 }
 
-constexpr int kRowSlots = 40;          // vectors per thread k_mod_row keeps: rows up to 163840 bfloat16 / 81920 float32 entries
+// Vectors per thread that k_mod_row keeps.  40: rows up to 163840 bfloat16 / 81920 float32 entries, one workgroup per
+// compute unit.  12: up to 49152 / 24576 entries, three workgroups per compute unit, which a row of few vectors needs, since
+// its load, sum and stores follow one another.  32 x 8 drafts of 8, bfloat16, by 40, by 12 and by k_mod_stats (rows read
+// twice), us a call: V = 8193 133, 81, 80; 16385 184, 129, 138; 40961 353, 321, 359.  (8 or 16 are each 3 - 10 % slower at
+// one end of the range that they share with 12.)
+constexpr int kRowSlots = 40, kShortRowSlots = 12;
 
 // Four floats to an address that needs the alignment of one only.
 __device__ __forceinline__ void store16_any(float *dst, float a, float b, float c, float d)
@@ -130,8 +135,9 @@ __device__ __forceinline__ void store_vals(float *dst, const float (&v)[N])
 // k_mod_stats for rows of at most kRowSlots * kModThreads vectors, with the row kept in registers: the workgroup
 // then also writes the row's natural-log probabilities unless a modification is pending for it (target rows below
 // the prefix's count: k_mod_norm and k_mod_write do those).  grid.x = target rows followed by draft rows; all of a
-// thread's loads are issued before the first is used.
-template <typename T>
+// thread's loads are issued before the first is used.  WHOLE: the row is a multiple of the vector (masking a repeated end in
+// all slots instead costs 2 - 9 % in float32: 2 x 8 drafts of 4 at V = 64000 58 us, 62 with it).
+template <typename T, bool WHOLE, int SLOTS>
 __global__ void __launch_bounds__(kModThreads)
 k_mod_row(const T *__restrict__ target, const T *__restrict__ draft, const int32_t *__restrict__ tokens, int K,
           int M, int bonus, int V, float c, long long n_trows, const int32_t *__restrict__ modify_count,
@@ -149,24 +155,24 @@ k_mod_row(const T *__restrict__ target, const T *__restrict__ draft, const int32
     const int r = static_cast<int>(row % (is_draft ? M : rows_t));
     const long long bk = row / (is_draft ? M : rows_t);
     constexpr int PV = Elem<T>::kPerVec;
-    const int nvec = row_vectors<T>(V);                    // host: nvec <= kRowSlots * kModThreads
+    const int nvec = row_vectors<T>(V);                    // host: nvec <= SLOTS * kModThreads
     const int tid = threadIdx.x;
-    U4 v[kRowSlots];
+    U4 v[SLOTS];
 #pragma unroll
-    for (int j = 0; j < kRowSlots; ++j) {
+    for (int j = 0; j < SLOTS; ++j) {
         const int idx = j * kModThreads + tid;
         if (j * kModThreads < nvec)                        // (uniform: slots the row does not reach issue nothing)
-            v[j] = load16_stream_any(z_row + vector_entry<T>(idx < nvec ? idx : nvec - 1, V));
+            v[j] = load16_stream_any(z_row + (WHOLE ? (idx < nvec ? idx : nvec - 1) * PV : vector_entry<T>(idx, V)));
         else
             v[j] = U4{0, 0, 0, 0};
     }
     RunningSum acc;
 #pragma unroll
-    for (int j = 0; j < kRowSlots; ++j) {
+    for (int j = 0; j < SLOTS; ++j) {
         if (j * kModThreads + tid < nvec) {
             float z[PV];
             Elem<T>::unpack(v[j], z);
-            mask_repeated<T>(z, j * kModThreads + tid, V);
+            if constexpr (!WHOLE) mask_repeated<T>(z, j * kModThreads + tid, V);
             acc.add(z, c);
         }
     }
@@ -192,14 +198,14 @@ k_mod_row(const T *__restrict__ target, const T *__restrict__ draft, const int32
     const float h = static_cast<float>(lse2);
     const float dlt = static_cast<float>(lse2 - static_cast<double>(h));
 #pragma unroll
-    for (int j = 0; j < kRowSlots; ++j) {
+    for (int j = 0; j < SLOTS; ++j) {
         const int idx = j * kModThreads + tid;
         if (idx < nvec) {
             float z[PV], a[PV];
             Elem<T>::unpack(v[j], z);
 #pragma unroll
             for (int e = 0; e < PV; ++e) a[e] = (fmaf(z[e], c, -h) - dlt) * kLn2f;
-            store_vals(out + vector_entry<T>(idx, V), a);          // (repeated entries: the same values again)
+            store_vals(out + (WHOLE ? idx * PV : vector_entry<T>(idx, V)), a);     // (repeated entries: the same values again)
         }
     }
 }
@@ -347,11 +353,16 @@ hipError_t launch_modify_typed(const void *target_v, const void *draft_v, const 
     const bool vec = read_by_vectors<T>(V) && !(in_place && V % Elem<T>::kPerVec != 0);
     // rows short enough to stay in a workgroup's registers are read once unless a modification is pending for them
     const bool rows_fit = vec && !in_place && row_vectors<T>(V) <= kRowSlots * kModThreads;
+    const bool short_rows = row_vectors<T>(V) <= kShortRowSlots * kModThreads, whole = V % Elem<T>::kPerVec == 0;
+#define SPECGBV_MOD_ROW(WHOLE, SLOTS)                                                                                \
+    hipLaunchKernelGGL((k_mod_row<T, WHOLE, SLOTS>), dim3(static_cast<unsigned>(n_t + n_d)), blk, 0, stream, target, \
+                       draft, tokens, K, M, bonus, V, c, n_t, count, tstat, dstat, out_logq, out_logp)
 #define SPECGBV_MOD_LAUNCH(VEC)                                                                                   \
     do {                                                                                                          \
-        if (rows_fit)                                                                                             \
-            hipLaunchKernelGGL((k_mod_row<T>), dim3(static_cast<unsigned>(n_t + n_d)), blk, 0, stream, target,     \
-                               draft, tokens, K, M, bonus, V, c, n_t, count, tstat, dstat, out_logq, out_logp);   \
+        if (rows_fit && short_rows && whole) SPECGBV_MOD_ROW(true, kShortRowSlots);                               \
+        else if (rows_fit && short_rows) SPECGBV_MOD_ROW(false, kShortRowSlots);                                  \
+        else if (rows_fit && whole) SPECGBV_MOD_ROW(true, kRowSlots);                                             \
+        else if (rows_fit) SPECGBV_MOD_ROW(false, kRowSlots);                                                     \
         else                                                                                                      \
             hipLaunchKernelGGL((k_mod_stats<T, VEC>), dim3(static_cast<unsigned>(n_t + n_d)), blk, 0, stream,      \
                                target, draft, tokens, M, bonus, V, c, n_t, tstat, dstat);                         \
@@ -364,6 +375,7 @@ hipError_t launch_modify_typed(const void *target_v, const void *draft_v, const 
     if (vec) SPECGBV_MOD_LAUNCH(true);
     else SPECGBV_MOD_LAUNCH(false);
 #undef SPECGBV_MOD_LAUNCH
+#undef SPECGBV_MOD_ROW
     return hipGetLastError();
 }
 

@@ -31,6 +31,14 @@ def test_modify(V, dtype):
     _check_modify(np.ascontiguousarray(t[:, :, :3]), d, tok, 0.9, np.array([0.2, -0.4]), np.array([2, 1], np.int32), "odd rows modify %d %s" % (V, dtype))
 
 
+@pytest.mark.parametrize("V,dtype", [(49152, "bf16"), (49145, "bf16"), (49153, "bf16"), (4097, "bf16"),
+                                     (24576, "f32"), (24573, "f32"), (24577, "f32"), (24580, "f32"), (2049, "f32")])
+def test_modify_rows_in_registers(V, dtype):
+    """Both sides of the edge between the two tiles (12 and 40 vectors for each of 512 threads), whole vectors and a repeated
+    end, and an end of its own slot."""
+    test_modify(V, dtype)
+
+
 @pytest.mark.parametrize("V,dtype", [s for s in SHAPES if s[0] > 100])
 def test_pending(V, dtype):
     t, d, tok = _inputs(6, 2, 4, V, dtype)
