@@ -23,7 +23,10 @@
 // table by waves it leaves idle, a wave's loads all leave before the first is unpacked (behind a branch each they were
 // waited for one by one), and the search runs in one wave without a barrier.  Before / after, us in this kernel:
 // V = 1000, one prefix 11.4 / 9.5; V = 128256, one prefix 17.7 / 12.2; 32 prefixes 23.4 / 19.2; rows at odd addresses
-// (entry by entry before) 41 prefixes of V = 32003 74 / 18.
+// (entry by entry before) 41 prefixes of V = 32003 74 / 18.  Since then the table's float64 chains stand side by side and
+// the outputs that are not waited for are written by all waves (time stamps at V = 32000, 8 prefixes: table 2.1 -> 1.7 us,
+// partial sums in parts added four loads at a time; one prefix of V = 128256 28.7 -> 27.3 us a call), and rows that need E
+// are summed by waves, not by workgroups (excess_sums).
 #include "specgbv_internal.hpp"
 
 namespace specgbv {
@@ -34,24 +37,27 @@ constexpr int kSegAtOnce = 4;                // residual segments whose loads a 
 
 // ---------------------------------------------------------------- k_decide
 
-// (1 - (1-P)^K) / P = sum_{j<K} (1-P)^j: chance that one of K i.i.d. drafts equals a block of
-// draft probability P, over P.  The geometric sum has no cancellation for tiny P (it tends to K)
-// and costs K - 1 fused multiply-adds instead of a log1p and an expm1.
-__device__ double c_K(double P, int K)
+// exp2_small without its branches: an acceptance-table entry takes three of them, and the compiler interleaves them only
+// where no control flow lies between (one after the other they were a good part of the table's time).
+__device__ __forceinline__ double exp2_flat(double x)
 {
-    if (!(P > 0.0)) return static_cast<double>(K);
-    if (P >= 1.0) return 1.0;
-    const double a = 1.0 - P;
-    double c = 1.0;
-    for (int j = 1; j < K; ++j) c = fma(c, a, 1.0);
-    return c;
-}
-
-// max(1 - 1/nu, 0)^K from 1/nu.
-__device__ double g_K(double inv_nu, int K)
-{
-    const double t = 1.0 - inv_nu;
-    return t > 0.0 ? powi_uniform(t, K) : 0.0;
+    const double xc = fmin(fmax(x, -1001.0), 1001.0);
+    const double n = rint(xc), f = (xc - n) * 0.693147180559945309417;
+    double p = 1.0 / 479001600.0;
+    p = fma(p, f, 1.0 / 39916800.0);
+    p = fma(p, f, 1.0 / 3628800.0);
+    p = fma(p, f, 1.0 / 362880.0);
+    p = fma(p, f, 1.0 / 40320.0);
+    p = fma(p, f, 1.0 / 5040.0);
+    p = fma(p, f, 1.0 / 720.0);
+    p = fma(p, f, 1.0 / 120.0);
+    p = fma(p, f, 1.0 / 24.0);
+    p = fma(p, f, 1.0 / 6.0);
+    p = fma(p, f, 0.5);
+    p = fma(p, f, 1.0);
+    p = fma(p, f, 1.0);
+    const double r = ldexp(p, static_cast<int>(n));
+    return x > 1000.0 ? INFINITY : (x > -1000.0 ? r : 0.0);      // (not a number: 0)
 }
 
 // Bitwise OR over the 64 lanes of the wave with data-parallel-primitive moves (row shifts by
@@ -133,8 +139,10 @@ __device__ __forceinline__ void decide_prefix(const DecideIO &io, int b, int K, 
     double *lq = lds + 3 * KL;                              // [K*L] log2 normaliser of target row r
     double *lp = lds + 4 * KL;                              // [K*L] log2 normaliser of draft row r
     double *ex = lds + 5 * KL;                              // [K*L] nu^2 (s - g) where it was summed without cancellation, else < 0
-    unsigned long long *acc_bits = reinterpret_cast<unsigned long long *>(lds + 6 * KL);   // [K] bit i: eta_{k,i} < h_{k,i}
-    int *tok = reinterpret_cast<int *>(acc_bits + K);       // [K*L]
+    double *dd = lds + 6 * KL;                              // [K*L] (1 - Q) S2 of the entries marked kExcessPending
+    unsigned long long *acc_bits = reinterpret_cast<unsigned long long *>(lds + 7 * KL);   // [K] bit i: eta_{k,i} < h_{k,i}
+    unsigned long long *was_tested = acc_bits + K, *was_skipped = was_tested + K;          // [K] bit i: what happened at length i
+    int *tok = reinterpret_cast<int *>(was_skipped + K);    // [K*L]
     float *et = reinterpret_cast<float *>(tok + KL);        // [K*L + 1] the uniforms (24 bits: exact in float32)
     int *list = reinterpret_cast<int *>(et + KL + 1);       // [K*L] scratch of excess_sums
     unsigned char *cpl = reinterpret_cast<unsigned char *>(list + KL);   // [K*K] common prefix lengths (at most L <= 62)
@@ -142,7 +150,7 @@ __device__ __forceinline__ void decide_prefix(const DecideIO &io, int b, int K, 
     const long long base = static_cast<long long>(b) * KL;
     constexpr double kLn2 = 0.693147180559945309417;
 
-    for (int idx = tid; idx < K; idx += kDecideThreads) acc_bits[idx] = 0ull;
+    for (int idx = tid; idx < K; idx += kDecideThreads) acc_bits[idx] = was_tested[idx] = was_skipped[idx] = 0ull;
     for (int idx = tid; idx < KL; idx += kDecideThreads) {
         const RowStat st = stats[base + idx];
         const int tok_raw = tokens[base + idx];
@@ -158,7 +166,14 @@ __device__ __forceinline__ void decide_prefix(const DecideIO &io, int b, int K, 
         double s = 0.0, e = -1.0;
         if (i < L) {
             if (io.s_parts > 1) {                           // in part order: the same bits in every workgroup
-                for (int q = 0; q < io.s_parts; ++q) s += io.s_part[(base + k * L + i) * kPendParts + q];
+                const double *src = io.s_part + (base + k * L + i) * kPendParts;
+                for (int q = 0; q < io.s_parts; q += 4) {   // (four loads in flight; kPendParts is a multiple of four)
+                    double v[4];
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) v[a] = src[q + a];
+#pragma unroll
+                    for (int a = 0; a < 4; ++a) s += q + a < io.s_parts ? v[a] : 0.0;
+                }
                 if (write) io.s_store[base + k * L + i] = s;
             } else {
                 s = s_arr[base + k * L + i];
@@ -182,65 +197,63 @@ __device__ __forceinline__ void decide_prefix(const DecideIO &io, int b, int K, 
         while (n < L && tok[k1 * L + n] == tok[k2 * L + n]) ++n;
         cpl[idx] = static_cast<unsigned char>(n);
     }
-    // One entry of the acceptance table.  With may_mark (e_coop, first visit): a row whose s and g cancel
-    // so far that h needs E = nu^2 (s - g) summed term by term (the kernels' two tests; rows under pending
-    // modifications keep the plain sum) is marked instead and true is returned; its entry is made after the
-    // workgroups of the prefix have summed E together.
-    auto table_entry = [&](int idx, bool may_mark) -> bool {
-        const double e = static_cast<double>(et[idx]);
+    // One entry of the acceptance table.  With may_mark (e_coop): a row whose s and g cancel so far that h needs
+    // E = nu^2 (s - g) summed term by term (the kernels' two tests; rows under pending modifications keep the plain sum)
+    // is marked instead and true is returned; its entry is finished after the workgroups of the prefix have summed E
+    // together.  The time is that of one chain of float64 latencies: the running sums are read four entries at a time, the
+    // three exponentials and the three recurrences over K stand side by side, and all cases share one division.
+    auto finish_entry = [&](int idx, double num, double den, bool exact) {
         const int k = idx / L, i = idx % L + 1;
-        const double s = l2nu[idx];                         // parked by this thread above
-        double log2nu = 0.0, log2P = 0.0;
-        for (int j = 0; j < i; ++j) {
-            log2nu += tq[k * L + j] - tp[k * L + j];
-            log2P += tp[k * L + j];
-        }
-        const double log_nu = log2nu * kLn2, log_P = log2P * kLn2;
-        // two exponentials per entry: 1/nu (nu by one division) and P
-        const double inv_nu = exp2_small(-log2nu), P = exp2_small(log2P);
-        const double nu = 1.0 / inv_nu;
-        const double g = g_K(inv_nu, K), cK = c_K(P, K);
-        double hv;
-        if (i < L && log2nu > 0.0) {
-            if (may_mark && excess_wanted(static_cast<float>(log2nu), static_cast<float>(s), K) &&
-                excess_needed(log2nu, log2P, s, K)) {
-                bool modified = false;
-                if (io.pend)
-                    for (int l = 0; l < io.nlev; ++l)
-                        modified = modified || io.pend[static_cast<long long>(l) * io.n_rows + base + idx + 1].flag != 0;
-                if (!modified) { ex[idx] = kExcessPending; return true; }
-            }
-            // Block ratio above one: the denominator c_K(P) - nu (1 - s) equals [c_K(P) - c_K(1/nu)] + nu (s - g),
-            // and c_K(P) - c_K(1/nu) = (1 - Q) S2 / nu with Q = nu P the block's joint target probability and
-            // S2 = sum_{j=1}^{K-1} sum_{m<j} (1-P)^m (1 - 1/nu)^(j-1-m) (by the recurrence U_1 = 1,
-            // U_{j+1} = (1-P) U_j + (1 - 1/nu)^j), every term non-negative.  With E = nu^2 (s - g):
-            // h = E / (E + (1 - Q) S2), where E comes from the sum kernels when s and g nearly cancel.
-            const double A = 1.0 - P, t1 = 1.0 - inv_nu;
-            double U = 1.0, S2 = 0.0, pw = 1.0;
-            for (int j = 1; j <= K - 1; ++j) { S2 += U; pw *= t1; U = fma(A, U, pw); }
-            const double one_Q = fmax(1.0 - exp2_small(log2nu + log2P), 0.0);
-            const double E = ex[idx];
-            if (E >= 0.0) {
-                const double den = E + one_Q * S2;
-                hv = !(E < 1.0e300) ? 1.0 : (den > 0.0 ? clamp01(E / den) : 1.0);
-            } else {
-                const double num = nu * (s - g);
-                const double den = inv_nu * one_Q * S2 + num;
-                hv = den > 0.0 ? clamp01(num / den) : 1.0;
-            }
-        } else if (i < L) {
-            const double num = nu * (s - g);
-            const double den = cK - nu * (1.0 - s);
-            hv = den > 0.0 ? clamp01(num / den) : 1.0;
-        } else {
-            hv = clamp01(nu * (1.0 - g) / cK);
-        }
-        l2nu[idx] = log2nu;
+        const double hv = (exact && !(num < 1.0e300)) || !(den > 0.0) ? 1.0 : clamp01(num / den);
+        const double e = static_cast<double>(et[idx]);
         if (e < hv) atomicOr(&acc_bits[k], 1ull << i);
-        if (write) {
-            io.log_nu_out[base + idx] = log_nu; io.log_P_out[base + idx] = log_P;
-            io.h_out[base + idx] = hv; io.eta_out[base + idx] = e;
+        if (write) { io.h_out[base + idx] = hv; io.eta_out[base + idx] = e; }
+    };
+    auto table_entry = [&](int idx, bool may_mark) -> bool {
+        const int k = idx / L, i = idx % L + 1;
+        const double s = l2nu[idx], E = ex[idx];            // s: parked by this thread above
+        double log2nu = 0.0, log2P = 0.0;
+        for (int j0 = 0; j0 < i; j0 += 4) {
+            double a[4], c[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int at = k * L + (j0 + j < i ? j0 + j : i - 1);
+                a[j] = tq[at]; c[j] = tp[at];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                log2nu += j0 + j < i ? a[j] - c[j] : 0.0;
+                log2P += j0 + j < i ? c[j] : 0.0;
+            }
         }
+        // 1/nu (nu by one division), P and Q = nu P
+        const double inv_nu = exp2_flat(-log2nu), P = exp2_flat(log2P), Q = exp2_flat(log2nu + log2P);
+        const double nu = 1.0 / inv_nu, t1 = 1.0 - inv_nu, A = 1.0 - P;
+        // c_K(P) = (1 - (1-P)^K) / P = sum_{j<K} (1-P)^j: chance that one of K i.i.d. drafts equals a block of draft
+        // probability P, over P (the geometric sum has no cancellation for tiny P: it tends to K); g = max(t1, 0)^K; and
+        // S2 = sum_{j=1}^{K-1} sum_{m<j} (1-P)^m t1^(j-1-m), by the recurrence U_1 = 1, U_{j+1} = (1-P) U_j + t1^j
+        const double Ac = fmax(A, 0.0);
+        double cK = 1.0, U = 1.0, S2 = 0.0, pw = 1.0;
+        for (int j = 1; j <= K - 1; ++j) { cK = fma(cK, Ac, 1.0); S2 += U; pw *= t1; U = fma(A, U, pw); }
+        const double g = t1 > 0.0 ? pw * t1 : 0.0;
+        // Block ratio above one: the denominator c_K(P) - nu (1 - s) equals [c_K(P) - c_K(1/nu)] + nu (s - g),
+        // and c_K(P) - c_K(1/nu) = (1 - Q) S2 / nu, every term non-negative.  With E = nu^2 (s - g):
+        // h = E / (E + (1 - Q) S2), where E comes from the sum kernels when s and g nearly cancel.
+        const bool sub = i < L, above = sub && log2nu > 0.0, exact = above && E >= 0.0;
+        const double D = fmax(1.0 - Q, 0.0) * S2, plain = nu * (s - g);
+        l2nu[idx] = log2nu;
+        if (write) { io.log_nu_out[base + idx] = log2nu * kLn2; io.log_P_out[base + idx] = log2P * kLn2; }
+        if (may_mark && above && excess_wanted(static_cast<float>(log2nu), static_cast<float>(s), K) &&
+            excess_needed(log2nu, log2P, s, K)) {
+            bool modified = false;
+            if (io.pend)
+                for (int l = 0; l < io.nlev; ++l)
+                    modified = modified || io.pend[static_cast<long long>(l) * io.n_rows + base + idx + 1].flag != 0;
+            if (!modified) { ex[idx] = kExcessPending; dd[idx] = D; return true; }
+        }
+        const double num = exact ? E : (sub ? plain : nu * (1.0 - g));
+        const double den = exact ? E + D : (above ? inv_nu * D + plain : (sub ? cK - nu * (1.0 - s) : cK));
+        finish_entry(idx, num, den, exact);
         return false;
     };
     const bool e_coop = io.e_coop != 0;
@@ -256,7 +269,7 @@ __device__ __forceinline__ void decide_prefix(const DecideIO &io, int b, int K, 
             excess_sums(tq, tp, lq, lp, ex, list);
             int n = 0;
             for (int idx = tid; idx < KL; idx += kDecideThreads, ++n)
-                if (marked >> n & 1u) table_entry(idx, false);
+                if (marked >> n & 1u) finish_entry(idx, ex[idx], ex[idx] + dd[idx], true);
         }
     }
     __syncthreads();
@@ -299,10 +312,7 @@ __device__ __forceinline__ void decide_prefix(const DecideIO &io, int b, int K, 
         }
         if (lane == k) { st_lo = tested; st_hi = skipped; rejected = tested & ~acc_k; }
     }
-    if (write && lane < K)
-        for (int i = 1; i <= L; ++i)
-            io.state_out[base + lane * L + i - 1] =
-                static_cast<int32_t>(((st_lo >> i) & 1ull) | (((st_hi >> i) & 1ull) << 1));
+    if (write && lane < K) { was_tested[lane] = st_lo; was_skipped[lane] = st_hi; }
 
     const int kf = f < 0 ? 0 : f;
     // the levels' entries of the selected row, one lane per level (independent loads instead of a serial walk)
@@ -359,12 +369,19 @@ __device__ __forceinline__ void decide_prefix(const DecideIO &io, int b, int K, 
             sel_out->lse2_q = lse2_q + sumN;
         }
     }
-    // position tau belongs to the final token, which the locating workgroup writes
-    if (write)
-        for (int j = lane; j <= L; j += kWave)
-            if (j != tau) io.out_tokens[static_cast<long long>(b) * (L + 1) + j] = j < tau ? tok[kf * L + j] : -1;
+    if (lane == 0) list[0] = kf;                            // (for the outputs below; excess_sums is done with it)
     }
     __syncthreads();
+    if (write) {                                            // (by all waves: one store per thread, not a loop in the first wave)
+        for (int idx = tid; idx < KL; idx += kDecideThreads) {
+            const int k = idx / L, i = idx % L + 1;
+            io.state_out[base + idx] = static_cast<int32_t>(((was_tested[k] >> i) & 1ull) | (((was_skipped[k] >> i) & 1ull) << 1));
+        }
+        // position tau belongs to the final token, which the locating workgroup writes
+        const int tau = sel_out->tau, kf = list[0];
+        for (int j = tid; j <= L; j += kDecideThreads)
+            if (j != tau) io.out_tokens[static_cast<long long>(b) * (L + 1) + j] = j < tau ? tok[kf * L + j] : -1;
+    }
 }
 
 // ------------------------------------------------- comparison verifier: the K-SEQ scan (Section 3.2)
@@ -386,7 +403,7 @@ __device__ __forceinline__ void decide_kseq(const T *target, const T *draft, con
     unsigned long long *eq = reinterpret_cast<unsigned long long *>(lds + KL);  // [K*L] drafts with draft j's token at position i
     unsigned long long *won = reinterpret_cast<unsigned long long *>(lds + 2 * KL);   // [L] drafts whose test at position i succeeds
     unsigned long long *tested = won + L;                                       // [L] drafts tested at position i
-    int *lead_of = reinterpret_cast<int *>(tested + L);                         // [K*L] (in all 3 K L + 2 L doubles of the 6 K L + K)
+    int *lead_of = reinterpret_cast<int *>(tested + L);                         // [K*L] (in all 3 K L + 2 L doubles of the 7 K L + 3 K)
     int *tok = lead_of + KL;                                                    // [K*L]
     const int tid = threadIdx.x;
     const long long base = static_cast<long long>(b) * KL;
@@ -581,55 +598,76 @@ __device__ __forceinline__ double group4_sum(double v)
 // left them); its row count shrinks by tau + 1; used-up levels are dropped, the others move down,
 // and the modification this iteration creates (carry_new, count_new) is appended.  Lanes 4 m .. 4 m + 3
 // look after level m (at most kMaxPend = 16 levels), lane 4 m + q after its emitted rows j = q, q + 4, ...
-template <typename T>
-__device__ __forceinline__ void update_pending_state(const T *target, const T *draft, const DecideIO &io, const FinalOut &fo,
-                                                     const Selection &sl, int b, int K, int L, int V, float c, int winner,
-                                                     int tokid_w, double carry_w, int mcount_w)
+struct PendingLoads {
+    int count_m;                 // old state of level m (read by every lane of its group before anything is written)
+    double carry_m;
+    double val;                  // what level m does to the log2 probability of the tokens emitted at this lane's rows j < tau
+    double base;                 // log2 q_j[e_j] - log2 p_j[e_j] under the unmodified rows, row j = lane < tau
+    RowStat st_tau;              // the final token's row
+    PendRow pt;                  // lane 4 l: level l's entry of that row
+};
+
+// A level survives only if tau + 1 < count <= L - 1; in particular after a whole accepted block every level ends.
+__device__ __forceinline__ bool some_level_may_survive(int tau, int L) { return tau + 2 <= L - 1; }
+
+// What the bookkeeping needs from memory, none of which depends on the final token: asked for in front of the search inside
+// the segment (behind it these loads were two more latencies at the end of the kernel).
+__device__ __forceinline__ PendingLoads pending_loads(const DecideIO &io, const FinalOut &fo, const Selection &sl, int b, int K, int L)
 {
-    static_assert(kMaxPend * 4 == kWave, "four lanes per level");
-    constexpr double kLn2 = 0.693147180559945309417;
     const int lane = threadIdx.x & (kWave - 1);
     const int m = lane >> 2, q = lane & 3;
-    const int nlev = io.nlev, tau = sl.tau;
-    const int batch = static_cast<int>(gridDim.y);
-    const int tokid = __builtin_amdgcn_readlane(tokid_w, winner);
-    const int count_new = __builtin_amdgcn_readlane(mcount_w, winner);
-    const double carry_new = lane_value(carry_w, winner);
-    // old state of level m (read by every lane of its group before anything is written)
-    int count_m = 0;
-    double carry_m = 0.0;
-    if (m < nlev) { count_m = fo.state_count[static_cast<size_t>(m) * batch + b]; carry_m = fo.state_carry[static_cast<size_t>(m) * batch + b]; }
-    double val = 0.0;            // what level m does to the log2 probability of the tokens emitted at this lane's rows
-    double base = 0.0;           // log2 q_j[e_j] - log2 p_j[e_j] under the unmodified rows, row j = lane
-    const bool some_may_survive = tau + 2 <= L - 1;   // a level survives only if tau + 1 < count <= L - 1
-    if (some_may_survive) {      // uniform; otherwise (in particular after a whole accepted block) every level ends
+    const int nlev = io.nlev, tau = sl.tau, batch = static_cast<int>(gridDim.y);
+    PendingLoads pl;
+    pl.count_m = 0; pl.carry_m = 0.0; pl.val = 0.0; pl.base = 0.0;
+    pl.st_tau.lse2_q = pl.st_tau.lse2_p = pl.st_tau.tok2_q = pl.st_tau.tok2_p = 0.0;
+    pl.pt.log2mu = 0.0; pl.pt.log2N = 0.0; pl.pt.tokadj = 0.0; pl.pt.flag = 0; pl.pt.pad = 0;
+    if (m < nlev) { pl.count_m = fo.state_count[static_cast<size_t>(m) * batch + b]; pl.carry_m = fo.state_carry[static_cast<size_t>(m) * batch + b]; }
+    if (some_level_may_survive(tau, L)) {                    // uniform
         const int kf = static_cast<int>(sl.draft_row / L - static_cast<long long>(b) * K);
         const long long row0 = (static_cast<long long>(b) * K + kf) * L;
         // accepted draft tokens: rows j < tau
         if (m < nlev)
             for (int j = q; j < tau; j += 4) {
                 const PendRow pr = io.pend[m * io.n_rows + row0 + j];
-                val += pr.tokadj - pr.log2N;
+                pl.val += pr.tokadj - pr.log2N;
             }
         if (lane < tau) {
             const RowStat st = io.stats[row0 + lane];
-            base = (st.tok2_q - st.lse2_q) - (st.tok2_p - st.lse2_p);
+            pl.base = (st.tok2_q - st.lse2_q) - (st.tok2_p - st.lse2_p);
         }
+        pl.st_tau = io.stats[row0 + tau];
+        if (m < nlev && q == 0) pl.pt = io.pend[m * io.n_rows + row0 + tau];
+    }
+    return pl;
+}
+
+__device__ __forceinline__ void update_pending_state(const DecideIO &io, const FinalOut &fo, const PendingLoads &pl,
+                                                     const Selection &sl, int b, int K, int L, float c, int winner,
+                                                     float zq_w, float zp_w, double carry_w, int mcount_w)
+{
+    static_assert(kMaxPend * 4 == kWave, "four lanes per level");
+    constexpr double kLn2 = 0.693147180559945309417;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int nlev = io.nlev, tau = sl.tau;
+    const int batch = static_cast<int>(gridDim.y);
+    const int count_new = __builtin_amdgcn_readlane(mcount_w, winner);
+    const double carry_new = lane_value(carry_w, winner);
+    const int count_m = pl.count_m;
+    const double carry_m = pl.carry_m;
+    double val = pl.val, base = pl.base;
+    const bool some_may_survive = some_level_may_survive(tau, L);
+    if (some_may_survive) {      // uniform
         // the final token y at row tau: its probabilities under the unmodified rows ...
-        const RowStat st_tau = io.stats[row0 + tau];
-        const double zq_y = static_cast<double>(Elem<T>::scalar(target + sl.target_row * V + tokid)) * static_cast<double>(c);
-        const double zp_y = static_cast<double>(Elem<T>::scalar(draft + sl.draft_row * V + tokid)) * static_cast<double>(c);
-        const double by = ((zq_y - st_tau.lse2_q) - (zp_y - st_tau.lse2_p)) * (1.0 + io.c_rel);
+        const double zq_y = static_cast<double>(__uint_as_float(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(zq_w)), winner))) * static_cast<double>(c);
+        const double zp_y = static_cast<double>(__uint_as_float(__builtin_amdgcn_readlane(static_cast<int>(__float_as_uint(zp_w)), winner))) * static_cast<double>(c);
+        const double by = ((zq_y - pl.st_tau.lse2_q) - (zp_y - pl.st_tau.lse2_p)) * (1.0 + io.c_rel);
         if (lane == tau) base = by;
         // ... and the levels' factors there, one level after the other (wave-uniform loop; lane 4 l holds level l's entry)
-        PendRow pt;
-        pt.log2mu = 0.0; pt.log2N = 0.0; pt.tokadj = 0.0; pt.flag = 0; pt.pad = 0;
-        if (m < nlev && q == 0) pt = io.pend[m * io.n_rows + row0 + tau];
         double log2T = 0.0, sumN = 0.0;
         for (int l = 0; l < nlev; ++l) {
             const int src = l * 4;
-            if (!__builtin_amdgcn_readlane(pt.flag, src)) continue;
-            const double log2mu = lane_value(pt.log2mu, src), log2N = lane_value(pt.log2N, src);
+            if (!__builtin_amdgcn_readlane(pl.pt.flag, src)) continue;
+            const double log2mu = lane_value(pl.pt.log2mu, src), log2N = lane_value(pl.pt.log2N, src);
             const double t = 1.0 - exp2_small(-by - log2mu + sumN - log2T);        // 1 - p[y] / (mu_l q^(l)[y])
             const double adj = t > 0.0 ? static_cast<double>(K) * log2(t) : -INFINITY;
             if (lane == src) val += adj - log2N;
@@ -704,9 +742,14 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
         // the same rows), and for the rare row that fails them the workgroups sum E together, straight from memory (this
         // function, called only then): the (row, part) units of all such rows, at most kPendParts parts each, are dealt out
         // to the workgroups and left in the workspace with device-scope stores; every workgroup needs all parts (each runs
-        // the decision itself) and polls for them, a part per thread.  (Row after row, with a wait for every row, took 8 - 9 us
-        // a row: 8 x 4 drafts of 5 at V = 32000 with two such rows 22 us in this kernel, 19.6 now; with pending modifications
-        // 8 x 4 of 8 at V = 128256 43 us, 27 now.)  The wait is bounded: a part that has not
+        // the decision itself) and polls for them, a part per thread.  A unit is a few thousand entries, and what it takes is
+        // its latencies (loads, the row's float64 constants, the sum over the wave), so a workgroup with several units gives
+        // each to a wave or two instead of taking them in turn, and a marked entry of the table keeps its denominator, so that
+        // only the division is left.  Stamps from the table to the end of this function, 40 x 8 drafts of 8 at V = 32000
+        // bfloat16, unit after unit / now: 18 / 10 us, 41 x 7 of 6 at V = 32003 18 / 11, 8 x 4 of 5 at V = 32000 float32 9 / 6;
+        // whole calls 135.6 / 125.6, 115.2 / 110.3, 39.3 / 36.5.  (The sum kernel's workgroup taking a second sweep over its row
+        // alone, k_ot_sum on whole rows: 129.8 and 109, but 32 x 4 of 4 at V = 66000 68 -> 74, a row at the end of the grid
+        // holding the kernel up.)  The wait is bounded: a part that has not
         // arrived after io.e_polls looks (its workgroup has not been scheduled yet, say) is summed by the waiting
         // workgroup itself -- the same bits, stored again -- so no workgroup depends on another one's progress.
         auto excess_sums = [&](const double *tq, const double *tp, const double *lq, const double *lp, double *ex, int *list) {
@@ -728,55 +771,78 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
             }
             __syncthreads();
             const int nmark = __builtin_amdgcn_readfirstlane(sh_nmark);
-            auto unit_sum = [&](int u) {                               // part u % nparts of marked row u / nparts, by the whole workgroup
+            // Waves that share a unit: the whole workgroup where there are no more units than workgroups, else fewer, and it takes
+            // several units at once.
+            constexpr int kWaves = kSegThreads / kWave;
+            const int total = nmark * nparts, gx = static_cast<int>(gridDim.x);
+            const int G = total <= gx ? kWaves : (total <= 2 * gx ? kWaves / 2 : 1);
+            auto wave_share = [&](int u, int sub) {                    // of part u % nparts of marked row u / nparts: wave `sub` of its G
                 const int idx = __builtin_amdgcn_readfirstlane(list[u / nparts]), part = u % nparts;
                 const int k = idx / L, i = idx % L + 1;
                 const long long bk = static_cast<long long>(b) * K + k, pair = bk * L + i;
-                double log2nu = 0.0;
-                for (int j = 0; j < i; ++j) log2nu += tq[k * L + j] - tp[k * L + j];
-                const ExcessConst ec = make_excess_const(lq[k * L + i], lp[k * L + i], log2nu, K, c);
                 const T *rq = target + (bk * (L + 1) + i) * static_cast<long long>(V);
                 const T *rp = draft + pair * static_cast<long long>(V);
                 const int lo = part * per, hi = lo + per < units ? lo + per : units;
-                float acc = 0.0f;
-                if (V >= N) {                                      // uniform
-                    for (int v0 = lo + tid; v0 < hi; v0 += kAhead * kSegThreads) {
-                        U4 q4[kAhead], p4[kAhead];
+                const int step = G * kWave;
+                U4 q4[kAhead], p4[kAhead];
+                auto fetch = [&](int v0) {                             // (no branch around a load: past the end the part's last vector)
+#pragma unroll
+                    for (int a = 0; a < kAhead; ++a) {
+                        const int v = v0 + a * step < hi ? v0 + a * step : hi - 1;
+                        int e = v * N;
+                        e = e < V - N ? e : V - N;
+                        q4[a] = load16_stream_any(rq + e);
+                        p4[a] = load16_stream_any(rp + e);
+                    }
+                };
+                const int first = lo + sub * kWave + lane;
+                if (V >= N && lo < hi) fetch(first);                   // (the row's constants are made while the vectors travel)
+                double log2nu = 0.0;
+                for (int j = 0; j < i; ++j) log2nu += tq[k * L + j] - tp[k * L + j];
+                const ExcessConst ec = make_excess_const(lq[k * L + i], lp[k * L + i], log2nu, K, c);
+                double acc = 0.0;
+                if (V >= N) {                                          // uniform
+                    for (int v0 = first; v0 < hi; v0 += kAhead * step) {
 #pragma unroll
                         for (int a = 0; a < kAhead; ++a) {
-                            const int v = v0 + a * kSegThreads;
-                            int e = (v < hi ? v : v0) * N;
-                            e = e < V - N ? e : V - N;
-                            q4[a] = load16_stream_any(rq + e);
-                            p4[a] = load16_stream_any(rp + e);
-                        }
-#pragma unroll
-                        for (int a = 0; a < kAhead; ++a) {
-                            const int v = v0 + a * kSegThreads;
+                            const int v = v0 + a * step;
                             float zq[N], zp[N];
                             Elem<T>::unpack(q4[a], zq);
                             Elem<T>::unpack(p4[a], zp);
-                            if (rem != 0 && v == units - 1) {      // the entries that the vector before it holds
+                            if (rem != 0 && v == units - 1) {          // the entries that the vector before it holds
                                 asm volatile("");
 #pragma unroll
                                 for (int e = 0; e < N; ++e)
                                     if (e < N - rem) { zq[e] = -INFINITY; zp[e] = -INFINITY; }
                             }
-                            if (v < hi) acc += excess_terms(zq, zp, ec);
+                            if (v < hi) acc += static_cast<double>(excess_terms(zq, zp, ec));
                         }
+                        if (v0 + kAhead * step < hi) fetch(v0 + kAhead * step);
                     }
-                } else if (lo < hi && tid < V) {
-                    const float zq[1] = {Elem<T>::scalar(rq + tid)}, zp[1] = {Elem<T>::scalar(rp + tid)};
-                    acc = excess_terms(zq, zp, ec);
+                } else if (lo < hi && sub == 0 && lane < V) {          // (a row shorter than a vector: its entries are the lanes')
+                    const float zq[1] = {Elem<T>::scalar(rq + lane)}, zp[1] = {Elem<T>::scalar(rp + lane)};
+                    acc = static_cast<double>(excess_terms(zq, zp, ec));
                 }
-                const double v = block_sum(static_cast<double>(acc), sh_d) * ec.scale;
-                if (tid == 0)
-                    __hip_atomic_store(reinterpret_cast<unsigned long long *>(io.e_part_rw + pair * kPendParts + part),
-                                       static_cast<unsigned long long>(__double_as_longlong(v)), __ATOMIC_RELAXED,
-                                       __HIP_MEMORY_SCOPE_AGENT);
-                return v;                                              // (in every thread)
+                return wave_sum(acc) * ec.scale;
             };
-            for (int u = static_cast<int>(blockIdx.x); u < nmark * nparts; u += static_cast<int>(gridDim.x)) unit_sum(u);
+            auto unit_store = [&](int u, double v) {
+                const int idx = list[u / nparts], k = idx / L, i = idx % L + 1;
+                __hip_atomic_store(reinterpret_cast<unsigned long long *>(io.e_part_rw + ((static_cast<long long>(b) * K + k) * L + i) * kPendParts + u % nparts),
+                                   static_cast<unsigned long long>(__double_as_longlong(v)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            };
+            const int each = kWaves / G;                               // units this workgroup takes at once
+            for (int u0 = static_cast<int>(blockIdx.x); u0 < total; u0 += gx * each) {      // uniform
+                const int u = u0 + wid / G * gx;
+                const double v = u < total ? wave_share(u, wid % G) : 0.0;
+                if (lane == 0) sh_d[wid] = v;
+                __syncthreads();
+                if (wid % G == 0 && lane == 0 && u < total) {
+                    double e = 0.0;
+                    for (int w = 0; w < G; ++w) e += sh_d[wid + w];
+                    unit_store(u, e);
+                }
+                __syncthreads();
+            }
             constexpr int kRowsAtOnce = kSegThreads / kPendParts;
             for (int r0 = 0; r0 < nmark; r0 += kRowsAtOnce) {          // uniform: a part per thread
                 const int nu = (nmark - r0 < kRowsAtOnce ? nmark - r0 : kRowsAtOnce) * nparts;
@@ -794,9 +860,15 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
                 if (__syncthreads_or(v == -1.0)) {                     // normally none is missing
                     for (int w = 0; w < nu; ++w) {
                         if (sh_excess[w] == -1.0) {                    // uniform
-                            const double own = unit_sum(r0 * nparts + w);
+                            const double own = wid < G ? wave_share(r0 * nparts + w, wid) : 0.0;
+                            if (lane == 0) sh_d[wid] = own;
                             __syncthreads();
-                            if (tid == 0) sh_excess[w] = own;
+                            if (tid == 0) {
+                                double e = 0.0;
+                                for (int x = 0; x < G; ++x) e += sh_d[x];
+                                unit_store(r0 * nparts + w, e);
+                                sh_excess[w] = e;
+                            }
                             __syncthreads();
                         }
                     }
@@ -997,11 +1069,12 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
     const double total_here = ldexp(W, up);
 
     // inside the segment: one wave, lane order = token-id order
-    float w[8], wq[8];
+    float w[8], wq[8], zq[8], zp[8];
+    PendingLoads pl;
     {
         SegVec<T> vq, vp;
-        float zq[8], zp[8];
         segment_load<T>(target, draft, sl, V, seg, lane, vq, vp);
+        if constexpr (PEND) if (fo.state_carry) pl = pending_loads(io, fo, sl, b, K, L);
         segment_unpack<T>(vq, vp, target, draft, sl, V, seg, lane, zq, zp);
         segment_weigh<PEND>(sl, sh_tab, V, K, c, seg, lane, m2_seg, zq, zp, w, wq);
     }
@@ -1020,8 +1093,9 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
     if (cross) winner = __ffsll(static_cast<long long>(cross)) - 1;
     else if (pos) winner = 63 - __clzll(static_cast<long long>(pos));
     else winner = 0;
-    int tokid_w = 0, mcount_w = 0;               // the winner lane's results, for the state update below
+    int mcount_w = 0;                            // the winner lane's results, for the state update below
     double carry_w = 0.0;
+    float zq_w = 0.0f, zp_w = 0.0f;              // the token's two logits
     if (lane == winner) {
         const long long e0 = static_cast<long long>(seg) * kSegElems + lane * 8;
         double run = excl;
@@ -1035,13 +1109,19 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
             if (ws[j] > 0.0) last = j;
             if (y < 0 && run > local_target) {
                 y = j;
-                const double lo = local_target - prev, hi = run - local_target;
-                mg = (lo < hi ? lo : hi) / total_here;
+                mg = fmin(local_target - prev, run - local_target);
             }
         }
         if (y < 0) { y = last < 0 ? 0 : last; mg = 0.0; }
+        mg = mg / total_here;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) { zq_w = j == y ? zq[j] : zq_w; zp_w = j == y ? zp[j] : zp_w; }
         long long tokid = e0 + y;
-        if (tokid >= V) tokid = V - 1;
+        if (tokid >= V) {                            // (no weight anywhere, in the row's last segment)
+            tokid = V - 1;
+            zq_w = Elem<T>::scalar(target + sl.target_row * V + tokid);
+            if (sl.draft_row >= 0) zp_w = Elem<T>::scalar(draft + sl.draft_row * V + tokid);
+        }
         out_tokens[static_cast<long long>(b) * (L + 1) + sl.tau] = static_cast<int32_t>(tokid);
         margin_out[b] = mg;
         u_final[b] = u;
@@ -1053,8 +1133,7 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
         // the final token, ln [nu_tau q_tau[y] / p_tau[y]], and the number of rows it modifies
         double carry = 0.0;
         if (sl.draft_row >= 0) {
-            const double zq = static_cast<double>(Elem<T>::scalar(target + sl.target_row * V + tokid));
-            const double zp = static_cast<double>(Elem<T>::scalar(draft + sl.draft_row * V + tokid));
+            const double zq = static_cast<double>(zq_w), zp = static_cast<double>(zp_w);
             double l2 = sl.C2 + static_cast<double>(c) * (zq - zp);        // log2 of nu_tau q[y] / p[y]
             // y's two log-probabilities at the caller's temperature (token_scaled); p[y] = 0 leaves the ratio infinite
             const double adj = static_cast<double>(c) * (zq - zp) + sl.lse2_pq;
@@ -1071,9 +1150,9 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
         }
         carry_out[b] = carry;
         mcount_out[b] = sl.draft_row < 0 ? 0 : L - sl.tau - 1;
-        tokid_w = static_cast<int>(tokid); carry_w = carry; mcount_w = sl.draft_row < 0 ? 0 : L - sl.tau - 1;
+        carry_w = carry; mcount_w = sl.draft_row < 0 ? 0 : L - sl.tau - 1;
     }
-    if (PEND && fo.state_carry) update_pending_state<T>(target, draft, io, fo, sl, b, K, L, V, c, winner, tokid_w, carry_w, mcount_w);
+    if (PEND && fo.state_carry) update_pending_state(io, fo, pl, sl, b, K, L, c, winner, zq_w, zp_w, carry_w, mcount_w);
 }
 
 // Consecutive segments a wave takes: as few as keep the grid within two and a half workgroups per compute unit.  Fewer
@@ -1139,8 +1218,8 @@ hipError_t launch_final_typed(const Problem &p)
     fo.mcount = reinterpret_cast<int32_t *>(p.ws + p.lay.mcount);
     fo.state_carry = p.state_carry; fo.state_count = p.state_count;
     const int KL = p.K * p.L;
-    // (66 KB at the largest accepted K L = 1024, K = 64, and 2.4 KB static: within the 160 KB a workgroup may have)
-    const size_t lds = sizeof(double) * (6 * KL + p.K) + sizeof(int) * (3 * KL + 1) + ((static_cast<size_t>(p.K) * p.K + 7) & ~static_cast<size_t>(7));
+    // (75 KB at the largest accepted K L = 1024, K = 64, and 2.4 KB static: within the 160 KB a workgroup may have)
+    const size_t lds = sizeof(double) * (7 * KL + 3 * p.K) + sizeof(int) * (3 * KL + 1) + ((static_cast<size_t>(p.K) * p.K + 7) & ~static_cast<size_t>(7));
 #define SPECGBV_FINAL_LAUNCH(PEND, FAR)                                                                         \
     hipLaunchKernelGGL((k_final<T, PEND, FAR>), g, dim3(kSegThreads), lds, p.stream, target, draft, io, fo, p.V, p.K, \
                        p.L, p.c, p.lay.nseg, spw, p.seed, p.offset)
