@@ -21,7 +21,7 @@
 // Rows of up to kRowSlots * 512 sixteen-byte vectors take a shorter route: k_mod_row keeps a row in the registers of
 // its workgroup between the statistics sweep and the store of its log-probabilities, so every row that no
 // modification touches (all draft rows, the target rows from the prefix's count on, the bonus row) is read once;
-// k_mod_norm and k_mod_write then run for the modified target rows only.
+// k_mod_pair then makes normaliser and ln q_new of the modified target rows.
 #include "specgbv_internal.hpp"
 
 namespace specgbv {
@@ -134,7 +134,7 @@ __device__ __forceinline__ void store_vals(float *dst, const float (&v)[N])
 
 // k_mod_stats for rows of at most kRowSlots * kModThreads vectors, with the row kept in registers: the workgroup
 // then also writes the row's natural-log probabilities unless a modification is pending for it (target rows below
-// the prefix's count: k_mod_norm and k_mod_write do those).  grid.x = target rows followed by draft rows; all of a
+// the prefix's count: k_mod_pair does those).  grid.x = target rows followed by draft rows; all of a
 // thread's loads are issued before the first is used.  WHOLE: the row is a multiple of the vector (masking a repeated end in
 // all slots instead costs 2 - 9 % in float32: 2 x 8 drafts of 4 at V = 64000 58 us, 62 with it).
 template <typename T, bool WHOLE, int SLOTS>
@@ -265,14 +265,127 @@ k_mod_norm(const T *__restrict__ target, const T *__restrict__ draft, int K, int
     }
 }
 
-// grid.x = batch * K * (M + bonus) target rows; plain_done: k_mod_row has written every row without a pending
-// modification and all of ln p, so those workgroups leave at once
+// Modified row pairs of rows that k_mod_row takes: normaliser and ln q_new in one kernel.  grid.x = batch * K * M, row index
+// slowest as in k_mod_norm; row pairs with r >= count leave at once.  What bounds it: HBM, one read of the pair and one write
+// (the two kernels it replaces read the pair twice).  A workgroup keeps the first SLOTS vector pairs per thread in registers
+// between the sum and the stores; the rest of a longer row is read again by the workgroup that has just read it, last vectors
+// first, so that most of it comes from the caches (hence no non-temporal hint on its first read).  Two workgroups per compute
+// unit: one loads while the other stores.  Microseconds a call with the two kernels / with this one: 32 x 8 drafts of 8,
+// bfloat16, V = 128256 841 / 822 (the reads and writes together run at 5 TB/s, as a copy does), 32000 223 / 209, 8193 82.7 /
+// 78.4; 16 x 8 of 8, V = 40961 192 / 161; 32 x 4 of 8, V = 12000 float32 71 / 59.6; 2 x 3 of 8, V = 128256 84 / 74.  Slots: 20
+// (one workgroup per unit) 833 at V = 128256 and 225 at 32000, 6 831 and 206; rows of up to 6 slots in the tile of 9
+// 63.9 instead of 59.6 (V = 12000), 49.8 instead of 48.6 (32 x 8 of 8, V = 4096).
+constexpr int kPairSlots = 9, kShortPairSlots = 6;
+
+template <typename T, bool WHOLE, int SLOTS>
+__global__ void __launch_bounds__(kModThreads, 4)
+k_mod_pair(const T *__restrict__ target, const T *__restrict__ draft, int K, int M, int bonus, int V, float c,
+           const double *__restrict__ carry_log_nu, const int32_t *__restrict__ modify_count,
+           const ModStat *__restrict__ tstat, const ModStat *__restrict__ dstat, double *__restrict__ norm,
+           int32_t *__restrict__ fb_out, float *__restrict__ out_logq)
+{
+    constexpr float kLn2f = 0.693147180559945309417f;
+    __shared__ double sh_d[kModThreads / kWave];
+    const long long nbk = gridDim.x / M;
+    const int r = static_cast<int>(blockIdx.x / nbk);
+    const long long bk = blockIdx.x % nbk;
+    const long long drow = bk * M + r;
+    const int b = static_cast<int>(bk / K);
+    const int rows_t = M + bonus, tid = threadIdx.x;
+    if (r >= modify_count[b]) {                       // uniform over the workgroup
+        if (tid == 0) { norm[drow] = 1.0; fb_out[drow] = 0; }
+        return;
+    }
+    constexpr int PV = Elem<T>::kPerVec;
+    const T *rq = target + (bk * rows_t + r) * static_cast<long long>(V);
+    const T *rp = draft + drow * static_cast<long long>(V);
+    float *oq = out_logq + (bk * rows_t + r) * static_cast<long long>(V);
+    const int nvec = row_vectors<T>(V);
+    auto entry = [&](int v) { return WHOLE ? (v < nvec ? v : nvec - 1) * PV : vector_entry<T>(v, V); };   // (in the row for any v)
+    U4 q[SLOTS], p[SLOTS];
+#pragma unroll
+    for (int j = 0; j < SLOTS; ++j) {
+        q[j] = p[j] = U4{0, 0, 0, 0};
+        if (j * kModThreads < nvec) {                 // (uniform)
+            const int e = entry(j * kModThreads + tid);
+            q[j] = load16_stream_any(rq + e);
+            p[j] = load16_stream_any(rp + e);
+        }
+    }
+    const ModStat sq = tstat[bk * rows_t + r], sp = dstat[drow];
+    const float shift_q = static_cast<float>(sq.lse2);
+    const RatioConst rc(sp.lse2 - sq.lse2 + mod_log2nu(tstat, dstat, bk, rows_t, M, r, carry_log_nu[b]));
+    float acc = 0.0f;
+    auto add = [&](const U4 &a, const U4 &d, int v) {
+        float zq[PV], zp[PV], wq[PV], w[PV];
+        Elem<T>::unpack(a, zq);
+        Elem<T>::unpack(d, zp);
+        if constexpr (!WHOLE) { mask_repeated<T>(zq, v, V); mask_repeated<T>(zp, v, V); }
+        ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
+#pragma unroll
+        for (int e = 0; e < PV; ++e) acc += w[e];
+    };
+    // (a slot's registers pass through a point in program order: its unpacked values are neither formed ahead of time nor kept)
+    auto touch = [](U4 &v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); };
+#pragma unroll
+    for (int j = 0; j < SLOTS; ++j) {
+        if (j * kModThreads + tid < nvec) {
+            touch(q[j]); touch(p[j]);
+            add(q[j], p[j], j * kModThreads + tid);
+        }
+    }
+    for (int v = SLOTS * kModThreads + tid; v < nvec; v += 2 * kModThreads) {
+        const int e0 = entry(v), e1 = entry(v + kModThreads);
+        const U4 q0 = load16_any(rq + e0), p0 = load16_any(rp + e0), q1 = load16_any(rq + e1), p1 = load16_any(rp + e1);
+        add(q0, p0, v);
+        if (v + kModThreads < nvec) add(q1, p1, v + kModThreads);
+    }
+    const double S = block_sum(static_cast<double>(acc), sh_d);           // relative to 2^shift_q
+    const double W = S * exp2(static_cast<double>(shift_q) - sq.lse2);
+    const bool zero = !(W > 0.0);                     // every weight is zero: the row stays q
+    if (tid == 0) { norm[drow] = zero ? 1.0 : W; fb_out[drow] = zero ? 1 : 0; }
+    // ln q_new = ln q + K ln t - ln W; log2 q[x] = fma(z, c, -hq) - dq with a float reference hq and its float64 remainder dq
+    const float hq = shift_q, Kf = zero ? 0.0f : static_cast<float>(K);
+    const float dq = zero ? static_cast<float>(sq.lse2 - static_cast<double>(hq))
+                          : static_cast<float>(log2(W) + sq.lse2 - static_cast<double>(hq));
+    auto write = [&](const U4 &a, const U4 &d, int v) {
+        float zq[PV], zp[PV], o[PV];
+        Elem<T>::unpack(a, zq);
+        Elem<T>::unpack(d, zp);
+        if (zero) {                                   // uniform
+#pragma unroll
+            for (int e = 0; e < PV; ++e) o[e] = (fmaf(zq[e], c, -hq) - dq) * kLn2f;
+        } else {
+#pragma unroll
+            for (int e = 0; e < PV; ++e)
+                o[e] = (fmaf(Kf, __log2f(rc.one_minus_ratio(zp[e] - zq[e], c)), fmaf(zq[e], c, -hq)) - dq) * kLn2f;
+        }
+        store_vals(oq + entry(v), o);                 // (repeated entries: the same values again)
+    };
+    // the vectors that are read again, last first
+    for (int j = (nvec - 1) / kModThreads; j >= SLOTS; j -= 2) {          // uniform
+        const int v = j * kModThreads + tid, u = j - 1 >= SLOTS ? v - kModThreads : v;
+        const int e0 = entry(v), e1 = entry(u);
+        const U4 q0 = load16_any(rq + e0), p0 = load16_any(rp + e0), q1 = load16_any(rq + e1), p1 = load16_any(rp + e1);
+        if (v < nvec) write(q0, p0, v);
+        if (u != v) write(q1, p1, u);
+    }
+#pragma unroll
+    for (int j = 0; j < SLOTS; ++j) {
+        if (j * kModThreads + tid < nvec) {
+            touch(q[j]); touch(p[j]);
+            write(q[j], p[j], j * kModThreads + tid);
+        }
+    }
+}
+
+// grid.x = batch * K * (M + bonus) target rows
 template <typename T, bool VEC>
 __global__ void __launch_bounds__(kModThreads)
 k_mod_write(const T *__restrict__ target, const T *__restrict__ draft, int K, int M, int bonus, int V, float c,
             const double *__restrict__ carry_log_nu, const int32_t *__restrict__ modify_count,
             const ModStat *__restrict__ tstat, const ModStat *__restrict__ dstat, const double *__restrict__ norm,
-            const int32_t *__restrict__ fb_in, float *__restrict__ out_logq, float *__restrict__ out_logp, int plain_done)
+            const int32_t *__restrict__ fb_in, float *__restrict__ out_logq, float *__restrict__ out_logp)
 {
     constexpr float kLn2f = 0.693147180559945309417f;
     const long long trow = blockIdx.x;
@@ -287,12 +400,11 @@ k_mod_write(const T *__restrict__ target, const T *__restrict__ draft, int K, in
     const float hq = static_cast<float>(sq.lse2), hp = static_cast<float>(sp.lse2);
     const float dq = static_cast<float>(sq.lse2 - static_cast<double>(hq));
     const float dp = static_cast<float>(sp.lse2 - static_cast<double>(hp));
-    if (plain_done && !(has_draft && r < modify_count[b])) return;     // (uniform over the workgroup)
     const bool modified = has_draft && r < modify_count[b] && fb_in[drow] == 0;
     const T *rq = target + trow * static_cast<long long>(V);
     const T *rp = has_draft ? draft + drow * static_cast<long long>(V) : rq;   // bonus row: no second stream
     float *oq = out_logq + trow * static_cast<long long>(V);
-    float *op = (out_logp && has_draft && !plain_done) ? out_logp + drow * static_cast<long long>(V) : nullptr;
+    float *op = (out_logp && has_draft) ? out_logp + drow * static_cast<long long>(V) : nullptr;
     constexpr int N = VEC ? Elem<T>::kPerVec : 1;
     if (modified) {
         // ln q_new = ln q + K ln t - ln W
@@ -354,28 +466,36 @@ hipError_t launch_modify_typed(const void *target_v, const void *draft_v, const 
     // rows short enough to stay in a workgroup's registers are read once unless a modification is pending for them
     const bool rows_fit = vec && !in_place && row_vectors<T>(V) <= kRowSlots * kModThreads;
     const bool short_rows = row_vectors<T>(V) <= kShortRowSlots * kModThreads, whole = V % Elem<T>::kPerVec == 0;
-#define SPECGBV_MOD_ROW(WHOLE, SLOTS)                                                                                \
-    hipLaunchKernelGGL((k_mod_row<T, WHOLE, SLOTS>), dim3(static_cast<unsigned>(n_t + n_d)), blk, 0, stream, target, \
-                       draft, tokens, K, M, bonus, V, c, n_t, count, tstat, dstat, out_logq, out_logp)
+    if (rows_fit) {
+#define SPECGBV_MOD_ROWS(WHOLE, SLOTS, PAIR_SLOTS)                                                                   \
+    do {                                                                                                             \
+        hipLaunchKernelGGL((k_mod_row<T, WHOLE, SLOTS>), dim3(static_cast<unsigned>(n_t + n_d)), blk, 0, stream, target, \
+                           draft, tokens, K, M, bonus, V, c, n_t, count, tstat, dstat, out_logq, out_logp);          \
+        hipLaunchKernelGGL((k_mod_pair<T, WHOLE, PAIR_SLOTS>), dim3(static_cast<unsigned>(n_d)), blk, 0, stream, target, \
+                           draft, K, M, bonus, V, c, carry, count, tstat, dstat, norm, fb, out_logq);                \
+    } while (0)
+        const bool short_pairs = row_vectors<T>(V) <= kShortPairSlots * kModThreads;
+        if (short_pairs && whole) SPECGBV_MOD_ROWS(true, kShortRowSlots, kShortPairSlots);
+        else if (short_pairs) SPECGBV_MOD_ROWS(false, kShortRowSlots, kShortPairSlots);
+        else if (short_rows && whole) SPECGBV_MOD_ROWS(true, kShortRowSlots, kPairSlots);
+        else if (short_rows) SPECGBV_MOD_ROWS(false, kShortRowSlots, kPairSlots);
+        else if (whole) SPECGBV_MOD_ROWS(true, kRowSlots, kPairSlots);
+        else SPECGBV_MOD_ROWS(false, kRowSlots, kPairSlots);
+#undef SPECGBV_MOD_ROWS
+        return hipGetLastError();
+    }
 #define SPECGBV_MOD_LAUNCH(VEC)                                                                                   \
     do {                                                                                                          \
-        if (rows_fit && short_rows && whole) SPECGBV_MOD_ROW(true, kShortRowSlots);                               \
-        else if (rows_fit && short_rows) SPECGBV_MOD_ROW(false, kShortRowSlots);                                  \
-        else if (rows_fit && whole) SPECGBV_MOD_ROW(true, kRowSlots);                                             \
-        else if (rows_fit) SPECGBV_MOD_ROW(false, kRowSlots);                                                     \
-        else                                                                                                      \
-            hipLaunchKernelGGL((k_mod_stats<T, VEC>), dim3(static_cast<unsigned>(n_t + n_d)), blk, 0, stream,      \
-                               target, draft, tokens, M, bonus, V, c, n_t, tstat, dstat);                         \
+        hipLaunchKernelGGL((k_mod_stats<T, VEC>), dim3(static_cast<unsigned>(n_t + n_d)), blk, 0, stream,          \
+                           target, draft, tokens, M, bonus, V, c, n_t, tstat, dstat);                             \
         hipLaunchKernelGGL((k_mod_norm<T, VEC>), dim3(static_cast<unsigned>(n_d)), blk, 0, stream, target, draft,  \
                            K, M, bonus, V, c, carry, count, tstat, dstat, norm, fb);                              \
         hipLaunchKernelGGL((k_mod_write<T, VEC>), dim3(static_cast<unsigned>(n_t)), blk, 0, stream, target, draft, \
-                           K, M, bonus, V, c, carry, count, tstat, dstat, norm, fb, out_logq, out_logp,           \
-                           rows_fit ? 1 : 0);                                                                     \
+                           K, M, bonus, V, c, carry, count, tstat, dstat, norm, fb, out_logq, out_logp);          \
     } while (0)
     if (vec) SPECGBV_MOD_LAUNCH(true);
     else SPECGBV_MOD_LAUNCH(false);
 #undef SPECGBV_MOD_LAUNCH
-#undef SPECGBV_MOD_ROW
     return hipGetLastError();
 }
 
