@@ -569,6 +569,52 @@ __device__ __forceinline__ void for_each_pair_range(const T *rq, const T *rp, in
     }
 }
 
+// The first step of for_each_pair_range, asked for before the constants of the sweep are made (the row statistics they come
+// from and their float64 arithmetic pass while the vectors travel), and the sweep that begins with it.  (A row of at least one
+// vector; what a thread loads beyond the range lies in the row and is not used.)  k_ot_sum and k_ot_sum_parts, us a call without
+// and with: three iterations of Algorithm 3, 8 x 4 drafts of 8, V = 128256 bfloat16 342 / 336; one prompt under two levels 64.2 /
+// 63.2; 41 x 7 of 6, V = 32003 111.4 / 110.3; 32 x 8 of 8, V = 24000 92.1 / 91.1; but 4 x 4 of 5, V = 32000 float32 under two
+// levels 57 / 59.  In k_pend_norm the registers cost more than it gains (32 x 8 of 8, V = 128256 571 / 583).
+struct FirstPairs { U4 q0, p0, q1, p1; };
+template <typename T, bool VEC, int THREADS>
+__device__ __forceinline__ FirstPairs first_pairs(const T *rq, const T *rp, int V, int lo)
+{
+    FirstPairs f;
+    if constexpr (VEC) {
+        const int e0 = vector_entry<T>(lo + static_cast<int>(threadIdx.x), V), e1 = vector_entry<T>(lo + static_cast<int>(threadIdx.x) + THREADS, V);
+        f.q0 = load16_stream_any(rq + e0); f.p0 = load16_stream_any(rp + e0);
+        f.q1 = load16_stream_any(rq + e1); f.p1 = load16_stream_any(rp + e1);
+    }
+    return f;
+}
+template <typename T, bool VEC, int THREADS, typename F>
+__device__ __forceinline__ void for_each_pair_from(const FirstPairs &first, const T *rq, const T *rp, int V, int lo, int hi, F f)
+{
+    if constexpr (VEC) {
+        constexpr int PV = Elem<T>::kPerVec;
+        auto one = [&](const U4 &q, const U4 &p, int v) {
+            float zq[PV], zp[PV];
+            Elem<T>::unpack(q, zq);
+            Elem<T>::unpack(p, zp);
+            mask_repeated<T>(zq, v, V);
+            mask_repeated<T>(zp, v, V);
+            f(vector_entry<T>(v, V), zq, zp);
+        };
+        U4 q0 = first.q0, p0 = first.p0, q1 = first.q1, p1 = first.p1;
+        for (int v = lo + static_cast<int>(threadIdx.x); v < hi; v += 2 * THREADS) {     // four loads in flight per thread
+            if (v != lo + static_cast<int>(threadIdx.x)) {
+                const int e0 = vector_entry<T>(v, V), e1 = vector_entry<T>(v + THREADS, V);
+                q0 = load16_stream_any(rq + e0); p0 = load16_stream_any(rp + e0);
+                q1 = load16_stream_any(rq + e1); p1 = load16_stream_any(rp + e1);
+            }
+            one(q0, p0, v);
+            if (v + THREADS < hi) one(q1, p1, v + THREADS);
+        }
+    } else {
+        for_each_pair_range<T, false, THREADS>(rq, rp, V, lo, hi, f);
+    }
+}
+
 // The whole row pair.
 template <typename T, bool VEC, int THREADS, bool KEEP = false, bool REPEAT = false, typename F>
 __device__ __forceinline__ void for_each_pair(const T *rq, const T *rp, int V, F f)

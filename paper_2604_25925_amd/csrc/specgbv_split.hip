@@ -243,6 +243,12 @@ k_ot_sum_parts(const T *__restrict__ target, const T *__restrict__ draft, const 
     const int i = static_cast<int>(idx % (L - 1)) + 1;
     const long long bk = idx / (L - 1);
     const long long pair = bk * L + i;
+    const T *rq = target + (bk * (L + 1) + i) * static_cast<long long>(V);
+    const T *rp = draft + pair * static_cast<long long>(V);
+    const int units = VEC ? row_vectors<T>(V) : V;
+    const int per = (units + P - 1) / P;
+    const int lo = part * per, hi = lo + per < units ? lo + per : units;
+    const FirstPairs first = first_pairs<T, VEC, kStatThreads>(rq, rp, V, lo);
     RowStat st;
     double log2nu = 0.0;
     if (stat_P > 1) {
@@ -286,23 +292,18 @@ k_ot_sum_parts(const T *__restrict__ target, const T *__restrict__ draft, const 
         sumN = sh_sumN;
     }
     const float shift_q = static_cast<float>(st.lse2_q);
-    const T *rq = target + (bk * (L + 1) + i) * static_cast<long long>(V);
-    const T *rp = draft + pair * static_cast<long long>(V);
     constexpr int N = VEC ? Elem<T>::kPerVec : 1;
     const RatioConst rc(ratio_const(st.lse2_p, st.lse2_q, log2nu, c_rel) - sumN);
-    const int units = VEC ? row_vectors<T>(V) : V;
-    const int per = (units + P - 1) / P;
-    const int lo = part * per, hi = lo + per < units ? lo + per : units;
     float acc = 0.0f;
     if (PEND && sh_tab.n > 0) {                   // uniform over the workgroup
-        for_each_pair_range<T, VEC, kStatThreads>(rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_from<T, VEC, kStatThreads>(first, rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             pending_weights(zq, zp, c, shift_q, sh_tab, rc, K, wq, w);
 #pragma unroll
             for (int j = 0; j < N; ++j) acc += w[j];
         });
     } else {
-        for_each_pair_range<T, VEC, kStatThreads>(rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_from<T, VEC, kStatThreads>(first, rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
 #pragma unroll
@@ -363,6 +364,11 @@ k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, int K, in
     const int r = j / K;
     const long long bk = static_cast<long long>(b) * K + j % K;
     const long long pair = bk * L + r;            // (b*K + k)*L + r
+    const T *rq = target + (bk * (L + 1) + r) * static_cast<long long>(V);
+    const T *rp = draft + pair * static_cast<long long>(V);
+    const int units = VEC ? row_vectors<T>(V) : V;
+    const int per = (units + P - 1) / P;
+    const int lo = part * per, hi = lo + per < units ? lo + per : units;
     const RowStat st = stats[pair];
     // block ratio in front of row r: the carried one continued along the drafted tokens with the
     // distribution this level modifies (the target rows as modified by the levels below)
@@ -377,12 +383,7 @@ k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, int K, in
     const double log2mu = sh_log2mu, sumN = sh_sumN;
     const float shift_q = static_cast<float>(st.lse2_q);
     const RatioConst rc(st.lse2_p - st.lse2_q + log2mu - sumN);
-    const T *rq = target + (bk * (L + 1) + r) * static_cast<long long>(V);
-    const T *rp = draft + pair * static_cast<long long>(V);
     constexpr int N = VEC ? Elem<T>::kPerVec : 1;
-    const int units = VEC ? row_vectors<T>(V) : V;
-    const int per = (units + P - 1) / P;
-    const int lo = part * per, hi = lo + per < units ? lo + per : units;
     float acc = 0.0f;
     if (sh_tab.n == 0) {
         for_each_pair_range<T, VEC, kStatThreads>(rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
@@ -450,6 +451,10 @@ k_ot_sum(const T *__restrict__ target, const T *__restrict__ draft, const int32_
     const long long idx = blockIdx.x;             // bk*(L-1) + (i-1)
     const int i = static_cast<int>(idx % (L - 1)) + 1;
     const long long bk = idx / (L - 1);
+    const T *rq = target + (bk * (L + 1) + i) * static_cast<long long>(V);
+    const T *rp = draft + (bk * L + i) * static_cast<long long>(V);
+    const int units = VEC ? row_vectors<T>(V) : V;
+    const FirstPairs first = first_pairs<T, VEC, kStatThreads>(rq, rp, V, 0);
     const RowStat st = stats[bk * L + i];
     // block likelihood ratio of the length-i block, from the rows before row i (their token
     // probabilities under the modified rows where levels are pending)
@@ -468,20 +473,18 @@ k_ot_sum(const T *__restrict__ target, const T *__restrict__ draft, const int32_
         }
     }
     const float shift_q = static_cast<float>(st.lse2_q);
-    const T *rq = target + (bk * (L + 1) + i) * static_cast<long long>(V);
-    const T *rp = draft + (bk * L + i) * static_cast<long long>(V);
     constexpr int N = VEC ? Elem<T>::kPerVec : 1;
     const RatioConst rc(ratio_const(st.lse2_p, st.lse2_q, log2nu, c_rel) - sumN);
     float acc = 0.0f;
     if (PEND && sh_tab.n > 0) {                   // uniform over the workgroup
-        for_each_pair<T, VEC, kStatThreads>(rq, rp, V, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_from<T, VEC, kStatThreads>(first, rq, rp, V, 0, units, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             pending_weights(zq, zp, c, shift_q, sh_tab, rc, K, wq, w);
 #pragma unroll
             for (int j = 0; j < N; ++j) acc += w[j];
         });
     } else {
-        for_each_pair<T, VEC, kStatThreads>(rq, rp, V, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_from<T, VEC, kStatThreads>(first, rq, rp, V, 0, units, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
 #pragma unroll
@@ -546,8 +549,11 @@ hipError_t launch_typed(const Problem &p)
     if (e != hipSuccess) return e;
     PendRow *pend = reinterpret_cast<PendRow *>(p.ws + p.lay.pend);
     for (int level = 0; level < p.pend_levels; ++level) {
-        // one workgroup per row pair, but at least about four per compute unit, so that a small batch's rows can be shared
-        const long long min_grid = 4LL * compute_units();
+        // one workgroup per row pair, but at least two per compute unit, so that a small batch's rows can be shared: as
+        // many as are resident at once (one, two, four per unit, us a call: three iterations of Algorithm 3 with 8 x 4 drafts of
+        // 8, V = 128256 352, 339, 356, of which a pass whose level is empty took 2.4 at four; 16 x 4 of 8, V = 32000 84.9,
+        // 85.0, 89.8; one prompt of 3 drafts 63.8, 64.1, 64.1)
+        const long long min_grid = 2LL * compute_units();
         const dim3 gp(static_cast<unsigned>(pairs > min_grid ? pairs : min_grid));
         const double *carry_l = p.pend_carry + static_cast<size_t>(level) * p.batch;
         const int32_t *count_l = p.pend_count + static_cast<size_t>(level) * p.batch;
