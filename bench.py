@@ -484,7 +484,7 @@ def main() -> int:
                      "frac": achieved / HBM_PEAK_GBS, "traffic": traffic,
                      "kernel": "the vocabulary-streaming kernel(s) that compute the statistics and the sums of Eq. (hik) "
                                "for every row: k_chain on the chain schedule (with k_row0_parts under --shared-row0), "
-                               "k_rows_begin + k_rows or k_short_rows on the rows schedule, k_row_stats + k_ot_sum (or "
+                               "k_rows or k_short_rows on the rows schedule, k_row_stats + k_ot_sum (or "
                                "their _parts variants) on the two-pass schedule; the chain schedule's follow-up kernel "
                                "for rows summed a second time (4 us when there is none) and the final-token kernel are outside the event bracket and inside ms_per_step",
                      "kernel_ms_avg": main_avg, "kernel_ms_min": main_ms[0],

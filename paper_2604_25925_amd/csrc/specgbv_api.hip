@@ -1,5 +1,7 @@
 // C ABI of libspecgbv.so: argument checks, workspace layout, kernel sequencing.
 #include <atomic>
+#include <chrono>
+#include <random>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -87,6 +89,21 @@ int wait_polls()
     if (!polls) return 1024;
     const long n = std::strtol(polls, nullptr, 10);
     return n < 0 ? 0 : (n > 1048576 ? 1048576 : static_cast<int>(n));
+}
+
+// A counter from a start that differs from process to process (words that memory handed on from another one may hold), put
+// through a bijection (splitmix64), so that no two calls share a number.  0 is what cleared words would agree to.
+uint64_t call_nonce()
+{
+    static std::atomic<uint64_t> next{static_cast<uint64_t>(std::chrono::steady_clock::now().time_since_epoch().count()) ^
+                                      (static_cast<uint64_t>(std::random_device{}()) << 32)};
+    for (;;) {
+        uint64_t z = next.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);
+        z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+        z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+        z ^= z >> 31;
+        if (z != 0) return z;
+    }
 }
 
 static bool shape_ok(int batch, int K, int L, int V)
@@ -218,6 +235,7 @@ specgbv_status specgbv_verify_ex(
         }
     }
 
+    if (p.rows_parts > 0) p.nonce = call_nonce();
     p.s_parts = use_chain ? 1 : (p.rows_parts > 0 ? p.rows_parts : split_sum_parts(p));
     p.e_parts = (use_chain && !pending) ? chain_excess_parts(p) : 0;
     p.e_coop = (use_chain || p.rows_parts == 1) ? 0 : 1;

@@ -111,6 +111,8 @@ struct DecideIO {
     double *log_nu_out, *log_P_out, *h_out, *eta_out;
     int32_t *state_out;
     int32_t *accepted_len, *accepted_draft_idx, *out_tokens;
+    unsigned long long *row_words;   // rows schedule: the words of the rows' normalisers, which are cleared here; or null
+    int word_parts;                  // parts of a row that have such words
     double c_rel;               // relative rounding error of the float scale c (token_scaled)
     int kseq_ndrafts;           // > 0: comparison verifier (K-SEQ rule) on the first kseq_ndrafts drafts; s_arr then holds
                                 // rho and e_arr beta(rho) of every row pair
@@ -729,6 +731,15 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
     int32_t *__restrict__ fallback_out = fo.fallback, *__restrict__ mcount_out = fo.mcount;
     double *__restrict__ carry_out = fo.carry;
 
+    // The rows schedule's words of this prefix, so that a replay of this call from a graph, which has the same number, does not
+    // find them (the kernel that reads them has ended).
+    if (io.row_words) {
+        const int n = K * L * 2 * io.word_parts;
+        for (int w = static_cast<int>(blockIdx.x) * kSegThreads + tid; w < n; w += static_cast<int>(gridDim.x) * kSegThreads) {
+            unsigned long long *const dst = io.row_words + ((static_cast<long long>(b) * K * L * 2 + w / io.word_parts) * kRowParts + w % io.word_parts) * kWordsPerPart;
+            dst[0] = 0ull; dst[1] = 0ull;
+        }
+    }
     // ---- 1. decision (redundantly per workgroup; the first one of the prefix writes it out)
     if (io.kseq_ndrafts > 0) {             // comparison verifier: K-SEQ scan; its replacement weights are the K = 1 ones
         decide_kseq<T>(target, draft, io, b, K, L, V, c, seed, offset, blockIdx.x == 0, lds_decide, &sh_sel, &sh_u, &sh_tab);
@@ -1197,6 +1208,8 @@ hipError_t launch_final_typed(const Problem &p)
     io.e_coop = (p.e_coop != 0 && p.kseq_ndrafts == 0) ? 1 : 0;
     io.e_part_rw = reinterpret_cast<double *>(p.ws + p.lay.excess_part);
     io.e_polls = wait_polls();
+    io.row_words = p.rows_parts > 0 && !short_rows_schedule(p) ? reinterpret_cast<unsigned long long *>(p.ws + p.lay.stat_part) : nullptr;
+    io.word_parts = p.rows_parts > 0 ? p.rows_parts : 1;
     io.log_nu_out = reinterpret_cast<double *>(p.ws + p.lay.log_nu);
     io.log_P_out = reinterpret_cast<double *>(p.ws + p.lay.log_P);
     io.h_out = reinterpret_cast<double *>(p.ws + p.lay.h);

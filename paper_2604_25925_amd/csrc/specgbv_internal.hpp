@@ -47,6 +47,7 @@ struct Workspace {
 constexpr int kMaxChainGrid = 1024;            // workgroups of the chain kernel at most (one or two per compute unit)
 constexpr int kPendParts = 16;                 // workgroups a modified row's normaliser is shared among, at most
 constexpr int kRowParts = 16;                  // workgroups a row is shared among at most when the batch is small
+constexpr int kWordsPerPart = 2;               // rows schedule: 64-bit words of a part's log2-normaliser
 constexpr int kRow0Parts = 16;                 // slices a shared row 0 is reduced in
 struct Row0Part { double ref; double Z; };     // sum over the slice of 2^(c z - ref), ref an integer
 
@@ -55,6 +56,8 @@ constexpr int kSegElems = kWave * 8;           // vocabulary entries per residua
 
 int compute_units();                           // of the current device
 int wait_polls();                              // looks a workgroup takes at what another one owes before it computes that itself
+
+uint64_t call_nonce();                         // a number other than zero that no other call of this process gets
 
 Workspace make_workspace(int batch, int K, int L, int V);
 
@@ -84,6 +87,7 @@ struct Problem {
     int s_parts;                   // > 1: the sums of Eq. (hik) are left as this many partial sums per row (small batches)
     int e_parts;                   // > 0 (chain schedule): rows marked kExcessPending have their E in this many parts
     int rows_parts;                // > 0: the rows schedule, with this many parts per row
+    uint64_t nonce;                // the rows schedule's number of this call
     int e_coop;                    // != 0 (two-pass schedule, rows in parts): the final-token kernel finds the rows that need E and sums it
     int kseq_ndrafts;              // > 0: the comparison verifier (K-SEQ rule of Section 3.2) on the first kseq_ndrafts drafts
 };
@@ -100,6 +104,7 @@ int split_sum_parts(const Problem &p);
 // Schedule "rows": every row pair (or one of its parts, a power of two of them) in the registers of one workgroup.
 // rows_schedule_parts(): the number of parts, 0 where the schedule does not take the shape or the two-pass one is ahead.
 int rows_schedule_parts(const Problem &p);
+bool short_rows_schedule(const Problem &p);  // k_short_rows takes it, which leaves no words between workgroups
 hipError_t launch_rows_main(const Problem &p);
 
 // Schedule "chain": one workgroup per (prefix, draft) keeps each row pair on chip between

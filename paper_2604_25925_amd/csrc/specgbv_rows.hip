@@ -1,11 +1,10 @@
 // Schedule "rows": every (target, draft) row pair is read from HBM once, by workgroups that each keep one row pair
 // (or one of its P parts) in registers.
 //
-//   k_rows_begin : marks the parts' normalisers as "not there yet" and clears the final-token kernel's counters
-//   k_rows       : workgroup (prefix, draft, row, part), part fastest:
+//   k_rows : workgroup (prefix, draft, row, part), part fastest:
 //                    1. loads its part of the row pair (every load issued before the first is used)
 //                    2. sweep 1: the part's soft-max statistics, log2 sum_x 2^(c z[x]) of either row, which it leaves in
-//                       the workspace (one 64-bit device-scope store per row: the value says by itself that it is there)
+//                       the workspace (two 64-bit device-scope words per row, which say by themselves that they are there)
 //                    3. collects the statistics of its draft's rows 0 .. i from the workgroups that own them
 //                    4. sweep 2, from the registers: the part's share of the vocabulary sum of Eq. (hik)
 //                         s_i = sum_x q_i[x] max(1 - p_i[x] / (nu_i q_i[x]), 0)^K
@@ -15,6 +14,12 @@
 // bfloat16 entries, of which 5 us are arithmetic), and a number of drafts that is not a multiple of the compute units
 // leaves some idle for a whole draft.  Here a row is the unit of work, two to four workgroups share a compute unit,
 // and one's loads run beside another's arithmetic.
+//
+// A normaliser is there when the exclusive or of its two words is the call's own number (call_nonce: no two calls of a process
+// have the same, so whatever the workspace held before, words of an earlier call among it, is not taken for one).  A call
+// captured in a graph has the same number in every replay; the final-token kernel, which runs behind this one and reads none
+// of the words, therefore clears them.  (A kernel in front that marks the words as not there yet, which this one had before,
+// cost 2 - 5 us a call.)
 //
 // Step 3 waits for workgroups with a lower index only (the same draft's earlier rows) or with the same row (its other
 // parts); workgroups are dispatched in index order, so what is waited for is running or has run.  Nothing relies on
@@ -30,10 +35,13 @@ namespace specgbv {
 namespace {
 
 constexpr int kRowsMaxL = 64;                          // rows of a draft (L <= 62)
+static_assert(sizeof(Row0Part) == kWordsPerPart * sizeof(unsigned long long), "the words take the room of a part's statistics");
 
 struct RowsArgs {
     const int32_t *tokens;
-    unsigned long long *words;     // [n_rows][2][kRowParts] log2-normalisers of the parts (float64 bits; all ones: not there yet)
+    unsigned long long *words;     // [n_rows][2][kRowParts][2] log2-normalisers of the parts: float64 bits, and those ^ nonce
+    unsigned long long nonce;
+    int32_t *final_counter;        // [batch] arrival counters of the final-token kernel, cleared here
     RowStat *stats;
     double *s_out, *e_out;         // P = 1: the row's sum, and nu^2 (s - g) where it is needed (else -1)
     double *s_part, *e_part;       // P > 1: the parts' sums; the final-token kernel's parts of E start as "not there yet"
@@ -42,16 +50,7 @@ struct RowsArgs {
     double c_rel;
 };
 
-constexpr unsigned long long kNotThere = ~0ull;        // (a NaN that no sum produces)
-
-__global__ void __launch_bounds__(256)
-k_rows_begin(unsigned long long *__restrict__ words, long long nwords, int P, int32_t *__restrict__ final_counter, int batch)
-{
-    const long long step = static_cast<long long>(gridDim.x) * blockDim.x;
-    const long long at = static_cast<long long>(blockIdx.x) * blockDim.x + threadIdx.x;
-    for (long long i = at; i < nwords; i += step) words[(i / P) * kRowParts + i % P] = kNotThere;
-    for (long long i = at; i < batch; i += step) final_counter[i] = 0;
-}
+constexpr unsigned long long kNotThere = ~0ull;        // a word that has not been found yet (a NaN that no sum produces)
 
 // This thread's vectors of units [lo, lo + n) of a row pair, n <= NS * TH.  Every slot is loaded, without a
 // branch (a load under one is waited for where the branch ends): lanes and slots past the part's end read masked
@@ -235,9 +234,9 @@ k_rows(const T *__restrict__ target, const T *__restrict__ draft, RowsArgs ar)
     uint32_t ztok = 0;
     U4 q[NS], p[NS];
     int r_now = i, part_now = part;                        // whose vectors q, p hold (uniform)
-    unsigned long long *const words = ar.words + bk * L * (2 * kRowParts);
+    unsigned long long *const words = ar.words + bk * L * (2 * kRowParts * kWordsPerPart);
     const int nwords = nstat * P;                          // word w: row w / (2 P), model w / P % 2, part w % P
-    auto word_at = [&](int w) { return words + (w >> logP) * kRowParts + (w & (P - 1)); };
+    auto word_at = [&](int w) { return words + ((w >> logP) * kRowParts + (w & (P - 1))) * kWordsPerPart; };
     for (bool first = true;; first = false) {
         const T *rq = target + (bk * (L + 1) + r_now) * static_cast<long long>(V);
         const T *rp = draft + (bk * L + r_now) * static_cast<long long>(V);
@@ -280,9 +279,13 @@ k_rows(const T *__restrict__ target, const T *__restrict__ draft, RowsArgs ar)
             }
             const double l = (Z > 0.0 && ref > -1.0e300) ? ref + rows_log2(Z) : -static_cast<double>(__builtin_inff());
             sh_own[tid] = l;
-            if (first)
-                __hip_atomic_store(words + (2 * r_now + tid) * kRowParts + part_now, static_cast<unsigned long long>(__double_as_longlong(l)),
-                                   __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (first) {
+                unsigned long long *const dst = words + ((2 * r_now + tid) * kRowParts + part_now) * kWordsPerPart;
+                const unsigned long long bits = static_cast<unsigned long long>(__double_as_longlong(l));
+                __hip_atomic_store(dst, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(dst + 1, bits ^ ar.nonce, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                if (tid == 0 && i == 0 && part == 0 && pair_u % static_cast<unsigned>(K * L) == 0u) ar.final_counter[pair_u / static_cast<unsigned>(K * L)] = 0;
+            }
         }
         if (first && i == 0 && L > 1) return;              // row 0 has no sum; the workgroup of row 1 stores its statistics
         __syncthreads();
@@ -293,9 +296,12 @@ k_rows(const T *__restrict__ target, const T *__restrict__ draft, RowsArgs ar)
             if ((w >> (logP + 1)) == r_now && (w & (P - 1)) == part_now) bits = static_cast<unsigned long long>(__double_as_longlong(sh_own[m]));
             else if (first) {
                 bits = kNotThere;
+                const unsigned long long *const src = word_at(w);
                 for (int look = 0; look < ar.polls && bits == kNotThere; ++look) {
-                    bits = __hip_atomic_load(word_at(w), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                    if (bits == kNotThere) __builtin_amdgcn_s_sleep(2);
+                    const unsigned long long v = __hip_atomic_load(src, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    const unsigned long long x = __hip_atomic_load(src + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    if ((v ^ x) == ar.nonce) bits = v;     // (one word of this call beside one of another is not)
+                    else __builtin_amdgcn_s_sleep(2);
                 }
             } else bits = static_cast<unsigned long long>(__double_as_longlong(sh_word[w]));
             sh_word[w] = __longlong_as_double(static_cast<long long>(bits));
@@ -528,12 +534,8 @@ hipError_t launch_rows_typed(const Problem &p)
     ar.e_part = reinterpret_cast<double *>(p.ws + p.lay.excess_part);
     ar.K = p.K; ar.L = p.L; ar.V = p.V; ar.logP = __builtin_ctz(static_cast<unsigned>(P)); ar.polls = wait_polls();
     ar.c = p.c; ar.c_rel = p.c_rel;
-    const long long nwords = pairs * 2 * P;
-    const long long want = (nwords + 255) / 256;
-    hipLaunchKernelGGL(k_rows_begin, dim3(static_cast<unsigned>(want < 1024 ? want : 1024)), dim3(256), 0, p.stream, ar.words,
-                       nwords, P, reinterpret_cast<int32_t *>(p.ws + p.lay.counter), p.batch);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    ar.nonce = p.nonce;
+    ar.final_counter = reinterpret_cast<int32_t *>(p.ws + p.lay.counter);
     const T *target = static_cast<const T *>(p.target), *draft = static_cast<const T *>(p.draft);
     const int nv = (p.V + PV - 1) / PV, per = (nv + P - 1) / P;
     const dim3 grid(static_cast<unsigned>(pairs * P));
@@ -594,6 +596,8 @@ int rows_schedule_parts(const Problem &p)
     }
     return pairs * P < (1LL << 31) ? P : 0;
 }
+
+bool short_rows_schedule(const Problem &p) { return short_rows(p); }
 
 hipError_t launch_rows_main(const Problem &p)
 {
