@@ -763,6 +763,15 @@ __device__ __forceinline__ double with_token_term(double total, const RowStat &s
     return (total - old) + token_term(log2q, log2r, K) * exp2_small(st.lse2_q - static_cast<double>(shift_q));
 }
 
+// log2 of a positive finite double: a float logarithm and one Newton step on 2^y = m (error about 1e-14).
+__device__ __forceinline__ double log2_newton(double z)
+{
+    int e;
+    const double m = frexp(z, &e);
+    const double y0 = static_cast<double>(__log2f(static_cast<float>(m)));
+    return static_cast<double>(e) + (y0 + (m * exp2_small(-y0) - 1.0) * 1.44269504088896340736);
+}
+
 // Integral reference exponent of a group of entries whose largest logit is m (partial sums taken relative to
 // integral references rescale exactly).  A group without a finite entry (m = -3e38 or -inf: every entry
 // masked) gets the finite reference -3e38, against which all its weights are 2^(-inf) = 0.

@@ -59,15 +59,15 @@ __device__ __forceinline__ KseqSums kseq_block_sums(double G, double S, double D
 // sweeps, 8 % where 64 drafts nearly coincide with the target; by the step alone, and with rho kept in float32, rho was off by
 // up to 1e-2 at K = 4, V = 100, T = 0.3, drafts close to the target, where it is good to 1e-6.)
 // (rho, beta) is the pair of the last sweep, or its continuation along the tangent of G by at most 2e-7 rho.
-// sweep(rho, turn): KseqSums.
+// at_one: the sums at rho = 1; sweep(rho, turn): KseqSums.
 struct KseqRoot { double rho, beta; };
 template <typename Sweep>
-__device__ __forceinline__ KseqRoot kseq_root(int n, Sweep sweep)
+__device__ __forceinline__ KseqRoot kseq_root(int n, const KseqSums &at_one, Sweep sweep)
 {
     constexpr double kStep = 2.0e-7;
     double rho = 1.0, lo = 1.0, hi = static_cast<double>(n), beta = 0.0;
     for (int it = 0;; ++it) {
-        const KseqSums sm = sweep(rho, it & 1);
+        const KseqSums sm = it == 0 ? at_one : sweep(rho, it & 1);
         beta = sm.G / rho;
         if (n <= 1) break;                                 // one candidate: rho = 1 (Section 3.1)
         const double b1 = beta < 1.0 ? beta : 1.0, A = 1.0 - b1;
@@ -129,16 +129,13 @@ __device__ __forceinline__ void kseq_begin(const KseqPair &w, const int32_t *tok
         if (same) atomicAdd(sh_n, 1);
     }
 }
-template <typename T>
-__device__ __forceinline__ void kseq_store_stats(const KseqPair &w, const T *rq, const T *rp, const int32_t *tokens, int V, double lse2_q,
-                                                 double lse2_p, float c, double c_rel, RowStat *stats)
+// (zq, zp: the drafted token's two logits)
+__device__ __forceinline__ void kseq_store_stats(const KseqPair &w, float zq, float zp, double lse2_q, double lse2_p, float c, double c_rel, RowStat *stats)
 {
-    int tok = tokens[w.pair];
-    tok = tok < 0 ? 0 : (tok >= V ? V - 1 : tok);
     RowStat st;
     st.lse2_q = lse2_q; st.lse2_p = lse2_p;
-    st.tok2_q = token_scaled(static_cast<double>(Elem<T>::scalar(rq + tok)) * static_cast<double>(c), lse2_q, c_rel);
-    st.tok2_p = token_scaled(static_cast<double>(Elem<T>::scalar(rp + tok)) * static_cast<double>(c), lse2_p, c_rel);
+    st.tok2_q = token_scaled(static_cast<double>(zq) * static_cast<double>(c), lse2_q, c_rel);
+    st.tok2_p = token_scaled(static_cast<double>(zp) * static_cast<double>(c), lse2_p, c_rel);
     stats[w.pair] = st;
 }
 
@@ -169,12 +166,16 @@ k_kseq_rows(const T *__restrict__ target, const T *__restrict__ draft, const int
     const float Mp = block_max(ap.m2, sh_f);
     const double Zp = block_sum(ap.Z > 0.0f ? static_cast<double>(ap.Z) * exp2(static_cast<double>(ap.m2) - static_cast<double>(Mp)) : 0.0, sh_d);
     const double lse2_q = static_cast<double>(Mq) + log2(Zq), lse2_p = static_cast<double>(Mp) + log2(Zp);
-    if (tid == 0) kseq_store_stats(w, rq, rp, tokens, V, lse2_q, lse2_p, c, c_rel, stats);
+    if (tid == 0) {
+        int tok = tokens[w.pair];
+        tok = tok < 0 ? 0 : (tok >= V ? V - 1 : tok);
+        kseq_store_stats(w, Elem<T>::scalar(rq + tok), Elem<T>::scalar(rp + tok), lse2_q, lse2_p, c, c_rel, stats);
+    }
     const int n = sh_n;                                    // (the block sums above contain the barriers that publish it)
     const float shift_q = rintf(static_cast<float>(lse2_q));
     const double C1 = lse2_p - lse2_q;
     __syncthreads();                                       // (the last block sum has been read)
-    const KseqRoot root = kseq_root(n, [&](double rho, int turn) {
+    auto sweep = [&](double rho, int turn) {
         const RatioConst rc(C1 - log2(rho));               // rho p / q = 2^(c (z_p - z_q) - C2)
         const float kappa = -rc.neg_kappa;
         // summed as min{rho p, q} (not as max{q - rho p, 0} = q - min): where the two models hardly overlap the sum is
@@ -192,7 +193,8 @@ k_kseq_rows(const T *__restrict__ target, const T *__restrict__ draft, const int
             }
         });
         return kseq_block_sums(static_cast<double>(G), static_cast<double>(S), static_cast<double>(Dr), sh_d, turn);
-    });
+    };
+    const KseqRoot root = kseq_root(n, sweep(1.0, 0), sweep);
     if (tid == 0) { rho_out[w.pair] = root.rho; beta_out[w.pair] = root.beta; }
 }
 
@@ -201,7 +203,11 @@ k_kseq_rows(const T *__restrict__ target, const T *__restrict__ draft, const int
 // memory.  At 64 entries per thread a workgroup has the compute unit's registers to itself; what bounds it is a row's
 // own chain: load, statistics, and a step's sweep and barrier for each of five steps in the rows 0 (most others have a
 // single candidate and one step).  Before, a workgroup streamed its row pair alone for every step, 27 us each at
-// V = 32000 float32: 32 x 4 drafts of 8 took 206 us a call, 99 now; 64 x 8 in bfloat16 634, 280 now.
+// V = 32000 float32: 32 x 4 drafts of 8 took 206 us a call, 99 now; 64 x 8 in bfloat16 634, 280 now.  A row of one candidate
+// takes 18 us there, 7 of them its load and the rest arithmetic (two waves per SIMD, one behind the other), so the first
+// step's sums are taken while the weights are formed: 102.7 / 100.3 us a call, 64 x 8 in bfloat16 269.7 / 258.1, 16 x 4 of 5,
+// V = 20000 float32 45.2 / 44.7.  (1024 threads with half the entries each: 118 and 317.  One candidate's sums apart, nothing
+// kept: the compiler then holds a row twice, 108.)
 template <typename T, int NS>
 __global__ void __launch_bounds__(kKseqThreads, 2)
 k_kseq_onchip(const T *__restrict__ target, const T *__restrict__ draft, const int32_t *__restrict__ tokens, int K, int L,
@@ -210,13 +216,15 @@ k_kseq_onchip(const T *__restrict__ target, const T *__restrict__ draft, const i
 {
     constexpr int PV = Elem<T>::kPerVec, NE = NS * PV;
     __shared__ double sh_d[2 * 3 * (kKseqThreads / kWave)];
-    __shared__ float sh_f[kKseqThreads / kWave];
+    __shared__ double sh_Z[2 * (kKseqThreads / kWave)];
+    __shared__ float sh_ref[2 * (kKseqThreads / kWave)];
     __shared__ int sh_n;
     const int tid = threadIdx.x;
     const KseqPair w = kseq_pair(K, L, ndrafts);
     const T *rq = target + (w.bk * (L + 1) + w.r) * static_cast<long long>(V);
     const T *rp = draft + w.pair * static_cast<long long>(V);
     const int nv = (V + PV - 1) / PV, before = (PV - V % PV) % PV;      // entries of the last vector that the one before it holds
+    const int tok_raw = token_index_queued(tokens, w.pair);
     U4 q[NS], p[NS];
 #pragma unroll
     for (int j = 0; j < NS; ++j) {                         // (no branch: a load under one is waited for where the branch ends)
@@ -226,6 +234,10 @@ k_kseq_onchip(const T *__restrict__ target, const T *__restrict__ draft, const i
         q[j] = load16_stream_any(rq + e);
         p[j] = load16_stream_any(rp + e);
     }
+    // (the token's logits are asked for behind the row's loads: fetched where the statistics are stored, their latency held up
+    // the whole workgroup at the next barrier)
+    const int tok = token_index_used(tok_raw, V);
+    const uint32_t tok_q = Elem<T>::bits(rq + tok), tok_p = Elem<T>::bits(rp + tok);
     kseq_begin(w, tokens, K, L, ndrafts, final_counter, &sh_n);
     // entries of slot j: those beyond the row, or held by the vector before, become -inf
     auto unpack = [&](int j, float (&zq)[PV], float (&zp)[PV]) {
@@ -269,39 +281,61 @@ k_kseq_onchip(const T *__restrict__ target, const T *__restrict__ draft, const i
         m2q = aq.m2; m2p = ap.m2;
         zsum_q = aq.Z; zsum_p = ap.Z;
     }
-    const float Mq = block_max(m2q, sh_f), Mp = block_max(m2p, sh_f);
-    const double Zq = block_sum(zsum_q > 0.0 ? zsum_q * exp2_small(static_cast<double>(m2q) - static_cast<double>(Mq)) : 0.0, sh_d);
-    const double Zp = block_sum(zsum_p > 0.0 ? zsum_p * exp2_small(static_cast<double>(m2p) - static_cast<double>(Mp)) : 0.0, sh_d);
-    const double lse2_q = static_cast<double>(Mq) + log2(Zq), lse2_p = static_cast<double>(Mp) + log2(Zp);
-    if (tid == 0) kseq_store_stats(w, rq, rp, tokens, V, lse2_q, lse2_p, c, c_rel, stats);
-    const int n = __builtin_amdgcn_readfirstlane(sh_n);    // (the block sums above contain the barriers that publish it)
+    // The waves' sums relative to integral references meet behind one barrier; every thread adds them up.
+    constexpr int kWaves = kKseqThreads / kWave;
+    const int lane = tid & (kWave - 1), wid = tid / kWave;
+    {
+        const float ref_q = integral_reference(wave_max(m2q), 1.0f), ref_p = integral_reference(wave_max(m2p), 1.0f);
+        const double a = wave_sum(zsum_q > 0.0 ? zsum_q * exp2_small(static_cast<double>(m2q) - static_cast<double>(ref_q)) : 0.0);
+        const double b = wave_sum(zsum_p > 0.0 ? zsum_p * exp2_small(static_cast<double>(m2p) - static_cast<double>(ref_p)) : 0.0);
+        if (lane == 0) { sh_ref[wid] = ref_q; sh_ref[kWaves + wid] = ref_p; sh_Z[wid] = a; sh_Z[kWaves + wid] = b; }
+    }
+    __syncthreads();
+    double lse2_q, lse2_p;
+    {                                                      // even lanes: the target's row, odd lanes: the draft's
+        const int at = (lane & 1) * kWaves;
+        float M = -3.0e38f;
+#pragma unroll
+        for (int x = 0; x < kWaves; ++x) M = fmaxf(M, sh_Z[at + x] > 0.0 ? sh_ref[at + x] : -3.0e38f);
+        double Z = 0.0;
+#pragma unroll
+        for (int x = 0; x < kWaves; ++x) Z += ldexp(sh_Z[at + x], reference_shift(sh_ref[at + x], M));
+        const double l = Z > 0.0 ? static_cast<double>(M) + log2_newton(Z) : -static_cast<double>(__builtin_inff());
+        lse2_q = lane_value(l, 0); lse2_p = lane_value(l, 1);
+    }
+    if (tid == 0) kseq_store_stats(w, Elem<T>::from_bits(tok_q), Elem<T>::from_bits(tok_p), lse2_q, lse2_p, c, c_rel, stats);
+    const int n = __builtin_amdgcn_readfirstlane(sh_n);    // (written in front of the barrier above)
     const float shift_q = rintf(static_cast<float>(lse2_q));
     const RatioConst rc(lse2_p - lse2_q);
     const float kappa = -rc.neg_kappa;
+    // The weights and ratios, and the first step's sums (rho = 1) as they are formed.
     float ew[NE], rw[NE];
+    float C0 = 0.0f, S0 = 0.0f, D0 = 0.0f;
+    auto add = [](float e, float r, float &C, float &S, float &Dr) {
+        const float s = 1.0f - r;
+        const bool open = s > 0.0f;                        // rho p < q, the same for all three sums
+        Dr = fmaf(e, open ? r : 0.0f, Dr);
+        S = fmaf(e, fmaxf(s, 0.0f), S);
+        C += open ? 0.0f : e;                              // mass of q where rho p >= q
+    };
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
         float zq[PV], zp[PV];
         unpack(j, zq, zp);
 #pragma unroll
         for (int e = 0; e < PV; ++e) {
-            ew[j * PV + e] = exp2_fast(fmaf(zq[e], c, -shift_q));
-            rw[j * PV + e] = exp2_fast(fmaf(zp[e] - zq[e], c, -rc.C2_hi)) * kappa;     // (masked entries: weight 0, whatever the ratio)
+            const float x = exp2_fast(fmaf(zq[e], c, -shift_q));
+            const float r = exp2_fast(fmaf(zp[e] - zq[e], c, -rc.C2_hi)) * kappa;     // (masked entries: weight 0, whatever the ratio)
+            ew[j * PV + e] = x; rw[j * PV + e] = r;
+            add(x, r, C0, S0, D0);
         }
     }
-    __syncthreads();                                       // (the last block sum has been read)
-    const KseqRoot root = kseq_root(n, [&](double rho, int turn) {
+    const KseqSums at_one = kseq_block_sums(static_cast<double>(C0) + static_cast<double>(D0), static_cast<double>(S0), static_cast<double>(D0), sh_d, 0);
+    const KseqRoot root = kseq_root(n, at_one, [&](double rho, int turn) {
         const float rf = static_cast<float>(rho), rl = static_cast<float>(rho - static_cast<double>(rf));
-        float C = 0.0f, S = 0.0f, Dr = 0.0f;               // C: mass of q where rho p >= q
+        float C = 0.0f, S = 0.0f, Dr = 0.0f;
 #pragma unroll
-        for (int e = 0; e < NE; ++e) {
-            const float r = fmaf(rf, rw[e], rl * rw[e]);   // rho p / q (where p / q overflows r may be NaN: then not open)
-            const float s = 1.0f - r;
-            const bool open = s > 0.0f;                    // rho p < q, the same for all three sums
-            Dr = fmaf(ew[e], open ? r : 0.0f, Dr);
-            S = fmaf(ew[e], fmaxf(s, 0.0f), S);
-            C += open ? 0.0f : ew[e];
-        }
+        for (int e = 0; e < NE; ++e) add(ew[e], fmaf(rf, rw[e], rl * rw[e]), C, S, Dr);     // (where p / q overflows r may be NaN: then not open)
         return kseq_block_sums(static_cast<double>(C) + static_cast<double>(Dr), static_cast<double>(S), static_cast<double>(Dr), sh_d, turn);
     });
     if (tid == 0) { rho_out[w.pair] = root.rho; beta_out[w.pair] = root.beta; }

@@ -160,15 +160,6 @@ __device__ __forceinline__ WaveSum rows_wave_sum(U4 (&v)[NS], const Slots<T, TH>
     return s;
 }
 
-// log2 of a positive finite double: a float logarithm and one Newton step on 2^y = m (error about 1e-14).
-__device__ __forceinline__ double rows_log2(double z)
-{
-    int e;
-    const double m = frexp(z, &e);
-    const double y0 = static_cast<double>(__log2f(static_cast<float>(m)));
-    return static_cast<double>(e) + (y0 + (m * exp2_small(-y0) - 1.0) * 1.44269504088896340736);
-}
-
 // E = nu^2 (s - g) of a whole row pair, from memory (rare rows; see excess_needed), by the whole workgroup.
 template <typename T, int TH>
 __device__ __forceinline__ double rows_excess(const T *rq, const T *rp, int V, double lse2_q, double lse2_p, double log2nu, int K,
@@ -277,7 +268,7 @@ k_rows(const T *__restrict__ target, const T *__restrict__ draft, RowsArgs ar)
                 Z = (Z > 0.0 ? Z * exp2_small(ref - top) : 0.0) + (t - top == 0.0 ? 1.0 : exp2_small(t - top));
                 ref = top;
             }
-            const double l = (Z > 0.0 && ref > -1.0e300) ? ref + rows_log2(Z) : -static_cast<double>(__builtin_inff());
+            const double l = (Z > 0.0 && ref > -1.0e300) ? ref + log2_newton(Z) : -static_cast<double>(__builtin_inff());
             sh_own[tid] = l;
             if (first) {
                 unsigned long long *const dst = words + ((2 * r_now + tid) * kRowParts + part_now) * kWordsPerPart;
@@ -330,7 +321,7 @@ k_rows(const T *__restrict__ target, const T *__restrict__ draft, RowsArgs ar)
         if (P > 1) {
             double Z = l > -1.0e300 ? exp2_small(l - top) : 0.0;
             for (int o = 1; o < P; o <<= 1) Z += __shfl_xor(Z, o);
-            lse = top > -1.0e300 ? top + rows_log2(Z) : top;
+            lse = top > -1.0e300 ? top + log2_newton(Z) : top;
         }
         if (w < nwords && (w & (P - 1)) == 0) sh_lse[w >> logP] = lse;
     }
@@ -468,7 +459,7 @@ k_short_rows(const T *__restrict__ target, const T *__restrict__ draft, const in
         const double t = static_cast<double>(ztok) * static_cast<double>(c);
         const double top = Z0 > 0.0 ? fmax(ref, t) : t;
         const double Z = (Z0 > 0.0 ? Z0 * exp2_small(ref - top) : 0.0) + (t - top == 0.0 ? 1.0 : exp2_small(t - top));
-        const double lse = top + rows_log2(Z);
+        const double lse = top + log2_newton(Z);
         if (lane < 2) { sh_lse[2 * r + lane] = lse; sh_tok[2 * r + lane] = token_scaled(t, lse, c_rel); }
     }
     __syncthreads();
