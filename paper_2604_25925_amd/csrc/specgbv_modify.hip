@@ -118,26 +118,98 @@ __device__ __forceinline__ void store16_any(float *dst, float a, float b, float 
     typedef F4 F4any __attribute__((aligned(4)));
     *(__attribute__((address_space(1))) F4any *)dst = F4{a, b, c, d};
 }
+// ... which nothing reads again soon (for stores of a wave that lie side by side: with gaps between the lanes they are slower).
+__device__ __forceinline__ void store16_stream_any(float *dst, float a, float b, float c, float d)
+{
+    typedef float F4 __attribute__((ext_vector_type(4)));
+    typedef F4 F4any __attribute__((aligned(4)));
+    __builtin_nontemporal_store(F4{a, b, c, d}, (__attribute__((address_space(1))) F4any *)dst);
+}
 
-// 8 (or 4) consecutive floats of an output row
+// 8 (or 4) consecutive floats of an output row.  (k_mod_write: four are a wave's 1 KiB without gaps, 8 x 8 drafts of 8 at
+// V = 128000 float32 403 / 394 us a call.)
 template <int N>
 __device__ __forceinline__ void store_vals(float *dst, const float (&v)[N])
 {
     if (N % 4 == 0) {
 #pragma unroll
-        for (int j = 0; j < N; j += 4) store16_any(dst + j, v[j], v[j + 1], v[j + 2], v[j + 3]);
+        for (int j = 0; j < N; j += 4) {
+            if constexpr (N == 4) store16_stream_any(dst, v[0], v[1], v[2], v[3]);
+            else store16_any(dst + j, v[j], v[j + 1], v[j + 2], v[j + 3]);
+        }
     } else {
 #pragma unroll
         for (int j = 0; j < N; ++j) dst[j] = v[j];
     }
 }
 
+// How k_mod_row and k_mod_pair deal a row out: vector v of the row is lane v % 64's.  What bounds them is memory, two thirds of
+// it the results' stores (5.2 TB/s at V = 128256 before).  Of whole bfloat16 rows (V a multiple of 8) a lane takes two half
+// vectors, four entries each, 256 entries apart: the four floats that a half becomes then lie beside the neighbouring lane's,
+// so that a wave's store is 1 KiB without gaps and can pass the caches by.  (With a lane's eight floats in two stores, every
+// other 16 bytes each, stores that pass the caches by take 25 % longer than ordinary ones; halves with ordinary stores 109 us at
+// V = 16384 below.)  Us a call before / after: 32 x 8 drafts of 8 bfloat16, V = 128256 837 / 809, 49152 311 / 299, 32000 208 /
+// 187, 16384 111 / 99; float32, whose vectors always lay so, V = 64128 570 / 529, 32 x 4 of 8 at V = 12000 59 / 52.
+enum ModForm { kRagged, kWhole, kHalved };                     // (the row is not a multiple of the vector, is one, and in halves)
+template <typename T, ModForm FORM>
+struct ModLane {
+    static constexpr int PV = Elem<T>::kPerVec;
+    static constexpr bool WHOLE = FORM != kRagged, kHalves = FORM == kHalved;
+    static_assert(!kHalves || PV == 8, "halves of four entries");
+    static constexpr int kHalfStep = kWave * 4;                // entries from a lane's first half to its second
+    __device__ static __forceinline__ int first_entry(int v) { return (v & ~(kWave - 1)) * PV + (v & (kWave - 1)) * 4; }
+    // Whether the lane has entries of vector v in a row of nvec, and whether any lane of the wave has.
+    __device__ static __forceinline__ bool live(int v, int nvec) { return kHalves ? first_entry(v) < nvec * PV : v < nvec; }
+    __device__ static __forceinline__ bool any_live(int v, int nvec) { return (kHalves ? v & ~(kWave - 1) : v) < nvec; }
+    // (in the row for any v: what lies beyond it is not used)
+    template <bool STREAM>
+    __device__ static __forceinline__ U4 load(const T *row, int v, int nvec, int V)
+    {
+        if constexpr (kHalves) {
+            typedef unsigned int V2 __attribute__((ext_vector_type(2)));
+            typedef V2 V2any __attribute__((aligned(2)));
+            const int e0 = first_entry(v), e1 = e0 + kHalfStep;
+            const auto *a = (const __attribute__((address_space(1))) V2any *)(row + (e0 < V ? e0 : V - 4));
+            const auto *b = (const __attribute__((address_space(1))) V2any *)(row + (e1 < V ? e1 : V - 4));
+            const V2 x = STREAM ? __builtin_nontemporal_load(a) : *a, y = STREAM ? __builtin_nontemporal_load(b) : *b;
+            return U4{x.x, x.y, y.x, y.y};
+        } else {
+            const T *at = row + (WHOLE ? (v < nvec ? v : nvec - 1) * PV : vector_entry<T>(v, V));
+            return STREAM ? load16_stream_any(at) : load16_any(at);
+        }
+    }
+    // A live vector's logits; entries that are not the lane's become -inf.
+    __device__ static __forceinline__ void unpack(const U4 &raw, int v, int V, float (&z)[PV])
+    {
+        Elem<T>::unpack(raw, z);
+        if constexpr (kHalves) {
+            if (first_entry(v) + kHalfStep >= V) {
+#pragma unroll
+                for (int e = 4; e < PV; ++e) z[e] = -__builtin_inff();
+            }
+        } else if constexpr (!WHOLE) mask_repeated<T>(z, v, V);
+    }
+    // A live vector's results.  (Entries that the vector before holds too: the same values again.)
+    __device__ static __forceinline__ void store(float *row, int v, int V, const float (&o)[PV])
+    {
+        if constexpr (kHalves) {
+            float *dst = row + first_entry(v);
+            store16_stream_any(dst, o[0], o[1], o[2], o[3]);
+            if (first_entry(v) + kHalfStep < V) store16_stream_any(dst + kHalfStep, o[4], o[5], o[6], o[7]);
+        } else if constexpr (PV == 4) {
+            store16_stream_any(row + (WHOLE ? v * PV : vector_entry<T>(v, V)), o[0], o[1], o[2], o[3]);
+        } else {
+            store_vals(row + (WHOLE ? v * PV : vector_entry<T>(v, V)), o);
+        }
+    }
+};
+
 // k_mod_stats for rows of at most kRowSlots * kModThreads vectors, with the row kept in registers: the workgroup
 // then also writes the row's natural-log probabilities unless a modification is pending for it (target rows below
 // the prefix's count: k_mod_pair does those).  grid.x = target rows followed by draft rows; all of a
-// thread's loads are issued before the first is used.  WHOLE: the row is a multiple of the vector (masking a repeated end in
+// thread's loads are issued before the first is used.  FORM: see ModLane (masking a repeated end in
 // all slots instead costs 2 - 9 % in float32: 2 x 8 drafts of 4 at V = 64000 58 us, 62 with it).
-template <typename T, bool WHOLE, int SLOTS>
+template <typename T, ModForm FORM, int SLOTS>
 __global__ void __launch_bounds__(kModThreads)
 k_mod_row(const T *__restrict__ target, const T *__restrict__ draft, const int32_t *__restrict__ tokens, int K,
           int M, int bonus, int V, float c, long long n_trows, const int32_t *__restrict__ modify_count,
@@ -155,6 +227,7 @@ k_mod_row(const T *__restrict__ target, const T *__restrict__ draft, const int32
     const int r = static_cast<int>(row % (is_draft ? M : rows_t));
     const long long bk = row / (is_draft ? M : rows_t);
     constexpr int PV = Elem<T>::kPerVec;
+    using Lane = ModLane<T, FORM>;
     const int nvec = row_vectors<T>(V);                    // host: nvec <= SLOTS * kModThreads
     const int tid = threadIdx.x;
     U4 v[SLOTS];
@@ -162,17 +235,16 @@ k_mod_row(const T *__restrict__ target, const T *__restrict__ draft, const int32
     for (int j = 0; j < SLOTS; ++j) {
         const int idx = j * kModThreads + tid;
         if (j * kModThreads < nvec)                        // (uniform: slots the row does not reach issue nothing)
-            v[j] = load16_stream_any(z_row + (WHOLE ? (idx < nvec ? idx : nvec - 1) * PV : vector_entry<T>(idx, V)));
+            v[j] = Lane::template load<true>(z_row, idx, nvec, V);
         else
             v[j] = U4{0, 0, 0, 0};
     }
     RunningSum acc;
 #pragma unroll
     for (int j = 0; j < SLOTS; ++j) {
-        if (j * kModThreads + tid < nvec) {
+        if (Lane::live(j * kModThreads + tid, nvec)) {
             float z[PV];
-            Elem<T>::unpack(v[j], z);
-            if constexpr (!WHOLE) mask_repeated<T>(z, j * kModThreads + tid, V);
+            Lane::unpack(v[j], j * kModThreads + tid, V, z);
             acc.add(z, c);
         }
     }
@@ -200,12 +272,12 @@ k_mod_row(const T *__restrict__ target, const T *__restrict__ draft, const int32
 #pragma unroll
     for (int j = 0; j < SLOTS; ++j) {
         const int idx = j * kModThreads + tid;
-        if (idx < nvec) {
+        if (Lane::live(idx, nvec)) {
             float z[PV], a[PV];
             Elem<T>::unpack(v[j], z);
 #pragma unroll
             for (int e = 0; e < PV; ++e) a[e] = (fmaf(z[e], c, -h) - dlt) * kLn2f;
-            store_vals(out + (WHOLE ? idx * PV : vector_entry<T>(idx, V)), a);     // (repeated entries: the same values again)
+            Lane::store(out, idx, V, a);
         }
     }
 }
@@ -277,7 +349,7 @@ k_mod_norm(const T *__restrict__ target, const T *__restrict__ draft, int K, int
 // 63.9 instead of 59.6 (V = 12000), 49.8 instead of 48.6 (32 x 8 of 8, V = 4096).
 constexpr int kPairSlots = 9, kShortPairSlots = 6;
 
-template <typename T, bool WHOLE, int SLOTS>
+template <typename T, ModForm FORM, int SLOTS>
 __global__ void __launch_bounds__(kModThreads, 4)
 k_mod_pair(const T *__restrict__ target, const T *__restrict__ draft, int K, int M, int bonus, int V, float c,
            const double *__restrict__ carry_log_nu, const int32_t *__restrict__ modify_count,
@@ -297,19 +369,18 @@ k_mod_pair(const T *__restrict__ target, const T *__restrict__ draft, int K, int
         return;
     }
     constexpr int PV = Elem<T>::kPerVec;
+    using Lane = ModLane<T, FORM>;
     const T *rq = target + (bk * rows_t + r) * static_cast<long long>(V);
     const T *rp = draft + drow * static_cast<long long>(V);
     float *oq = out_logq + (bk * rows_t + r) * static_cast<long long>(V);
     const int nvec = row_vectors<T>(V);
-    auto entry = [&](int v) { return WHOLE ? (v < nvec ? v : nvec - 1) * PV : vector_entry<T>(v, V); };   // (in the row for any v)
     U4 q[SLOTS], p[SLOTS];
 #pragma unroll
     for (int j = 0; j < SLOTS; ++j) {
         q[j] = p[j] = U4{0, 0, 0, 0};
         if (j * kModThreads < nvec) {                 // (uniform)
-            const int e = entry(j * kModThreads + tid);
-            q[j] = load16_stream_any(rq + e);
-            p[j] = load16_stream_any(rp + e);
+            q[j] = Lane::template load<true>(rq, j * kModThreads + tid, nvec, V);
+            p[j] = Lane::template load<true>(rp, j * kModThreads + tid, nvec, V);
         }
     }
     const ModStat sq = tstat[bk * rows_t + r], sp = dstat[drow];
@@ -318,9 +389,8 @@ k_mod_pair(const T *__restrict__ target, const T *__restrict__ draft, int K, int
     float acc = 0.0f;
     auto add = [&](const U4 &a, const U4 &d, int v) {
         float zq[PV], zp[PV], wq[PV], w[PV];
-        Elem<T>::unpack(a, zq);
-        Elem<T>::unpack(d, zp);
-        if constexpr (!WHOLE) { mask_repeated<T>(zq, v, V); mask_repeated<T>(zp, v, V); }
+        Lane::unpack(a, v, V, zq);
+        Lane::unpack(d, v, V, zp);
         ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
 #pragma unroll
         for (int e = 0; e < PV; ++e) acc += w[e];
@@ -329,16 +399,17 @@ k_mod_pair(const T *__restrict__ target, const T *__restrict__ draft, int K, int
     auto touch = [](U4 &v) { asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w)); };
 #pragma unroll
     for (int j = 0; j < SLOTS; ++j) {
-        if (j * kModThreads + tid < nvec) {
+        if (Lane::live(j * kModThreads + tid, nvec)) {
             touch(q[j]); touch(p[j]);
             add(q[j], p[j], j * kModThreads + tid);
         }
     }
-    for (int v = SLOTS * kModThreads + tid; v < nvec; v += 2 * kModThreads) {
-        const int e0 = entry(v), e1 = entry(v + kModThreads);
-        const U4 q0 = load16_any(rq + e0), p0 = load16_any(rp + e0), q1 = load16_any(rq + e1), p1 = load16_any(rp + e1);
-        add(q0, p0, v);
-        if (v + kModThreads < nvec) add(q1, p1, v + kModThreads);
+    auto again = [&](const T *row, int v) { return Lane::template load<false>(row, v, nvec, V); };
+    for (int v = SLOTS * kModThreads + tid; Lane::any_live(v, nvec); v += 2 * kModThreads) {
+        const int u = v + kModThreads;
+        const U4 q0 = again(rq, v), p0 = again(rp, v), q1 = again(rq, u), p1 = again(rp, u);
+        if (Lane::live(v, nvec)) add(q0, p0, v);
+        if (Lane::live(u, nvec)) add(q1, p1, u);
     }
     const double S = block_sum(static_cast<double>(acc), sh_d);           // relative to 2^shift_q
     const double W = S * exp2(static_cast<double>(shift_q) - sq.lse2);
@@ -360,19 +431,18 @@ k_mod_pair(const T *__restrict__ target, const T *__restrict__ draft, int K, int
             for (int e = 0; e < PV; ++e)
                 o[e] = (fmaf(Kf, __log2f(rc.one_minus_ratio(zp[e] - zq[e], c)), fmaf(zq[e], c, -hq)) - dq) * kLn2f;
         }
-        store_vals(oq + entry(v), o);                 // (repeated entries: the same values again)
+        Lane::store(oq, v, V, o);
     };
     // the vectors that are read again, last first
     for (int j = (nvec - 1) / kModThreads; j >= SLOTS; j -= 2) {          // uniform
         const int v = j * kModThreads + tid, u = j - 1 >= SLOTS ? v - kModThreads : v;
-        const int e0 = entry(v), e1 = entry(u);
-        const U4 q0 = load16_any(rq + e0), p0 = load16_any(rp + e0), q1 = load16_any(rq + e1), p1 = load16_any(rp + e1);
-        if (v < nvec) write(q0, p0, v);
+        const U4 q0 = again(rq, v), p0 = again(rp, v), q1 = again(rq, u), p1 = again(rp, u);
+        if (Lane::live(v, nvec)) write(q0, p0, v);
         if (u != v) write(q1, p1, u);
     }
 #pragma unroll
     for (int j = 0; j < SLOTS; ++j) {
-        if (j * kModThreads + tid < nvec) {
+        if (Lane::live(j * kModThreads + tid, nvec)) {
             touch(q[j]); touch(p[j]);
             write(q[j], p[j], j * kModThreads + tid);
         }
@@ -467,20 +537,25 @@ hipError_t launch_modify_typed(const void *target_v, const void *draft_v, const 
     const bool rows_fit = vec && !in_place && row_vectors<T>(V) <= kRowSlots * kModThreads;
     const bool short_rows = row_vectors<T>(V) <= kShortRowSlots * kModThreads, whole = V % Elem<T>::kPerVec == 0;
     if (rows_fit) {
-#define SPECGBV_MOD_ROWS(WHOLE, SLOTS, PAIR_SLOTS)                                                                   \
+#define SPECGBV_MOD_ROWS(FORM, SLOTS, PAIR_SLOTS)                                                                    \
     do {                                                                                                             \
-        hipLaunchKernelGGL((k_mod_row<T, WHOLE, SLOTS>), dim3(static_cast<unsigned>(n_t + n_d)), blk, 0, stream, target, \
+        hipLaunchKernelGGL((k_mod_row<T, FORM, SLOTS>), dim3(static_cast<unsigned>(n_t + n_d)), blk, 0, stream, target, \
                            draft, tokens, K, M, bonus, V, c, n_t, count, tstat, dstat, out_logq, out_logp);          \
-        hipLaunchKernelGGL((k_mod_pair<T, WHOLE, PAIR_SLOTS>), dim3(static_cast<unsigned>(n_d)), blk, 0, stream, target, \
+        hipLaunchKernelGGL((k_mod_pair<T, FORM, PAIR_SLOTS>), dim3(static_cast<unsigned>(n_d)), blk, 0, stream, target, \
                            draft, K, M, bonus, V, c, carry, count, tstat, dstat, norm, fb, out_logq);                \
     } while (0)
         const bool short_pairs = row_vectors<T>(V) <= kShortPairSlots * kModThreads;
-        if (short_pairs && whole) SPECGBV_MOD_ROWS(true, kShortRowSlots, kShortPairSlots);
-        else if (short_pairs) SPECGBV_MOD_ROWS(false, kShortRowSlots, kShortPairSlots);
-        else if (short_rows && whole) SPECGBV_MOD_ROWS(true, kShortRowSlots, kPairSlots);
-        else if (short_rows) SPECGBV_MOD_ROWS(false, kShortRowSlots, kPairSlots);
-        else if (whole) SPECGBV_MOD_ROWS(true, kRowSlots, kPairSlots);
-        else SPECGBV_MOD_ROWS(false, kRowSlots, kPairSlots);
+        // Rows in halves from two and a quarter vectors per thread on: what a short row takes is its workgroup's instructions, and
+        // a half has its own address and bound.  Whole vectors / halves, us a call: 128 x 16 drafts of 8, V = 1024 242 / 279, 6000
+        // 351 / 382; 64 x 16 of 8, V = 8200 222 / 223, 10000 254 / 242, 12288 291 / 270, 24000 574 / 513.
+        constexpr ModForm kLong = Elem<T>::kPerVec == 8 ? kHalved : kWhole;
+        if (whole && row_vectors<T>(V) <= 9 * kModThreads / 4) SPECGBV_MOD_ROWS(kWhole, kShortRowSlots, kShortPairSlots);
+        else if (short_pairs && whole) SPECGBV_MOD_ROWS(kLong, kShortRowSlots, kShortPairSlots);
+        else if (short_pairs) SPECGBV_MOD_ROWS(kRagged, kShortRowSlots, kShortPairSlots);
+        else if (short_rows && whole) SPECGBV_MOD_ROWS(kLong, kShortRowSlots, kPairSlots);
+        else if (short_rows) SPECGBV_MOD_ROWS(kRagged, kShortRowSlots, kPairSlots);
+        else if (whole) SPECGBV_MOD_ROWS(kLong, kRowSlots, kPairSlots);
+        else SPECGBV_MOD_ROWS(kRagged, kRowSlots, kPairSlots);
 #undef SPECGBV_MOD_ROWS
         return hipGetLastError();
     }

@@ -21,3 +21,15 @@ def test_pairs(V, dtype):
     d[0, :, 0] = t[0, :, 0]                                # with a carried ratio of one: every weight of these rows is zero
     _, ora = _check_modify(t, d, tok, 0.9, np.array([0.0, -0.4]), np.array([2, 3], np.int32), "modified pairs %d %s" % (V, dtype))
     assert ora["fallback"][0, :, 0].all() and not ora["fallback"][:, :, 1:].all()
+
+
+@pytest.mark.parametrize("V", [9216, 9224, 9216 + 256, 9216 + 264, 9216 + 504, 9216 + 512, 9216 + 768, 24576 + 8 * 31, 24576 + 8 * 33,
+                               36864 + 8 * 40, 131072 + 8 * 63])
+def test_half_vectors(V):
+    """Whole bfloat16 rows of more than 9216 entries are dealt out in half vectors, 256 entries apart: last blocks of 512 entries
+    without a second half, with a part of the first, with a part of the second, and whole, beside rows read for their
+    log-probabilities alone."""
+    t, d, tok = make_inputs(Workload("halves", 2, 2, 2, V, "bf16", 2.0, 0.8, head=8, temperature=0.9), seed=V % 89)
+    t = np.ascontiguousarray(t[:, :, :2])
+    tok[:, 0, -1] = V - 1
+    _check_modify(t, d, tok, 0.9, np.array([-0.3, 0.2]), np.array([2, 1], np.int32), "half vectors %d" % V)
