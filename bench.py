@@ -114,7 +114,7 @@ def bench_modify(a, w, sg, torch, tl, dl, tk, ws, out):
                    "mean_rows_modified": float(np.mean(counts)), "outputs": "logq [B,K,L+1,V] and logp [B,K,L,V], float32"},
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS, "traffic": committed_traffic("modify_" + w.name),
-                     "kernel": "k_mod_row + k_mod_norm + k_mod_write",
+                     "kernel": "k_mod_row + k_mod_pair",
                      "kernel_ms_avg": avg, "kernel_ms_min": ker[0],
                      "algorithmic_bytes_per_launch": read_b + write_b,
                      "algorithmic_read_bytes": read_b, "algorithmic_write_bytes": write_b},
