@@ -197,6 +197,10 @@ __device__ __forceinline__ double rows_excess(const T *rq, const T *rp, int V, d
     return block_sum(static_cast<double>(acc), sh_d) * ec.scale;
 }
 
+// Registers: the tile of two vectors needs all 80 of its six waves per SIMD, and what it cannot keep costs more than anything
+// else here.  With the drafted tokens' addresses kept around the loop, and the counters cleared behind sweep 1, four of them and
+// eight scalars more were spilled: 128 x 16 drafts of 8, V = 4000 bfloat16 225.6 us a call, 212.2 without; 128 x 8 of 4, V = 8000
+// 80.9 / 77.2; float32 128 x 16 of 8, V = 4000 228.4 / 215.7.
 template <typename T, int TH, int NS>
 __global__ void __launch_bounds__(TH, NS >= 4 ? 4 : 6)
 k_rows(const T *__restrict__ target, const T *__restrict__ draft, RowsArgs ar)
@@ -216,12 +220,14 @@ k_rows(const T *__restrict__ target, const T *__restrict__ draft, RowsArgs ar)
     const long long pair = pair_u, bk = pair_u / static_cast<unsigned>(L);
     const int i = static_cast<int>(pair - bk * L);
     const int nv = (V + PV - 1) / PV, per = (nv + P - 1) >> logP;
-    if (tid == 0) sh_missing = 0x7fffffff;
+    if (tid == 0) {
+        sh_missing = 0x7fffffff;
+        if (part == 0 && pair_u % static_cast<unsigned>(K * L) == 0u) ar.final_counter[pair_u / static_cast<unsigned>(K * L)] = 0;
+    }
 
     // the drafted tokens of rows 0 .. i: thread 2 j + m looks after row j of the target (m = 0) or the draft (1)
     const int nstat = 2 * (i + 1);
-    // (threads beyond them repeat the last row's: a load under a branch is waited for where the branch ends)
-    const int jt = (tid >> 1) < i ? (tid >> 1) : i, mt = tid & 1;
+    const int mt = tid & 1;
     uint32_t ztok = 0;
     U4 q[NS], p[NS];
     int r_now = i, part_now = part;                        // whose vectors q, p hold (uniform)
@@ -232,6 +238,10 @@ k_rows(const T *__restrict__ target, const T *__restrict__ draft, RowsArgs ar)
         const T *rq = target + (bk * (L + 1) + r_now) * static_cast<long long>(V);
         const T *rp = draft + (bk * L + r_now) * static_cast<long long>(V);
         const int lo = part_now * per, hi = lo + per < nv ? lo + per : nv, n = hi > lo ? hi - lo : 0;
+        // (threads beyond nstat repeat the last row's: a load under a branch is waited for where the branch ends.  Opaque, so that
+        // the addresses are made here and not kept in registers around the loop)
+        int jt = (tid >> 1) < i ? (tid >> 1) : i;
+        asm volatile("" : "+v"(jt));
         const int tok_raw = token_index_queued(ar.tokens, bk * L + r_now), tok_t = ar.tokens[bk * L + jt];
         rows_load<T, TH, NS>(rq, rp, lo, n, V, q, p);
         {                                                  // (behind the row's loads, needed after sweep 1 only)
@@ -275,7 +285,6 @@ k_rows(const T *__restrict__ target, const T *__restrict__ draft, RowsArgs ar)
                 const unsigned long long bits = static_cast<unsigned long long>(__double_as_longlong(l));
                 __hip_atomic_store(dst, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(dst + 1, bits ^ ar.nonce, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                if (tid == 0 && i == 0 && part == 0 && pair_u % static_cast<unsigned>(K * L) == 0u) ar.final_counter[pair_u / static_cast<unsigned>(K * L)] = 0;
             }
         }
         if (first && i == 0 && L > 1) return;              // row 0 has no sum; the workgroup of row 1 stores its statistics
