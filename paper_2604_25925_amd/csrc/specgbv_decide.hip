@@ -736,7 +736,7 @@ k_final(const T *__restrict__ target, const T *__restrict__ draft, DecideIO io, 
     if (io.row_words) {
         const int n = K * L * 2 * io.word_parts;
         for (int w = static_cast<int>(blockIdx.x) * kSegThreads + tid; w < n; w += static_cast<int>(gridDim.x) * kSegThreads) {
-            unsigned long long *const dst = io.row_words + ((static_cast<long long>(b) * K * L * 2 + w / io.word_parts) * kRowParts + w % io.word_parts) * kWordsPerPart;
+            unsigned long long *const dst = io.row_words + ((static_cast<long long>(b) * K * L + w / (2 * io.word_parts)) * (2 * kRowParts) + w % (2 * io.word_parts)) * kWordsPerPart;
             dst[0] = 0ull; dst[1] = 0ull;
         }
     }

@@ -35,7 +35,7 @@ struct Workspace {
     size_t pend_part;  // double [B*K*L][kPendParts]  partial normalisers of a modified row shared among workgroups
     size_t pend_cnt;   // int32  [B*K*L]  workgroups of a shared row that have stored their partial normaliser
     size_t stat_part;  // Row0Part [B*K*L][2][kRowParts]  partial row statistics (two-pass schedule, small batches; the rows
-                       //             schedule keeps its parts' log2-normalisers there)
+                       //             schedule keeps its parts' log2-normalisers there, [B*K*L][kRowParts][2][kWordsPerPart] words)
     size_t row0;       // Row0Part [B][2][kRow0Parts]  partial statistics of the rows 0 a prefix's drafts share (chain schedule)
     size_t later;      // int32 [workgroups][1 + rows a workgroup sums]  chain schedule: per workgroup, the number of rows
                        //             whose Eq. (hik) sum is taken again without cancellation, then their row indices

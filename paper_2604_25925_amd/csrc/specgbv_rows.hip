@@ -19,7 +19,10 @@
 // have the same, so whatever the workspace held before, words of an earlier call among it, is not taken for one).  A call
 // captured in a graph has the same number in every replay; the final-token kernel, which runs behind this one and reads none
 // of the words, therefore clears them.  (A kernel in front that marks the words as not there yet, which this one had before,
-// cost 2 - 5 us a call.)
+// cost 2 - 5 us a call.)  The four words of a part, two of either model, share 32 bytes, so that they are looked for in as many
+// memory accesses as two words in places of their own were: one prompt of 3 drafts, V = 128256 28.8 us a call with the models'
+// words apart, 28.0 now; 128 x 16 of 8, V = 4000 bfloat16 212.2 / 211.1; 64 x 8 of 8, V = 8000 78.4 / 77.8.  (All words of a
+// draft without gaps: whole rows' words then share lines between workgroups, V = 4000 219.)
 //
 // Step 3 waits for workgroups with a lower index only (the same draft's earlier rows) or with the same row (its other
 // parts); workgroups are dispatched in index order, so what is waited for is running or has run.  Nothing relies on
@@ -39,7 +42,7 @@ static_assert(sizeof(Row0Part) == kWordsPerPart * sizeof(unsigned long long), "t
 
 struct RowsArgs {
     const int32_t *tokens;
-    unsigned long long *words;     // [n_rows][2][kRowParts][2] log2-normalisers of the parts: float64 bits, and those ^ nonce
+    unsigned long long *words;     // [n_rows][kRowParts][2][2] log2-normalisers of the parts: float64 bits, and those ^ nonce
     unsigned long long nonce;
     int32_t *final_counter;        // [batch] arrival counters of the final-token kernel, cleared here
     RowStat *stats;
@@ -233,7 +236,9 @@ k_rows(const T *__restrict__ target, const T *__restrict__ draft, RowsArgs ar)
     int r_now = i, part_now = part;                        // whose vectors q, p hold (uniform)
     unsigned long long *const words = ar.words + bk * L * (2 * kRowParts * kWordsPerPart);
     const int nwords = nstat * P;                          // word w: row w / (2 P), model w / P % 2, part w % P
-    auto word_at = [&](int w) { return words + ((w >> logP) * kRowParts + (w & (P - 1))) * kWordsPerPart; };
+    auto word_at = [&](int w) {
+        return words + (((w >> (logP + 1)) * kRowParts + (w & (P - 1))) * 2 + ((w >> logP) & 1)) * kWordsPerPart;
+    };
     for (bool first = true;; first = false) {
         const T *rq = target + (bk * (L + 1) + r_now) * static_cast<long long>(V);
         const T *rp = draft + (bk * L + r_now) * static_cast<long long>(V);
@@ -281,7 +286,7 @@ k_rows(const T *__restrict__ target, const T *__restrict__ draft, RowsArgs ar)
             const double l = (Z > 0.0 && ref > -1.0e300) ? ref + log2_newton(Z) : -static_cast<double>(__builtin_inff());
             sh_own[tid] = l;
             if (first) {
-                unsigned long long *const dst = words + ((2 * r_now + tid) * kRowParts + part_now) * kWordsPerPart;
+                unsigned long long *const dst = words + ((r_now * kRowParts + part_now) * 2 + tid) * kWordsPerPart;
                 const unsigned long long bits = static_cast<unsigned long long>(__double_as_longlong(l));
                 __hip_atomic_store(dst, bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 __hip_atomic_store(dst + 1, bits ^ ar.nonce, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
