@@ -9,7 +9,10 @@ from specgbv_synth import Workload, make_inputs
 
 pytestmark = pytest.mark.gpu
 
-SHAPES = [(2, 3, 5, 32768, "bf16"), (1, 2, 4, 70001, "f32"), (40, 4, 3, 6000, "bf16"), (3, 2, 1, 9000, "f32")]   # 4, 16, 1 and 4 parts
+# batch, K, L, V, type; in 8, 16, 1, 4, 8 and 1 parts, of 512, 1094, 750, 563, 1719 and 2125 vectors: each of the four tiles
+SHAPES = [(2, 3, 5, 32768, "bf16"), (1, 2, 4, 70001, "f32"), (40, 4, 3, 6000, "bf16"), (3, 2, 1, 9000, "f32"),
+          (3, 3, 4, 110000, "bf16"), (18, 3, 5, 8500, "f32")]
+PARTS = [8, 16, 1, 4, 8, 1]
 
 
 class _Calls:
@@ -44,6 +47,25 @@ class _Calls:
 
 def _same(a, b):
     return all(np.array_equal(x, y, equal_nan=True) for x, y in zip(a, b))
+
+
+@pytest.mark.parametrize("shape,parts", zip(SHAPES, PARTS))
+def test_words_are_used_and_cleared(shape, parts):
+    """In a workspace full of one byte, a call leaves zeros in exactly the words of its parts (32 bytes each, of the room of 16
+    parts per row): the shapes above go to the rows schedule in the parts that the other tests count on, and a replay with the
+    same number finds none of the words."""
+    import torch
+    c = _Calls(shape)
+    c.ws.fill_(165)
+    c.call()
+    torch.cuda.synchronize()
+    rows = shape[0] * shape[1] * shape[2]
+    ws = c.ws.cpu().numpy()
+    want = np.full((rows, 16, 32), 165, np.uint8)
+    want[:, :parts] = 0
+    want = want.reshape(-1)
+    at = [o for o in range(0, len(ws) - want.size + 1, 256) if ws[o] == 0 and np.array_equal(ws[o:o + want.size], want)]
+    assert at, "no such words"
 
 
 @pytest.mark.parametrize("shape", SHAPES)
