@@ -570,27 +570,32 @@ __device__ __forceinline__ void for_each_pair_range(const T *rq, const T *rp, in
 }
 
 // The first step of for_each_pair_range, asked for before the constants of the sweep are made (the row statistics they come
-// from and their float64 arithmetic pass while the vectors travel), and the sweep that begins with it.  (A row of at least one
-// vector; what a thread loads beyond the range lies in the row and is not used.)  k_ot_sum and k_ot_sum_parts, us a call without
-// and with: three iterations of Algorithm 3, 8 x 4 drafts of 8, V = 128256 bfloat16 342 / 336; one prompt under two levels 64.2 /
-// 63.2; 41 x 7 of 6, V = 32003 111.4 / 110.3; 32 x 8 of 8, V = 24000 92.1 / 91.1; but 4 x 4 of 5, V = 32000 float32 under two
-// levels 57 / 59.  In k_pend_norm the registers cost more than it gains (32 x 8 of 8, V = 128256 571 / 583).
+// from and their float64 arithmetic pass while the vectors travel), and the sweep that begins with it.  What a thread loads
+// beyond the range is the range's last vector, which is on its way anyway (other vectors there doubled what a part of 500
+// vectors reads).  Us a call without / with, of k_ot_sum: 40 x 8 drafts of 8, V = 32000 bfloat16 124.4 / 123.6; 128 x 1 of 5,
+// V = 24000 43.7 / 42.5; float32 under three levels 22 x 4 of 8, V = 11328 90.6 / 88.3, 16 x 4 of 6, V = 32000 114.8 / 115.9; of
+// k_ot_sum_parts: three iterations of Algorithm 3, 8 x 4 of 8, V = 128256 bfloat16 330.7 / 325.1; 16 x 2 of 6, V = 32000 under one
+// level 49.3 / 46.6; float32 8 x 4 of 8, V = 33000 42.4 / 41.6, 4 x 4 of 5, V = 32000 under two levels 56.4 / 56.2, 4 x 4 of
+// 8, V = 33000 33.9 / 34.3.  Not in k_ot_sum_parts of bfloat16 rows without levels (AHEAD false; sums_ahead), which has little
+// to make in front and loses: 4 x 4 of 8, V = 66000 36.5 / 36.9, 16 x 4 of 5, V = 70000 58.6 / 59.7, and 49.4 / 48.5 at 8 x 8 of
+// 4, V = 80000.  In k_pend_norm the registers cost more than it gains (32 x 8 of 8, V = 128256 571 / 583).
 struct FirstPairs { U4 q0, p0, q1, p1; };
-template <typename T, bool VEC, int THREADS>
-__device__ __forceinline__ FirstPairs first_pairs(const T *rq, const T *rp, int V, int lo)
+template <typename T, bool AHEAD, int THREADS>
+__device__ __forceinline__ FirstPairs first_pairs(const T *rq, const T *rp, int V, int lo, int hi)
 {
     FirstPairs f;
-    if constexpr (VEC) {
-        const int e0 = vector_entry<T>(lo + static_cast<int>(threadIdx.x), V), e1 = vector_entry<T>(lo + static_cast<int>(threadIdx.x) + THREADS, V);
+    if constexpr (AHEAD) {
+        const int v0 = lo + static_cast<int>(threadIdx.x), v1 = v0 + THREADS;
+        const int e0 = vector_entry<T>(v0 < hi ? v0 : hi - 1, V), e1 = vector_entry<T>(v1 < hi ? v1 : hi - 1, V);
         f.q0 = load16_stream_any(rq + e0); f.p0 = load16_stream_any(rp + e0);
         f.q1 = load16_stream_any(rq + e1); f.p1 = load16_stream_any(rp + e1);
     }
     return f;
 }
-template <typename T, bool VEC, int THREADS, typename F>
+template <typename T, bool VEC, bool AHEAD, int THREADS, typename F>
 __device__ __forceinline__ void for_each_pair_from(const FirstPairs &first, const T *rq, const T *rp, int V, int lo, int hi, F f)
 {
-    if constexpr (VEC) {
+    if constexpr (AHEAD) {
         constexpr int PV = Elem<T>::kPerVec;
         auto one = [&](const U4 &q, const U4 &p, int v) {
             float zq[PV], zp[PV];
@@ -600,18 +605,20 @@ __device__ __forceinline__ void for_each_pair_from(const FirstPairs &first, cons
             mask_repeated<T>(zp, v, V);
             f(vector_entry<T>(v, V), zq, zp);
         };
+        int v = lo + static_cast<int>(threadIdx.x);
+        if (v >= hi) return;
         U4 q0 = first.q0, p0 = first.p0, q1 = first.q1, p1 = first.p1;
-        for (int v = lo + static_cast<int>(threadIdx.x); v < hi; v += 2 * THREADS) {     // four loads in flight per thread
-            if (v != lo + static_cast<int>(threadIdx.x)) {
-                const int e0 = vector_entry<T>(v, V), e1 = vector_entry<T>(v + THREADS, V);
-                q0 = load16_stream_any(rq + e0); p0 = load16_stream_any(rp + e0);
-                q1 = load16_stream_any(rq + e1); p1 = load16_stream_any(rp + e1);
-            }
+        for (;;) {                                         // four loads in flight per thread
             one(q0, p0, v);
             if (v + THREADS < hi) one(q1, p1, v + THREADS);
+            v += 2 * THREADS;
+            if (v >= hi) break;
+            const int e0 = vector_entry<T>(v, V), e1 = vector_entry<T>(v + THREADS < hi ? v + THREADS : hi - 1, V);
+            q0 = load16_stream_any(rq + e0); p0 = load16_stream_any(rp + e0);
+            q1 = load16_stream_any(rq + e1); p1 = load16_stream_any(rp + e1);
         }
     } else {
-        for_each_pair_range<T, false, THREADS>(rq, rp, V, lo, hi, f);
+        for_each_pair_range<T, VEC, THREADS>(rq, rp, V, lo, hi, f);
     }
 }
 

@@ -221,6 +221,10 @@ __device__ __forceinline__ double lse2_from_parts(const Row0Part *pp, int P)
     return ref + log2(Z);
 }
 
+// Whether a sums' kernel asks for its first vectors ahead of the row's constants (measured at first_pairs).
+template <typename T, bool PEND, bool PARTS>
+constexpr bool sums_ahead() { return !(PARTS && !PEND && Elem<T>::kPerVec == 8); }
+
 // grid rows * P, rows = batch * K * (L - 1): block row * P + part sums part `part` of the Eq. (hik) terms of row
 // pair i = 1 .. L-1 of a draft (PEND: against the row as the pending levels leave it, exactly as k_ot_sum does).
 // With stat_P > 1 the statistics of the draft's rows 0 .. i are still in parts
@@ -248,7 +252,8 @@ k_ot_sum_parts(const T *__restrict__ target, const T *__restrict__ draft, const 
     const int units = VEC ? row_vectors<T>(V) : V;
     const int per = (units + P - 1) / P;
     const int lo = part * per, hi = lo + per < units ? lo + per : units;
-    const FirstPairs first = first_pairs<T, VEC, kStatThreads>(rq, rp, V, lo);
+    constexpr bool kAhead = VEC && sums_ahead<T, PEND, true>();
+    const FirstPairs first = first_pairs<T, kAhead, kStatThreads>(rq, rp, V, lo, hi);
     RowStat st;
     double log2nu = 0.0;
     if (stat_P > 1) {
@@ -296,14 +301,14 @@ k_ot_sum_parts(const T *__restrict__ target, const T *__restrict__ draft, const 
     const RatioConst rc(ratio_const(st.lse2_p, st.lse2_q, log2nu, c_rel) - sumN);
     float acc = 0.0f;
     if (PEND && sh_tab.n > 0) {                   // uniform over the workgroup
-        for_each_pair_from<T, VEC, kStatThreads>(first, rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             pending_weights(zq, zp, c, shift_q, sh_tab, rc, K, wq, w);
 #pragma unroll
             for (int j = 0; j < N; ++j) acc += w[j];
         });
     } else {
-        for_each_pair_from<T, VEC, kStatThreads>(first, rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
 #pragma unroll
@@ -454,7 +459,8 @@ k_ot_sum(const T *__restrict__ target, const T *__restrict__ draft, const int32_
     const T *rq = target + (bk * (L + 1) + i) * static_cast<long long>(V);
     const T *rp = draft + (bk * L + i) * static_cast<long long>(V);
     const int units = VEC ? row_vectors<T>(V) : V;
-    const FirstPairs first = first_pairs<T, VEC, kStatThreads>(rq, rp, V, 0);
+    constexpr bool kAhead = VEC && sums_ahead<T, PEND, false>();
+    const FirstPairs first = first_pairs<T, kAhead, kStatThreads>(rq, rp, V, 0, units);
     const RowStat st = stats[bk * L + i];
     // block likelihood ratio of the length-i block, from the rows before row i (their token
     // probabilities under the modified rows where levels are pending)
@@ -477,14 +483,14 @@ k_ot_sum(const T *__restrict__ target, const T *__restrict__ draft, const int32_
     const RatioConst rc(ratio_const(st.lse2_p, st.lse2_q, log2nu, c_rel) - sumN);
     float acc = 0.0f;
     if (PEND && sh_tab.n > 0) {                   // uniform over the workgroup
-        for_each_pair_from<T, VEC, kStatThreads>(first, rq, rp, V, 0, units, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, rq, rp, V, 0, units, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             pending_weights(zq, zp, c, shift_q, sh_tab, rc, K, wq, w);
 #pragma unroll
             for (int j = 0; j < N; ++j) acc += w[j];
         });
     } else {
-        for_each_pair_from<T, VEC, kStatThreads>(first, rq, rp, V, 0, units, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, rq, rp, V, 0, units, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
 #pragma unroll

@@ -53,3 +53,9 @@ def test_rows_of_one_or_two_vectors_per_thread_do_not_spill(kernels):
     """Three workgroups of 512 threads per compute unit, at most 80 registers, and the kernel needs all of them."""
     for k in _instances(kernels, "k_rows", "Li512ELi2"):
         assert k[".vgpr_count"] <= 80 and k[".vgpr_spill_count"] == 0 and k[".private_segment_fixed_size"] == 0, k[".name"]
+
+
+def test_sums_in_parts_leave_room_for_four_workgroups(kernels):
+    """Partial sums without pending levels: eight waves per SIMD of 512 threads, so that all parts of a small batch are resident at once."""
+    for k in _instances(kernels, "k_ot_sum_parts", "Lb1ELb0"):
+        assert k[".vgpr_count"] <= 64 and k[".vgpr_spill_count"] == 0, k[".name"]
