@@ -354,7 +354,7 @@ __global__ void __launch_bounds__(kStatThreads)
 k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, int K, int L, int V, float c,
             const double *__restrict__ carry_l, const int32_t *__restrict__ count_l,
             const RowStat *__restrict__ stats, PendRow *pend, long long n_rows, int level,
-            const int32_t *__restrict__ off, int batch, double *part_buf, int32_t *arrive)
+            const int32_t *__restrict__ off, int batch, double *part_buf, int32_t *arrive, int resident)
 {
     __shared__ double sh_d[kStatThreads / kWave];
     __shared__ PendTable sh_tab;
@@ -371,6 +371,7 @@ k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, int K, in
     const int T_live = off[batch];
     if (T_live <= 0) return;                      // uniform over the grid
     int P = static_cast<int>(gridDim.x / static_cast<unsigned>(T_live));   // >= 1: the modified rows are among the grid's rows
+    if (T_live * P > resident && T_live * 3 <= resident) P = resident / T_live;
     P = P > kPendParts ? kPendParts : P;
     if (static_cast<long long>(blockIdx.x) >= static_cast<long long>(T_live) * P) return;
     const int item = static_cast<int>(blockIdx.x) / P, part = static_cast<int>(blockIdx.x) % P;
@@ -568,21 +569,33 @@ hipError_t launch_typed(const Problem &p)
     if (e != hipSuccess) return e;
     PendRow *pend = reinterpret_cast<PendRow *>(p.ws + p.lay.pend);
     for (int level = 0; level < p.pend_levels; ++level) {
-        // one workgroup per row pair, but at least two per compute unit, so that a small batch's rows can be shared: as
-        // many as are resident at once (one, two, four per unit, us a call: three iterations of Algorithm 3 with 8 x 4 drafts of
-        // 8, V = 128256 352, 339, 356, of which a pass whose level is empty took 2.4 at four; 16 x 4 of 8, V = 32000 84.9,
-        // 85.0, 89.8; one prompt of 3 drafts 63.8, 64.1, 64.1)
-        const long long min_grid = 2LL * compute_units();
-        const dim3 gp(static_cast<unsigned>(pairs > min_grid ? pairs : min_grid));
+        // One workgroup per row pair, but at least two per compute unit, so that a small batch's rows can be shared (one, two, four per
+        // unit, us a call: three iterations of Algorithm 3 with 8 x 4 drafts of 8, V = 128256 352, 339, 356, of which a pass whose
+        // level is empty took 2.4 at four; 16 x 4 of 8, V = 32000 84.9, 85.0, 89.8; one prompt of 3 drafts 63.8, 64.1, 64.1).
+        // With two per unit a level of more than half as many rows has a workgroup for each row alone, on half the places of the chip;
+        // where that takes long (long rows, and the levels below them to be applied to every entry) the grid is large enough for
+        // two, and has three per unit: 16 x 4 of 8, V = 128256 bfloat16 under three levels two / three / four per unit / as here
+        // 271 / 259 / 254 / 246, 9 x 8 of 8, V = 129472 304 / 277 / 282 / 276, 14 x 5 of 8, V = 100000 245 / 233 / 229 / 222, 30 x 2 of
+        // 8, V = 128256 under two 207 / 194 / 199 / 193.  Not the first level (16 x 4 of 8 144 / 145 / 148), not where the levels are
+        // the library's own, most of which are empty (two iterations, 16 x 4 of 8, V = 64000 204 / 205 / 212), not of shorter rows (20 x 4
+        // of 8, V = 8000 float32 under two levels 61.7 / 62.0 / 67.2), and in float32, whose sweeps are shorter, only where two per
+        // unit are not enough for two workgroups a row (10 x 8 of 4, V = 70000 127 / 130 / 135, 9 x 8 of 8, V = 64000 234 / 223 / 230).
+        const long long cu = compute_units();
+        long long grid = pairs > 2 * cu ? pairs : 2 * cu;
+        if (level > 0 && !p.state_count && row_vectors<T>(p.V) >= 6000 && 2 * pairs > (Elem<T>::kPerVec == 8 ? cu : 3 * cu) && 2 * pairs < 7 * cu)
+            grid = 2 * pairs <= 3 * cu ? 3 * cu : 7 * cu / 2;
+        // (three per unit are resident at once; not with every grid that a row pair each asks for)
+        const int resident = grid > pairs ? static_cast<int>(3 * cu) : 0x7fffffff;
+        const dim3 gp(static_cast<unsigned>(grid));
         const double *carry_l = p.pend_carry + static_cast<size_t>(level) * p.batch;
         const int32_t *count_l = p.pend_count + static_cast<size_t>(level) * p.batch;
         const int32_t *off_l = pend_off + static_cast<size_t>(level) * (p.batch + 1);
         if (vec)
             hipLaunchKernelGGL((k_pend_norm<T, true>), gp, dim3(kStatThreads), 0, p.stream, target, draft, p.K, p.L,
-                               p.V, p.c, carry_l, count_l, stats, pend, pairs, level, off_l, p.batch, pend_part, pend_cnt);
+                               p.V, p.c, carry_l, count_l, stats, pend, pairs, level, off_l, p.batch, pend_part, pend_cnt, resident);
         else
             hipLaunchKernelGGL((k_pend_norm<T, false>), gp, dim3(kStatThreads), 0, p.stream, target, draft, p.K, p.L,
-                               p.V, p.c, carry_l, count_l, stats, pend, pairs, level, off_l, p.batch, pend_part, pend_cnt);
+                               p.V, p.c, carry_l, count_l, stats, pend, pairs, level, off_l, p.batch, pend_part, pend_cnt, resident);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
