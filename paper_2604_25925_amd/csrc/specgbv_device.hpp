@@ -573,11 +573,12 @@ __device__ __forceinline__ void for_each_pair_range(const T *rq, const T *rp, in
 // from and their float64 arithmetic pass while the vectors travel), and the sweep that begins with it.  What a thread loads
 // beyond the range is the range's last vector, which is on its way anyway (other vectors there doubled what a part of 500
 // vectors reads).  Us a call without / with, of k_ot_sum: 40 x 8 drafts of 8, V = 32000 bfloat16 124.4 / 123.6; 128 x 1 of 5,
-// V = 24000 43.7 / 42.5; float32 under three levels 22 x 4 of 8, V = 11328 90.6 / 88.3, 16 x 4 of 6, V = 32000 114.8 / 115.9; of
+// V = 24000 43.7 / 42.5; float32 under levels 22 x 4 of 8, V = 11328 91.1 / 88.7, 42 x 6 of 4, V = 20000 123.6 / 121.2, but not of rows
+// of 28000 entries and more: 11 x 6 of 4, V = 28768 60.1 / 60.1, 28 x 4 of 8, V = 64000 264 / 266, 5 x 16 of 12, V = 94510 354 / 360; of
 // k_ot_sum_parts: three iterations of Algorithm 3, 8 x 4 of 8, V = 128256 bfloat16 330.7 / 325.1; 16 x 2 of 6, V = 32000 under one
 // level 49.3 / 46.6; float32 8 x 4 of 8, V = 33000 42.4 / 41.6, 4 x 4 of 5, V = 32000 under two levels 56.4 / 56.2, 4 x 4 of
-// 8, V = 33000 33.9 / 34.3.  Not in k_ot_sum_parts of bfloat16 rows without levels (AHEAD false; sums_ahead), which has little
-// to make in front and loses: 4 x 4 of 8, V = 66000 36.5 / 36.9, 16 x 4 of 5, V = 70000 58.6 / 59.7, and 49.4 / 48.5 at 8 x 8 of
+// 8, V = 33000 33.9 / 34.3.  Not in k_ot_sum_parts of bfloat16 rows without levels, which has little to make in front and
+// loses: 4 x 4 of 8, V = 66000 36.5 / 36.9, 16 x 4 of 5, V = 70000 58.6 / 59.7, and 49.4 / 48.5 at 8 x 8 of
 // 4, V = 80000.  In k_pend_norm the registers cost more than it gains (32 x 8 of 8, V = 128256 571 / 583).
 struct FirstPairs { U4 q0, p0, q1, p1; };
 template <typename T, bool AHEAD, int THREADS>

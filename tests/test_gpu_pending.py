@@ -351,10 +351,12 @@ def test_pending_chain_schedule_is_rejected():
 
 
 # Rows long enough for the later levels' passes to have more workgroups than the first's: three per compute unit for 136 row pairs
-# (34 or 102 of them modified), three and a half for 392 (294 modified) and 512 (256).
+# (34 or 102 of them modified), three and a half for 392 (294 modified) and 512 (256).  The last
+# two stand on either side of where float32 sums ask for their first vectors ahead of the row's constants.
 @pytest.mark.parametrize("B,K,L,V,dtype,counts", [
     (17, 2, 4, 49024, "bf16", [[1], [3]]), (17, 2, 4, 49021, "bf16", [[3], [1]]),
-    (49, 2, 4, 48000, "bf16", [[2], [3]]), (49, 2, 4, 24003, "f32", [[3], [3]]), (64, 2, 4, 24000, "f32", [[1], [2]])])
+    (49, 2, 4, 48000, "bf16", [[2], [3]]), (49, 2, 4, 24003, "f32", [[3], [3]]), (64, 2, 4, 24000, "f32", [[1], [2]]),
+    (44, 2, 4, 27993, "f32", [[1], [2]]), (44, 2, 4, 28000, "f32", [[1], [2]])])
 def test_later_levels_of_long_rows(B, K, L, V, dtype, counts):
     t, d, tok = make_inputs(Workload("later", B, K, L, V, dtype, 2.0, 0.8, head=8, temperature=0.9), seed=V % 89)
     carry = np.random.RandomState(V % 71).normal(0.0, 0.4, (2, B))
