@@ -59,15 +59,16 @@ __device__ __forceinline__ KseqSums kseq_block_sums(double G, double S, double D
 // sweeps, 8 % where 64 drafts nearly coincide with the target; by the step alone, and with rho kept in float32, rho was off by
 // up to 1e-2 at K = 4, V = 100, T = 0.3, drafts close to the target, where it is good to 1e-6.)
 // (rho, beta) is the pair of the last sweep, or its continuation along the tangent of G by at most 2e-7 rho.
-// at_one: the sums at rho = 1; sweep(rho, turn): KseqSums.
+// sweep(rho, it): KseqSums of step it, the first at rho = 1.  (It is called at one place: a second copy of a sweep over memory took
+// k_kseq_rows from three resident workgroups per compute unit to two.)
 struct KseqRoot { double rho, beta; };
 template <typename Sweep>
-__device__ __forceinline__ KseqRoot kseq_root(int n, const KseqSums &at_one, Sweep sweep)
+__device__ __forceinline__ KseqRoot kseq_root(int n, Sweep sweep)
 {
     constexpr double kStep = 2.0e-7;
     double rho = 1.0, lo = 1.0, hi = static_cast<double>(n), beta = 0.0;
     for (int it = 0;; ++it) {
-        const KseqSums sm = it == 0 ? at_one : sweep(rho, it & 1);
+        const KseqSums sm = sweep(rho, it);
         beta = sm.G / rho;
         if (n <= 1) break;                                 // one candidate: rho = 1 (Section 3.1)
         const double b1 = beta < 1.0 ? beta : 1.0, A = 1.0 - b1;
@@ -175,7 +176,7 @@ k_kseq_rows(const T *__restrict__ target, const T *__restrict__ draft, const int
     const float shift_q = rintf(static_cast<float>(lse2_q));
     const double C1 = lse2_p - lse2_q;
     __syncthreads();                                       // (the last block sum has been read)
-    auto sweep = [&](double rho, int turn) {
+    const KseqRoot root = kseq_root(n, [&](double rho, int it) {
         const RatioConst rc(C1 - log2(rho));               // rho p / q = 2^(c (z_p - z_q) - C2)
         const float kappa = -rc.neg_kappa;
         // summed as min{rho p, q} (not as max{q - rho p, 0} = q - min): where the two models hardly overlap the sum is
@@ -192,9 +193,8 @@ k_kseq_rows(const T *__restrict__ target, const T *__restrict__ draft, const int
                 Dr += open ? e * r : 0.0f;
             }
         });
-        return kseq_block_sums(static_cast<double>(G), static_cast<double>(S), static_cast<double>(Dr), sh_d, turn);
-    };
-    const KseqRoot root = kseq_root(n, sweep(1.0, 0), sweep);
+        return kseq_block_sums(static_cast<double>(G), static_cast<double>(S), static_cast<double>(Dr), sh_d, it & 1);
+    });
     if (tid == 0) { rho_out[w.pair] = root.rho; beta_out[w.pair] = root.beta; }
 }
 
@@ -331,12 +331,13 @@ k_kseq_onchip(const T *__restrict__ target, const T *__restrict__ draft, const i
         }
     }
     const KseqSums at_one = kseq_block_sums(static_cast<double>(C0) + static_cast<double>(D0), static_cast<double>(S0), static_cast<double>(D0), sh_d, 0);
-    const KseqRoot root = kseq_root(n, at_one, [&](double rho, int turn) {
+    const KseqRoot root = kseq_root(n, [&](double rho, int it) {
+        if (it == 0) return at_one;                        // (uniform)
         const float rf = static_cast<float>(rho), rl = static_cast<float>(rho - static_cast<double>(rf));
         float C = 0.0f, S = 0.0f, Dr = 0.0f;
 #pragma unroll
         for (int e = 0; e < NE; ++e) add(ew[e], fmaf(rf, rw[e], rl * rw[e]), C, S, Dr);     // (where p / q overflows r may be NaN: then not open)
-        return kseq_block_sums(static_cast<double>(C) + static_cast<double>(Dr), static_cast<double>(S), static_cast<double>(Dr), sh_d, turn);
+        return kseq_block_sums(static_cast<double>(C) + static_cast<double>(Dr), static_cast<double>(S), static_cast<double>(Dr), sh_d, it & 1);
     });
     if (tid == 0) { rho_out[w.pair] = root.rho; beta_out[w.pair] = root.beta; }
 }

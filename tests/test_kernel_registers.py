@@ -59,3 +59,10 @@ def test_sums_in_parts_leave_room_for_four_workgroups(kernels):
     """Partial sums without pending levels: eight waves per SIMD of 512 threads, so that all parts of a small batch are resident at once."""
     for k in _instances(kernels, "k_ot_sum_parts", "Lb1ELb0"):
         assert k[".vgpr_count"] <= 64 and k[".vgpr_spill_count"] == 0, k[".name"]
+
+
+def test_kseq_rows_from_memory_leave_room_for_three_workgroups(kernels):
+    """One copy of the sweep; bfloat16 rows by vectors need a few more registers than that (85)."""
+    for args in ("Lb0", "Lb1"):
+        for k in _instances(kernels, "k_kseq_rows", args):
+            assert k[".vgpr_count"] <= (88 if "k_kseq_rowsItLb1" in k[".name"] else 80) and k[".vgpr_spill_count"] == 0, k[".name"]
