@@ -771,13 +771,16 @@ __device__ __forceinline__ double with_token_term(double total, const RowStat &s
     return (total - old) + token_term(log2q, log2r, K) * exp2_small(st.lse2_q - static_cast<double>(shift_q));
 }
 
-// log2 of a positive finite double: a float logarithm and one Newton step on 2^y = m (error about 1e-14).
-__device__ __forceinline__ double log2_newton(double z)
+// log2 of a positive finite double: a float logarithm y0 and the series of the logarithm of m 2^-y0 = 1 + d, |d| < 2e-7, to its
+// second term (the third is below 1e-20).  Error at most 2.2e-15 for sums up to e^12, rms 4.8e-16, as the library function's
+// (1.8e-15, 4.7e-16); with the first term alone 1.3e-14 and 1.9e-15, all of one sign.
+__device__ __forceinline__ double log2_series(double z)
 {
     int e;
     const double m = frexp(z, &e);
     const double y0 = static_cast<double>(__log2f(static_cast<float>(m)));
-    return static_cast<double>(e) + (y0 + (m * exp2_small(-y0) - 1.0) * 1.44269504088896340736);
+    const double d = m * exp2_small(-y0) - 1.0;
+    return static_cast<double>(e) + (y0 + fma(-0.5 * d, d, d) * 1.44269504088896340736);
 }
 
 // Integral reference exponent of a group of entries whose largest logit is m (partial sums taken relative to

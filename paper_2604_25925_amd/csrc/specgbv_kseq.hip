@@ -300,7 +300,7 @@ k_kseq_onchip(const T *__restrict__ target, const T *__restrict__ draft, const i
         double Z = 0.0;
 #pragma unroll
         for (int x = 0; x < kWaves; ++x) Z += ldexp(sh_Z[at + x], reference_shift(sh_ref[at + x], M));
-        const double l = Z > 0.0 ? static_cast<double>(M) + log2_newton(Z) : -static_cast<double>(__builtin_inff());
+        const double l = Z > 0.0 ? static_cast<double>(M) + log2_series(Z) : -static_cast<double>(__builtin_inff());
         lse2_q = lane_value(l, 0); lse2_p = lane_value(l, 1);
     }
     if (tid == 0) kseq_store_stats(w, Elem<T>::from_bits(tok_q), Elem<T>::from_bits(tok_p), lse2_q, lse2_p, c, c_rel, stats);

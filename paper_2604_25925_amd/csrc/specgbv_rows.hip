@@ -283,7 +283,7 @@ k_rows(const T *__restrict__ target, const T *__restrict__ draft, RowsArgs ar)
                 Z = (Z > 0.0 ? Z * exp2_small(ref - top) : 0.0) + (t - top == 0.0 ? 1.0 : exp2_small(t - top));
                 ref = top;
             }
-            const double l = (Z > 0.0 && ref > -1.0e300) ? ref + log2_newton(Z) : -static_cast<double>(__builtin_inff());
+            const double l = (Z > 0.0 && ref > -1.0e300) ? ref + log2_series(Z) : -static_cast<double>(__builtin_inff());
             sh_own[tid] = l;
             if (first) {
                 unsigned long long *const dst = words + ((r_now * kRowParts + part_now) * 2 + tid) * kWordsPerPart;
@@ -335,7 +335,7 @@ k_rows(const T *__restrict__ target, const T *__restrict__ draft, RowsArgs ar)
         if (P > 1) {
             double Z = l > -1.0e300 ? exp2_small(l - top) : 0.0;
             for (int o = 1; o < P; o <<= 1) Z += __shfl_xor(Z, o);
-            lse = top > -1.0e300 ? top + log2_newton(Z) : top;
+            lse = top > -1.0e300 ? top + log2_series(Z) : top;
         }
         if (w < nwords && (w & (P - 1)) == 0) sh_lse[w >> logP] = lse;
     }
@@ -473,7 +473,7 @@ k_short_rows(const T *__restrict__ target, const T *__restrict__ draft, const in
         const double t = static_cast<double>(ztok) * static_cast<double>(c);
         const double top = Z0 > 0.0 ? fmax(ref, t) : t;
         const double Z = (Z0 > 0.0 ? Z0 * exp2_small(ref - top) : 0.0) + (t - top == 0.0 ? 1.0 : exp2_small(t - top));
-        const double lse = top + log2_newton(Z);
+        const double lse = top + log2_series(Z);
         if (lane < 2) { sh_lse[2 * r + lane] = lse; sh_tok[2 * r + lane] = token_scaled(t, lse, c_rel); }
     }
     __syncthreads();
