@@ -780,7 +780,7 @@ __device__ __forceinline__ double log2_series(double z)
     const double m = frexp(z, &e);
     const double y0 = static_cast<double>(__log2f(static_cast<float>(m)));
     const double d = m * exp2_small(-y0) - 1.0;
-    return static_cast<double>(e) + (y0 + fma(-0.5 * d, d, d) * 1.44269504088896340736);
+    return static_cast<double>(e) + fma(d * 1.44269504088896340736, fma(d, -0.5, 1.0), y0);
 }
 
 // Integral reference exponent of a group of entries whose largest logit is m (partial sums taken relative to
