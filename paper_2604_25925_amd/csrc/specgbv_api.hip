@@ -1,12 +1,13 @@
 // C ABI of libspecgbv.so: argument checks, workspace layout, kernel sequencing.
 #include <atomic>
-#include <chrono>
-#include <random>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <ctime>
+#include <sys/random.h>
+#include <unistd.h>
 
 #include "../../include/specgbv.h"
 #include "specgbv_internal.hpp"
@@ -91,12 +92,23 @@ int wait_polls()
     return n < 0 ? 0 : (n > 1048576 ? 1048576 : static_cast<int>(n));
 }
 
-// A counter from a start that differs from process to process (words that memory handed on from another one may hold), put
-// through a bijection (splitmix64), so that no two calls share a number.  0 is what cleared words would agree to.
-uint64_t call_nonce()
+// Where this process's numbers start: its own place (words that memory handed on from another process may hold were made from another
+// one) from the kernel's random numbers or, where it has none to give at once, from the clock, the process and where it is loaded.
+// Nothing here throws or waits: the callers are C functions.
+static uint64_t nonce_start() noexcept
 {
-    static std::atomic<uint64_t> next{static_cast<uint64_t>(std::chrono::steady_clock::now().time_since_epoch().count()) ^
-                                      (static_cast<uint64_t>(std::random_device{}()) << 32)};
+    uint64_t start = 0;
+    if (getrandom(&start, sizeof start, GRND_NONBLOCK) == static_cast<ssize_t>(sizeof start)) return start;
+    timespec now{};
+    clock_gettime(CLOCK_REALTIME, &now);
+    return (static_cast<uint64_t>(now.tv_sec) << 30 ^ static_cast<uint64_t>(now.tv_nsec)) ^ static_cast<uint64_t>(getpid()) << 44 ^
+           reinterpret_cast<uintptr_t>(&start);
+}
+
+// A counter put through a bijection (splitmix64), so that no two calls share a number.  0 is what cleared words would agree to.
+uint64_t call_nonce() noexcept
+{
+    static std::atomic<uint64_t> next{nonce_start()};
     for (;;) {
         uint64_t z = next.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);
         z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;

@@ -57,7 +57,7 @@ constexpr int kSegElems = kWave * 8;           // vocabulary entries per residua
 int compute_units();                           // of the current device
 int wait_polls();                              // looks a workgroup takes at what another one owes before it computes that itself
 
-uint64_t call_nonce();                         // a number other than zero that no other call of this process gets
+uint64_t call_nonce() noexcept;                         // a number other than zero that no other call of this process gets
 
 Workspace make_workspace(int batch, int K, int L, int V);
 

@@ -185,3 +185,11 @@ def test_ctypes_structures_match_the_c_header(tmp_path):
         assert int(got[cname]) == ctypes.sizeof(cls), cname
         for field, _ in cls._fields_:
             assert int(got["%s.%s" % (cname, field)]) == getattr(cls, field).offset, "%s.%s" % (cname, field)
+
+
+def test_nothing_in_the_library_throws():
+    """A C++ exception must not reach a C caller: the library imports nothing that raises one (no throw of its own, no allocation,
+    no random_device, which throws where its source cannot be opened)."""
+    blob = open(binding._LIB_PATH, "rb").read()
+    for name in (b"random_device", b"__cxa_throw", b"_ZSt20__throw", b"_ZSt17__throw", b"_Znwm", b"_Znam"):
+        assert name not in blob, name
