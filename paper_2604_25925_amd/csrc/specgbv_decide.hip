@@ -37,29 +37,6 @@ constexpr int kSegAtOnce = 4;                // residual segments whose loads a 
 
 // ---------------------------------------------------------------- k_decide
 
-// exp2_small without its branches: an acceptance-table entry takes three of them, and the compiler interleaves them only
-// where no control flow lies between (one after the other they were a good part of the table's time).
-__device__ __forceinline__ double exp2_flat(double x)
-{
-    const double xc = fmin(fmax(x, -1001.0), 1001.0);
-    const double n = rint(xc), f = (xc - n) * 0.693147180559945309417;
-    double p = 1.0 / 479001600.0;
-    p = fma(p, f, 1.0 / 39916800.0);
-    p = fma(p, f, 1.0 / 3628800.0);
-    p = fma(p, f, 1.0 / 362880.0);
-    p = fma(p, f, 1.0 / 40320.0);
-    p = fma(p, f, 1.0 / 5040.0);
-    p = fma(p, f, 1.0 / 720.0);
-    p = fma(p, f, 1.0 / 120.0);
-    p = fma(p, f, 1.0 / 24.0);
-    p = fma(p, f, 1.0 / 6.0);
-    p = fma(p, f, 0.5);
-    p = fma(p, f, 1.0);
-    p = fma(p, f, 1.0);
-    const double r = ldexp(p, static_cast<int>(n));
-    return x > 1000.0 ? INFINITY : (x > -1000.0 ? r : 0.0);      // (not a number: 0)
-}
-
 // Bitwise OR over the 64 lanes of the wave with data-parallel-primitive moves (row shifts by
 // 1, 2, 4, 8 inside each row of 16 lanes, then the two row broadcasts), result read from lane 63.
 __device__ __forceinline__ unsigned wave_or32(unsigned v)
@@ -228,7 +205,7 @@ __device__ __forceinline__ void decide_prefix(const DecideIO &io, int b, int K, 
                 log2P += j0 + j < i ? c[j] : 0.0;
             }
         }
-        // 1/nu (nu by one division), P and Q = nu P
+        // 1/nu (nu by one division), P and Q = nu P (interleaved: one after the other they were a good part of the table's time)
         const double inv_nu = exp2_flat(-log2nu), P = exp2_flat(log2P), Q = exp2_flat(log2nu + log2P);
         const double nu = 1.0 / inv_nu, t1 = 1.0 - inv_nu, A = 1.0 - P;
         // c_K(P) = (1 - (1-P)^K) / P = sum_{j<K} (1-P)^j: chance that one of K i.i.d. drafts equals a block of draft

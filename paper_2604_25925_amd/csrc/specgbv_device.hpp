@@ -165,14 +165,9 @@ __device__ __forceinline__ float one_minus_clamped(float r) {
     return __builtin_amdgcn_fmed3f(1.0f - r, 0.0f, 1.0f);
 }
 
-// 2^x in float64 (0 below x = -1000, infinity above x = 1000) by a degree-12 polynomial on [-1/2, 1/2] and an exponent shift
-// (relative error about 1e-15; far less code than the general library routine, which matters
-// in kernels whose run time is mostly instruction fetch, and few registers, which matters where
-// the register file is full of data).
-__device__ __forceinline__ double exp2_small(double x)
+// 2^x in float64 for |x| <= 1001, by a degree-12 polynomial on [-1/2, 1/2] and an exponent shift (relative error about 1e-15).
+__device__ __forceinline__ double exp2_poly(double x)
 {
-    if (!(x > -1000.0)) return 0.0;
-    if (x > 1000.0) return INFINITY;
     const double n = rint(x);
     const double f = (x - n) * 0.693147180559945309417;      // |f| <= 0.3466
     double p = 1.0 / 479001600.0;
@@ -189,6 +184,23 @@ __device__ __forceinline__ double exp2_small(double x)
     p = fma(p, f, 1.0);
     p = fma(p, f, 1.0);
     return ldexp(p, static_cast<int>(n));
+}
+
+// The same for any x: 0 below x = -1000 and for what is not a number, infinity above x = 1000 (far less code than the general
+// library routine, which matters in kernels whose run time is mostly instruction fetch, and few registers, which matters
+// where the register file is full of data).
+__device__ __forceinline__ double exp2_small(double x)
+{
+    if (!(x > -1000.0)) return 0.0;
+    if (x > 1000.0) return INFINITY;
+    return exp2_poly(x);
+}
+
+// The same without branches: the compiler interleaves several of them only where no control flow lies between.
+__device__ __forceinline__ double exp2_flat(double x)
+{
+    const double r = exp2_poly(fmin(fmax(x, -1001.0), 1001.0));
+    return x > 1000.0 ? INFINITY : (x > -1000.0 ? r : 0.0);
 }
 
 // The ratio p[x] / (nu q[x]) = 2^(c (z_p - z_q) - C2) with a float64 constant C2 that can be
