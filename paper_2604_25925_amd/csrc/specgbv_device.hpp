@@ -581,17 +581,20 @@ __device__ __forceinline__ void for_each_pair_range(const T *rq, const T *rp, in
     }
 }
 
-// The first step of for_each_pair_range, asked for before the constants of the sweep are made (the row statistics they come
-// from and their float64 arithmetic pass while the vectors travel), and the sweep that begins with it.  What a thread loads
-// beyond the range is the range's last vector, which is on its way anyway (other vectors there doubled what a part of 500
-// vectors reads).  Us a call without / with, of k_ot_sum: 40 x 8 drafts of 8, V = 32000 bfloat16 124.4 / 123.6; 128 x 1 of 5,
-// V = 24000 43.7 / 42.5; float32 under levels 22 x 4 of 8, V = 11328 91.1 / 88.7, 42 x 6 of 4, V = 20000 123.6 / 121.2, but not of rows
-// of 28000 entries and more: 11 x 6 of 4, V = 28768 60.1 / 60.1, 28 x 4 of 8, V = 64000 264 / 266, 5 x 16 of 12, V = 94510 354 / 360; of
-// k_ot_sum_parts: three iterations of Algorithm 3, 8 x 4 of 8, V = 128256 bfloat16 330.7 / 325.1; 16 x 2 of 6, V = 32000 under one
-// level 49.3 / 46.6; float32 8 x 4 of 8, V = 33000 42.4 / 41.6, 4 x 4 of 5, V = 32000 under two levels 56.4 / 56.2, 4 x 4 of
-// 8, V = 33000 33.9 / 34.3.  Not in k_ot_sum_parts of bfloat16 rows without levels, which has little to make in front and
-// loses: 4 x 4 of 8, V = 66000 36.5 / 36.9, 16 x 4 of 5, V = 70000 58.6 / 59.7, and 49.4 / 48.5 at 8 x 8 of
-// 4, V = 80000.  In k_pend_norm the registers cost more than it gains (32 x 8 of 8, V = 128256 571 / 583).
+// The first step of a sweep, asked for before its constants are made (the row statistics they come from and their float64
+// arithmetic pass while the vectors travel), and the sweep that begins with it; AHEAD false: the sweep alone.  Where
+// for_each_pair_range ends on single vectors, both vectors of the last step are loaded, the second one's place beyond the range
+// taken by the range's last vector, which is on its way anyway (other vectors there doubled what a part of 500 vectors reads).
+// Us a call, for_each_pair_range / this sweep / this sweep begun ahead:
+//   k_ot_sum without levels, begun ahead: 128 x 1 drafts of 5, V = 24000 bfloat16 43.7 / 43.3 / 42.8; 32 x 8 of 8, V = 24000 89.5 / 89.0 /
+//     88.4; 128 x 1 of 5, V = 12000 float32 40.5 / 40.1 / 39.6;
+//   under levels, not: 48 x 5 of 8, V = 9000 bfloat16 105.2 / 105.2 / 106.4, 14000 123.3 / 120.5 / 121.5; float32 V = 4096 93.0 / 92.8 /
+//     94.3, 7000 111.0 / 108.9 / 109.2;
+//   k_ot_sum_parts, begun ahead: three iterations of Algorithm 3, 8 x 4 of 8, V = 128256 bfloat16 331 / 328.5 / 326.6; float32 8 x 4 of 8,
+//     V = 33000 42.4 / 42.5 / 41.7 (but 4 x 4 of 8 33.9 / 33.2 / 34.4), 16 x 2 of 6, V = 64000 under two levels 90.9 / 90.3 / 89.6;
+//   of bfloat16 rows without levels, where little is made in front, not: 4 x 4 of 8, V = 66000 36.3 / 35.5 / 36.9, 8 x 8 of 4,
+//     V = 80000 49.9 / 49.0 / 48.5, 16 x 4 of 5, V = 70000 57.4 / 57.3 / 58.4.
+// In k_pend_norm the registers cost more than it gains (32 x 8 of 8, V = 128256 571 / 583).
 struct FirstPairs { U4 q0, p0, q1, p1; };
 template <typename T, bool AHEAD, int THREADS>
 __device__ __forceinline__ FirstPairs first_pairs(const T *rq, const T *rp, int V, int lo, int hi)
@@ -608,30 +611,40 @@ __device__ __forceinline__ FirstPairs first_pairs(const T *rq, const T *rp, int 
 template <typename T, bool VEC, bool AHEAD, int THREADS, typename F>
 __device__ __forceinline__ void for_each_pair_from(const FirstPairs &first, const T *rq, const T *rp, int V, int lo, int hi, F f)
 {
-    if constexpr (AHEAD) {
+    if constexpr (VEC) {
         constexpr int PV = Elem<T>::kPerVec;
-        auto one = [&](const U4 &q, const U4 &p, int v) {
+        auto one = [&](const U4 &q, const U4 &p, int v, int e) {
             float zq[PV], zp[PV];
             Elem<T>::unpack(q, zq);
             Elem<T>::unpack(p, zp);
             mask_repeated<T>(zq, v, V);
             mask_repeated<T>(zp, v, V);
-            f(vector_entry<T>(v, V), zq, zp);
+            f(e, zq, zp);
         };
+        auto second = [&](int v) { return vector_entry<T>(v + THREADS < hi ? v + THREADS : hi - 1, V); };
         int v = lo + static_cast<int>(threadIdx.x);
-        if (v >= hi) return;
-        U4 q0 = first.q0, p0 = first.p0, q1 = first.q1, p1 = first.p1;
-        for (;;) {                                         // four loads in flight per thread
-            one(q0, p0, v);
-            if (v + THREADS < hi) one(q1, p1, v + THREADS);
-            v += 2 * THREADS;
-            if (v >= hi) break;
-            const int e0 = vector_entry<T>(v, V), e1 = vector_entry<T>(v + THREADS < hi ? v + THREADS : hi - 1, V);
-            q0 = load16_stream_any(rq + e0); p0 = load16_stream_any(rp + e0);
-            q1 = load16_stream_any(rq + e1); p1 = load16_stream_any(rp + e1);
+        if constexpr (AHEAD) {
+            if (v >= hi) return;
+            U4 q0 = first.q0, p0 = first.p0, q1 = first.q1, p1 = first.p1;
+            for (;;) {                                     // four loads in flight per thread
+                one(q0, p0, v, vector_entry<T>(v, V));
+                if (v + THREADS < hi) one(q1, p1, v + THREADS, vector_entry<T>(v + THREADS, V));
+                v += 2 * THREADS;
+                if (v >= hi) break;
+                const int e0 = vector_entry<T>(v, V), e1 = second(v);
+                q0 = load16_stream_any(rq + e0); p0 = load16_stream_any(rp + e0);
+                q1 = load16_stream_any(rq + e1); p1 = load16_stream_any(rp + e1);
+            }
+        } else {
+            for (; v < hi; v += 2 * THREADS) {
+                const int e0 = vector_entry<T>(v, V), e1 = second(v);
+                const U4 q0 = load16_stream_any(rq + e0), p0 = load16_stream_any(rp + e0), q1 = load16_stream_any(rq + e1), p1 = load16_stream_any(rp + e1);
+                one(q0, p0, v, e0);
+                if (v + THREADS < hi) one(q1, p1, v + THREADS, e1);
+            }
         }
     } else {
-        for_each_pair_range<T, VEC, THREADS>(rq, rp, V, lo, hi, f);
+        for_each_pair_range<T, false, THREADS>(rq, rp, V, lo, hi, f);
     }
 }
 

@@ -453,7 +453,7 @@ k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, int K, in
     }
 }
 
-template <typename T, bool VEC, bool PEND, bool AHEAD>
+template <typename T, bool VEC, bool PEND>
 __global__ void __launch_bounds__(kStatThreads)
 k_ot_sum(const T *__restrict__ target, const T *__restrict__ draft, const int32_t *__restrict__ tokens, int K, int L, int V,
          float c, const RowStat *__restrict__ stats, const PendRow *__restrict__ pend, long long n_rows, int nlev,
@@ -469,7 +469,8 @@ k_ot_sum(const T *__restrict__ target, const T *__restrict__ draft, const int32_
     const T *rq = target + (bk * (L + 1) + i) * static_cast<long long>(V);
     const T *rp = draft + (bk * L + i) * static_cast<long long>(V);
     const int units = VEC ? row_vectors<T>(V) : V;
-    const FirstPairs first = first_pairs<T, AHEAD, kStatThreads>(rq, rp, V, 0, units);
+    constexpr bool kAhead = VEC && !PEND;         // (see first_pairs)
+    const FirstPairs first = first_pairs<T, kAhead, kStatThreads>(rq, rp, V, 0, units);
     const RowStat st = stats[bk * L + i];
     // block likelihood ratio of the length-i block, from the rows before row i (their token
     // probabilities under the modified rows where levels are pending)
@@ -492,14 +493,14 @@ k_ot_sum(const T *__restrict__ target, const T *__restrict__ draft, const int32_
     const RatioConst rc(ratio_const(st.lse2_p, st.lse2_q, log2nu, c_rel) - sumN);
     float acc = 0.0f;
     if (PEND && sh_tab.n > 0) {                   // uniform over the workgroup
-        for_each_pair_from<T, VEC, AHEAD, kStatThreads>(first, rq, rp, V, 0, units, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, rq, rp, V, 0, units, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             pending_weights(zq, zp, c, shift_q, sh_tab, rc, K, wq, w);
 #pragma unroll
             for (int j = 0; j < N; ++j) acc += w[j];
         });
     } else {
-        for_each_pair_from<T, VEC, AHEAD, kStatThreads>(first, rq, rp, V, 0, units, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, rq, rp, V, 0, units, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
 #pragma unroll
@@ -610,16 +611,12 @@ hipError_t launch_typed(const Problem &p)
         return hipGetLastError();
     }
     const dim3 g2(static_cast<unsigned>(rows));
-#define SPECGBV_OT_LAUNCH(VEC, PEND, AHEAD)                                                                           \
-    hipLaunchKernelGGL((k_ot_sum<T, VEC, PEND, AHEAD>), g2, dim3(kStatThreads), 0, p.stream, target, draft, p.tokens, p.K, p.L, \
+#define SPECGBV_OT_LAUNCH(VEC, PEND)                                                                           \
+    hipLaunchKernelGGL((k_ot_sum<T, VEC, PEND>), g2, dim3(kStatThreads), 0, p.stream, target, draft, p.tokens, p.K, p.L, \
                        p.V, p.c, stats, pend, pairs, p.pend_levels, s, reinterpret_cast<double *>(p.ws + p.lay.excess),        \
                        reinterpret_cast<double *>(p.ws + p.lay.excess_part), p.c_rel)
-    // first loads ahead of the row's constants (measured at first_pairs), but not of long float32 rows under levels
-    const bool ahead = Elem<T>::kPerVec == 8 || row_vectors<T>(p.V) < 7000;
-    if (!vec) { if (p.pend_levels > 0) SPECGBV_OT_LAUNCH(false, true, false); else SPECGBV_OT_LAUNCH(false, false, false); }
-    else if (p.pend_levels == 0) SPECGBV_OT_LAUNCH(true, false, true);
-    else if (ahead) SPECGBV_OT_LAUNCH(true, true, true);
-    else if constexpr (Elem<T>::kPerVec == 4) SPECGBV_OT_LAUNCH(true, true, false);
+    if (p.pend_levels > 0) { if (vec) SPECGBV_OT_LAUNCH(true, true); else SPECGBV_OT_LAUNCH(false, true); }
+    else { if (vec) SPECGBV_OT_LAUNCH(true, false); else SPECGBV_OT_LAUNCH(false, false); }
 #undef SPECGBV_OT_LAUNCH
     return hipGetLastError();
 }

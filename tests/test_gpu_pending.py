@@ -352,7 +352,7 @@ def test_pending_chain_schedule_is_rejected():
 
 # Rows long enough for the later levels' passes to have more workgroups than the first's: three per compute unit for 136 row pairs
 # (34 or 102 of them modified), three and a half for 392 (294 modified) and 512 (256).  The last
-# two stand on either side of where float32 sums ask for their first vectors ahead of the row's constants.
+# two are whole rows of float32 whose sweep ends on a step of 831 and of 832 vectors.
 @pytest.mark.parametrize("B,K,L,V,dtype,counts", [
     (17, 2, 4, 49024, "bf16", [[1], [3]]), (17, 2, 4, 49021, "bf16", [[3], [1]]),
     (49, 2, 4, 48000, "bf16", [[2], [3]]), (49, 2, 4, 24003, "f32", [[3], [3]]), (64, 2, 4, 24000, "f32", [[1], [2]]),
