@@ -106,7 +106,9 @@ k_mod_stats(const T *__restrict__ target, const T *__restrict__ draft, const int
 
 // Vectors per thread that k_mod_row keeps.  40: rows up to 163840 bfloat16 / 81920 float32 entries, one workgroup per
 // compute unit.  12: up to 49152 / 24576 entries, three workgroups per compute unit, which a row of few vectors needs, since
-// its load, sum and stores follow one another.  32 x 8 drafts of 8, bfloat16, by 40, by 12 and by k_mod_stats (rows read
+// its load, sum and stores follow one another; two of rows in halves (ModLane), whose second addresses take it to 82 registers.
+// (Held to 80, with three: 64 x 16 drafts of 8, V = 10000 241 us a call / 237, 12288 271 / 267, but 32 x 8 of 8, V = 24000 140 /
+// 148, 32000 188 / 197.)  32 x 8 drafts of 8, bfloat16, by 40, by 12 and by k_mod_stats (rows read
 // twice), us a call: V = 8193 133, 81, 80; 16385 184, 129, 138; 40961 353, 321, 359.  (8 or 16 are each 3 - 10 % slower at
 // one end of the range that they share with 12.)
 constexpr int kRowSlots = 40, kShortRowSlots = 12;
@@ -338,10 +340,12 @@ k_mod_norm(const T *__restrict__ target, const T *__restrict__ draft, int K, int
 }
 
 // Modified row pairs of rows that k_mod_row takes: normaliser and ln q_new in one kernel.  grid.x = batch * K * M, row index
-// slowest as in k_mod_norm; row pairs with r >= count leave at once.  What bounds it: HBM, one read of the pair and one write
-// (the two kernels it replaces read the pair twice).  A workgroup keeps the first SLOTS vector pairs per thread in registers
-// between the sum and the stores; the rest of a longer row is read again by the workgroup that has just read it, last vectors
-// first, so that most of it comes from the caches (hence no non-temporal hint on its first read).  Two workgroups per compute
+// slowest as in k_mod_norm; row pairs with r >= count leave at once.  What bounds it: HBM, the pair's reads and one write of the
+// row.  A workgroup keeps the first SLOTS vector pairs per thread in registers between the sum and the stores; the rest of a longer
+// row is read again by the workgroup that has just read it, last vectors first, with no non-temporal hint on its first read.  (At
+// V = 128256 bfloat16 nine of 32 slots are kept and 71 % of the pair is read again; 1.61 times the pair passes the second-level
+// caches, so that 0.1 of the 0.71 is met there, and how much the last-level cache holds no counter here tells.  The two
+// kernels this one replaces read all of it twice.)  Two workgroups per compute
 // unit: one loads while the other stores.  Microseconds a call with the two kernels / with this one: 32 x 8 drafts of 8,
 // bfloat16, V = 128256 841 / 822 (the reads and writes together run at 5 TB/s, as a copy does), 32000 223 / 209, 8193 82.7 /
 // 78.4; 16 x 8 of 8, V = 40961 192 / 161; 32 x 4 of 8, V = 12000 float32 71 / 59.6; 2 x 3 of 8, V = 128256 84 / 74.  Slots: 20
