@@ -1,5 +1,5 @@
 """The largest accepted number of table entries per prefix, K L = 1024 (and K L = 992 with the most rows): the decision takes
-several visits per thread and 66 KB of LDS there (needs an MI355X: run with -m gpu)."""
+several visits per thread and 75 KB of LDS there (needs an MI355X: run with -m gpu)."""
 import numpy as np
 import pytest
 
