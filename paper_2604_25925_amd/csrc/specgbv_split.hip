@@ -341,7 +341,7 @@ __device__ __forceinline__ float vector_sum(const float (&w)[N])
 // grid.x >= batch * K * L.  Workgroup w first writes the empty entry of row pair w (if there is one) if the level
 // leaves that row alone.  Then it takes a unit of work: the T rows the level modifies are enumerated prefix by prefix (off[b] rows
 // before prefix b; within a prefix row index slowest) and each is shared among P = min(grid / T, kPendParts)
-// workgroups, so that a level with few rows left still occupies the chip (one workgroup streaming a whole row
+// workgroups (three or more of them only as far as all are resident at once: a second round costs more than larger parts), so that a level with few rows left still occupies the chip (one workgroup streaming a whole row
 // pair with several levels of arithmetic per entry takes 100 - 200 us).  Unit u = blockIdx.x < T * P is part
 // u % P of row u / P; the parts' sums meet in the workspace (device-scope relaxed atomic accesses) and the
 // workgroup that arrives last at the row's counter finishes the row.  No workgroup waits for another one.
