@@ -61,7 +61,7 @@ Workspace make_workspace(int batch, int K, int L, int V)
     w.pend = take(n * kMaxPend * sizeof(PendRow));
     w.pend_off = take(static_cast<size_t>(kMaxPend) * (static_cast<size_t>(batch) + 1) * sizeof(int32_t));
     w.pend_part = take(n * kPendParts * sizeof(double));
-    w.pend_cnt = take(n * sizeof(int32_t));
+    w.spare = take(n * sizeof(int32_t));
     w.stat_part = take(n * 2 * kRowParts * sizeof(Row0Part));
     w.row0 = take(static_cast<size_t>(batch) * 2 * kRow0Parts * sizeof(Row0Part));
     // (lists of g <= kMaxChainGrid workgroups, each 1 + ceil(chains / g) (L - 1) entries: at most this many in all)

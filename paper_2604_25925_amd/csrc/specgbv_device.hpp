@@ -39,7 +39,7 @@ struct PendRow {
     double log2N;    // log2 of N_l = sum_x q^(l)[x] t_l[x]^K (0 when the level does not modify the row)
     double tokadj;   // K log2 t_l[token of this row]: log2 q^(l+1)[token] = log2 q^(l)[token] + tokadj - log2N (0 when not modified)
     int32_t flag;    // 1: the level modifies the row; 0: row beyond its count, or N_l = 0 (the row stays q^(l))
-    int32_t pad;
+    int32_t pad;     // (two-pass schedule: workgroups of the row that have summed their part, until the entry is there)
 };
 
 // Constants of the levels that modify one row, in order (workgroup-uniform; kept in LDS):
@@ -216,6 +216,7 @@ struct RatioConst {
         const double kappa = exp2_small(static_cast<double>(C2_hi) - C2);     // (a non-finite C2 gives 0)
         neg_kappa = (kappa > 0.5 && kappa < 2.0) ? -static_cast<float>(kappa) : -1.0f;   // non-finite C2
     }
+    __device__ __forceinline__ RatioConst(float hi, float nk) : C2_hi(hi), neg_kappa(nk) {}     // (made before)
     // max(1 - p/(nu q), 0) for logit difference d = z_p - z_q
     __device__ __forceinline__ float one_minus_ratio(float d, float c) const {
         const float r = __builtin_amdgcn_exp2f(fmaf(d, c, -C2_hi));

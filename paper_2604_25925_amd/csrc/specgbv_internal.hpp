@@ -32,9 +32,10 @@ struct Workspace {
                        //             streaming kernels of every call
     size_t pend;       // PendRow [kMaxPend][B*K*L]  rows under pending modifications (written only by calls that carry some)
     size_t pend_off;   // int32  [kMaxPend][B+1]  per level: rows the level modifies in the prefixes before b (two-pass schedule)
-    size_t pend_part;  // double [B*K*L][kPendParts]  partial normalisers of a modified row shared among workgroups
-    size_t pend_cnt;   // int32  [B*K*L]  workgroups of a shared row that have stored their partial normaliser
-    size_t stat_part;  // Row0Part [B*K*L][2][kRowParts]  partial row statistics (two-pass schedule, small batches; the rows
+    size_t pend_part;  // double [B*K*L][kPendParts]  partial sums of Eq. (hik)
+    size_t spare;      // int32  [B*K*L]  (not used: what callers allocate, and which shapes the static scratch holds, stays as it was)
+    size_t stat_part;  // Row0Part [B*K*L][2][kRowParts]  partial row statistics (two-pass schedule, small batches; with pending
+                       //             levels the partial normalisers of their rows; the rows
                        //             schedule keeps its parts' log2-normalisers there, [B*K*L][kRowParts][2][kWordsPerPart] words)
     size_t row0;       // Row0Part [B][2][kRow0Parts]  partial statistics of the rows 0 a prefix's drafts share (chain schedule)
     size_t later;      // int32 [workgroups][1 + rows a workgroup sums]  chain schedule: per workgroup, the number of rows

@@ -10,8 +10,8 @@
 //   k_pend_norm : per modified row, the block ratio mu Algorithm 2 uses there, the normaliser
 //                 N = sum_x q[x] max(1 - p[x] / (mu q[x]), 0)^K of q_new, and the drafted
 //                 token's factor,
-// and k_ot_sum evaluates its sum against q_new = q t^K / N formed per entry (one pass of k_pend_norm per
-// pending level; a level's rows are shared among workgroups when it has few of them left).
+// and k_ot_sum evaluates its sum against q_new = q t^K / N formed per entry (k_pend_norm takes the
+// levels in turn; a level's rows are shared among workgroups when it has few of them left).
 //
 // Small batches, where a workgroup per row would leave most of the chip idle, use k_row_stats_parts and
 // k_ot_sum_parts instead: every row is cut into
@@ -71,15 +71,15 @@ __device__ __forceinline__ void add_vector(RunningSum &acc, const U4 &raw, int v
 }
 
 // grid (row pairs + pending levels, 2): blocks (pair, 0 / 1) reduce the target / draft row of the pair; with
-// pending modifications blocks (pairs + l, 0) compute level l's offsets (pend_offsets) and the row blocks clear
-// the arrival counters of the level passes.
+// pending modifications blocks (pairs + l, 0) compute level l's offsets (pend_offsets) and the row blocks write the levels'
+// entries of their row: empty, or not there yet.
 template <typename T, bool VEC>
 __global__ void __launch_bounds__(kStatThreads)
 k_row_stats(const T *__restrict__ target, const T *__restrict__ draft,
             const int32_t *__restrict__ tokens, int K, int L, int V, float c,
             RowStat *__restrict__ stats, int32_t *__restrict__ final_counter, long long n_rows, int batch,
-            const int32_t *__restrict__ pend_count, int32_t *__restrict__ pend_off, int32_t *__restrict__ pend_cnt,
-            double c_rel)
+            const int32_t *__restrict__ pend_count, int32_t *__restrict__ pend_off,
+            PendRow *__restrict__ pend, int nlev, double c_rel)
 {
     __shared__ double sh_d[kStatThreads / kWave];
     __shared__ float sh_f[kStatThreads / kWave];
@@ -97,7 +97,13 @@ k_row_stats(const T *__restrict__ target, const T *__restrict__ draft,
     if (threadIdx.x == 0 && !is_draft) {
         if (pair % (static_cast<long long>(K) * L) == 0)
             final_counter[pair / (static_cast<long long>(K) * L)] = 0;  // arrival counter of the final-token kernel
-        if (pend_cnt) pend_cnt[pair] = 0;
+    }
+    // the level's entries of this row: empty beyond its count, else not there yet (k_pend_levels)
+    if (!is_draft && static_cast<int>(threadIdx.x) < nlev) {
+        const bool modified = r < pend_count[static_cast<size_t>(threadIdx.x) * batch + bk / K];
+        unsigned long long *const w = reinterpret_cast<unsigned long long *>(pend + threadIdx.x * n_rows + pair);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = modified ? ~0ull : 0ull;
     }
     const T *row = is_draft ? draft + (bk * L + r) * static_cast<long long>(V)
                             : target + (bk * (L + 1) + r) * static_cast<long long>(V);
@@ -337,119 +343,335 @@ __device__ __forceinline__ float vector_sum(const float (&w)[N])
     }
 }
 
-// One level of pending modification (the levels below it are done: their PendRow entries are read).
-// grid.x >= batch * K * L.  Workgroup w first writes the empty entry of row pair w (if there is one) if the level
-// leaves that row alone.  Then it takes a unit of work: the T rows the level modifies are enumerated prefix by prefix (off[b] rows
-// before prefix b; within a prefix row index slowest) and each is shared among P = min(grid / T, kPendParts)
-// workgroups (three or more of them only as far as all are resident at once: a second round costs more than larger parts), so that a level with few rows left still occupies the chip (one workgroup streaming a whole row
-// pair with several levels of arithmetic per entry takes 100 - 200 us).  Unit u = blockIdx.x < T * P is part
-// u % P of row u / P; the parts' sums meet in the workspace (device-scope relaxed atomic accesses) and the
-// workgroup that arrives last at the row's counter finishes the row.  No workgroup waits for another one.
-template <typename T, bool VEC>
-__global__ void __launch_bounds__(kStatThreads)
-k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, int K, int L, int V, float c,
-            const double *__restrict__ carry_l, const int32_t *__restrict__ count_l,
-            const RowStat *__restrict__ stats, PendRow *pend, long long n_rows, int level,
-            const int32_t *__restrict__ off, int batch, double *part_buf, int32_t *arrive, int resident)
+// The levels [from, to) of pending modification (those before them are done).  A level's T rows are enumerated prefix by prefix (off[b]
+// rows before prefix b; within a prefix row index slowest) and each is shared among P workgroups (level_parts), so that a level with
+// few rows left still occupies the chip (one workgroup streaming a whole row pair with several levels of arithmetic per entry takes
+// 100 - 200 us).  The levels' T P units stand in one line, level after level; a workgroup does the unit of its own number (kChunks: as
+// many units in a row as the grid has to take), and those behind the last unit leave at once.  A row's parts meet in the workspace
+// (device-scope relaxed atomic accesses): the workgroup that arrives last at the entry's counter leaves the entry.  Sums and
+// counters are a level's own, so that it does not matter in which order units of different levels come to them.
+//
+// A unit needs the entries of the levels below its own for its row and for the rows of its draft in front of it.  k_row_stats has marked
+// the entries of modified rows as not there yet (all four words), so a unit looks for them until they are there.  They come from units of
+// lower numbers, that is of workgroups of lower index (or from its own earlier ones), and workgroups are dispatched in index order, so
+// what is waited for is running or has run.  Nothing relies on it: after `polls` looks a workgroup makes the entries itself, with
+// the parts and in the order that their units have (the same bits).
+//
+// What bounds a level: where its rows fill the chip, arithmetic; else latencies (load, sum, hand-over: 8 - 15 us) and, before, launches: a
+// kernel for every level, 3 us each, of which a call that updates its state in place makes L - 1, most of them of levels in which nothing is
+// alive, and each of those had a workgroup per row to find that out.  Us a call, a launch per level / as here: three iterations of
+// Algorithm 3, 8 x 4 drafts of 8, V = 128256 bfloat16 344 / 313; one prompt of 3 drafts 195 / 158; 3 x 3 of 8, V = 50257 float32 203 / 167;
+// 64 x 4 of 12, V = 9000 482 / 391; 128 x 8 of 8, V = 8000 890 / 789; 32 x 8 of 8, V = 128256 1433 / 1410; three given levels on 16 x 4 of 8,
+// V = 32000 110.7 / 101.8; two on 64 x 16 of 8, V = 8000 309 / 289; one on 40 x 8 of 8, V = 32000 178 / 171.
+// The float64 constants are made by one wave, a level per lane, with the exponential's coefficients in LDS: as library calls of every
+// thread they took 142 registers in this loop, or 224 bytes of scratch at 80 (three workgroups per compute unit), which cost more than
+// the launches.
+constexpr unsigned long long kNotThere = ~0ull;        // (a NaN that no sum produces)
+constexpr unsigned long long kNoLevel = 0x8000000000000000ull;     // log2 N = -0.0: the level leaves the row as it is
+
+__device__ __forceinline__ void entry_store(PendRow *pr, double log2mu, double log2N, double tokadj, bool some)
 {
+    unsigned long long *const w = reinterpret_cast<unsigned long long *>(pr);
+    static_assert(sizeof(PendRow) == 32, "four words");
+    __hip_atomic_store(w, static_cast<unsigned long long>(__double_as_longlong(log2mu)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(w + 1, static_cast<unsigned long long>(__double_as_longlong(log2N)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(w + 2, static_cast<unsigned long long>(__double_as_longlong(tokadj)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(w + 3, some ? 1ull : 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ unsigned long long entry_load(const PendRow *pr, int word)
+{
+    return __hip_atomic_load(reinterpret_cast<const unsigned long long *>(pr) + word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+constexpr int kSumSlots = 2 * kRowParts * sizeof(Row0Part) / sizeof(double);      // sums of a row's parts, all levels of a launch together
+
+struct LevelArgs {
+    const double *carry;           // [nlev][batch]
+    const int32_t *count;          // [nlev][batch]
+    const int32_t *off;            // [nlev][batch + 1] rows a level modifies in the prefixes before
+    const RowStat *stats;
+    PendRow *pend;                 // [nlev][n_rows]
+    double *sums;                  // [n_rows][kSumSlots]: [level - from][most]
+    long long n_rows;
+    int K, L, V, batch, polls;
+    int from, to, most;            // the levels of this launch; parts of a row at most
+    int first_grid, grid;          // workgroups that share a level's rows: the first level's, any other's
+    int first_resident, resident;
+    float c;
+};
+
+// Workgroups that share a row of a level of T rows (three or more of them only as far as all are resident at once: a second
+// round costs more than larger parts).
+__device__ __forceinline__ int level_parts(const LevelArgs &ar, int level, int T)
+{
+    if (T <= 0) return 0;
+    const int grid = level == 0 ? ar.first_grid : ar.grid, resident = level == 0 ? ar.first_resident : ar.resident;
+    int P = grid / T;                                  // >= 1: the modified rows are among the grid's rows
+    if (T * P > resident && T * 3 <= resident) P = resident / T;
+    return P > ar.most ? ar.most : P;
+}
+
+// What the levels do to the rows of a draft, and the constants of one sweep (LDS).
+struct Levels {
+    PendTable tab;                         // the levels in front that modify the row at hand
+    double N[kMaxPend * kMaxRows], adj[kMaxPend * kMaxRows], mu[kMaxPend * kMaxRows];       // [level][row]
+    double run;                            // log2 q^(l)[token] - log2 p[token] of the row at hand
+    double scale;                          // log2 of what the sum is relative to, under the levels in front
+    double sums[kPendParts];
+    float shift_q, C2_hi, neg_kappa;
+    int cnt[kMaxPend];                     // rows the levels modify
+    int begin[kMaxPend + 1], parts[kMaxPend];                // each level's first unit, and the parts of its rows
+    double exp2_coef[11];                  // (see exp2_from)
+};
+
+// exp2_small with its polynomial's coefficients in LDS: hoisted out of a loop, they would take registers that the sweeps need.
+__device__ __forceinline__ double exp2_from(const double *coef, double x)
+{
+    const double n = rint(x), f = (x - n) * 0.693147180559945309417;
+    double p = coef[0];
+#pragma unroll
+    for (int i = 1; i < 11; ++i) p = fma(p, f, coef[i]);
+    p = fma(p, f, 1.0);
+    p = fma(p, f, 1.0);
+    return x > 1000.0 ? INFINITY : (x > -1000.0 ? ldexp(p, static_cast<int>(fmin(fmax(n, -1001.0), 1001.0))) : 0.0);
+}
+__device__ const double g_exp2_coef[11] = {1.0 / 479001600.0, 1.0 / 39916800.0, 1.0 / 3628800.0, 1.0 / 362880.0, 1.0 / 40320.0, 1.0 / 5040.0,
+                                           1.0 / 720.0, 1.0 / 120.0, 1.0 / 24.0, 1.0 / 6.0, 0.5};
+// log2_series with it.
+__device__ __forceinline__ double log2_from(const double *coef, double z)
+{
+    int e;
+    const double m = frexp(z, &e);
+    const double y0 = static_cast<double>(__log2f(static_cast<float>(m)));
+    const double d = m * exp2_from(coef, -y0) - 1.0;
+    return static_cast<double>(e) + fma(d * 1.44269504088896340736, fma(d, -0.5, 1.0), y0);
+}
+
+enum LevelsForm { kOneLevel, kUnits, kChunks };        // (level 0 alone; a unit per workgroup; as many as it takes)
+template <typename T, bool VEC, LevelsForm FORM>
+__global__ void __launch_bounds__(kStatThreads, VEC ? 6 : 8)
+k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, LevelArgs ar)
+{
+    constexpr bool ONE = FORM == kOneLevel;
     __shared__ double sh_d[kStatThreads / kWave];
-    __shared__ PendTable sh_tab;
-    __shared__ PendRow sh_pr[kMaxPend];           // the levels below, at this row
-    __shared__ double sh_log2mu, sh_sumN;
+    __shared__ Levels sh;
     __shared__ int sh_b, sh_last;
-    PendRow out;
-    out.log2mu = 0.0; out.log2N = 0.0; out.tokadj = 0.0; out.flag = 0; out.pad = 0;
-    {
-        const long long pair0 = blockIdx.x;
-        const int r0 = static_cast<int>(pair0 % L);
-        if (threadIdx.x == 0 && pair0 < n_rows && r0 >= count_l[(pair0 / L) / K]) pend[level * n_rows + pair0] = out;
-    }
-    const int T_live = off[batch];
-    if (T_live <= 0) return;                      // uniform over the grid
-    int P = static_cast<int>(gridDim.x / static_cast<unsigned>(T_live));   // >= 1: the modified rows are among the grid's rows
-    if (T_live * P > resident && T_live * 3 <= resident) P = resident / T_live;
-    P = P > kPendParts ? kPendParts : P;
-    if (static_cast<long long>(blockIdx.x) >= static_cast<long long>(T_live) * P) return;
-    const int item = static_cast<int>(blockIdx.x) / P, part = static_cast<int>(blockIdx.x) % P;
-    for (int base = 0; base < batch; base += kStatThreads) {
-        const int bb = base + static_cast<int>(threadIdx.x);
-        if (bb < batch && off[bb] <= item && item < off[bb + 1]) sh_b = bb;          // exactly one thread
-    }
-    __syncthreads();
-    const int b = sh_b;
-    const int j = item - off[b];
-    const int r = j / K;
-    const long long bk = static_cast<long long>(b) * K + j % K;
-    const long long pair = bk * L + r;            // (b*K + k)*L + r
-    const T *rq = target + (bk * (L + 1) + r) * static_cast<long long>(V);
-    const T *rp = draft + pair * static_cast<long long>(V);
-    const int units = VEC ? row_vectors<T>(V) : V;
-    const int per = (units + P - 1) / P;
-    const int lo = part * per, hi = lo + per < units ? lo + per : units;
-    const RowStat st = stats[pair];
-    // block ratio in front of row r: the carried one continued along the drafted tokens with the
-    // distribution this level modifies (the target rows as modified by the levels below)
-    const double ahead = pend_block_ratio(stats, pend, n_rows, level, bk * L, r, sh_d);
-    if (static_cast<int>(threadIdx.x) < level) sh_pr[threadIdx.x] = pend[static_cast<long long>(threadIdx.x) * n_rows + pair];
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        sh_log2mu = carry_l[b] * 1.44269504088896340736 + ahead;
-        sh_sumN = pend_build_table(sh_pr, 1, level, 0, st.lse2_p - st.lse2_q, sh_tab);
-    }
-    __syncthreads();
-    const double log2mu = sh_log2mu, sumN = sh_sumN;
-    const float shift_q = static_cast<float>(st.lse2_q);
-    const RatioConst rc(st.lse2_p - st.lse2_q + log2mu - sumN);
-    constexpr int N = VEC ? Elem<T>::kPerVec : 1;
-    float acc = 0.0f;
-    if (sh_tab.n == 0) {
-        for_each_pair_range<T, VEC, kStatThreads>(rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
-            float wq[N], w[N];
-            ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
-            acc += vector_sum(w);
-        });
+    const int K = ar.K, L = ar.L, V = ar.V, batch = ar.batch;
+    const float c = ar.c;
+    int tid = threadIdx.x, lane = tid & (kWave - 1);
+    int level = 0, P, at = static_cast<int>(blockIdx.x), P_l = 0, u = 0, left = 1;
+    if constexpr (ONE) {
+        const int T_0 = ar.off[batch];
+        P = level_parts(ar, 0, T_0);
+        if (at >= T_0 * P) return;                // uniform over the workgroup
     } else {
-        for_each_pair_range<T, VEC, kStatThreads>(rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
-            float wq[N], w[N];
-            pending_weights(zq, zp, c, shift_q, sh_tab, rc, K, wq, w);
-            acc += vector_sum(w);
-        });
+        // where each level's units end: a lane looks after a level, in every wave
+        const int T_l = lane >= ar.from && lane < ar.to ? ar.off[lane * (batch + 1) + batch] : 0;
+        if (!__ballot(T_l > 0)) return;           // uniform over the workgroup
+        P_l = level_parts(ar, lane, T_l);
+        const int end = static_cast<int>(wave_inclusive_sum(static_cast<double>(T_l) * static_cast<double>(P_l)));
+        if constexpr (FORM == kChunks) {
+            const int units = __builtin_amdgcn_readlane(end, kWave - 1);
+            left = (units + static_cast<int>(gridDim.x) - 1) / static_cast<int>(gridDim.x);
+            u = at * left;
+            if (u >= units) return;               // uniform
+            left = u + left < units ? left : units - u;
+            if (tid < kMaxPend) { sh.begin[tid + 1] = end; sh.parts[tid] = P_l; }
+            if (tid == 0) sh.begin[0] = 0;
+            __syncthreads();
+        } else {
+            const unsigned long long behind = __ballot(at < end);
+            if (!behind) return;                  // uniform
+            level = __ffsll(static_cast<long long>(behind)) - 1;
+            P = __builtin_amdgcn_readlane(P_l, level);
+            at -= __builtin_amdgcn_readlane(end, level) - __builtin_amdgcn_readlane(T_l, level) * P;
+        }
     }
-    double S = block_sum(static_cast<double>(acc), sh_d);                 // relative to 2^shift_q
-    if (P > 1) {
-        // the store is a device-scope access; the wait lasts until it has been performed, so the counter update that
-        // follows (same thread) cannot be seen before it
-        if (threadIdx.x == 0) {
-            __hip_atomic_store(reinterpret_cast<unsigned long long *>(part_buf + pair * kPendParts + part),
-                               static_cast<unsigned long long>(__double_as_longlong(S)), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-            wait_for_stores();
-            const int arrived = __hip_atomic_fetch_add(&arrive[pair], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            sh_last = arrived == P - 1;
+    auto parts_of = [&](int l_) { return FORM == kChunks ? __builtin_amdgcn_readfirstlane(sh.parts[l_]) : __builtin_amdgcn_readlane(P_l, l_); };
+    if (tid < 11) sh.exp2_coef[tid] = g_exp2_coef[tid];
+    for (;;) {                                    // (kChunks: unit after unit)
+        if constexpr (FORM == kChunks) {
+            asm volatile("" : "+v"(tid));             // (opaque: nothing made of it is kept from unit to unit)
+            lane = tid & (kWave - 1);
+            level = __ffsll(static_cast<long long>(__ballot(lane < kMaxPend && u < sh.begin[lane < kMaxPend ? lane + 1 : 0]))) - 1;
+            P = parts_of(level);
+            at = u - __builtin_amdgcn_readfirstlane(sh.begin[level]);
+        }
+        const int item = at / P, part = at - item * P;
+        const int32_t *const off = ar.off + level * (batch + 1);
+        for (int base = 0; base < batch; base += kStatThreads) {
+            const int bb = base + tid;
+            if (bb < batch && off[bb] <= item && item < off[bb + 1]) sh_b = bb;          // exactly one thread
         }
         __syncthreads();
-        if (!sh_last) return;
-        if (threadIdx.x == 0) {
-            S = 0.0;
-            for (int q = 0; q < P; ++q)                                   // in part order: the same bits whoever finishes
-                S += __longlong_as_double(static_cast<long long>(__hip_atomic_load(
-                    reinterpret_cast<const unsigned long long *>(part_buf + pair * kPendParts + q), __ATOMIC_RELAXED,
-                    __HIP_MEMORY_SCOPE_AGENT)));
-            __hip_atomic_store(&arrive[pair], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);   // for the next level's pass
+        const int b = __builtin_amdgcn_readfirstlane(sh_b);
+        const int j = item - off[b], r = j / K;
+        const long long bk = static_cast<long long>(b) * K + (j - r * K), pair = bk * L + r;
+        const int n_units = VEC ? row_vectors<T>(V) : V;
+        struct In { RowStat st; double carry; };
+        auto loads = [&](int l_, int row_) {
+            In in;
+            in.st = ar.stats[bk * L + (lane < row_ ? lane : row_)];
+            in.carry = ar.carry[static_cast<size_t>(l_) * batch + b];
+            return in;
+        };
+        In in{};
+        if constexpr (VEC) in = loads(level, r);      // (beside the entries; rows read entry by entry have no registers to spare)
+        // What is summed: this unit's part, once; if an entry that it builds on does not appear, all parts of those entries first.
+        int l = level, row = r, q = part, parts = P;
+        bool alone = false;
+        if constexpr (!ONE) {
+            bool none = false;
+            for (int t = tid; t < level * (r + 1); t += kStatThreads) {
+                const int tl = t / (r + 1), tr = t - tl * (r + 1), to = tl * kMaxRows + tr;
+                const PendRow *const pr = ar.pend + tl * ar.n_rows + bk * L + tr;
+                unsigned long long mu = 0ull, n = 0ull, a = 0ull, f = 0ull;
+                bool there = tl < ar.from;            // (a level of an earlier launch)
+                if (there) {
+                    const PendRow e = *pr;
+                    mu = static_cast<unsigned long long>(__double_as_longlong(e.log2mu)); n = static_cast<unsigned long long>(__double_as_longlong(e.log2N));
+                    a = static_cast<unsigned long long>(__double_as_longlong(e.tokadj)); f = e.flag != 0 ? 1ull : 0ull;
+                }
+                for (int look = 0; look < ar.polls && !there; ++look) {
+                    mu = entry_load(pr, 0); n = entry_load(pr, 1); a = entry_load(pr, 2); f = entry_load(pr, 3);
+                    there = mu != kNotThere && n != kNotThere && a != kNotThere && static_cast<unsigned>(f) != ~0u;     // (f: flag and counter)
+                    if (!there) __builtin_amdgcn_s_sleep(2);
+                }
+                none = none || !there;
+                sh.mu[to] = __longlong_as_double(static_cast<long long>(mu));
+                sh.N[to] = __longlong_as_double(static_cast<long long>(f != 0ull ? n : kNoLevel));
+                sh.adj[to] = __longlong_as_double(static_cast<long long>(a));
+            }
+            alone = __syncthreads_or(none) != 0;
+            if (alone) {                              // (normally none is missing)
+                if (tid < level) {
+                    const int cnt = ar.count[static_cast<size_t>(tid) * batch + b];
+                    sh.cnt[tid] = cnt < 0 ? 0 : (cnt > L ? L : cnt);
+                }
+                __syncthreads();
+                l = ar.from; row = 0; q = 0;          // (an earlier launch's are there)
+                parts = parts_of(l);
+            }
         }
-    }
-    if (threadIdx.x == 0) {
-        const double W = S * exp2(static_cast<double>(shift_q) - st.lse2_q - sumN);   // mass of q^(level) t^K
-        out.log2mu = log2mu;
-        if (W > 0.0) {                            // otherwise every weight is zero and the row stays q^(level)
-            out.flag = 1;
-            out.log2N = log2(W);
-            const double tq_eff = (st.tok2_q - st.lse2_q) + pend_token_adjust(sh_pr, 1, level, 0);
-            const double ratio = exp2((st.tok2_p - st.lse2_p) - tq_eff - log2mu);
-            const double t = 1.0 - ratio;
-            out.tokadj = t > 0.0 ? static_cast<double>(K) * log2(t) : -INFINITY;
+        for (;;) {                                    // (uniform, as everything here; normally one pass)
+            const bool own = ONE || (l == level && row == r);
+            if (own || row < sh.cnt[l]) {
+                if (tid < kWave) {
+                    // block ratio in front of the row: the carried one continued along the drafted tokens with the distribution this level
+                    // modifies (the target rows as modified by the levels below)
+                    if (alone || !VEC) in = loads(l, row);
+                    double run = (in.st.tok2_q - in.st.lse2_q) - (in.st.tok2_p - in.st.lse2_p);
+                    if constexpr (!ONE)
+                        if (lane <= row)
+                            for (int m = 0; m < l; ++m) run += sh.adj[m * kMaxRows + lane] - sh.N[m * kMaxRows + lane];
+                    RowStat st;
+                    st.lse2_q = lane_value(in.st.lse2_q, row); st.lse2_p = lane_value(in.st.lse2_p, row);
+                    const double log2mu = in.carry * 1.44269504088896340736 + wave_sum(lane < row ? run : 0.0);
+                    if (lane == row) sh.run = run;
+                    // the levels in front, a lane each; lane l: this level's ratio
+                    const double base = st.lse2_p - st.lse2_q;
+                    bool on = false;
+                    double upto = 0.0, n_l = 0.0;
+                    if constexpr (!ONE) {
+                        on = lane < l && static_cast<unsigned long long>(__double_as_longlong(sh.N[(lane < l ? lane : 0) * kMaxRows + row])) != kNoLevel;
+                        n_l = on ? sh.N[lane * kMaxRows + row] : 0.0;
+                        upto = wave_inclusive_sum(n_l);
+                    }
+                    const unsigned long long ons = __ballot(on);
+                    const double sumN = ONE ? 0.0 : lane_value(upto, kWave - 1);
+                    const double C = on ? base + sh.mu[lane * kMaxRows + row] - (upto - n_l) : base + log2mu - sumN;
+                    const float C_hi = static_cast<float>(C);                 // (as RatioConst)
+                    const double kappa = exp2_from(sh.exp2_coef, static_cast<double>(C_hi) - C);
+                    const float nk = (kappa > 0.5 && kappa < 2.0) ? -static_cast<float>(kappa) : -1.0f;
+                    if (on) {
+                        const int to = __popcll(ons & ((1ull << lane) - 1ull));
+                        sh.tab.C_hi[to] = C_hi;
+                        sh.tab.neg_kappa[to] = nk;
+                    }
+                    if (lane == l) {
+                        sh.mu[l * kMaxRows + row] = log2mu;
+                        sh.tab.n = __popcll(ons);
+                        sh.shift_q = static_cast<float>(st.lse2_q); sh.C2_hi = C_hi; sh.neg_kappa = nk;
+                        sh.scale = static_cast<double>(static_cast<float>(st.lse2_q)) - st.lse2_q - sumN;
+                    }
+                }
+                __syncthreads();
+                const T *rq = target + (bk * (L + 1) + row) * static_cast<long long>(V);
+                const T *rp = draft + (bk * L + row) * static_cast<long long>(V);
+                const int per = (n_units + parts - 1) / parts, lo = q * per, hi = lo + per < n_units ? lo + per : n_units;
+                const float shift_q = sh.shift_q;
+                const RatioConst rc(sh.C2_hi, sh.neg_kappa);
+                constexpr int N = VEC ? Elem<T>::kPerVec : 1;
+                float acc = 0.0f;
+                if (ONE || sh.tab.n == 0) {
+                    for_each_pair_from<T, VEC, false, kStatThreads>(FirstPairs(), rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+                        float wq[N], w[N];
+                        ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
+                        acc += vector_sum(w);
+                    });
+                } else {
+                    for_each_pair_from<T, VEC, false, kStatThreads>(FirstPairs(), rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+                        float wq[N], w[N];
+                        pending_weights(zq, zp, c, shift_q, sh.tab, rc, K, wq, w);
+                        acc += vector_sum(w);
+                    });
+                }
+                double S = block_sum(static_cast<double>(acc), sh_d);         // relative to 2^shift_q
+                if (own && parts > 1) {
+                    // the store is a device-scope access; the wait lasts until it has been performed, so the counter update that
+                    // follows (same thread) cannot be seen before it
+                    unsigned long long *const sums = reinterpret_cast<unsigned long long *>(ar.sums + pair * kSumSlots + (level - ar.from) * ar.most);
+                    if (tid == 0) {
+                        __hip_atomic_store(sums + part, static_cast<unsigned long long>(__double_as_longlong(S)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        wait_for_stores();
+                        // (the counter lies beside the entry's flag, which is not there yet, and starts from -1 as that does)
+                        const int arrived = __hip_atomic_fetch_add(&ar.pend[level * ar.n_rows + pair].pad, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                        sh_last = arrived == parts - 2;
+                    }
+                    __syncthreads();
+                    if (!sh_last) break;
+                    if (tid < parts)
+                        sh.sums[tid] = __longlong_as_double(static_cast<long long>(__hip_atomic_load(sums + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
+                } else if (tid == 0) {
+                    sh.sums[q] = S;
+                }
+                __syncthreads();
+                if (tid == 0 && (own || q == parts - 1)) {
+                    S = 0.0;
+                    for (int x = 0; x < parts; ++x) S += sh.sums[x];          // in part order: the same bits whoever does it
+                    const double W = S * exp2_from(sh.exp2_coef, sh.scale), log2mu = sh.mu[l * kMaxRows + row];     // mass of q^(l) t^K
+                    const bool some = W > 0.0;        // otherwise every weight is zero and the row stays q^(l)
+                    double log2N = 0.0, tokadj = 0.0;
+                    if (some) {
+                        log2N = log2_from(sh.exp2_coef, W);
+                        const double x = -sh.run - log2mu, t = 1.0 - exp2_from(sh.exp2_coef, x);     // 1 - p[token] / (mu q^(l)[token])
+                        tokadj = x == x && t > 0.0 ? static_cast<double>(K) * log2_from(sh.exp2_coef, t) : -INFINITY;
+                    }
+                    if (own) {
+                        entry_store(ar.pend + l * ar.n_rows + pair, log2mu, log2N, tokadj, some);
+                        wait_for_stores();
+                    }
+                    sh.N[l * kMaxRows + row] = some ? log2N : -0.0;
+                    sh.adj[l * kMaxRows + row] = tokadj;
+                }
+            } else if (tid == 0) {
+                sh.N[l * kMaxRows + row] = -0.0; sh.adj[l * kMaxRows + row] = 0.0;
+            }
+            if (own) break;
+            __syncthreads();
+            if (row < sh.cnt[l] && q + 1 < parts) ++q;
+            else {
+                q = 0;
+                if (++row > r) {
+                    row = 0; ++l;
+                    if (l == level) { row = r; q = part; }
+                    parts = parts_of(l);
+                }
+            }
         }
-        pend[level * n_rows + pair] = out;
+        ++u;
+        if (FORM != kChunks || --left == 0) return;
+        __syncthreads();
     }
 }
 
@@ -539,8 +761,8 @@ hipError_t launch_typed(const Problem &p)
     const long long pairs = static_cast<long long>(p.batch) * p.K * p.L;
     const bool vec = read_by_vectors<T>(p.V);
     int32_t *pend_off = reinterpret_cast<int32_t *>(p.ws + p.lay.pend_off);
-    int32_t *pend_cnt = p.pend_levels > 0 ? reinterpret_cast<int32_t *>(p.ws + p.lay.pend_cnt) : nullptr;
     double *pend_part = reinterpret_cast<double *>(p.ws + p.lay.pend_part);
+    PendRow *pend = reinterpret_cast<PendRow *>(p.ws + p.lay.pend);
     // rows shared among workgroups (small batches); the sums' kernel then finishes the statistics, so L >= 2
     const int stat_parts = (p.pend_levels > 0 || p.s_parts < 2) ? 1 : row_parts(2 * pairs, p.V);
     Row0Part *stat_part = reinterpret_cast<Row0Part *>(p.ws + p.lay.stat_part);
@@ -556,17 +778,16 @@ hipError_t launch_typed(const Problem &p)
         const dim3 g1(static_cast<unsigned>(pairs + p.pend_levels), 2);
         if (vec)
             hipLaunchKernelGGL((k_row_stats<T, true>), g1, dim3(kStatThreads), 0, p.stream, target, draft,
-                               p.tokens, p.K, p.L, p.V, p.c, stats, counter, pairs, p.batch, p.pend_count, pend_off, pend_cnt, p.c_rel);
+                               p.tokens, p.K, p.L, p.V, p.c, stats, counter, pairs, p.batch, p.pend_count, pend_off, pend, p.pend_levels, p.c_rel);
         else
             hipLaunchKernelGGL((k_row_stats<T, false>), g1, dim3(kStatThreads), 0, p.stream, target, draft,
-                               p.tokens, p.K, p.L, p.V, p.c, stats, counter, pairs, p.batch, p.pend_count, pend_off, pend_cnt, p.c_rel);
+                               p.tokens, p.K, p.L, p.V, p.c, stats, counter, pairs, p.batch, p.pend_count, pend_off, pend, p.pend_levels, p.c_rel);
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    PendRow *pend = reinterpret_cast<PendRow *>(p.ws + p.lay.pend);
-    for (int level = 0; level < p.pend_levels; ++level) {
+    if (p.pend_levels > 0) {
         // One workgroup per row pair, but at least two per compute unit, so that a small batch's rows can be shared (one, two, four per
-        // unit, us a call: three iterations of Algorithm 3 with 8 x 4 drafts of 8, V = 128256 352, 339, 356, of which a pass whose
+        // unit, us a call: three iterations of Algorithm 3 with 8 x 4 drafts of 8, V = 128256 352, 339, 356, of which a launch whose
         // level is empty took 2.4 at four; 16 x 4 of 8, V = 32000 84.9, 85.0, 89.8; one prompt of 3 drafts 63.8, 64.1, 64.1).
         // With two per unit a level of more than half as many rows has a workgroup for each row alone, on half the places of the chip;
         // where that takes long (long rows, and the levels below them to be applied to every entry) the grid is large enough for
@@ -577,23 +798,41 @@ hipError_t launch_typed(const Problem &p)
         // of 8, V = 8000 float32 under two levels 61.7 / 62.0 / 67.2), and in float32, whose sweeps are shorter, only where two per
         // unit are not enough for two workgroups a row (10 x 8 of 4, V = 70000 127 / 130 / 135, 9 x 8 of 8, V = 64000 234 / 223 / 230).
         const long long cu = compute_units();
-        long long grid = pairs > 2 * cu ? pairs : 2 * cu;
-        if (level > 0 && !p.state_count && row_vectors<T>(p.V) >= 6000 && 2 * pairs > (Elem<T>::kPerVec == 8 ? cu : 3 * cu) && 2 * pairs < 7 * cu)
+        LevelArgs la;
+        la.carry = p.pend_carry; la.count = p.pend_count; la.off = pend_off;
+        la.stats = stats; la.pend = pend; la.sums = reinterpret_cast<double *>(stat_part);
+        la.n_rows = pairs; la.K = p.K; la.L = p.L; la.V = p.V; la.batch = p.batch; la.polls = wait_polls(); la.c = p.c;
+        const long long least = pairs > 2 * cu ? pairs : 2 * cu;
+        long long grid = least;
+        if (!p.state_count && row_vectors<T>(p.V) >= 6000 && 2 * pairs > (Elem<T>::kPerVec == 8 ? cu : 3 * cu) && 2 * pairs < 7 * cu)
             grid = 2 * pairs <= 3 * cu ? 3 * cu : 7 * cu / 2;
         // (three per unit are resident at once; not with every grid that a row pair each asks for)
-        const int resident = grid > pairs ? static_cast<int>(3 * cu) : 0x7fffffff;
-        const dim3 gp(static_cast<unsigned>(grid));
-        const double *carry_l = p.pend_carry + static_cast<size_t>(level) * p.batch;
-        const int32_t *count_l = p.pend_count + static_cast<size_t>(level) * p.batch;
-        const int32_t *off_l = pend_off + static_cast<size_t>(level) * (p.batch + 1);
-        if (vec)
-            hipLaunchKernelGGL((k_pend_norm<T, true>), gp, dim3(kStatThreads), 0, p.stream, target, draft, p.K, p.L,
-                               p.V, p.c, carry_l, count_l, stats, pend, pairs, level, off_l, p.batch, pend_part, pend_cnt, resident);
-        else
-            hipLaunchKernelGGL((k_pend_norm<T, false>), gp, dim3(kStatThreads), 0, p.stream, target, draft, p.K, p.L,
-                               p.V, p.c, carry_l, count_l, stats, pend, pairs, level, off_l, p.batch, pend_part, pend_cnt, resident);
-        e = hipGetLastError();
-        if (e != hipSuccess) return e;
+        const auto resident = [&](long long g) { return g > pairs ? static_cast<int>(3 * cu) : 0x7fffffff; };
+        la.first_grid = static_cast<int>(least); la.grid = static_cast<int>(grid);
+        la.first_resident = resident(least); la.resident = resident(grid);
+        // Levels per launch.  Up to six rows per compute unit: all of the library's own (L - 1, most of them empty), and all that are given
+        // unless rows are long (us a call, each level its own launch / together: two levels on 16 x 4 drafts of 8, V = 8000 bfloat16
+        // 50.5 / 49.6, 32 x 4 of 8, V = 32000 118.1 / 117.0; but 32 x 3 of 8, V = 128256 265 / 273, 16 x 4 of 6, V = 70000 float32
+        // 153.5 / 156.2: workgroups that wait hold places that a level's later parts could use).  With more rows each level's fill the
+        // chip, and what is given is launched level by level (64 x 4 of 8, V = 8000 two levels 100.3 / 102.4, 128 x 16 542 / 596); of the
+        // library's own the first, the only one that most prefixes have, alone and the others together, in a grid of one workgroup per
+        // row, which takes several units a workgroup where that many are alive (three iterations with 128 x 8 of 8, V = 8000: all together
+        // 916, level by level 875, the others with a workgroup for every unit there may be 857, as here 789).
+        const bool small = pairs <= 6 * cu;
+        for (la.from = 0; la.from < p.pend_levels; la.from = la.to) {
+            if (p.state_count) la.to = small || la.from == 1 ? p.pend_levels : la.from + 1;
+            else la.to = small && row_vectors<T>(p.V) < 6000 ? p.pend_levels : la.from + 1;
+            la.most = kSumSlots / (la.to - la.from) < kPendParts ? kSumSlots / (la.to - la.from) : kPendParts;
+            const bool chunks = la.from > 0 && la.to - la.from > 1;
+            const dim3 gp(static_cast<unsigned>(chunks ? grid : (la.from == 0 ? least : grid) + (la.to - la.from - 1) * grid));
+#define SPECGBV_PEND_LAUNCH(VEC, FORM) hipLaunchKernelGGL((k_pend_norm<T, VEC, FORM>), gp, dim3(kStatThreads), 0, p.stream, target, draft, la)
+            if (la.to == 1) { if (vec) SPECGBV_PEND_LAUNCH(true, kOneLevel); else SPECGBV_PEND_LAUNCH(false, kOneLevel); }
+            else if (chunks) { if (vec) SPECGBV_PEND_LAUNCH(true, kChunks); else SPECGBV_PEND_LAUNCH(false, kChunks); }
+            else { if (vec) SPECGBV_PEND_LAUNCH(true, kUnits); else SPECGBV_PEND_LAUNCH(false, kUnits); }
+            e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+#undef SPECGBV_PEND_LAUNCH
     }
     if (p.L < 2) return hipSuccess;
     const long long rows = static_cast<long long>(p.batch) * p.K * (p.L - 1);
