@@ -541,6 +541,35 @@ __device__ __forceinline__ void mask_repeated(float (&z)[N], int v, int V)
     }
 }
 
+// Loads that do not start at a multiple of four bytes run at two thirds of the rate (rows of one workgroup each, 220 MB: V = 32002
+// 6.75 TB/s, 32003 5.1, half of whose rows start at an odd entry).  A row that does is read from the entry in front of it on, as a
+// row of V + 1 entries whose first has no weight: odd_start is what `row` and V are moved by (1 or 0; V is odd then, and V + 1
+// entries make no more vectors).  Not the first row of a tensor (`first`), in front of which nothing belongs to it.  Us a call
+// before / after, two-pass schedule: 41 x 7 drafts of 6, V = 32003 108.8 / 96.9, 40 x 8 of 8, V = 32001 149.4 / 129.0, 20 x 8 of 6,
+// V = 50257 102.9 / 89.
+template <typename T>
+__device__ __forceinline__ int odd_start(const T *row, bool first)
+{
+    return sizeof(T) == 2 && !first ? static_cast<int>(reinterpret_cast<uintptr_t>(row) >> 1 & 1u) : 0;
+}
+// Of a row pair only if both rows do: entries have to lie side by side.
+template <typename T>
+__device__ __forceinline__ int odd_start(const T *rq, const T *rp, bool first) { return odd_start(rq, first) & odd_start(rp, first); }
+// mask_repeated for a row so moved: the entry in front of it (the first of vector 0) has no weight either.
+template <typename T, int N>
+__device__ __forceinline__ void mask_ends(float (&z)[N], int v, int V, int shift)
+{
+    if (((V & (N - 1)) | shift) != 0) {                  // uniform
+        asm volatile("");
+        const int over = (v + 1) * N - V;
+        if (over > 0) {
+#pragma unroll
+            for (int j = 0; j < N; ++j) z[j] = j < over ? -__builtin_inff() : z[j];
+        }
+        if (shift != 0) z[0] = v == 0 ? -__builtin_inff() : z[0];
+    }
+}
+
 // f(first entry index, z_q[N], z_p[N]) for the entries of a (target, draft) row pair in the unit range [lo, hi),
 // N = 8 or 4 entries of one 16-byte vector (VEC, V >= N; a unit is a vector) or 1 (a unit is an entry); the workgroup's
 // THREADS threads stride over the range, each keeping the loads of two vectors of either row in flight.  (16-byte loads at any
@@ -609,8 +638,9 @@ __device__ __forceinline__ FirstPairs first_pairs(const T *rq, const T *rp, int 
     }
     return f;
 }
+// shift: the rows and V are moved (odd_start).
 template <typename T, bool VEC, bool AHEAD, int THREADS, typename F>
-__device__ __forceinline__ void for_each_pair_from(const FirstPairs &first, const T *rq, const T *rp, int V, int lo, int hi, F f)
+__device__ __forceinline__ void for_each_pair_from(const FirstPairs &first, const T *rq, const T *rp, int V, int lo, int hi, int shift, F f)
 {
     if constexpr (VEC) {
         constexpr int PV = Elem<T>::kPerVec;
@@ -618,8 +648,8 @@ __device__ __forceinline__ void for_each_pair_from(const FirstPairs &first, cons
             float zq[PV], zp[PV];
             Elem<T>::unpack(q, zq);
             Elem<T>::unpack(p, zp);
-            mask_repeated<T>(zq, v, V);
-            mask_repeated<T>(zp, v, V);
+            mask_ends<T>(zq, v, V, shift);
+            mask_ends<T>(zp, v, V, shift);
             f(e, zq, zp);
         };
         auto second = [&](int v) { return vector_entry<T>(v + THREADS < hi ? v + THREADS : hi - 1, V); };

@@ -60,12 +60,12 @@ constexpr int kAhead = 4;            // loads a thread of k_row_stats keeps in f
 
 // Vector v of a row into its running sum, without the drafted token and without entries the vector before holds.
 template <typename T>
-__device__ __forceinline__ void add_vector(RunningSum &acc, const U4 &raw, int v, int tok, int V, float c)
+__device__ __forceinline__ void add_vector(RunningSum &acc, const U4 &raw, int v, int tok, int V, int shift, float c)
 {
     constexpr int PV = Elem<T>::kPerVec;
     float z[PV];
     Elem<T>::unpack(raw, z);
-    mask_repeated<T>(z, v, V);
+    mask_ends<T>(z, v, V, shift);
     leave_out(z, v == tok / PV, tok - vector_entry<T>(v, V));
     acc.add(z, c);
 }
@@ -73,7 +73,9 @@ __device__ __forceinline__ void add_vector(RunningSum &acc, const U4 &raw, int v
 // grid (row pairs + pending levels, 2): blocks (pair, 0 / 1) reduce the target / draft row of the pair; with
 // pending modifications blocks (pairs + l, 0) compute level l's offsets (pend_offsets) and the row blocks write the levels'
 // entries of their row: empty, or not there yet.
-template <typename T, bool VEC>
+// ODD: V is odd and the type bfloat16, so that rows may start at odd entries (odd_start; an instance of their own, which spares the
+// others 0.2 - 0.5 % of a call).
+template <typename T, bool VEC, bool ODD>
 __global__ void __launch_bounds__(kStatThreads)
 k_row_stats(const T *__restrict__ target, const T *__restrict__ draft,
             const int32_t *__restrict__ tokens, int K, int L, int V, float c,
@@ -110,19 +112,19 @@ k_row_stats(const T *__restrict__ target, const T *__restrict__ draft,
     const int tok_raw = token_index_queued(tokens, pair);
     RunningSum acc;                               // the drafted token is left out (leave_out)
     if (VEC) {
-        const int nvec = row_vectors<T>(V);
+        const int shift = ODD ? odd_start(row, pair == 0) : 0, Vs = V + shift, nvec = row_vectors<T>(Vs);
         for (int i = threadIdx.x; i < nvec; i += kAhead * kStatThreads) {
             U4 v[kAhead];
 #pragma unroll
             for (int a = 0; a < kAhead; ++a) {            // (no branch around a load: past the end the last vector again)
                 const int at = i + a * kStatThreads;
-                v[a] = load16_stream_any(row + vector_entry<T>(at < nvec ? at : nvec - 1, V));
+                v[a] = load16_stream_any(row - shift + vector_entry<T>(at < nvec ? at : nvec - 1, Vs));
             }
-            const int tok = token_index_used(tok_raw, V);
+            const int tok = token_index_used(tok_raw, V) + shift;
 #pragma unroll
             for (int a = 0; a < kAhead; ++a) {
                 const int at = i + a * kStatThreads;
-                if (at < nvec) add_vector<T>(acc, v[a], at, tok, V, c);
+                if (at < nvec) add_vector<T>(acc, v[a], at, tok, Vs, shift, c);
             }
         }
     } else {
@@ -170,7 +172,8 @@ k_row_stats_parts(const T *__restrict__ target, const T *__restrict__ draft, con
     const T *row = is_draft ? draft + (bk * L + r) * static_cast<long long>(V)
                             : target + (bk * (L + 1) + r) * static_cast<long long>(V);
     constexpr int PV = Elem<T>::kPerVec;
-    const int units = VEC ? row_vectors<T>(V) : V;
+    const int shift = VEC ? odd_start(row, pair == 0) : 0, Vs = V + shift;
+    const int units = VEC ? row_vectors<T>(Vs) : V;
     const int per = (units + P - 1) / P;
     const int lo = part * per, hi = lo + per < units ? lo + per : units;
     const int tok_raw = token_index_queued(tokens, pair);
@@ -178,15 +181,15 @@ k_row_stats_parts(const T *__restrict__ target, const T *__restrict__ draft, con
     if (VEC) {
         int i = lo + static_cast<int>(threadIdx.x);
         for (; i + kStatThreads < hi; i += 2 * kStatThreads) {            // two loads in flight per thread
-            const U4 a = load16_stream_any(row + vector_entry<T>(i, V));
-            const U4 b2 = load16_stream_any(row + vector_entry<T>(i + kStatThreads, V));
-            const int tk = token_index_used(tok_raw, V);
-            add_vector<T>(acc, a, i, tk, V, c);
-            add_vector<T>(acc, b2, i + kStatThreads, tk, V, c);
+            const U4 a = load16_stream_any(row - shift + vector_entry<T>(i, Vs));
+            const U4 b2 = load16_stream_any(row - shift + vector_entry<T>(i + kStatThreads, Vs));
+            const int tk = token_index_used(tok_raw, V) + shift;
+            add_vector<T>(acc, a, i, tk, Vs, shift, c);
+            add_vector<T>(acc, b2, i + kStatThreads, tk, Vs, shift, c);
         }
         if (i < hi) {
-            const U4 a = load16_stream_any(row + vector_entry<T>(i, V));
-            add_vector<T>(acc, a, i, token_index_used(tok_raw, V), V, c);
+            const U4 a = load16_stream_any(row - shift + vector_entry<T>(i, Vs));
+            add_vector<T>(acc, a, i, token_index_used(tok_raw, V) + shift, Vs, shift, c);
         }
     } else {
         for (int x = lo + static_cast<int>(threadIdx.x); x < hi; x += kStatThreads) {
@@ -196,7 +199,7 @@ k_row_stats_parts(const T *__restrict__ target, const T *__restrict__ draft, con
         }
     }
     const int tok = token_index_used(tok_raw, V);
-    const int tok_unit = VEC ? tok / PV : tok;
+    const int tok_unit = VEC ? (tok + shift) / PV : tok;
     const float M = block_max(acc.m2, sh_f);
     const double mine = static_cast<double>(acc.Z) * exp2(static_cast<double>(acc.m2) - static_cast<double>(M));
     const double total = block_sum(acc.Z > 0.0f ? mine : 0.0, sh_d);
@@ -251,11 +254,12 @@ k_ot_sum_parts(const T *__restrict__ target, const T *__restrict__ draft, const 
     const long long pair = bk * L + i;
     const T *rq = target + (bk * (L + 1) + i) * static_cast<long long>(V);
     const T *rp = draft + pair * static_cast<long long>(V);
-    const int units = VEC ? row_vectors<T>(V) : V;
+    const int shift = VEC ? odd_start(rq, rp, false) : 0, Vs = V + shift;              // (i >= 1: not a tensor's first row)
+    const int units = VEC ? row_vectors<T>(Vs) : V;
     const int per = (units + P - 1) / P;
     const int lo = part * per, hi = lo + per < units ? lo + per : units;
     constexpr bool kAhead = VEC && (PEND || Elem<T>::kPerVec == 4);      // (see first_pairs)
-    const FirstPairs first = first_pairs<T, kAhead, kStatThreads>(rq, rp, V, lo, hi);
+    const FirstPairs first = first_pairs<T, kAhead, kStatThreads>(rq - shift, rp - shift, Vs, lo, hi);
     RowStat st;
     double log2nu = 0.0;
     if (stat_P > 1) {
@@ -303,14 +307,14 @@ k_ot_sum_parts(const T *__restrict__ target, const T *__restrict__ draft, const 
     const RatioConst rc(ratio_const(st.lse2_p, st.lse2_q, log2nu, c_rel) - sumN);
     float acc = 0.0f;
     if (PEND && sh_tab.n > 0) {                   // uniform over the workgroup
-        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, rq - shift, rp - shift, Vs, lo, hi, shift, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             pending_weights(zq, zp, c, shift_q, sh_tab, rc, K, wq, w);
 #pragma unroll
             for (int j = 0; j < N; ++j) acc += w[j];
         });
     } else {
-        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, rq - shift, rp - shift, Vs, lo, hi, shift, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
 #pragma unroll
@@ -319,7 +323,7 @@ k_ot_sum_parts(const T *__restrict__ target, const T *__restrict__ draft, const 
     }
     double total = block_sum(static_cast<double>(acc), sh_d);
     if (threadIdx.x == 0 && !(PEND && sh_tab.n > 0))
-        total = with_token_term<T>(total, st, log2nu, rq, rp, tokens + pair, V, lo * N, hi * N < V ? hi * N : V, c, shift_q, rc, K);
+        total = with_token_term<T>(total, st, log2nu, rq, rp, tokens + pair, V, lo * N - shift, hi * N < Vs ? hi * N - shift : V, c, shift_q, rc, K);
     // (whether the row's s and g nearly cancel, so that Eq. (hik) needs nu^2 (s - g) summed term by term, only the sum
     // over all parts can tell: the final-token kernel looks at it)
     if (threadIdx.x == 0) s_part[pair * kPendParts + part] = total * exp2(static_cast<double>(shift_q) - st.lse2_q - sumN);
@@ -604,13 +608,13 @@ k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, LevelArgs
                 constexpr int N = VEC ? Elem<T>::kPerVec : 1;
                 float acc = 0.0f;
                 if (ONE || sh.tab.n == 0) {
-                    for_each_pair_from<T, VEC, false, kStatThreads>(FirstPairs(), rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+                    for_each_pair_from<T, VEC, false, kStatThreads>(FirstPairs(), rq, rp, V, lo, hi, 0, [&](int, const float (&zq)[N], const float (&zp)[N]) {
                         float wq[N], w[N];
                         ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
                         acc += vector_sum(w);
                     });
                 } else {
-                    for_each_pair_from<T, VEC, false, kStatThreads>(FirstPairs(), rq, rp, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+                    for_each_pair_from<T, VEC, false, kStatThreads>(FirstPairs(), rq, rp, V, lo, hi, 0, [&](int, const float (&zq)[N], const float (&zp)[N]) {
                         float wq[N], w[N];
                         pending_weights(zq, zp, c, shift_q, sh.tab, rc, K, wq, w);
                         acc += vector_sum(w);
@@ -675,7 +679,7 @@ k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, LevelArgs
     }
 }
 
-template <typename T, bool VEC, bool PEND>
+template <typename T, bool VEC, bool PEND, bool ODD>
 __global__ void __launch_bounds__(kStatThreads)
 k_ot_sum(const T *__restrict__ target, const T *__restrict__ draft, const int32_t *__restrict__ tokens, int K, int L, int V,
          float c, const RowStat *__restrict__ stats, const PendRow *__restrict__ pend, long long n_rows, int nlev,
@@ -690,9 +694,10 @@ k_ot_sum(const T *__restrict__ target, const T *__restrict__ draft, const int32_
     const long long bk = idx / (L - 1);
     const T *rq = target + (bk * (L + 1) + i) * static_cast<long long>(V);
     const T *rp = draft + (bk * L + i) * static_cast<long long>(V);
-    const int units = VEC ? row_vectors<T>(V) : V;
+    const int shift = ODD ? odd_start(rq, rp, false) : 0, Vs = V + shift;              // (i >= 1: not a tensor's first row)
+    const int units = VEC ? row_vectors<T>(Vs) : V;
     constexpr bool kAhead = VEC && !PEND;         // (see first_pairs)
-    const FirstPairs first = first_pairs<T, kAhead, kStatThreads>(rq, rp, V, 0, units);
+    const FirstPairs first = first_pairs<T, kAhead, kStatThreads>(rq - shift, rp - shift, Vs, 0, units);
     const RowStat st = stats[bk * L + i];
     // block likelihood ratio of the length-i block, from the rows before row i (their token
     // probabilities under the modified rows where levels are pending)
@@ -715,14 +720,14 @@ k_ot_sum(const T *__restrict__ target, const T *__restrict__ draft, const int32_
     const RatioConst rc(ratio_const(st.lse2_p, st.lse2_q, log2nu, c_rel) - sumN);
     float acc = 0.0f;
     if (PEND && sh_tab.n > 0) {                   // uniform over the workgroup
-        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, rq, rp, V, 0, units, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, rq - shift, rp - shift, Vs, 0, units, shift, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             pending_weights(zq, zp, c, shift_q, sh_tab, rc, K, wq, w);
 #pragma unroll
             for (int j = 0; j < N; ++j) acc += w[j];
         });
     } else {
-        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, rq, rp, V, 0, units, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, rq - shift, rp - shift, Vs, 0, units, shift, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
 #pragma unroll
@@ -760,6 +765,8 @@ hipError_t launch_typed(const Problem &p)
     int32_t *counter = reinterpret_cast<int32_t *>(p.ws + p.lay.counter);
     const long long pairs = static_cast<long long>(p.batch) * p.K * p.L;
     const bool vec = read_by_vectors<T>(p.V);
+    constexpr bool kMayBeOdd = sizeof(T) == 2;
+    const bool odd = kMayBeOdd && vec && p.V % 2 != 0;
     int32_t *pend_off = reinterpret_cast<int32_t *>(p.ws + p.lay.pend_off);
     double *pend_part = reinterpret_cast<double *>(p.ws + p.lay.pend_part);
     PendRow *pend = reinterpret_cast<PendRow *>(p.ws + p.lay.pend);
@@ -776,12 +783,13 @@ hipError_t launch_typed(const Problem &p)
                                p.L, p.V, p.c, stat_parts, stat_part);
     } else {
         const dim3 g1(static_cast<unsigned>(pairs + p.pend_levels), 2);
-        if (vec)
-            hipLaunchKernelGGL((k_row_stats<T, true>), g1, dim3(kStatThreads), 0, p.stream, target, draft,
-                               p.tokens, p.K, p.L, p.V, p.c, stats, counter, pairs, p.batch, p.pend_count, pend_off, pend, p.pend_levels, p.c_rel);
-        else
-            hipLaunchKernelGGL((k_row_stats<T, false>), g1, dim3(kStatThreads), 0, p.stream, target, draft,
-                               p.tokens, p.K, p.L, p.V, p.c, stats, counter, pairs, p.batch, p.pend_count, pend_off, pend, p.pend_levels, p.c_rel);
+#define SPECGBV_STATS_LAUNCH(VEC, ODD)                                                                              \
+    hipLaunchKernelGGL((k_row_stats<T, VEC, ODD>), g1, dim3(kStatThreads), 0, p.stream, target, draft, p.tokens, p.K, p.L, p.V, \
+                       p.c, stats, counter, pairs, p.batch, p.pend_count, pend_off, pend, p.pend_levels, p.c_rel)
+        if (odd) SPECGBV_STATS_LAUNCH(true, kMayBeOdd);
+        else if (vec) SPECGBV_STATS_LAUNCH(true, false);
+        else SPECGBV_STATS_LAUNCH(false, false);
+#undef SPECGBV_STATS_LAUNCH
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
@@ -850,12 +858,19 @@ hipError_t launch_typed(const Problem &p)
         return hipGetLastError();
     }
     const dim3 g2(static_cast<unsigned>(rows));
-#define SPECGBV_OT_LAUNCH(VEC, PEND)                                                                           \
-    hipLaunchKernelGGL((k_ot_sum<T, VEC, PEND>), g2, dim3(kStatThreads), 0, p.stream, target, draft, p.tokens, p.K, p.L, \
+#define SPECGBV_OT_LAUNCH(VEC, PEND, ODD)                                                                       \
+    hipLaunchKernelGGL((k_ot_sum<T, VEC, PEND, ODD>), g2, dim3(kStatThreads), 0, p.stream, target, draft, p.tokens, p.K, p.L, \
                        p.V, p.c, stats, pend, pairs, p.pend_levels, s, reinterpret_cast<double *>(p.ws + p.lay.excess),        \
                        reinterpret_cast<double *>(p.ws + p.lay.excess_part), p.c_rel)
-    if (p.pend_levels > 0) { if (vec) SPECGBV_OT_LAUNCH(true, true); else SPECGBV_OT_LAUNCH(false, true); }
-    else { if (vec) SPECGBV_OT_LAUNCH(true, false); else SPECGBV_OT_LAUNCH(false, false); }
+    if (p.pend_levels > 0) {
+        if (odd) SPECGBV_OT_LAUNCH(true, true, kMayBeOdd);
+        else if (vec) SPECGBV_OT_LAUNCH(true, true, false);
+        else SPECGBV_OT_LAUNCH(false, true, false);
+    } else {
+        if (odd) SPECGBV_OT_LAUNCH(true, false, kMayBeOdd);
+        else if (vec) SPECGBV_OT_LAUNCH(true, false, false);
+        else SPECGBV_OT_LAUNCH(false, false, false);
+    }
 #undef SPECGBV_OT_LAUNCH
     return hipGetLastError();
 }
