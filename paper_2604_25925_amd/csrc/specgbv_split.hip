@@ -84,7 +84,7 @@ k_row_stats(const T *__restrict__ target, const T *__restrict__ draft,
             PendRow *__restrict__ pend, int nlev, double c_rel)
 {
     __shared__ double sh_d[kStatThreads / kWave];
-    __shared__ float sh_f[kStatThreads / kWave];
+    __shared__ float sh_ref[kStatThreads / kWave];
     const long long pair = blockIdx.x;            // (b*K + k)*L + r
     const bool is_draft = blockIdx.y == 1;
     if (pair >= n_rows) {                         // uniform: one of the offset blocks
@@ -110,6 +110,7 @@ k_row_stats(const T *__restrict__ target, const T *__restrict__ draft,
     const T *row = is_draft ? draft + (bk * L + r) * static_cast<long long>(V)
                             : target + (bk * (L + 1) + r) * static_cast<long long>(V);
     const int tok_raw = token_index_queued(tokens, pair);
+    uint32_t tok_bits = 0;                        // the token's logit, asked for behind the row's first loads
     RunningSum acc;                               // the drafted token is left out (leave_out)
     if (VEC) {
         const int shift = ODD ? odd_start(row, pair == 0) : 0, Vs = V + shift, nvec = row_vectors<T>(Vs);
@@ -121,6 +122,7 @@ k_row_stats(const T *__restrict__ target, const T *__restrict__ draft,
                 v[a] = load16_stream_any(row - shift + vector_entry<T>(at < nvec ? at : nvec - 1, Vs));
             }
             const int tok = token_index_used(tok_raw, V) + shift;
+            if (i == static_cast<int>(threadIdx.x)) tok_bits = Elem<T>::bits(row + (tok - shift));
 #pragma unroll
             for (int a = 0; a < kAhead; ++a) {
                 const int at = i + a * kStatThreads;
@@ -134,14 +136,29 @@ k_row_stats(const T *__restrict__ target, const T *__restrict__ draft,
             acc.add(z, c);
         }
     }
-    const int tok = token_index_used(tok_raw, V);
-    const float M = block_max(acc.m2, sh_f);
-    const double part = static_cast<double>(acc.Z) * exp2(static_cast<double>(acc.m2) - static_cast<double>(M));
-    const double total = block_sum(acc.Z > 0.0f ? part : 0.0, sh_d);
-    if (threadIdx.x == 0) {
-        const double tok2_raw = static_cast<double>(Elem<T>::scalar(row + tok)) * static_cast<double>(c);
+    // The waves' sums relative to integral references meet behind one barrier, and the first thread adds them up: a workgroup holds its
+    // place on the compute unit through all of this, with nothing of its row to load any more.  Us a call, with a maximum and a sum
+    // over the workgroup (four barriers), library exponentials and the token's logit fetched here / as here: one level on 100 x 8
+    // drafts of 8, V = 3000 float32 165.3 / 149.8, two on 128 x 4 of 8, V = 8000 bfloat16 159.3 / 150.6, three iterations of 128 x 8 of
+    // 8, V = 8000 782 / 730, 8 x 4 of 8, V = 128256 294.4 / 291.5; 32 x 8 of 8, V = 24000 without levels 88.5 / 86.0, 41 x 7 of 6,
+    // V = 32003 96.5 / 95.9; 40 x 8 of 8, V = 32000 the same.
+    constexpr int kWaves = kStatThreads / kWave;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
+    const float wave_ref = integral_reference(wave_max(acc.m2), 1.0f);
+    const double wave_Z = wave_sum(acc.Z > 0.0f ? static_cast<double>(acc.Z) * exp2_small(static_cast<double>(acc.m2) - static_cast<double>(wave_ref)) : 0.0);
+    if (lane == 0) { sh_ref[wid] = wave_ref; sh_d[wid] = wave_Z; }
+    __syncthreads();
+    if (tid == 0) {
+        float M = -3.0e38f;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) M = fmaxf(M, sh_d[w] > 0.0 ? sh_ref[w] : -3.0e38f);
+        double total = 0.0;
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) total += ldexp(sh_d[w], reference_shift(sh_ref[w], M));
+        const float ztok = VEC ? Elem<T>::from_bits(tok_bits) : Elem<T>::scalar(row + token_index_used(tok_raw, V));
+        const double tok2_raw = static_cast<double>(ztok) * static_cast<double>(c);
         const RefSum all = with_token(static_cast<double>(M), total, tok2_raw);
-        const double lse2 = all.ref + log2(all.Z);
+        const double lse2 = all.Z > 0.0 ? all.ref + log2_series(all.Z) : all.ref + log2(all.Z);
         const double tok2 = token_scaled(tok2_raw, lse2, c_rel);
         if (is_draft) { stats[pair].lse2_p = lse2; stats[pair].tok2_p = tok2; }
         else { stats[pair].lse2_q = lse2; stats[pair].tok2_q = tok2; }
