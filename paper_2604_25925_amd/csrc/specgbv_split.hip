@@ -139,9 +139,10 @@ k_row_stats(const T *__restrict__ target, const T *__restrict__ draft,
     // The waves' sums relative to integral references meet behind one barrier, and the first thread adds them up: a workgroup holds its
     // place on the compute unit through all of this, with nothing of its row to load any more.  Us a call, with a maximum and a sum
     // over the workgroup (four barriers), library exponentials and the token's logit fetched here / as here: one level on 100 x 8
-    // drafts of 8, V = 3000 float32 165.3 / 149.8, two on 128 x 4 of 8, V = 8000 bfloat16 159.3 / 150.6, three iterations of 128 x 8 of
-    // 8, V = 8000 782 / 730, 8 x 4 of 8, V = 128256 294.4 / 291.5; 32 x 8 of 8, V = 24000 without levels 88.5 / 86.0, 41 x 7 of 6,
-    // V = 32003 96.5 / 95.9; 40 x 8 of 8, V = 32000 the same.
+    // drafts of 8, V = 3000 float32 165.3 / 150.8, two on 128 x 4 of 8, V = 8000 bfloat16 159.3 / 151.3, three iterations of 128 x 8 of
+    // 8, V = 8000 782 / 734, 8 x 4 of 8, V = 128256 294.4 / 292.1; 32 x 8 of 8, V = 24000 without levels 88.5 / 86.1, 41 x 7 of 6,
+    // V = 32003 96.5 / 95.9; 40 x 8 of 8, V = 32000 the same.  The logarithm stays the library's and
+    // gives the bits it gave (log2_series, no less exact, takes another 0.2 - 0.6 % off calls with levels, and other bits).
     constexpr int kWaves = kStatThreads / kWave;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
     const float wave_ref = integral_reference(wave_max(acc.m2), 1.0f);
@@ -158,7 +159,7 @@ k_row_stats(const T *__restrict__ target, const T *__restrict__ draft,
         const float ztok = VEC ? Elem<T>::from_bits(tok_bits) : Elem<T>::scalar(row + token_index_used(tok_raw, V));
         const double tok2_raw = static_cast<double>(ztok) * static_cast<double>(c);
         const RefSum all = with_token(static_cast<double>(M), total, tok2_raw);
-        const double lse2 = all.Z > 0.0 ? all.ref + log2_series(all.Z) : all.ref + log2(all.Z);
+        const double lse2 = all.ref + log2(all.Z);
         const double tok2 = token_scaled(tok2_raw, lse2, c_rel);
         if (is_draft) { stats[pair].lse2_p = lse2; stats[pair].tok2_p = tok2; }
         else { stats[pair].lse2_q = lse2; stats[pair].tok2_q = tok2; }
