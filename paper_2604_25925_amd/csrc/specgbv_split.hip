@@ -368,14 +368,14 @@ __device__ __forceinline__ float vector_sum(const float (&w)[N])
 // The levels [from, to) of pending modification (those before them are done).  A level's T rows are enumerated prefix by prefix (off[b]
 // rows before prefix b; within a prefix row index slowest) and each is shared among P workgroups (level_parts), so that a level with
 // few rows left still occupies the chip (one workgroup streaming a whole row pair with several levels of arithmetic per entry takes
-// 100 - 200 us).  The levels' T P units stand in one line, level after level; a workgroup does the unit of its own number (kChunks: as
-// many units in a row as the grid has to take), and those behind the last unit leave at once.  A row's parts meet in the workspace
-// (device-scope relaxed atomic accesses): the workgroup that arrives last at the entry's counter leaves the entry.  Sums and
-// counters are a level's own, so that it does not matter in which order units of different levels come to them.
+// 100 - 200 us).  The levels' T P units stand in one line, level after level; a workgroup does the unit of its own number,
+// and those behind the last unit leave at once.  A row's parts meet in the workspace (device-scope relaxed atomic accesses): the
+// workgroup that arrives last at the entry's counter leaves the entry.  Sums and counters are a level's own, so that it does
+// not matter in which order units of different levels come to them.
 //
 // A unit needs the entries of the levels below its own for its row and for the rows of its draft in front of it.  k_row_stats has marked
 // the entries of modified rows as not there yet (all four words), so a unit looks for them until they are there.  They come from units of
-// lower numbers, that is of workgroups of lower index (or from its own earlier ones), and workgroups are dispatched in index order, so
+// lower numbers, that is of workgroups of lower index, and workgroups are dispatched in index order, so
 // what is waited for is running or has run.  Nothing relies on it: after `polls` looks a workgroup makes the entries itself, with
 // the parts and in the order that their units have (the same bits).
 //
@@ -383,10 +383,10 @@ __device__ __forceinline__ float vector_sum(const float (&w)[N])
 // kernel for every level, 3 us each, of which a call that updates its state in place makes L - 1, most of them of levels in which nothing is
 // alive, and each of those had a workgroup per row to find that out.  Us a call, a launch per level / as here: three iterations of
 // Algorithm 3, 8 x 4 drafts of 8, V = 128256 bfloat16 344 / 313; one prompt of 3 drafts 195 / 158; 3 x 3 of 8, V = 50257 float32 203 / 167;
-// 64 x 4 of 12, V = 9000 482 / 391; 128 x 8 of 8, V = 8000 890 / 789; 32 x 8 of 8, V = 128256 1433 / 1410; three given levels on 16 x 4 of 8,
-// V = 32000 110.7 / 101.8; two on 64 x 16 of 8, V = 8000 309 / 289; one on 40 x 8 of 8, V = 32000 178 / 171.
+// one iteration once two to six levels are alive on average, 24 x 8 of 8, V = 128256 584 / 531, the same drafts over and over 760 / 673;
+// 8 x 4 of 16, V = 32000 372 / 330; 10 x 8 of 12, V = 3000 float32 209 / 157; three given levels on 16 x 4 of 8, V = 32000 110.7 / 101.8.
 // The float64 constants are made by one wave, a level per lane, with the exponential's coefficients in LDS: as library calls of every
-// thread they took 142 registers in this loop, or 224 bytes of scratch at 80 (three workgroups per compute unit), which cost more than
+// thread they took 142 registers, or 224 bytes of scratch at 80 (three workgroups per compute unit), which cost more than
 // the launches.
 constexpr unsigned long long kNotThere = ~0ull;        // (a NaN that no sum produces)
 constexpr unsigned long long kNoLevel = 0x8000000000000000ull;     // log2 N = -0.0: the level leaves the row as it is
@@ -442,7 +442,6 @@ struct Levels {
     double sums[kPendParts];
     float shift_q, C2_hi, neg_kappa;
     int cnt[kMaxPend];                     // rows the levels modify
-    int begin[kMaxPend + 1], parts[kMaxPend];                // each level's first unit, and the parts of its rows
     double exp2_coef[11];                  // (see exp2_from)
 };
 
@@ -469,19 +468,18 @@ __device__ __forceinline__ double log2_from(const double *coef, double z)
     return static_cast<double>(e) + fma(d * 1.44269504088896340736, fma(d, -0.5, 1.0), y0);
 }
 
-enum LevelsForm { kOneLevel, kUnits, kChunks };        // (level 0 alone; a unit per workgroup; as many as it takes)
-template <typename T, bool VEC, LevelsForm FORM>
+// ONE: level 0 alone, which has none below it.
+template <typename T, bool VEC, bool ONE>
 __global__ void __launch_bounds__(kStatThreads, VEC ? 6 : 8)
 k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, LevelArgs ar)
 {
-    constexpr bool ONE = FORM == kOneLevel;
     __shared__ double sh_d[kStatThreads / kWave];
     __shared__ Levels sh;
     __shared__ int sh_b, sh_last;
     const int K = ar.K, L = ar.L, V = ar.V, batch = ar.batch;
     const float c = ar.c;
-    int tid = threadIdx.x, lane = tid & (kWave - 1);
-    int level = 0, P, at = static_cast<int>(blockIdx.x), P_l = 0, u = 0, left = 1;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    int level = 0, P, at = static_cast<int>(blockIdx.x), P_l = 0;
     if constexpr (ONE) {
         const int T_0 = ar.off[batch];
         P = level_parts(ar, 0, T_0);
@@ -492,208 +490,185 @@ k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, LevelArgs
         if (!__ballot(T_l > 0)) return;           // uniform over the workgroup
         P_l = level_parts(ar, lane, T_l);
         const int end = static_cast<int>(wave_inclusive_sum(static_cast<double>(T_l) * static_cast<double>(P_l)));
-        if constexpr (FORM == kChunks) {
-            const int units = __builtin_amdgcn_readlane(end, kWave - 1);
-            left = (units + static_cast<int>(gridDim.x) - 1) / static_cast<int>(gridDim.x);
-            u = at * left;
-            if (u >= units) return;               // uniform
-            left = u + left < units ? left : units - u;
-            if (tid < kMaxPend) { sh.begin[tid + 1] = end; sh.parts[tid] = P_l; }
-            if (tid == 0) sh.begin[0] = 0;
+        const unsigned long long behind = __ballot(at < end);
+        if (!behind) return;                      // uniform
+        level = __ffsll(static_cast<long long>(behind)) - 1;
+        P = __builtin_amdgcn_readlane(P_l, level);
+        at -= __builtin_amdgcn_readlane(end, level) - __builtin_amdgcn_readlane(T_l, level) * P;
+    }
+    auto parts_of = [&](int l_) { return __builtin_amdgcn_readlane(P_l, l_); };
+    if (tid < 11) sh.exp2_coef[tid] = g_exp2_coef[tid];
+    const int item = at / P, part = at - item * P;
+    const int32_t *const off = ar.off + level * (batch + 1);
+    for (int base = 0; base < batch; base += kStatThreads) {
+        const int bb = base + tid;
+        if (bb < batch && off[bb] <= item && item < off[bb + 1]) sh_b = bb;          // exactly one thread
+    }
+    __syncthreads();
+    const int b = __builtin_amdgcn_readfirstlane(sh_b);
+    const int j = item - off[b], r = j / K;
+    const long long bk = static_cast<long long>(b) * K + (j - r * K), pair = bk * L + r;
+    const int n_units = VEC ? row_vectors<T>(V) : V;
+    struct In { RowStat st; double carry; };
+    auto loads = [&](int l_, int row_) {
+        In in;
+        in.st = ar.stats[bk * L + (lane < row_ ? lane : row_)];
+        in.carry = ar.carry[static_cast<size_t>(l_) * batch + b];
+        return in;
+    };
+    In in{};
+    if constexpr (VEC) in = loads(level, r);      // (beside the entries; rows read entry by entry have no registers to spare)
+    // What is summed: this unit's part, once; if an entry that it builds on does not appear, all parts of those entries first.
+    int l = level, row = r, q = part, parts = P;
+    bool alone = false;
+    if constexpr (!ONE) {
+        bool none = false;
+        for (int t = tid; t < level * (r + 1); t += kStatThreads) {
+            const int tl = t / (r + 1), tr = t - tl * (r + 1), to = tl * kMaxRows + tr;
+            const PendRow *const pr = ar.pend + tl * ar.n_rows + bk * L + tr;
+            unsigned long long mu = 0ull, n = 0ull, a = 0ull, f = 0ull;
+            bool there = tl < ar.from;            // (a level of an earlier launch)
+            if (there) {
+                const PendRow e = *pr;
+                mu = static_cast<unsigned long long>(__double_as_longlong(e.log2mu)); n = static_cast<unsigned long long>(__double_as_longlong(e.log2N));
+                a = static_cast<unsigned long long>(__double_as_longlong(e.tokadj)); f = e.flag != 0 ? 1ull : 0ull;
+            }
+            for (int look = 0; look < ar.polls && !there; ++look) {
+                mu = entry_load(pr, 0); n = entry_load(pr, 1); a = entry_load(pr, 2); f = entry_load(pr, 3);
+                there = mu != kNotThere && n != kNotThere && a != kNotThere && static_cast<unsigned>(f) != ~0u;     // (f: flag and counter)
+                if (!there) __builtin_amdgcn_s_sleep(2);
+            }
+            none = none || !there;
+            sh.mu[to] = __longlong_as_double(static_cast<long long>(mu));
+            sh.N[to] = __longlong_as_double(static_cast<long long>(f != 0ull ? n : kNoLevel));
+            sh.adj[to] = __longlong_as_double(static_cast<long long>(a));
+        }
+        alone = __syncthreads_or(none) != 0;
+        if (alone) {                              // (normally none is missing)
+            if (tid < level) {
+                const int cnt = ar.count[static_cast<size_t>(tid) * batch + b];
+                sh.cnt[tid] = cnt < 0 ? 0 : (cnt > L ? L : cnt);
+            }
             __syncthreads();
-        } else {
-            const unsigned long long behind = __ballot(at < end);
-            if (!behind) return;                  // uniform
-            level = __ffsll(static_cast<long long>(behind)) - 1;
-            P = __builtin_amdgcn_readlane(P_l, level);
-            at -= __builtin_amdgcn_readlane(end, level) - __builtin_amdgcn_readlane(T_l, level) * P;
+            l = ar.from; row = 0; q = 0;          // (an earlier launch's are there)
+            parts = parts_of(l);
         }
     }
-    auto parts_of = [&](int l_) { return FORM == kChunks ? __builtin_amdgcn_readfirstlane(sh.parts[l_]) : __builtin_amdgcn_readlane(P_l, l_); };
-    if (tid < 11) sh.exp2_coef[tid] = g_exp2_coef[tid];
-    for (;;) {                                    // (kChunks: unit after unit)
-        if constexpr (FORM == kChunks) {
-            asm volatile("" : "+v"(tid));             // (opaque: nothing made of it is kept from unit to unit)
-            lane = tid & (kWave - 1);
-            level = __ffsll(static_cast<long long>(__ballot(lane < kMaxPend && u < sh.begin[lane < kMaxPend ? lane + 1 : 0]))) - 1;
-            P = parts_of(level);
-            at = u - __builtin_amdgcn_readfirstlane(sh.begin[level]);
-        }
-        const int item = at / P, part = at - item * P;
-        const int32_t *const off = ar.off + level * (batch + 1);
-        for (int base = 0; base < batch; base += kStatThreads) {
-            const int bb = base + tid;
-            if (bb < batch && off[bb] <= item && item < off[bb + 1]) sh_b = bb;          // exactly one thread
-        }
-        __syncthreads();
-        const int b = __builtin_amdgcn_readfirstlane(sh_b);
-        const int j = item - off[b], r = j / K;
-        const long long bk = static_cast<long long>(b) * K + (j - r * K), pair = bk * L + r;
-        const int n_units = VEC ? row_vectors<T>(V) : V;
-        struct In { RowStat st; double carry; };
-        auto loads = [&](int l_, int row_) {
-            In in;
-            in.st = ar.stats[bk * L + (lane < row_ ? lane : row_)];
-            in.carry = ar.carry[static_cast<size_t>(l_) * batch + b];
-            return in;
-        };
-        In in{};
-        if constexpr (VEC) in = loads(level, r);      // (beside the entries; rows read entry by entry have no registers to spare)
-        // What is summed: this unit's part, once; if an entry that it builds on does not appear, all parts of those entries first.
-        int l = level, row = r, q = part, parts = P;
-        bool alone = false;
-        if constexpr (!ONE) {
-            bool none = false;
-            for (int t = tid; t < level * (r + 1); t += kStatThreads) {
-                const int tl = t / (r + 1), tr = t - tl * (r + 1), to = tl * kMaxRows + tr;
-                const PendRow *const pr = ar.pend + tl * ar.n_rows + bk * L + tr;
-                unsigned long long mu = 0ull, n = 0ull, a = 0ull, f = 0ull;
-                bool there = tl < ar.from;            // (a level of an earlier launch)
-                if (there) {
-                    const PendRow e = *pr;
-                    mu = static_cast<unsigned long long>(__double_as_longlong(e.log2mu)); n = static_cast<unsigned long long>(__double_as_longlong(e.log2N));
-                    a = static_cast<unsigned long long>(__double_as_longlong(e.tokadj)); f = e.flag != 0 ? 1ull : 0ull;
+    for (;;) {                                    // (uniform, as everything here; normally one pass)
+        const bool own = ONE || (l == level && row == r);
+        if (own || row < sh.cnt[l]) {
+            if (tid < kWave) {
+                // block ratio in front of the row: the carried one continued along the drafted tokens with the distribution this level
+                // modifies (the target rows as modified by the levels below)
+                if (alone || !VEC) in = loads(l, row);
+                double run = (in.st.tok2_q - in.st.lse2_q) - (in.st.tok2_p - in.st.lse2_p);
+                if constexpr (!ONE)
+                    if (lane <= row)
+                        for (int m = 0; m < l; ++m) run += sh.adj[m * kMaxRows + lane] - sh.N[m * kMaxRows + lane];
+                RowStat st;
+                st.lse2_q = lane_value(in.st.lse2_q, row); st.lse2_p = lane_value(in.st.lse2_p, row);
+                const double log2mu = in.carry * 1.44269504088896340736 + wave_sum(lane < row ? run : 0.0);
+                if (lane == row) sh.run = run;
+                // the levels in front, a lane each; lane l: this level's ratio
+                const double base = st.lse2_p - st.lse2_q;
+                bool on = false;
+                double upto = 0.0, n_l = 0.0;
+                if constexpr (!ONE) {
+                    on = lane < l && static_cast<unsigned long long>(__double_as_longlong(sh.N[(lane < l ? lane : 0) * kMaxRows + row])) != kNoLevel;
+                    n_l = on ? sh.N[lane * kMaxRows + row] : 0.0;
+                    upto = wave_inclusive_sum(n_l);
                 }
-                for (int look = 0; look < ar.polls && !there; ++look) {
-                    mu = entry_load(pr, 0); n = entry_load(pr, 1); a = entry_load(pr, 2); f = entry_load(pr, 3);
-                    there = mu != kNotThere && n != kNotThere && a != kNotThere && static_cast<unsigned>(f) != ~0u;     // (f: flag and counter)
-                    if (!there) __builtin_amdgcn_s_sleep(2);
+                const unsigned long long ons = __ballot(on);
+                const double sumN = ONE ? 0.0 : lane_value(upto, kWave - 1);
+                const double C = on ? base + sh.mu[lane * kMaxRows + row] - (upto - n_l) : base + log2mu - sumN;
+                const float C_hi = static_cast<float>(C);                 // (as RatioConst)
+                const double kappa = exp2_from(sh.exp2_coef, static_cast<double>(C_hi) - C);
+                const float nk = (kappa > 0.5 && kappa < 2.0) ? -static_cast<float>(kappa) : -1.0f;
+                if (on) {
+                    const int to = __popcll(ons & ((1ull << lane) - 1ull));
+                    sh.tab.C_hi[to] = C_hi;
+                    sh.tab.neg_kappa[to] = nk;
                 }
-                none = none || !there;
-                sh.mu[to] = __longlong_as_double(static_cast<long long>(mu));
-                sh.N[to] = __longlong_as_double(static_cast<long long>(f != 0ull ? n : kNoLevel));
-                sh.adj[to] = __longlong_as_double(static_cast<long long>(a));
+                if (lane == l) {
+                    sh.mu[l * kMaxRows + row] = log2mu;
+                    sh.tab.n = __popcll(ons);
+                    sh.shift_q = static_cast<float>(st.lse2_q); sh.C2_hi = C_hi; sh.neg_kappa = nk;
+                    sh.scale = static_cast<double>(static_cast<float>(st.lse2_q)) - st.lse2_q - sumN;
+                }
             }
-            alone = __syncthreads_or(none) != 0;
-            if (alone) {                              // (normally none is missing)
-                if (tid < level) {
-                    const int cnt = ar.count[static_cast<size_t>(tid) * batch + b];
-                    sh.cnt[tid] = cnt < 0 ? 0 : (cnt > L ? L : cnt);
+            __syncthreads();
+            const T *rq = target + (bk * (L + 1) + row) * static_cast<long long>(V);
+            const T *rp = draft + (bk * L + row) * static_cast<long long>(V);
+            const int per = (n_units + parts - 1) / parts, lo = q * per, hi = lo + per < n_units ? lo + per : n_units;
+            const float shift_q = sh.shift_q;
+            const RatioConst rc(sh.C2_hi, sh.neg_kappa);
+            constexpr int N = VEC ? Elem<T>::kPerVec : 1;
+            float acc = 0.0f;
+            if (ONE || sh.tab.n == 0) {
+                for_each_pair_from<T, VEC, false, kStatThreads>(FirstPairs(), rq, rp, V, lo, hi, 0, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+                    float wq[N], w[N];
+                    ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
+                    acc += vector_sum(w);
+                });
+            } else {
+                for_each_pair_from<T, VEC, false, kStatThreads>(FirstPairs(), rq, rp, V, lo, hi, 0, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+                    float wq[N], w[N];
+                    pending_weights(zq, zp, c, shift_q, sh.tab, rc, K, wq, w);
+                    acc += vector_sum(w);
+                });
+            }
+            double S = block_sum(static_cast<double>(acc), sh_d);         // relative to 2^shift_q
+            if (own && parts > 1) {
+                // the store is a device-scope access; the wait lasts until it has been performed, so the counter update that
+                // follows (same thread) cannot be seen before it
+                unsigned long long *const sums = reinterpret_cast<unsigned long long *>(ar.sums + pair * kSumSlots + (level - ar.from) * ar.most);
+                if (tid == 0) {
+                    __hip_atomic_store(sums + part, static_cast<unsigned long long>(__double_as_longlong(S)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    wait_for_stores();
+                    // (the counter lies beside the entry's flag, which is not there yet, and starts from -1 as that does)
+                    const int arrived = __hip_atomic_fetch_add(&ar.pend[level * ar.n_rows + pair].pad, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                    sh_last = arrived == parts - 2;
                 }
                 __syncthreads();
-                l = ar.from; row = 0; q = 0;          // (an earlier launch's are there)
+                if (!sh_last) break;
+                if (tid < parts)
+                    sh.sums[tid] = __longlong_as_double(static_cast<long long>(__hip_atomic_load(sums + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
+            } else if (tid == 0) {
+                sh.sums[q] = S;
+            }
+            __syncthreads();
+            if (tid == 0 && (own || q == parts - 1)) {
+                S = 0.0;
+                for (int x = 0; x < parts; ++x) S += sh.sums[x];          // in part order: the same bits whoever does it
+                const double W = S * exp2_from(sh.exp2_coef, sh.scale), log2mu = sh.mu[l * kMaxRows + row];     // mass of q^(l) t^K
+                const bool some = W > 0.0;        // otherwise every weight is zero and the row stays q^(l)
+                double log2N = 0.0, tokadj = 0.0;
+                if (some) {
+                    log2N = log2_from(sh.exp2_coef, W);
+                    const double x = -sh.run - log2mu, t = 1.0 - exp2_from(sh.exp2_coef, x);     // 1 - p[token] / (mu q^(l)[token])
+                    tokadj = x == x && t > 0.0 ? static_cast<double>(K) * log2_from(sh.exp2_coef, t) : -INFINITY;
+                }
+                if (own) {
+                    entry_store(ar.pend + l * ar.n_rows + pair, log2mu, log2N, tokadj, some);
+                    wait_for_stores();
+                }
+                sh.N[l * kMaxRows + row] = some ? log2N : -0.0;
+                sh.adj[l * kMaxRows + row] = tokadj;
+            }
+        } else if (tid == 0) {
+            sh.N[l * kMaxRows + row] = -0.0; sh.adj[l * kMaxRows + row] = 0.0;
+        }
+        if (own) break;
+        __syncthreads();
+        if (row < sh.cnt[l] && q + 1 < parts) ++q;
+        else {
+            q = 0;
+            if (++row > r) {
+                row = 0; ++l;
+                if (l == level) { row = r; q = part; }
                 parts = parts_of(l);
             }
         }
-        for (;;) {                                    // (uniform, as everything here; normally one pass)
-            const bool own = ONE || (l == level && row == r);
-            if (own || row < sh.cnt[l]) {
-                if (tid < kWave) {
-                    // block ratio in front of the row: the carried one continued along the drafted tokens with the distribution this level
-                    // modifies (the target rows as modified by the levels below)
-                    if (alone || !VEC) in = loads(l, row);
-                    double run = (in.st.tok2_q - in.st.lse2_q) - (in.st.tok2_p - in.st.lse2_p);
-                    if constexpr (!ONE)
-                        if (lane <= row)
-                            for (int m = 0; m < l; ++m) run += sh.adj[m * kMaxRows + lane] - sh.N[m * kMaxRows + lane];
-                    RowStat st;
-                    st.lse2_q = lane_value(in.st.lse2_q, row); st.lse2_p = lane_value(in.st.lse2_p, row);
-                    const double log2mu = in.carry * 1.44269504088896340736 + wave_sum(lane < row ? run : 0.0);
-                    if (lane == row) sh.run = run;
-                    // the levels in front, a lane each; lane l: this level's ratio
-                    const double base = st.lse2_p - st.lse2_q;
-                    bool on = false;
-                    double upto = 0.0, n_l = 0.0;
-                    if constexpr (!ONE) {
-                        on = lane < l && static_cast<unsigned long long>(__double_as_longlong(sh.N[(lane < l ? lane : 0) * kMaxRows + row])) != kNoLevel;
-                        n_l = on ? sh.N[lane * kMaxRows + row] : 0.0;
-                        upto = wave_inclusive_sum(n_l);
-                    }
-                    const unsigned long long ons = __ballot(on);
-                    const double sumN = ONE ? 0.0 : lane_value(upto, kWave - 1);
-                    const double C = on ? base + sh.mu[lane * kMaxRows + row] - (upto - n_l) : base + log2mu - sumN;
-                    const float C_hi = static_cast<float>(C);                 // (as RatioConst)
-                    const double kappa = exp2_from(sh.exp2_coef, static_cast<double>(C_hi) - C);
-                    const float nk = (kappa > 0.5 && kappa < 2.0) ? -static_cast<float>(kappa) : -1.0f;
-                    if (on) {
-                        const int to = __popcll(ons & ((1ull << lane) - 1ull));
-                        sh.tab.C_hi[to] = C_hi;
-                        sh.tab.neg_kappa[to] = nk;
-                    }
-                    if (lane == l) {
-                        sh.mu[l * kMaxRows + row] = log2mu;
-                        sh.tab.n = __popcll(ons);
-                        sh.shift_q = static_cast<float>(st.lse2_q); sh.C2_hi = C_hi; sh.neg_kappa = nk;
-                        sh.scale = static_cast<double>(static_cast<float>(st.lse2_q)) - st.lse2_q - sumN;
-                    }
-                }
-                __syncthreads();
-                const T *rq = target + (bk * (L + 1) + row) * static_cast<long long>(V);
-                const T *rp = draft + (bk * L + row) * static_cast<long long>(V);
-                const int per = (n_units + parts - 1) / parts, lo = q * per, hi = lo + per < n_units ? lo + per : n_units;
-                const float shift_q = sh.shift_q;
-                const RatioConst rc(sh.C2_hi, sh.neg_kappa);
-                constexpr int N = VEC ? Elem<T>::kPerVec : 1;
-                float acc = 0.0f;
-                if (ONE || sh.tab.n == 0) {
-                    for_each_pair_from<T, VEC, false, kStatThreads>(FirstPairs(), rq, rp, V, lo, hi, 0, [&](int, const float (&zq)[N], const float (&zp)[N]) {
-                        float wq[N], w[N];
-                        ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
-                        acc += vector_sum(w);
-                    });
-                } else {
-                    for_each_pair_from<T, VEC, false, kStatThreads>(FirstPairs(), rq, rp, V, lo, hi, 0, [&](int, const float (&zq)[N], const float (&zp)[N]) {
-                        float wq[N], w[N];
-                        pending_weights(zq, zp, c, shift_q, sh.tab, rc, K, wq, w);
-                        acc += vector_sum(w);
-                    });
-                }
-                double S = block_sum(static_cast<double>(acc), sh_d);         // relative to 2^shift_q
-                if (own && parts > 1) {
-                    // the store is a device-scope access; the wait lasts until it has been performed, so the counter update that
-                    // follows (same thread) cannot be seen before it
-                    unsigned long long *const sums = reinterpret_cast<unsigned long long *>(ar.sums + pair * kSumSlots + (level - ar.from) * ar.most);
-                    if (tid == 0) {
-                        __hip_atomic_store(sums + part, static_cast<unsigned long long>(__double_as_longlong(S)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        wait_for_stores();
-                        // (the counter lies beside the entry's flag, which is not there yet, and starts from -1 as that does)
-                        const int arrived = __hip_atomic_fetch_add(&ar.pend[level * ar.n_rows + pair].pad, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                        sh_last = arrived == parts - 2;
-                    }
-                    __syncthreads();
-                    if (!sh_last) break;
-                    if (tid < parts)
-                        sh.sums[tid] = __longlong_as_double(static_cast<long long>(__hip_atomic_load(sums + tid, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)));
-                } else if (tid == 0) {
-                    sh.sums[q] = S;
-                }
-                __syncthreads();
-                if (tid == 0 && (own || q == parts - 1)) {
-                    S = 0.0;
-                    for (int x = 0; x < parts; ++x) S += sh.sums[x];          // in part order: the same bits whoever does it
-                    const double W = S * exp2_from(sh.exp2_coef, sh.scale), log2mu = sh.mu[l * kMaxRows + row];     // mass of q^(l) t^K
-                    const bool some = W > 0.0;        // otherwise every weight is zero and the row stays q^(l)
-                    double log2N = 0.0, tokadj = 0.0;
-                    if (some) {
-                        log2N = log2_from(sh.exp2_coef, W);
-                        const double x = -sh.run - log2mu, t = 1.0 - exp2_from(sh.exp2_coef, x);     // 1 - p[token] / (mu q^(l)[token])
-                        tokadj = x == x && t > 0.0 ? static_cast<double>(K) * log2_from(sh.exp2_coef, t) : -INFINITY;
-                    }
-                    if (own) {
-                        entry_store(ar.pend + l * ar.n_rows + pair, log2mu, log2N, tokadj, some);
-                        wait_for_stores();
-                    }
-                    sh.N[l * kMaxRows + row] = some ? log2N : -0.0;
-                    sh.adj[l * kMaxRows + row] = tokadj;
-                }
-            } else if (tid == 0) {
-                sh.N[l * kMaxRows + row] = -0.0; sh.adj[l * kMaxRows + row] = 0.0;
-            }
-            if (own) break;
-            __syncthreads();
-            if (row < sh.cnt[l] && q + 1 < parts) ++q;
-            else {
-                q = 0;
-                if (++row > r) {
-                    row = 0; ++l;
-                    if (l == level) { row = r; q = part; }
-                    parts = parts_of(l);
-                }
-            }
-        }
-        ++u;
-        if (FORM != kChunks || --left == 0) return;
-        __syncthreads();
     }
 }
 
@@ -836,25 +811,23 @@ hipError_t launch_typed(const Problem &p)
         const auto resident = [&](long long g) { return g > pairs ? static_cast<int>(3 * cu) : 0x7fffffff; };
         la.first_grid = static_cast<int>(least); la.grid = static_cast<int>(grid);
         la.first_resident = resident(least); la.resident = resident(grid);
-        // Levels per launch.  Up to six rows per compute unit: all of the library's own (L - 1, most of them empty), and all that are given
-        // unless rows are long (us a call, each level its own launch / together: two levels on 16 x 4 drafts of 8, V = 8000 bfloat16
-        // 50.5 / 49.6, 32 x 4 of 8, V = 32000 118.1 / 117.0; but 32 x 3 of 8, V = 128256 265 / 273, 16 x 4 of 6, V = 70000 float32
-        // 153.5 / 156.2: workgroups that wait hold places that a level's later parts could use).  With more rows each level's fill the
-        // chip, and what is given is launched level by level (64 x 4 of 8, V = 8000 two levels 100.3 / 102.4, 128 x 16 542 / 596); of the
-        // library's own the first, the only one that most prefixes have, alone and the others together, in a grid of one workgroup per
-        // row, which takes several units a workgroup where that many are alive (three iterations with 128 x 8 of 8, V = 8000: all together
-        // 916, level by level 875, the others with a workgroup for every unit there may be 857, as here 789).
+        // Levels per launch.  Up to six rows per compute unit: all of the library's own (L - 1, most of them empty; an iteration once the
+        // state has settled, each level its own launch / together: 30 x 6 drafts of 8, V = 16000 240 / 215 us, 48 x 4 of 8, V = 8000 177 / 155,
+        // 24 x 8 of 8, V = 32000 float32 298 / 271, 1 x 4 of 8, V = 128256 62 / 56), and all that are given unless rows are long (two levels
+        // on 16 x 4 drafts of 8, V = 8000 bfloat16 50.5 / 49.6, 32 x 4 of 8, V = 32000 118.1 / 117.0; but 32 x 3 of 8, V = 128256 265 / 273,
+        // 16 x 4 of 6, V = 70000 float32 153.5 / 156.2: workgroups that wait hold places that a level's later parts could use).  With more
+        // rows each level's fill the chip, and levels are launched one by one (two given levels on 64 x 4 of 8, V = 8000 100.3 / 102.4,
+        // 128 x 16 542 / 596; three iterations with 128 x 8 of 8, V = 8000 875 / 916.  All but the first in one grid whose workgroups take
+        // as many units as there are: 789 there, but 269 against 207 for a settled state of 64 x 4 of 8, V = 8000 and 2667 against
+        // 952 for 32 x 8 of 8, V = 128256: the units of a level stand in a few workgroups, for which all the others wait).
         const bool small = pairs <= 6 * cu;
         for (la.from = 0; la.from < p.pend_levels; la.from = la.to) {
-            if (p.state_count) la.to = small || la.from == 1 ? p.pend_levels : la.from + 1;
-            else la.to = small && row_vectors<T>(p.V) < 6000 ? p.pend_levels : la.from + 1;
+            la.to = small && (p.state_count || row_vectors<T>(p.V) < 6000) ? p.pend_levels : la.from + 1;
             la.most = kSumSlots / (la.to - la.from) < kPendParts ? kSumSlots / (la.to - la.from) : kPendParts;
-            const bool chunks = la.from > 0 && la.to - la.from > 1;
-            const dim3 gp(static_cast<unsigned>(chunks ? grid : (la.from == 0 ? least : grid) + (la.to - la.from - 1) * grid));
-#define SPECGBV_PEND_LAUNCH(VEC, FORM) hipLaunchKernelGGL((k_pend_norm<T, VEC, FORM>), gp, dim3(kStatThreads), 0, p.stream, target, draft, la)
-            if (la.to == 1) { if (vec) SPECGBV_PEND_LAUNCH(true, kOneLevel); else SPECGBV_PEND_LAUNCH(false, kOneLevel); }
-            else if (chunks) { if (vec) SPECGBV_PEND_LAUNCH(true, kChunks); else SPECGBV_PEND_LAUNCH(false, kChunks); }
-            else { if (vec) SPECGBV_PEND_LAUNCH(true, kUnits); else SPECGBV_PEND_LAUNCH(false, kUnits); }
+            const dim3 gp(static_cast<unsigned>((la.from == 0 ? least : grid) + (la.to - la.from - 1) * grid));
+#define SPECGBV_PEND_LAUNCH(VEC, ONE) hipLaunchKernelGGL((k_pend_norm<T, VEC, ONE>), gp, dim3(kStatThreads), 0, p.stream, target, draft, la)
+            if (la.to == 1) { if (vec) SPECGBV_PEND_LAUNCH(true, true); else SPECGBV_PEND_LAUNCH(false, true); }
+            else { if (vec) SPECGBV_PEND_LAUNCH(true, false); else SPECGBV_PEND_LAUNCH(false, false); }
             e = hipGetLastError();
             if (e != hipSuccess) return e;
         }

@@ -1,5 +1,4 @@
-"""The levels of pending modification: launched together, one by one, alone or in chunks, by the number of rows and their length
-(k_pend_norm).  Whichever it is, a workgroup that looks in vain for the entries it builds on makes them itself, with the same bits."""
+"""The levels of pending modification: launched together or one by one, by the number of rows and their length (k_pend_norm).  Whichever it is, a workgroup that looks in vain for the entries it builds on makes them itself, with the same bits."""
 import numpy as np
 import pytest
 
@@ -39,7 +38,7 @@ def test_given_levels(B, K, L, V, dtype, levels, monkeypatch):
 @pytest.mark.parametrize("B,K,L,V,dtype,full", [(4, 3, 6, 4104, "f32", False), (65, 4, 7, 520, "f32", False), (65, 4, 7, 520, "f32", True),
                                                  (130, 3, 5, 1030, "bf16", True)])
 def test_levels_of_a_state(B, K, L, V, dtype, full, monkeypatch):
-    """As given levels, and alone; full: more units than workgroups, so that each takes several."""
+    """As given levels; full: every level modifies every row."""
     import torch
     import paper_2604_25925_amd as sg
     t, d, tok, carry, count = _case(B, K, L, V, dtype, L - 1)
