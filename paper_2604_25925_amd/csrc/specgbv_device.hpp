@@ -542,33 +542,55 @@ __device__ __forceinline__ void mask_repeated(float (&z)[N], int v, int V)
 }
 
 // Loads that do not start at a multiple of four bytes run at two thirds of the rate (rows of one workgroup each, 220 MB: V = 32002
-// 6.75 TB/s, 32003 5.1, half of whose rows start at an odd entry).  A row that does is read from the entry in front of it on, as a
-// row of V + 1 entries whose first has no weight: odd_start is what `row` and V are moved by (1 or 0; V is odd then, and V + 1
-// entries make no more vectors).  Not the first row of a tensor (`first`), in front of which nothing belongs to it.  Us a call
-// before / after, two-pass schedule: 41 x 7 drafts of 6, V = 32003 108.8 / 96.9, 40 x 8 of 8, V = 32001 149.4 / 129.0, 20 x 8 of 6,
-// V = 50257 102.9 / 89.
-template <typename T>
-__device__ __forceinline__ int odd_start(const T *row, bool first)
-{
-    return sizeof(T) == 2 && !first ? static_cast<int>(reinterpret_cast<uintptr_t>(row) >> 1 & 1u) : 0;
-}
-// Of a row pair only if both rows do: entries have to lie side by side.
-template <typename T>
-__device__ __forceinline__ int odd_start(const T *rq, const T *rp, bool first) { return odd_start(rq, first) & odd_start(rp, first); }
-// mask_repeated for a row so moved: the entry in front of it (the first of vector 0) has no weight either.
-template <typename T, int N>
-__device__ __forceinline__ void mask_ends(float (&z)[N], int v, int V, int shift)
-{
-    if (((V & (N - 1)) | shift) != 0) {                  // uniform
-        asm volatile("");
-        const int over = (v + 1) * N - V;
-        if (over > 0) {
-#pragma unroll
-            for (int j = 0; j < N; ++j) z[j] = j < over ? -__builtin_inff() : z[j];
+// 6.75 TB/s, 32003 5.1, half of whose rows start at an odd entry).  A vector of such a row is put together in registers (ODD:
+// instances for bfloat16 rows of an odd vocabulary) from the sixteen bytes that start one entry in front of it and its own last
+// entry, which is the first that the next lane has loaded.  It holds the same entries wherever the row starts, so that equal rows
+// give equal bits.  Lanes whose neighbour has loaded something else (the wave's last, the last of the range and the last two of
+// the row) load their last entry, the others beside them the wave's last one.  Not the first row of a tensor (`first`), in front of
+// which nothing belongs to it: its vectors are loaded as they lie.
+// Us a call of the two-pass schedule, loaded as they lie / every lane loading its last entry / as here: 41 x 7 drafts of 6, V = 32003
+// 108.8 / 106.8 / 96.6, 40 x 8 of 8, V = 32001 149.5 / 146.2 / 129.0, 20 x 8 of 6, V = 50257 102.7 / 100.7 / 90.4; three iterations of
+// 8 x 4 of 8, V = 50257 219.4 with every lane's / 210.0.  (Rows moved by an entry, with masks at their ends, gain the same, and another
+// 1 - 2 % under levels, but give bits that depend on the address.)
+template <bool ODD> struct Loaded { U4 v; };
+template <> struct Loaded<true> { U4 v; uint32_t last; };
+template <typename T, bool ODD>
+struct RowLoads {
+    const T *row;
+    int V;
+    int own;                       // lanes load the last entry of vectors from this one on
+    uint32_t turn;                 // bits by which what was loaded is turned: 16 or, where the row starts at an even entry, 0 (uniform)
+    // hi: the vectors that are asked for end in front of this one
+    __device__ __forceinline__ RowLoads(const T *r, int V_, int hi, bool first) : row(r), V(V_), own(0), turn(0) {
+        if constexpr (ODD) {
+            turn = first ? 0u : static_cast<uint32_t>(reinterpret_cast<uintptr_t>(r) << 3) & 16u;
+            const int n = row_vectors<T>(V) - 2;
+            own = hi - 1 < n ? hi - 1 : n;
         }
-        if (shift != 0) z[0] = v == 0 ? -__builtin_inff() : z[0];
     }
-}
+    __device__ __forceinline__ Loaded<ODD> load(int v) const {
+        Loaded<ODD> l;
+        const int e = vector_entry<T>(v, V);
+        if constexpr (ODD) {
+            const int lane = static_cast<int>(threadIdx.x) & (kWave - 1);
+            const uint32_t end = static_cast<uint32_t>(v >= own ? v : v - lane + kWave - 1) * Elem<T>::kPerVec + Elem<T>::kPerVec - 1, n = V;
+            l.v = load16_stream_any(row - (turn >> 4) + e);
+            l.last = Elem<T>::bits(row + (turn == 0 ? 0 : (end < n ? end : n - 1)));
+        } else {
+            l.v = load16_stream_any(row + e);
+        }
+        return l;
+    }
+    __device__ __forceinline__ U4 vector(const Loaded<ODD> &l, int v) const {
+        if constexpr (ODD) {
+            const uint32_t next = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(static_cast<int>(l.last), static_cast<int>(l.v.x), 0x130, 0xf, 0xf, false));   // (wave_shl:1)
+            return U4{__builtin_amdgcn_alignbit(l.v.y, l.v.x, turn), __builtin_amdgcn_alignbit(l.v.z, l.v.y, turn),
+                      __builtin_amdgcn_alignbit(l.v.w, l.v.z, turn), __builtin_amdgcn_alignbit(v >= own ? l.last : next, l.v.w, turn)};
+        } else {
+            return l.v;
+        }
+    }
+};
 
 // f(first entry index, z_q[N], z_p[N]) for the entries of a (target, draft) row pair in the unit range [lo, hi),
 // N = 8 or 4 entries of one 16-byte vector (VEC, V >= N; a unit is a vector) or 1 (a unit is an entry); the workgroup's
@@ -625,57 +647,55 @@ __device__ __forceinline__ void for_each_pair_range(const T *rq, const T *rp, in
 //   of bfloat16 rows without levels, where little is made in front, not: 4 x 4 of 8, V = 66000 36.3 / 35.5 / 36.9, 8 x 8 of 4,
 //     V = 80000 49.9 / 49.0 / 48.5, 16 x 4 of 5, V = 70000 57.4 / 57.3 / 58.4.
 // In k_pend_norm the registers cost more than it gains (32 x 8 of 8, V = 128256 571 / 583).
-struct FirstPairs { U4 q0, p0, q1, p1; };
-template <typename T, bool AHEAD, int THREADS>
-__device__ __forceinline__ FirstPairs first_pairs(const T *rq, const T *rp, int V, int lo, int hi)
+template <bool ODD> struct FirstPairs { Loaded<ODD> q0, p0, q1, p1; };
+template <typename T, bool AHEAD, int THREADS, bool ODD>
+__device__ __forceinline__ FirstPairs<ODD> first_pairs(const RowLoads<T, ODD> &rq, const RowLoads<T, ODD> &rp, int lo, int hi)
 {
-    FirstPairs f;
+    FirstPairs<ODD> f;
     if constexpr (AHEAD) {
-        const int v0 = lo + static_cast<int>(threadIdx.x), v1 = v0 + THREADS;
-        const int e0 = vector_entry<T>(v0 < hi ? v0 : hi - 1, V), e1 = vector_entry<T>(v1 < hi ? v1 : hi - 1, V);
-        f.q0 = load16_stream_any(rq + e0); f.p0 = load16_stream_any(rp + e0);
-        f.q1 = load16_stream_any(rq + e1); f.p1 = load16_stream_any(rp + e1);
+        int v0 = lo + static_cast<int>(threadIdx.x), v1 = v0 + THREADS;
+        v0 = v0 < hi ? v0 : hi - 1;
+        v1 = v1 < hi ? v1 : hi - 1;
+        f.q0 = rq.load(v0); f.p0 = rp.load(v0);
+        f.q1 = rq.load(v1); f.p1 = rp.load(v1);
     }
     return f;
 }
-// shift: the rows and V are moved (odd_start).
-template <typename T, bool VEC, bool AHEAD, int THREADS, typename F>
-__device__ __forceinline__ void for_each_pair_from(const FirstPairs &first, const T *rq, const T *rp, int V, int lo, int hi, int shift, F f)
+template <typename T, bool VEC, bool AHEAD, int THREADS, bool ODD, typename F>
+__device__ __forceinline__ void for_each_pair_from(const FirstPairs<ODD> &first, const RowLoads<T, ODD> &rq, const RowLoads<T, ODD> &rp, int V, int lo, int hi, F f)
 {
     if constexpr (VEC) {
         constexpr int PV = Elem<T>::kPerVec;
-        auto one = [&](const U4 &q, const U4 &p, int v, int e) {
+        auto one = [&](const Loaded<ODD> &q, const Loaded<ODD> &p, int v) {
             float zq[PV], zp[PV];
-            Elem<T>::unpack(q, zq);
-            Elem<T>::unpack(p, zp);
-            mask_ends<T>(zq, v, V, shift);
-            mask_ends<T>(zp, v, V, shift);
-            f(e, zq, zp);
+            Elem<T>::unpack(rq.vector(q, v), zq);
+            Elem<T>::unpack(rp.vector(p, v), zp);
+            mask_repeated<T>(zq, v, V);
+            mask_repeated<T>(zp, v, V);
+            f(vector_entry<T>(v, V), zq, zp);
         };
-        auto second = [&](int v) { return vector_entry<T>(v + THREADS < hi ? v + THREADS : hi - 1, V); };
+        auto second = [&](int v) { return v + THREADS < hi ? v + THREADS : hi - 1; };
         int v = lo + static_cast<int>(threadIdx.x);
         if constexpr (AHEAD) {
             if (v >= hi) return;
-            U4 q0 = first.q0, p0 = first.p0, q1 = first.q1, p1 = first.p1;
+            Loaded<ODD> q0 = first.q0, p0 = first.p0, q1 = first.q1, p1 = first.p1;
             for (;;) {                                     // four loads in flight per thread
-                one(q0, p0, v, vector_entry<T>(v, V));
-                if (v + THREADS < hi) one(q1, p1, v + THREADS, vector_entry<T>(v + THREADS, V));
+                one(q0, p0, v);
+                if (v + THREADS < hi) one(q1, p1, v + THREADS);
                 v += 2 * THREADS;
                 if (v >= hi) break;
-                const int e0 = vector_entry<T>(v, V), e1 = second(v);
-                q0 = load16_stream_any(rq + e0); p0 = load16_stream_any(rp + e0);
-                q1 = load16_stream_any(rq + e1); p1 = load16_stream_any(rp + e1);
+                q0 = rq.load(v); p0 = rp.load(v);
+                q1 = rq.load(second(v)); p1 = rp.load(second(v));
             }
         } else {
             for (; v < hi; v += 2 * THREADS) {
-                const int e0 = vector_entry<T>(v, V), e1 = second(v);
-                const U4 q0 = load16_stream_any(rq + e0), p0 = load16_stream_any(rp + e0), q1 = load16_stream_any(rq + e1), p1 = load16_stream_any(rp + e1);
-                one(q0, p0, v, e0);
-                if (v + THREADS < hi) one(q1, p1, v + THREADS, e1);
+                const Loaded<ODD> q0 = rq.load(v), p0 = rp.load(v), q1 = rq.load(second(v)), p1 = rp.load(second(v));
+                one(q0, p0, v);
+                if (v + THREADS < hi) one(q1, p1, v + THREADS);
             }
         }
     } else {
-        for_each_pair_range<T, false, THREADS>(rq, rp, V, lo, hi, f);
+        for_each_pair_range<T, false, THREADS>(rq.row, rp.row, V, lo, hi, f);
     }
 }
 

@@ -60,12 +60,12 @@ constexpr int kAhead = 4;            // loads a thread of k_row_stats keeps in f
 
 // Vector v of a row into its running sum, without the drafted token and without entries the vector before holds.
 template <typename T>
-__device__ __forceinline__ void add_vector(RunningSum &acc, const U4 &raw, int v, int tok, int V, int shift, float c)
+__device__ __forceinline__ void add_vector(RunningSum &acc, const U4 &raw, int v, int tok, int V, float c)
 {
     constexpr int PV = Elem<T>::kPerVec;
     float z[PV];
     Elem<T>::unpack(raw, z);
-    mask_ends<T>(z, v, V, shift);
+    mask_repeated<T>(z, v, V);
     leave_out(z, v == tok / PV, tok - vector_entry<T>(v, V));
     acc.add(z, c);
 }
@@ -73,8 +73,8 @@ __device__ __forceinline__ void add_vector(RunningSum &acc, const U4 &raw, int v
 // grid (row pairs + pending levels, 2): blocks (pair, 0 / 1) reduce the target / draft row of the pair; with
 // pending modifications blocks (pairs + l, 0) compute level l's offsets (pend_offsets) and the row blocks write the levels'
 // entries of their row: empty, or not there yet.
-// ODD: V is odd and the type bfloat16, so that rows may start at odd entries (odd_start; an instance of their own, which spares the
-// others 0.2 - 0.5 % of a call).
+// ODD: V is odd and the type bfloat16, so that every other row starts at an odd entry (RowLoads; an instance of its own, which spares
+// the others 0.2 - 0.5 % of a call).
 template <typename T, bool VEC, bool ODD>
 __global__ void __launch_bounds__(kStatThreads)
 k_row_stats(const T *__restrict__ target, const T *__restrict__ draft,
@@ -113,22 +113,28 @@ k_row_stats(const T *__restrict__ target, const T *__restrict__ draft,
     uint32_t tok_bits = 0;                        // the token's logit, asked for behind the row's first loads
     RunningSum acc;                               // the drafted token is left out (leave_out)
     if (VEC) {
-        const int shift = ODD ? odd_start(row, pair == 0) : 0, Vs = V + shift, nvec = row_vectors<T>(Vs);
-        for (int i = threadIdx.x; i < nvec; i += kAhead * kStatThreads) {
-            U4 v[kAhead];
+        const int nvec = row_vectors<T>(V);
+        auto sweep = [&](const auto &from) {
+            for (int i = threadIdx.x; i < nvec; i += kAhead * kStatThreads) {
+                decltype(from.load(0)) v[kAhead];
 #pragma unroll
-            for (int a = 0; a < kAhead; ++a) {            // (no branch around a load: past the end the last vector again)
-                const int at = i + a * kStatThreads;
-                v[a] = load16_stream_any(row - shift + vector_entry<T>(at < nvec ? at : nvec - 1, Vs));
-            }
-            const int tok = token_index_used(tok_raw, V) + shift;
-            if (i == static_cast<int>(threadIdx.x)) tok_bits = Elem<T>::bits(row + (tok - shift));
+                for (int a = 0; a < kAhead; ++a) {        // (no branch around a load: past the end the last vector again)
+                    const int at = i + a * kStatThreads;
+                    v[a] = from.load(at < nvec ? at : nvec - 1);
+                }
+                const int tok = token_index_used(tok_raw, V);
+                if (i == static_cast<int>(threadIdx.x)) tok_bits = Elem<T>::bits(row + tok);
 #pragma unroll
-            for (int a = 0; a < kAhead; ++a) {
-                const int at = i + a * kStatThreads;
-                if (at < nvec) add_vector<T>(acc, v[a], at, tok, Vs, shift, c);
+                for (int a = 0; a < kAhead; ++a) {
+                    const int at = i + a * kStatThreads;
+                    if (at < nvec) add_vector<T>(acc, from.vector(v[a], at), at, tok, V, c);
+                }
             }
-        }
+        };
+        // (rows of an odd vocabulary that start at an even entry as all others: 97.4 / 96.6 us a call at 41 x 7 drafts of 6, V = 32003)
+        const RowLoads<T, ODD> from(row, V, nvec, pair == 0);
+        if (from.turn != 0) sweep(from);
+        else sweep(RowLoads<T, false>(row, V, nvec, false));
     } else {
         for (int x = threadIdx.x; x < V; x += kStatThreads) {
             float z[1] = {Elem<T>::scalar(row + x)};
@@ -175,7 +181,7 @@ k_row_stats(const T *__restrict__ target, const T *__restrict__ draft,
 // partial sums per row, which the final-token kernel adds up in part order.  No workgroup waits for another one.
 
 // grid (row pairs * P, 2): block (pair * P + part, 0 / 1) reduces part `part` of the target / draft row of the pair
-template <typename T, bool VEC>
+template <typename T, bool VEC, bool ODD>
 __global__ void __launch_bounds__(kStatThreads)
 k_row_stats_parts(const T *__restrict__ target, const T *__restrict__ draft, const int32_t *__restrict__ tokens, int L,
                   int V, float c, int P, Row0Part *__restrict__ parts)
@@ -190,24 +196,20 @@ k_row_stats_parts(const T *__restrict__ target, const T *__restrict__ draft, con
     const T *row = is_draft ? draft + (bk * L + r) * static_cast<long long>(V)
                             : target + (bk * (L + 1) + r) * static_cast<long long>(V);
     constexpr int PV = Elem<T>::kPerVec;
-    const int shift = VEC ? odd_start(row, pair == 0) : 0, Vs = V + shift;
-    const int units = VEC ? row_vectors<T>(Vs) : V;
+    const int units = VEC ? row_vectors<T>(V) : V;
     const int per = (units + P - 1) / P;
     const int lo = part * per, hi = lo + per < units ? lo + per : units;
+    const RowLoads<T, ODD> from(row, V, hi, pair == 0);
     const int tok_raw = token_index_queued(tokens, pair);
     RunningSum acc;                               // the drafted token is left out (leave_out)
     if (VEC) {
-        int i = lo + static_cast<int>(threadIdx.x);
-        for (; i + kStatThreads < hi; i += 2 * kStatThreads) {            // two loads in flight per thread
-            const U4 a = load16_stream_any(row - shift + vector_entry<T>(i, Vs));
-            const U4 b2 = load16_stream_any(row - shift + vector_entry<T>(i + kStatThreads, Vs));
-            const int tk = token_index_used(tok_raw, V) + shift;
-            add_vector<T>(acc, a, i, tk, Vs, shift, c);
-            add_vector<T>(acc, b2, i + kStatThreads, tk, Vs, shift, c);
-        }
-        if (i < hi) {
-            const U4 a = load16_stream_any(row - shift + vector_entry<T>(i, Vs));
-            add_vector<T>(acc, a, i, token_index_used(tok_raw, V) + shift, Vs, shift, c);
+        // two loads in flight per thread (of the last step too: the second one's place beyond the part is the part's last vector)
+        for (int i = lo + static_cast<int>(threadIdx.x); i < hi; i += 2 * kStatThreads) {
+            const int i2 = i + kStatThreads;
+            const Loaded<ODD> a = from.load(i), b2 = from.load(i2 < hi ? i2 : hi - 1);
+            const int tk = token_index_used(tok_raw, V);
+            add_vector<T>(acc, from.vector(a, i), i, tk, V, c);
+            if (i2 < hi) add_vector<T>(acc, from.vector(b2, i2), i2, tk, V, c);
         }
     } else {
         for (int x = lo + static_cast<int>(threadIdx.x); x < hi; x += kStatThreads) {
@@ -217,7 +219,7 @@ k_row_stats_parts(const T *__restrict__ target, const T *__restrict__ draft, con
         }
     }
     const int tok = token_index_used(tok_raw, V);
-    const int tok_unit = VEC ? (tok + shift) / PV : tok;
+    const int tok_unit = VEC ? tok / PV : tok;
     const float M = block_max(acc.m2, sh_f);
     const double mine = static_cast<double>(acc.Z) * exp2(static_cast<double>(acc.m2) - static_cast<double>(M));
     const double total = block_sum(acc.Z > 0.0f ? mine : 0.0, sh_d);
@@ -253,12 +255,12 @@ __device__ __forceinline__ double lse2_from_parts(const Row0Part *pp, int P)
 // With stat_P > 1 the statistics of the draft's rows 0 .. i are still in parts
 // (k_row_stats_parts): every workgroup combines the ones it needs, and part 0 stores the RowStat entry of its
 // row (the workgroup of row 1 also that of row 0, and clears the arrival counter of the final-token kernel).
-template <typename T, bool VEC, bool PEND>
-__global__ void __launch_bounds__(kStatThreads)
-k_ot_sum_parts(const T *__restrict__ target, const T *__restrict__ draft, const int32_t *__restrict__ tokens, int K, int L,
-               int V, float c, int P, const Row0Part *__restrict__ stat_parts, int stat_P, RowStat *stats,
-               int32_t *__restrict__ final_counter, double *__restrict__ s_part, double *__restrict__ e_part,
-               const PendRow *__restrict__ pend, long long n_rows, int nlev, double c_rel)
+template <typename T, bool VEC, bool PEND, bool ODD>
+__device__ __forceinline__ void
+ot_sum_parts(const T *__restrict__ target, const T *__restrict__ draft, const int32_t *__restrict__ tokens, int K, int L,
+             int V, float c, int P, const Row0Part *__restrict__ stat_parts, int stat_P, RowStat *stats,
+             int32_t *__restrict__ final_counter, double *__restrict__ s_part, double *__restrict__ e_part,
+             const PendRow *__restrict__ pend, long long n_rows, int nlev, double c_rel)
 {
     __shared__ double sh_d[kStatThreads / kWave];
     __shared__ PendTable sh_tab;                  // PEND: the levels that modify this row
@@ -272,12 +274,12 @@ k_ot_sum_parts(const T *__restrict__ target, const T *__restrict__ draft, const 
     const long long pair = bk * L + i;
     const T *rq = target + (bk * (L + 1) + i) * static_cast<long long>(V);
     const T *rp = draft + pair * static_cast<long long>(V);
-    const int shift = VEC ? odd_start(rq, rp, false) : 0, Vs = V + shift;              // (i >= 1: not a tensor's first row)
-    const int units = VEC ? row_vectors<T>(Vs) : V;
+    const int units = VEC ? row_vectors<T>(V) : V;
     const int per = (units + P - 1) / P;
     const int lo = part * per, hi = lo + per < units ? lo + per : units;
     constexpr bool kAhead = VEC && (PEND || Elem<T>::kPerVec == 4);      // (see first_pairs)
-    const FirstPairs first = first_pairs<T, kAhead, kStatThreads>(rq - shift, rp - shift, Vs, lo, hi);
+    const RowLoads<T, ODD> from_q(rq, V, hi, false), from_p(rp, V, hi, false);         // (i >= 1: not a tensor's first row)
+    const FirstPairs<ODD> first = first_pairs<T, kAhead, kStatThreads>(from_q, from_p, lo, hi);
     RowStat st;
     double log2nu = 0.0;
     if (stat_P > 1) {
@@ -325,14 +327,14 @@ k_ot_sum_parts(const T *__restrict__ target, const T *__restrict__ draft, const 
     const RatioConst rc(ratio_const(st.lse2_p, st.lse2_q, log2nu, c_rel) - sumN);
     float acc = 0.0f;
     if (PEND && sh_tab.n > 0) {                   // uniform over the workgroup
-        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, rq - shift, rp - shift, Vs, lo, hi, shift, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, from_q, from_p, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             pending_weights(zq, zp, c, shift_q, sh_tab, rc, K, wq, w);
 #pragma unroll
             for (int j = 0; j < N; ++j) acc += w[j];
         });
     } else {
-        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, rq - shift, rp - shift, Vs, lo, hi, shift, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, from_q, from_p, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
 #pragma unroll
@@ -341,13 +343,33 @@ k_ot_sum_parts(const T *__restrict__ target, const T *__restrict__ draft, const 
     }
     double total = block_sum(static_cast<double>(acc), sh_d);
     if (threadIdx.x == 0 && !(PEND && sh_tab.n > 0))
-        total = with_token_term<T>(total, st, log2nu, rq, rp, tokens + pair, V, lo * N - shift, hi * N < Vs ? hi * N - shift : V, c, shift_q, rc, K);
+        total = with_token_term<T>(total, st, log2nu, rq, rp, tokens + pair, V, lo * N, hi * N < V ? hi * N : V, c, shift_q, rc, K);
     // (whether the row's s and g nearly cancel, so that Eq. (hik) needs nu^2 (s - g) summed term by term, only the sum
     // over all parts can tell: the final-token kernel looks at it)
     if (threadIdx.x == 0) s_part[pair * kPendParts + part] = total * exp2(static_cast<double>(shift_q) - st.lse2_q - sumN);
     // (the final-token kernel looks at the complete sums itself and takes E where a row needs it: its parts start as
     // "not there yet")
     if (part == 0 && threadIdx.x < kPendParts) e_part[pair * kPendParts + threadIdx.x] = -1.0;
+}
+
+template <typename T, bool VEC, bool PEND>
+__global__ void __launch_bounds__(kStatThreads)
+k_ot_sum_parts(const T *__restrict__ target, const T *__restrict__ draft, const int32_t *__restrict__ tokens, int K, int L,
+               int V, float c, int P, const Row0Part *__restrict__ stat_parts, int stat_P, RowStat *stats,
+               int32_t *__restrict__ final_counter, double *__restrict__ s_part, double *__restrict__ e_part,
+               const PendRow *__restrict__ pend, long long n_rows, int nlev, double c_rel)
+{
+    ot_sum_parts<T, VEC, PEND, false>(target, draft, tokens, K, L, V, c, P, stat_parts, stat_P, stats, final_counter, s_part, e_part, pend, n_rows, nlev, c_rel);
+}
+// bfloat16 rows of an odd vocabulary, by vectors
+template <bool PEND>
+__global__ void __launch_bounds__(kStatThreads)
+k_ot_sum_parts_odd(const uint16_t *__restrict__ target, const uint16_t *__restrict__ draft, const int32_t *__restrict__ tokens, int K, int L,
+                   int V, float c, int P, const Row0Part *__restrict__ stat_parts, int stat_P, RowStat *stats,
+                   int32_t *__restrict__ final_counter, double *__restrict__ s_part, double *__restrict__ e_part,
+                   const PendRow *__restrict__ pend, long long n_rows, int nlev, double c_rel)
+{
+    ot_sum_parts<uint16_t, true, PEND, true>(target, draft, tokens, K, L, V, c, P, stat_parts, stat_P, stats, final_counter, s_part, e_part, pend, n_rows, nlev, c_rel);
 }
 
 // The sum of a vector's terms, in pairs.  A thread adds it to what it has: term after term, a part of half as many workgroups would
@@ -600,18 +622,19 @@ k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, LevelArgs
             const T *rq = target + (bk * (L + 1) + row) * static_cast<long long>(V);
             const T *rp = draft + (bk * L + row) * static_cast<long long>(V);
             const int per = (n_units + parts - 1) / parts, lo = q * per, hi = lo + per < n_units ? lo + per : n_units;
+            const RowLoads<T, false> from_q(rq, V, hi, false), from_p(rp, V, hi, false);
             const float shift_q = sh.shift_q;
             const RatioConst rc(sh.C2_hi, sh.neg_kappa);
             constexpr int N = VEC ? Elem<T>::kPerVec : 1;
             float acc = 0.0f;
             if (ONE || sh.tab.n == 0) {
-                for_each_pair_from<T, VEC, false, kStatThreads>(FirstPairs(), rq, rp, V, lo, hi, 0, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+                for_each_pair_from<T, VEC, false, kStatThreads>(FirstPairs<false>(), from_q, from_p, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
                     float wq[N], w[N];
                     ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
                     acc += vector_sum(w);
                 });
             } else {
-                for_each_pair_from<T, VEC, false, kStatThreads>(FirstPairs(), rq, rp, V, lo, hi, 0, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+                for_each_pair_from<T, VEC, false, kStatThreads>(FirstPairs<false>(), from_q, from_p, V, lo, hi, [&](int, const float (&zq)[N], const float (&zp)[N]) {
                     float wq[N], w[N];
                     pending_weights(zq, zp, c, shift_q, sh.tab, rc, K, wq, w);
                     acc += vector_sum(w);
@@ -687,10 +710,10 @@ k_ot_sum(const T *__restrict__ target, const T *__restrict__ draft, const int32_
     const long long bk = idx / (L - 1);
     const T *rq = target + (bk * (L + 1) + i) * static_cast<long long>(V);
     const T *rp = draft + (bk * L + i) * static_cast<long long>(V);
-    const int shift = ODD ? odd_start(rq, rp, false) : 0, Vs = V + shift;              // (i >= 1: not a tensor's first row)
-    const int units = VEC ? row_vectors<T>(Vs) : V;
+    const int units = VEC ? row_vectors<T>(V) : V;
     constexpr bool kAhead = VEC && !PEND;         // (see first_pairs)
-    const FirstPairs first = first_pairs<T, kAhead, kStatThreads>(rq - shift, rp - shift, Vs, 0, units);
+    const RowLoads<T, ODD> from_q(rq, V, units, false), from_p(rp, V, units, false);   // (i >= 1: not a tensor's first row)
+    const FirstPairs<ODD> first = first_pairs<T, kAhead, kStatThreads>(from_q, from_p, 0, units);
     const RowStat st = stats[bk * L + i];
     // block likelihood ratio of the length-i block, from the rows before row i (their token
     // probabilities under the modified rows where levels are pending)
@@ -713,14 +736,14 @@ k_ot_sum(const T *__restrict__ target, const T *__restrict__ draft, const int32_
     const RatioConst rc(ratio_const(st.lse2_p, st.lse2_q, log2nu, c_rel) - sumN);
     float acc = 0.0f;
     if (PEND && sh_tab.n > 0) {                   // uniform over the workgroup
-        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, rq - shift, rp - shift, Vs, 0, units, shift, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, from_q, from_p, V, 0, units, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             pending_weights(zq, zp, c, shift_q, sh_tab, rc, K, wq, w);
 #pragma unroll
             for (int j = 0; j < N; ++j) acc += w[j];
         });
     } else {
-        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, rq - shift, rp - shift, Vs, 0, units, shift, [&](int, const float (&zq)[N], const float (&zp)[N]) {
+        for_each_pair_from<T, VEC, kAhead, kStatThreads>(first, from_q, from_p, V, 0, units, [&](int, const float (&zq)[N], const float (&zp)[N]) {
             float wq[N], w[N];
             ot_weights(zq, zp, c, shift_q, rc, K, wq, w);
 #pragma unroll
@@ -768,12 +791,13 @@ hipError_t launch_typed(const Problem &p)
     Row0Part *stat_part = reinterpret_cast<Row0Part *>(p.ws + p.lay.stat_part);
     if (stat_parts > 1) {
         const dim3 gs(static_cast<unsigned>(pairs * stat_parts), 2);
-        if (vec)
-            hipLaunchKernelGGL((k_row_stats_parts<T, true>), gs, dim3(kStatThreads), 0, p.stream, target, draft, p.tokens,
-                               p.L, p.V, p.c, stat_parts, stat_part);
-        else
-            hipLaunchKernelGGL((k_row_stats_parts<T, false>), gs, dim3(kStatThreads), 0, p.stream, target, draft, p.tokens,
-                               p.L, p.V, p.c, stat_parts, stat_part);
+#define SPECGBV_STATP_LAUNCH(VEC, ODD)                                                                              \
+    hipLaunchKernelGGL((k_row_stats_parts<T, VEC, ODD>), gs, dim3(kStatThreads), 0, p.stream, target, draft, p.tokens, p.L, p.V, \
+                       p.c, stat_parts, stat_part)
+        if (odd) SPECGBV_STATP_LAUNCH(true, kMayBeOdd);
+        else if (vec) SPECGBV_STATP_LAUNCH(true, false);
+        else SPECGBV_STATP_LAUNCH(false, false);
+#undef SPECGBV_STATP_LAUNCH
     } else {
         const dim3 g1(static_cast<unsigned>(pairs + p.pend_levels), 2);
 #define SPECGBV_STATS_LAUNCH(VEC, ODD)                                                                              \
@@ -837,14 +861,19 @@ hipError_t launch_typed(const Problem &p)
     const long long rows = static_cast<long long>(p.batch) * p.K * (p.L - 1);
     if (p.s_parts > 1) {                            // small batch: partial sums, added up by the final-token kernel
         const dim3 gq(static_cast<unsigned>(rows * p.s_parts));
-#define SPECGBV_OTP_LAUNCH(VEC, PEND)                                                                                 \
-    do {                                                                                                              \
-        hipLaunchKernelGGL((k_ot_sum_parts<T, VEC, PEND>), gq, dim3(kStatThreads), 0, p.stream, target, draft, p.tokens, \
-                           p.K, p.L, p.V, p.c, p.s_parts, stat_part, stat_parts, stats, counter, pend_part,            \
-                           reinterpret_cast<double *>(p.ws + p.lay.excess_part), pend, pairs, p.pend_levels, p.c_rel);  \
-    } while (0)
-        if (p.pend_levels > 0) { if (vec) SPECGBV_OTP_LAUNCH(true, true); else SPECGBV_OTP_LAUNCH(false, true); }
-        else { if (vec) SPECGBV_OTP_LAUNCH(true, false); else SPECGBV_OTP_LAUNCH(false, false); }
+#define SPECGBV_OTP_LAUNCH(KERNEL)                                                                                  \
+    hipLaunchKernelGGL(KERNEL, gq, dim3(kStatThreads), 0, p.stream, target, draft, p.tokens, p.K, p.L, p.V, p.c, p.s_parts, \
+                       stat_part, stat_parts, stats, counter, pend_part, reinterpret_cast<double *>(p.ws + p.lay.excess_part), \
+                       pend, pairs, p.pend_levels, p.c_rel)
+        if constexpr (kMayBeOdd) {
+            if (odd) {
+                if (p.pend_levels > 0) SPECGBV_OTP_LAUNCH((k_ot_sum_parts_odd<true>));
+                else SPECGBV_OTP_LAUNCH((k_ot_sum_parts_odd<false>));
+                return hipGetLastError();
+            }
+        }
+        if (p.pend_levels > 0) { if (vec) SPECGBV_OTP_LAUNCH((k_ot_sum_parts<T, true, true>)); else SPECGBV_OTP_LAUNCH((k_ot_sum_parts<T, false, true>)); }
+        else { if (vec) SPECGBV_OTP_LAUNCH((k_ot_sum_parts<T, true, false>)); else SPECGBV_OTP_LAUNCH((k_ot_sum_parts<T, false, false>)); }
 #undef SPECGBV_OTP_LAUNCH
         return hipGetLastError();
     }

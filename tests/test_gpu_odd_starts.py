@@ -1,6 +1,6 @@
 """bfloat16 rows that start at an odd entry are read from the entry in front of them on (two-pass schedule): the rows' first and
 last entries decide (drafted tokens there, and entries in front that would change every sum), with and without parts, and
-with tensors that themselves start at an odd entry."""
+with tensors that themselves start at an odd entry.  Where a row starts makes no difference to a bit of its results."""
 import numpy as np
 import pytest
 
@@ -34,26 +34,46 @@ def test_under_levels(B, K, L, V):
     check_pending(t, d, tok, 0.9, 4, 1, rng.normal(0, 0.5, (2, B)), rng.integers(0, L + 1, (2, B)).astype(np.int32), "odd starts %d" % V)
 
 
-@pytest.mark.parametrize("B,K,L,V", [(3, 3, 4, 4103), (1, 2, 4, 8199)])
-def test_tensors_that_start_at_an_odd_entry(B, K, L, V):
-    """The parity of every row is the other one; the sums are taken in another order of entries (float32 partial sums of
-    at most 32 terms a thread, 512 threads: 2e-6 of ln Z at most, and as much of s)."""
+def _run(tl, dl, tok, **how):
     import torch
     import paper_2604_25925_amd as sg
+    B, K, L, V = dl.shape
+    out = sg.specgbv_verify_ex(tl, dl, to_torch(tok), 0.9, 4, 1, algo="split", **how)
+    torch.cuda.synchronize()
+    return [o.cpu().numpy() for o in out[:3]], sg.specgbv_read_intermediates(out[3], B, K, L, V, 1)
+
+
+# (an even vocabulary, whose rows all start as the tensor does: with whole vectors, without, and in parts)
+@pytest.mark.parametrize("B,K,L,V", [(3, 3, 4, 4103), (1, 2, 4, 8199), (3, 3, 4, 4104), (3, 3, 4, 4098), (1, 2, 4, 8200), (1, 2, 4, 8194)])
+@pytest.mark.parametrize("levels", [0, 2])
+def test_tensors_that_start_at_an_odd_entry(B, K, L, V, levels):
+    """The parity of every row is the other one."""
+    import torch
 
     def run(shift):
         def moved(x):
             flat = torch.full((x.numel() + 1,), 100.0, dtype=x.dtype, device=x.device)      # (what lies in front of the tensor)
             flat[shift:shift + x.numel()] = x.reshape(-1)
             return flat[shift:shift + x.numel()].view(x.shape)
-        out = sg.specgbv_verify_ex(moved(tl), moved(dl), to_torch(tok), 0.9, 4, 1, algo="split")
-        torch.cuda.synchronize()
-        return [o.cpu().numpy() for o in out[:3]], sg.specgbv_read_intermediates(out[3], B, K, L, V, 1)
+        return _run(moved(tl), moved(dl), tok, pending=pend)
 
     t, d, tok = _inputs(B, K, L, V)
     tl, dl = to_torch(t), to_torch(d)
+    rng = np.random.default_rng(V)
+    pend = (torch.from_numpy(rng.normal(0, 0.5, (levels, B))).cuda(),
+            torch.from_numpy(rng.integers(0, L + 1, (levels, B)).astype(np.int32)).cuda()) if levels else None
     (o0, i0), (o1, i1) = run(0), run(1)
     for a, b in zip(o0, o1):
         assert np.array_equal(a, b)
+    for key in i0:
+        assert np.array_equal(i0[key], i1[key], equal_nan=True), key
+
+
+@pytest.mark.parametrize("B,K,L,V", [(2, 4, 3, 4101), (1, 3, 4, 8199), (20, 8, 3, 8193)])
+def test_equal_rows(B, K, L, V):
+    """Drafts that are copies of one another, whose rows start at even and odd entries in turn."""
+    t, d, tok = _inputs(B, K, L, V)
+    t, d, tok = (np.ascontiguousarray(np.repeat(x[:, :1], K, axis=1)) for x in (t, d, tok))
+    _, res = _run(to_torch(t), to_torch(d), tok)
     for key in ("lse_q", "lse_p", "log_nu", "s"):
-        assert np.allclose(i0[key], i1[key], rtol=2e-6, atol=2e-6, equal_nan=True), key
+        assert np.array_equal(res[key], np.repeat(res[key][:, :1], K, axis=1), equal_nan=True), key
