@@ -100,7 +100,7 @@ k_row_stats(const T *__restrict__ target, const T *__restrict__ draft,
         if (pair % (static_cast<long long>(K) * L) == 0)
             final_counter[pair / (static_cast<long long>(K) * L)] = 0;  // arrival counter of the final-token kernel
     }
-    // the level's entries of this row: empty beyond its count, else not there yet (k_pend_levels)
+    // the level's entries of this row: empty beyond its count, else not there yet (k_pend_norm)
     if (!is_draft && static_cast<int>(threadIdx.x) < nlev) {
         const bool modified = r < pend_count[static_cast<size_t>(threadIdx.x) * batch + bk / K];
         unsigned long long *const w = reinterpret_cast<unsigned long long *>(pend + threadIdx.x * n_rows + pair);
@@ -398,8 +398,11 @@ __device__ __forceinline__ float vector_sum(const float (&w)[N])
 // A unit needs the entries of the levels below its own for its row and for the rows of its draft in front of it.  k_row_stats has marked
 // the entries of modified rows as not there yet (all four words), so a unit looks for them until they are there.  They come from units of
 // lower numbers, that is of workgroups of lower index, and workgroups are dispatched in index order, so
-// what is waited for is running or has run.  Nothing relies on it: after `polls` looks a workgroup makes the entries itself, with
-// the parts and in the order that their units have (the same bits).
+// what is waited for is running or has run.  Nothing relies on it: after `looks` looks a workgroup makes the entries that are still
+// not there itself, one after the other (it looks again in front of each part), with the parts and in the order that their units
+// have (the same bits).  That is many times their units' work, so the looks have to outlast whatever they can be waiting for
+// (level_looks); 1024 of them did not: sixteen levels on all rows of 1 x 4 drafts of 17, V = 1000000 bfloat16 took 338 ms a call and
+// take 4.3 now, 4 x 4 drafts of 17 651 and 21, seven levels on 8 x 8 of 8, V = 256000 float32 9.6 and 2.5.
 //
 // What bounds a level: where its rows fill the chip, arithmetic; else latencies (load, sum, hand-over: 8 - 15 us) and, before, launches: a
 // kernel for every level, 3 us each, of which a call that updates its state in place makes L - 1, most of them of levels in which nothing is
@@ -410,13 +413,14 @@ __device__ __forceinline__ float vector_sum(const float (&w)[N])
 // The float64 constants are made by one wave, a level per lane, with the exponential's coefficients in LDS: as library calls of every
 // thread they took 142 registers, or 224 bytes of scratch at 80 (three workgroups per compute unit), which cost more than
 // the launches.
-constexpr unsigned long long kNotThere = ~0ull;        // (a NaN that no sum produces)
+constexpr unsigned long long kNotThere = ~0ull;        // (a NaN that no sum produces; see entry_store)
 constexpr unsigned long long kNoLevel = 0x8000000000000000ull;     // log2 N = -0.0: the level leaves the row as it is
 
 __device__ __forceinline__ void entry_store(PendRow *pr, double log2mu, double log2N, double tokadj, bool some)
 {
     unsigned long long *const w = reinterpret_cast<unsigned long long *>(pr);
     static_assert(sizeof(PendRow) == 32, "four words");
+    if (log2mu != log2mu) log2mu = __builtin_nan("");    // (a carried ratio may be any NaN, also the one that says not there)
     __hip_atomic_store(w, static_cast<unsigned long long>(__double_as_longlong(log2mu)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(w + 1, static_cast<unsigned long long>(__double_as_longlong(log2N)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(w + 2, static_cast<unsigned long long>(__double_as_longlong(tokadj)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -437,7 +441,8 @@ struct LevelArgs {
     PendRow *pend;                 // [nlev][n_rows]
     double *sums;                  // [n_rows][kSumSlots]: [level - from][most]
     long long n_rows;
-    int K, L, V, batch, polls;
+    int K, L, V, batch;
+    int looks;                     // at an entry that is not there yet, before a workgroup makes it itself
     int from, to, most;            // the levels of this launch; parts of a row at most
     int first_grid, grid;          // workgroups that share a level's rows: the first level's, any other's
     int first_resident, resident;
@@ -464,6 +469,10 @@ struct Levels {
     double sums[kPendParts];
     float shift_q, C2_hi, neg_kappa;
     int cnt[kMaxPend];                     // rows the levels modify
+    // (what only a unit that makes entries needs: kept here for want of scalar registers)
+    const PendRow *entries;                // of the draft
+    long long n_rows;
+    int looks;
     double exp2_coef[11];                  // (see exp2_from)
 };
 
@@ -538,6 +547,16 @@ k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, LevelArgs
         in.carry = ar.carry[static_cast<size_t>(l_) * batch + b];
         return in;
     };
+    // one look at a level's entry of row tr: whether it is there, and if so what it says
+    auto look = [&](const PendRow *pr, int tl, int tr) {
+        const unsigned long long mu = entry_load(pr, 0), n = entry_load(pr, 1), a = entry_load(pr, 2), f = entry_load(pr, 3);
+        if (mu == kNotThere || n == kNotThere || a == kNotThere || static_cast<unsigned>(f) == ~0u) return false;     // (f: flag and counter)
+        const int to = tl * kMaxRows + tr;
+        sh.mu[to] = __longlong_as_double(static_cast<long long>(mu));
+        sh.N[to] = __longlong_as_double(static_cast<long long>(f != 0ull ? n : kNoLevel));
+        sh.adj[to] = __longlong_as_double(static_cast<long long>(a));
+        return true;
+    };
     In in{};
     if constexpr (VEC) in = loads(level, r);      // (beside the entries; rows read entry by entry have no registers to spare)
     // What is summed: this unit's part, once; if an entry that it builds on does not appear, all parts of those entries first.
@@ -546,27 +565,22 @@ k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, LevelArgs
     if constexpr (!ONE) {
         bool none = false;
         for (int t = tid; t < level * (r + 1); t += kStatThreads) {
-            const int tl = t / (r + 1), tr = t - tl * (r + 1), to = tl * kMaxRows + tr;
-            const PendRow *const pr = ar.pend + tl * ar.n_rows + bk * L + tr;
-            unsigned long long mu = 0ull, n = 0ull, a = 0ull, f = 0ull;
+            const int tl = t / (r + 1), tr = t - tl * (r + 1);
             bool there = tl < ar.from;            // (a level of an earlier launch)
             if (there) {
-                const PendRow e = *pr;
-                mu = static_cast<unsigned long long>(__double_as_longlong(e.log2mu)); n = static_cast<unsigned long long>(__double_as_longlong(e.log2N));
-                a = static_cast<unsigned long long>(__double_as_longlong(e.tokadj)); f = e.flag != 0 ? 1ull : 0ull;
+                const PendRow e = ar.pend[tl * ar.n_rows + bk * L + tr];
+                sh.mu[tl * kMaxRows + tr] = e.log2mu; sh.adj[tl * kMaxRows + tr] = e.tokadj;
+                sh.N[tl * kMaxRows + tr] = e.flag != 0 ? e.log2N : -0.0;
             }
-            for (int look = 0; look < ar.polls && !there; ++look) {
-                mu = entry_load(pr, 0); n = entry_load(pr, 1); a = entry_load(pr, 2); f = entry_load(pr, 3);
-                there = mu != kNotThere && n != kNotThere && a != kNotThere && static_cast<unsigned>(f) != ~0u;     // (f: flag and counter)
+            for (int n = 0; n < ar.looks && !there; ++n) {
+                there = look(ar.pend + tl * ar.n_rows + bk * L + tr, tl, tr);
                 if (!there) __builtin_amdgcn_s_sleep(2);
             }
             none = none || !there;
-            sh.mu[to] = __longlong_as_double(static_cast<long long>(mu));
-            sh.N[to] = __longlong_as_double(static_cast<long long>(f != 0ull ? n : kNoLevel));
-            sh.adj[to] = __longlong_as_double(static_cast<long long>(a));
         }
         alone = __syncthreads_or(none) != 0;
         if (alone) {                              // (normally none is missing)
+            if (tid == 0) { sh.entries = ar.pend + bk * L; sh.n_rows = ar.n_rows; sh.looks = ar.looks; }
             if (tid < level) {
                 const int cnt = ar.count[static_cast<size_t>(tid) * batch + b];
                 sh.cnt[tid] = cnt < 0 ? 0 : (cnt > L ? L : cnt);
@@ -578,7 +592,17 @@ k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, LevelArgs
     }
     for (;;) {                                    // (uniform, as everything here; normally one pass)
         const bool own = ONE || (l == level && row == r);
-        if (own || row < sh.cnt[l]) {
+        bool there = false;
+        if constexpr (!ONE) {
+            if (!own) {                           // it may have come meanwhile
+                if (tid == 0) sh_last = sh.looks > 0 && look(sh.entries + l * sh.n_rows + row, l, row);
+                __syncthreads();
+                there = sh_last != 0;
+            }
+        }
+        if (there) {
+            // (sh has it)
+        } else if (own || row < sh.cnt[l]) {
             if (tid < kWave) {
                 // block ratio in front of the row: the carried one continued along the drafted tokens with the distribution this level
                 // modifies (the target rows as modified by the levels below)
@@ -683,7 +707,7 @@ k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, LevelArgs
         }
         if (own) break;
         __syncthreads();
-        if (row < sh.cnt[l] && q + 1 < parts) ++q;
+        if (!there && row < sh.cnt[l] && q + 1 < parts) ++q;
         else {
             q = 0;
             if (++row > r) {
@@ -771,6 +795,16 @@ int row_parts(long long workgroups_per_row_unit, int V)
     return static_cast<int>(want < 4 ? 1 : (want > kRowParts ? kRowParts : want));
 }
 
+// Looks that a unit of the levels takes at an entry, about a microsecond each: as many as elsewhere, and as many again for every
+// sixteen steps (of a workgroup over a row's `units`) of all levels.  A unit waits for the units of the levels below it, one
+// after the other, each at most a whole row long; a step under sixteen levels takes 8 us at most with three workgroups on a compute
+// unit, and here has 64.
+int level_looks(int units, int levels)
+{
+    const long long n = static_cast<long long>(wait_polls()) * (1 + static_cast<long long>(levels) * (units / kStatThreads) / 16);
+    return static_cast<int>(n < 1 << 30 ? n : 1 << 30);
+}
+
 template <typename T>
 hipError_t launch_typed(const Problem &p)
 {
@@ -826,7 +860,8 @@ hipError_t launch_typed(const Problem &p)
         LevelArgs la;
         la.carry = p.pend_carry; la.count = p.pend_count; la.off = pend_off;
         la.stats = stats; la.pend = pend; la.sums = reinterpret_cast<double *>(stat_part);
-        la.n_rows = pairs; la.K = p.K; la.L = p.L; la.V = p.V; la.batch = p.batch; la.polls = wait_polls(); la.c = p.c;
+        la.n_rows = pairs; la.K = p.K; la.L = p.L; la.V = p.V; la.batch = p.batch; la.c = p.c;
+        la.looks = level_looks(vec ? row_vectors<T>(p.V) : p.V, p.pend_levels);
         const long long least = pairs > 2 * cu ? pairs : 2 * cu;
         long long grid = least;
         if (!p.state_count && row_vectors<T>(p.V) >= 6000 && 2 * pairs > (Elem<T>::kPerVec == 8 ? cu : 3 * cu) && 2 * pairs < 7 * cu)

@@ -31,8 +31,9 @@ def test_given_levels(B, K, L, V, dtype, levels, monkeypatch):
     if levels < 4:                                  # (a few prefixes: check_pending allows one that the oracle cannot decide either)
         check_pending(t, d, tok, 0.8, 4, 1, carry, count, "levels %s" % ((B, K, L, V, dtype, levels),), gpu_slice=list(range(min(B, 8))))
     waited = run_gpu(t, d, tok, 0.8, 4, 1, pending=(carry, count))
-    monkeypatch.setenv("SPECGBV_EXCESS_POLLS", "0")
-    _same(waited, run_gpu(t, d, tok, 0.8, 4, 1, pending=(carry, count)))
+    for polls in ("0", "1"):                        # (all entries made alone; those that are not there yet)
+        monkeypatch.setenv("SPECGBV_EXCESS_POLLS", polls)
+        _same(waited, run_gpu(t, d, tok, 0.8, 4, 1, pending=(carry, count)))
 
 
 @pytest.mark.parametrize("B,K,L,V,dtype,full", [(4, 3, 6, 4104, "f32", False), (65, 4, 7, 520, "f32", False), (65, 4, 7, 520, "f32", True),
@@ -45,7 +46,7 @@ def test_levels_of_a_state(B, K, L, V, dtype, full, monkeypatch):
     if full:
         count[:] = L
     given = run_gpu(t, d, tok, 0.8, 4, 1, pending=(carry, count))
-    for polls in (None, "0"):
+    for polls in (None, "0", "1"):
         if polls is not None:
             monkeypatch.setenv("SPECGBV_EXCESS_POLLS", polls)
         state = _state_tensor(carry, count, B)
@@ -54,3 +55,61 @@ def test_levels_of_a_state(B, K, L, V, dtype, full, monkeypatch):
         got = dict(accepted_len=acc.cpu().numpy(), accepted_draft_idx=f.cpu().numpy(), out_tokens=out.cpu().numpy())
         got.update(sg.specgbv_read_intermediates(ws, B, K, L, V, 1 if dtype == "bf16" else 0))
         _same(got, given)
+
+
+def _all_rows_under_all_levels(B, K, L, V, polls, calls=3):
+    """Milliseconds of a call (the fastest of a few) whose state's L - 1 levels modify every row."""
+    import os
+    import torch
+    import paper_2604_25925_amd as sg
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(V)
+    t = torch.empty((B, K, L + 1, V), dtype=torch.bfloat16, device="cuda").normal_(0.0, 3.0, generator=gen)
+    d = torch.empty((B, K, L, V), dtype=torch.bfloat16, device="cuda").normal_(0.0, 3.0, generator=gen)
+    tok = torch.randint(V, (B, K, L), dtype=torch.int32, device="cuda", generator=gen)
+    start = _state_tensor(np.full((L - 1, B), 0.5), np.full((L - 1, B), L, np.int32), B)
+    best = []
+    for p in polls:
+        if p is None:
+            os.environ.pop("SPECGBV_EXCESS_POLLS", None)
+        else:
+            os.environ["SPECGBV_EXCESS_POLLS"] = p
+        times = []
+        for _ in range(calls + 1):
+            state = start.clone()
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            sg.specgbv_verify_ex(t, d, tok, 0.8, 4, 1, pending_state=state)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        best.append(min(times[1:]))
+    os.environ.pop("SPECGBV_EXCESS_POLLS", None)
+    return best
+
+
+# (a unit waits for fifteen levels, two milliseconds and more; for six, of the largest vocabularies)
+@pytest.mark.parametrize("B,K,L,V", [(1, 4, 17, 1000000), (8, 8, 8, 256000)])
+def test_long_rows_are_waited_for(B, K, L, V):
+    """The looks outlast the levels below: no longer than with a thousand times as many (130 and 2.7 times as long where they did not)."""
+    usual, many = _all_rows_under_all_levels(B, K, L, V, (None, "1048576"))
+    assert usual < 1.5 * many
+
+
+def test_entries_made_alone_cost_little():
+    """With next to no looks a workgroup makes only what is still not there: twice the time (all of it again: 75 times)."""
+    usual, few = _all_rows_under_all_levels(1, 4, 17, 128256, (None, "1"))
+    assert few < 8 * usual
+
+
+@pytest.mark.parametrize("polls", [None, "1"])
+def test_ratios_that_are_no_numbers(polls, monkeypatch):
+    """A carried NaN with all bits set, which is what an entry that is not there yet holds, as any other NaN."""
+    if polls:
+        monkeypatch.setenv("SPECGBV_EXCESS_POLLS", polls)
+    t, d, tok, carry, count = _case(3, 2, 5, 2049 * 4, "f32", 3)
+    count[:, 1] = 5
+    carry[0, 1] = np.nan
+    plain = run_gpu(t, d, tok, 0.8, 4, 1, pending=(carry, count))
+    carry[0, 1] = np.array([~np.uint64(0)]).view(np.float64)[0]
+    _same(plain, run_gpu(t, d, tok, 0.8, 4, 1, pending=(carry, count)))
