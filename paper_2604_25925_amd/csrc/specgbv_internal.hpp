@@ -33,13 +33,13 @@ struct Workspace {
     size_t pend;       // PendRow [kMaxPend][B*K*L]  rows under pending modifications (written only by calls that carry some)
     size_t pend_off;   // int32  [kMaxPend][B+1]  per level: rows the level modifies in the prefixes before b (two-pass schedule)
     size_t pend_part;  // double [B*K*L][kPendParts]  partial sums of Eq. (hik)
-    size_t spare;      // int32  [B*K*L]  (not used: what callers allocate, and which shapes the static scratch holds, stays as it was)
     size_t stat_part;  // Row0Part [B*K*L][2][kRowParts]  partial row statistics (two-pass schedule, small batches; with pending
-                       //             levels the partial normalisers of their rows; the rows
+                       //             levels the partial normalisers of their rows, there or in `later`; the rows
                        //             schedule keeps its parts' log2-normalisers there, [B*K*L][kRowParts][2][kWordsPerPart] words)
     size_t row0;       // Row0Part [B][2][kRow0Parts]  partial statistics of the rows 0 a prefix's drafts share (chain schedule)
     size_t later;      // int32 [workgroups][1 + rows a workgroup sums]  chain schedule: per workgroup, the number of rows
-                       //             whose Eq. (hik) sum is taken again without cancellation, then their row indices
+                       //             whose Eq. (hik) sum is taken again without cancellation, then their row indices (and room
+                       //             for another int32 [B*K*L])
     size_t kseq_pos;   // int32 [2][B*L]  comparison verifier: drafts retained at each position, and the lowest of them
     size_t total;
     int nseg;

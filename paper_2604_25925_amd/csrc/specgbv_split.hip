@@ -27,7 +27,7 @@ namespace {
 
 constexpr int kStatThreads = 512;
 constexpr int kMaxRows = 64;         // rows of a draft (L <= 62)
-static_assert(kRowParts <= kPendParts, "the partial Eq. (hik) sums use the level passes' buffer");
+static_assert(kRowParts <= kPendParts, "a row's partial Eq. (hik) sums have kPendParts places");
 
 // What the level passes need before they start (pending modifications only): per level l and prefix b the
 // number of rows the level modifies in the prefixes before b, K * sum_{b' < b} clamp(count[l][b'], 0, L), with the
@@ -402,7 +402,7 @@ __device__ __forceinline__ float vector_sum(const float (&w)[N])
 // not there itself, one after the other (it looks again in front of each part), with the parts and in the order that their units
 // have (the same bits).  That is many times their units' work, so the looks have to outlast whatever they can be waiting for
 // (level_looks); 1024 of them did not: sixteen levels on all rows of 1 x 4 drafts of 17, V = 1000000 bfloat16 took 338 ms a call and
-// take 4.3 now, 4 x 4 drafts of 17 651 and 21, seven levels on 8 x 8 of 8, V = 256000 float32 9.6 and 2.5.
+// take 2.7 now, 4 x 4 drafts of 17 651 and 21, seven levels on 8 x 8 of 8, V = 256000 float32 9.6 and 2.5.
 //
 // What bounds a level: where its rows fill the chip, arithmetic; else latencies (load, sum, hand-over: 8 - 15 us) and, before, launches: a
 // kernel for every level, 3 us each, of which a call that updates its state in place makes L - 1, most of them of levels in which nothing is
@@ -431,32 +431,30 @@ __device__ __forceinline__ unsigned long long entry_load(const PendRow *pr, int 
     return __hip_atomic_load(reinterpret_cast<const unsigned long long *>(pr) + word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-constexpr int kSumSlots = 2 * kRowParts * sizeof(Row0Part) / sizeof(double);      // sums of a row's parts, all levels of a launch together
-
 struct LevelArgs {
     const double *carry;           // [nlev][batch]
     const int32_t *count;          // [nlev][batch]
     const int32_t *off;            // [nlev][batch + 1] rows a level modifies in the prefixes before
     const RowStat *stats;
     PendRow *pend;                 // [nlev][n_rows]
-    double *sums;                  // [n_rows][kSumSlots]: [level - from][most]
+    double *sums;                  // [slots]: a unit's, by its place in the line
     long long n_rows;
     int K, L, V, batch;
     int looks;                     // at an entry that is not there yet, before a workgroup makes it itself
+    int slots;                     // >= kPendParts * n_rows
     int from, to, most;            // the levels of this launch; parts of a row at most
     int first_grid, grid;          // workgroups that share a level's rows: the first level's, any other's
-    int first_resident, resident;
+    int resident;                  // of a grid that is larger than the number of row pairs
     float c;
 };
 
 // Workgroups that share a row of a level of T rows (three or more of them only as far as all are resident at once: a second
-// round costs more than larger parts).
+// round costs more than larger parts; the first level's grid is no larger than that).
 __device__ __forceinline__ int level_parts(const LevelArgs &ar, int level, int T)
 {
     if (T <= 0) return 0;
-    const int grid = level == 0 ? ar.first_grid : ar.grid, resident = level == 0 ? ar.first_resident : ar.resident;
-    int P = grid / T;                                  // >= 1: the modified rows are among the grid's rows
-    if (T * P > resident && T * 3 <= resident) P = resident / T;
+    int P = (level == 0 ? ar.first_grid : ar.grid) / T;          // >= 1: the modified rows are among the grid's rows
+    if (level > 0 && T * P > ar.resident && T * 3 <= ar.resident) P = ar.resident / T;
     return P > ar.most ? ar.most : P;
 }
 
@@ -520,7 +518,12 @@ k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, LevelArgs
         const int T_l = lane >= ar.from && lane < ar.to ? ar.off[lane * (batch + 1) + batch] : 0;
         if (!__ballot(T_l > 0)) return;           // uniform over the workgroup
         P_l = level_parts(ar, lane, T_l);
-        const int end = static_cast<int>(wave_inclusive_sum(static_cast<double>(T_l) * static_cast<double>(P_l)));
+        int end = static_cast<int>(wave_inclusive_sum(static_cast<double>(T_l) * static_cast<double>(P_l)));
+        if (__builtin_amdgcn_readlane(end, kWave - 1) > ar.slots) {       // uniform (many given levels on a few short drafts)
+            const int most = ar.slots / static_cast<int>(wave_sum(static_cast<double>(T_l)));
+            P_l = P_l < most ? P_l : most;
+            end = static_cast<int>(wave_inclusive_sum(static_cast<double>(T_l) * static_cast<double>(P_l)));
+        }
         const unsigned long long behind = __ballot(at < end);
         if (!behind) return;                      // uniform
         level = __ffsll(static_cast<long long>(behind)) - 1;
@@ -668,7 +671,7 @@ k_pend_norm(const T *__restrict__ target, const T *__restrict__ draft, LevelArgs
             if (own && parts > 1) {
                 // the store is a device-scope access; the wait lasts until it has been performed, so the counter update that
                 // follows (same thread) cannot be seen before it
-                unsigned long long *const sums = reinterpret_cast<unsigned long long *>(ar.sums + pair * kSumSlots + (level - ar.from) * ar.most);
+                unsigned long long *const sums = reinterpret_cast<unsigned long long *>(ar.sums + (blockIdx.x - part));
                 if (tid == 0) {
                     __hip_atomic_store(sums + part, static_cast<unsigned long long>(__double_as_longlong(S)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                     wait_for_stores();
@@ -859,7 +862,7 @@ hipError_t launch_typed(const Problem &p)
         const long long cu = compute_units();
         LevelArgs la;
         la.carry = p.pend_carry; la.count = p.pend_count; la.off = pend_off;
-        la.stats = stats; la.pend = pend; la.sums = reinterpret_cast<double *>(stat_part);
+        la.stats = stats; la.pend = pend;
         la.n_rows = pairs; la.K = p.K; la.L = p.L; la.V = p.V; la.batch = p.batch; la.c = p.c;
         la.looks = level_looks(vec ? row_vectors<T>(p.V) : p.V, p.pend_levels);
         const long long least = pairs > 2 * cu ? pairs : 2 * cu;
@@ -867,9 +870,13 @@ hipError_t launch_typed(const Problem &p)
         if (!p.state_count && row_vectors<T>(p.V) >= 6000 && 2 * pairs > (Elem<T>::kPerVec == 8 ? cu : 3 * cu) && 2 * pairs < 7 * cu)
             grid = 2 * pairs <= 3 * cu ? 3 * cu : 7 * cu / 2;
         // (three per unit are resident at once; not with every grid that a row pair each asks for)
-        const auto resident = [&](long long g) { return g > pairs ? static_cast<int>(3 * cu) : 0x7fffffff; };
         la.first_grid = static_cast<int>(least); la.grid = static_cast<int>(grid);
-        la.first_resident = resident(least); la.resident = resident(grid);
+        la.resident = grid > pairs ? static_cast<int>(3 * cu) : 0x7fffffff;
+        // The parts' sums stand where this call keeps nothing else: 64 a row pair, or, where that is not enough for sixteen parts at every
+        // level of a few drafts, in the chain schedule's lists.
+        const size_t here = p.lay.row0 - p.lay.stat_part, there = p.lay.kseq_pos - p.lay.later, room = here > there ? here : there;
+        la.sums = here > there ? reinterpret_cast<double *>(stat_part) : reinterpret_cast<double *>(p.ws + p.lay.later);
+        la.slots = static_cast<int>(room / sizeof(double) < 0x7fffffff ? room / sizeof(double) : 0x7fffffff);
         // Levels per launch.  Up to six rows per compute unit: all of the library's own (L - 1, most of them empty; an iteration once the
         // state has settled, each level its own launch / together: 30 x 6 drafts of 8, V = 16000 240 / 215 us, 48 x 4 of 8, V = 8000 177 / 155,
         // 24 x 8 of 8, V = 32000 float32 298 / 271, 1 x 4 of 8, V = 128256 62 / 56), and all that are given unless rows are long (two levels
@@ -879,10 +886,17 @@ hipError_t launch_typed(const Problem &p)
         // 128 x 16 542 / 596; three iterations with 128 x 8 of 8, V = 8000 875 / 916.  All but the first in one grid whose workgroups take
         // as many units as there are: 789 there, but 269 against 207 for a settled state of 64 x 4 of 8, V = 8000 and 2667 against
         // 952 for 32 x 8 of 8, V = 128256: the units of a level stand in a few workgroups, for which all the others wait).
+        // Parts of a row: sixteen at most, and of levels that are launched together more than eight only where every thread of each part
+        // has two vectors of it: each unit holds a place while it waits, and short ones take no less time than these.  A settled state
+        // in sixteen parts / as here: 24 x 8 of 8, V = 32000 float32 274.1 / 267.1, 1 x 4 of 17, V = 32000 bfloat16 100.7 / 94.4, 4 x 4 of 12,
+        // V = 32000 float32 169.1 / 162.6, 8 x 4 of 8, V = 128256 bfloat16 178.6 / 179.1.  (In 64 parts for all levels of the launch,
+        // whether they modify a row or not: 268.5, 92.8, 174.8, 180.7; with all levels alive 1 x 4 of 16, V = 128256 619 against 388,
+        // 2 x 3 of 12, V = 256000 618 against 441.)
         const bool small = pairs <= 6 * cu;
         for (la.from = 0; la.from < p.pend_levels; la.from = la.to) {
             la.to = small && (p.state_count || row_vectors<T>(p.V) < 6000) ? p.pend_levels : la.from + 1;
-            la.most = kSumSlots / (la.to - la.from) < kPendParts ? kSumSlots / (la.to - la.from) : kPendParts;
+            const int steps = (vec ? row_vectors<T>(p.V) : p.V) / (2 * kStatThreads);
+            la.most = la.to - la.from < 2 || steps > kPendParts ? kPendParts : (steps > 8 ? steps : 8);
             const dim3 gp(static_cast<unsigned>((la.from == 0 ? least : grid) + (la.to - la.from - 1) * grid));
 #define SPECGBV_PEND_LAUNCH(VEC, ONE) hipLaunchKernelGGL((k_pend_norm<T, VEC, ONE>), gp, dim3(kStatThreads), 0, p.stream, target, draft, la)
             if (la.to == 1) { if (vec) SPECGBV_PEND_LAUNCH(true, true); else SPECGBV_PEND_LAUNCH(false, true); }

@@ -36,6 +36,7 @@ def test_given_levels(B, K, L, V, dtype, levels, monkeypatch):
         _same(waited, run_gpu(t, d, tok, 0.8, 4, 1, pending=(carry, count)))
 
 
+# (72 row pairs: together; the others by level)
 @pytest.mark.parametrize("B,K,L,V,dtype,full", [(4, 3, 6, 4104, "f32", False), (65, 4, 7, 520, "f32", False), (65, 4, 7, 520, "f32", True),
                                                  (130, 3, 5, 1030, "bf16", True)])
 def test_levels_of_a_state(B, K, L, V, dtype, full, monkeypatch):
@@ -55,6 +56,63 @@ def test_levels_of_a_state(B, K, L, V, dtype, full, monkeypatch):
         got = dict(accepted_len=acc.cpu().numpy(), accepted_draft_idx=f.cpu().numpy(), out_tokens=out.cpu().numpy())
         got.update(sg.specgbv_read_intermediates(ws, B, K, L, V, 1 if dtype == "bf16" else 0))
         _same(got, given)
+
+
+def _compute_units():
+    import torch
+    return torch.cuda.get_device_properties(0).multi_processor_count
+
+
+@pytest.mark.parametrize("V,dtype", [(1032, "bf16"), (520, "f32")])
+@pytest.mark.parametrize("over", [0, 1])
+def test_as_many_rows_as_are_launched_together(V, dtype, over, monkeypatch):
+    """Five levels that modify every row of as many row pairs as their levels are launched together for, six per compute unit (twice
+    what is resident at once), and of a prefix more, launched by level: given and as a state, and, of some prefixes, against the oracle."""
+    import torch
+    import paper_2604_25925_amd as sg
+    K, L, levels = 4, 6, 5
+    B = 6 * _compute_units() // (K * L) + over
+    t, d, tok, _, _ = _case(B, K, L, V, dtype, levels)
+    carry = np.random.default_rng(V).normal(2.0, 0.8, (levels, B))
+    count = np.full((levels, B), L, np.int32)
+    check_pending(t, d, tok, 0.8, 4, 1, carry, count, "all rows under five levels %s" % ((B, V, dtype),), gpu_slice=list(range(0, B, 11)))
+    given = run_gpu(t, d, tok, 0.8, 4, 1, pending=(carry, count))
+    for polls in (None, "0", "1"):
+        if polls is not None:
+            monkeypatch.setenv("SPECGBV_EXCESS_POLLS", polls)
+        acc, f, out, ws = sg.specgbv_verify_ex(to_torch(t), to_torch(d), to_torch(tok), 0.8, 4, 1, pending_state=_state_tensor(carry, count, B))
+        torch.cuda.synchronize()
+        got = dict(accepted_len=acc.cpu().numpy(), accepted_draft_idx=f.cpu().numpy(), out_tokens=out.cpu().numpy())
+        got.update(sg.specgbv_read_intermediates(ws, B, K, L, V, 1 if dtype == "bf16" else 0))
+        _same(got, given)
+
+
+def test_empty_levels_take_no_parts():
+    """One level of a state of eight, seven of them empty: its rows are shared among as many workgroups as those of the level alone
+    (sixteen, of 1088 vectors each), which the bits of its normalisers show."""
+    import torch
+    import paper_2604_25925_amd as sg
+    B, K, L, V = 1, 2, 9, 8 * 16 * 1088
+    t, d, tok, carry, count = _case(B, K, L, V, "bf16", 1)
+    count[:] = 4
+    alone = run_gpu(t, d, tok, 0.8, 4, 1, pending=(carry, count))
+    ws = sg.specgbv_verify_ex(to_torch(t), to_torch(d), to_torch(tok), 0.8, 4, 1, pending_state=_state_tensor(carry, count, B))[3]
+    torch.cuda.synchronize()
+    got = sg.specgbv_read_intermediates(ws, B, K, L, V, 1)
+    for key in ("lse_q", "log_nu", "s", "h"):
+        assert np.array_equal(got[key], alone[key], equal_nan=True), key
+
+
+@pytest.mark.parametrize("B,K,L,levels", [(1, 8, 2, 16), (1, 16, 1, 16), (2, 1, 2, 16), (1, 4, 17, 16)])
+def test_room_for_the_parts_sums(B, K, L, levels, monkeypatch):
+    """As many parts as fit: all levels' units of the first two have no room for eight parts a row, those of the others have."""
+    t, d, tok, carry, count = _case(B, K, L, 8200, "bf16", levels)
+    count[:] = L
+    check_pending(t, d, tok, 0.8, 4, 1, carry[:2] + 1.5, count[:2], "room %s" % ((B, K, L),))
+    waited = run_gpu(t, d, tok, 0.8, 4, 1, pending=(carry, count))
+    for polls in ("0", "1"):
+        monkeypatch.setenv("SPECGBV_EXCESS_POLLS", polls)
+        _same(waited, run_gpu(t, d, tok, 0.8, 4, 1, pending=(carry, count)))
 
 
 def _all_rows_under_all_levels(B, K, L, V, polls, calls=3):
