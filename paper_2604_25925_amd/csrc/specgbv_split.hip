@@ -887,16 +887,18 @@ hipError_t launch_typed(const Problem &p)
         // as many units as there are: 789 there, but 269 against 207 for a settled state of 64 x 4 of 8, V = 8000 and 2667 against
         // 952 for 32 x 8 of 8, V = 128256: the units of a level stand in a few workgroups, for which all the others wait).
         // Parts of a row: sixteen at most, and of levels that are launched together more than eight only where every thread of each part
-        // has two vectors of it: each unit holds a place while it waits, and short ones take no less time than these.  A settled state
+        // has two vectors of it, and more than four only where a row has two for every thread of one workgroup: each unit holds a place
+        // while it waits, and short ones take no less time than these.  A settled state
         // in sixteen parts / as here: 24 x 8 of 8, V = 32000 float32 274.1 / 267.1, 1 x 4 of 17, V = 32000 bfloat16 100.7 / 94.4, 4 x 4 of 12,
         // V = 32000 float32 169.1 / 162.6, 8 x 4 of 8, V = 128256 bfloat16 178.6 / 179.1.  (In 64 parts for all levels of the launch,
         // whether they modify a row or not: 268.5, 92.8, 174.8, 180.7; with all levels alive 1 x 4 of 16, V = 128256 619 against 388,
-        // 2 x 3 of 12, V = 256000 618 against 441.)
+        // 2 x 3 of 12, V = 256000 618 against 441.)  Short rows in eight, five, four parts: 10 x 8 of 12, V = 3000 float32 125.2, 123.0, 121.5,
+        // 40 x 4 of 8, V = 8000 bfloat16 129.2, 125.3, 123.0, 2 x 4 of 8 78.2, 76.8, 73.9, 2 x 2 of 16, V = 6000 168.5 and 149.5 in four.
         const bool small = pairs <= 6 * cu;
         for (la.from = 0; la.from < p.pend_levels; la.from = la.to) {
             la.to = small && (p.state_count || row_vectors<T>(p.V) < 6000) ? p.pend_levels : la.from + 1;
             const int steps = (vec ? row_vectors<T>(p.V) : p.V) / (2 * kStatThreads);
-            la.most = la.to - la.from < 2 || steps > kPendParts ? kPendParts : (steps > 8 ? steps : 8);
+            la.most = la.to - la.from < 2 || steps > kPendParts ? kPendParts : (steps > 8 ? steps : (steps > 0 ? 8 : 4));
             const dim3 gp(static_cast<unsigned>((la.from == 0 ? least : grid) + (la.to - la.from - 1) * grid));
 #define SPECGBV_PEND_LAUNCH(VEC, ONE) hipLaunchKernelGGL((k_pend_norm<T, VEC, ONE>), gp, dim3(kStatThreads), 0, p.stream, target, draft, la)
             if (la.to == 1) { if (vec) SPECGBV_PEND_LAUNCH(true, true); else SPECGBV_PEND_LAUNCH(false, true); }

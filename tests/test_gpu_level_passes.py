@@ -9,7 +9,8 @@ from test_gpu_pending import _state_tensor, check_pending
 pytestmark = pytest.mark.gpu
 
 # B, K, L, V, dtype, levels
-TOGETHER = [(3, 2, 5, 2049 * 4, "f32", 3), (5, 3, 4, 1029, "bf16", 2), (2, 2, 6, 4104, "bf16", 16)]
+TOGETHER = [(3, 2, 5, 2049 * 4, "f32", 3), (5, 3, 4, 1029, "bf16", 2), (2, 2, 6, 4104, "bf16", 16),
+            (4, 2, 4, 8 * 1023, "bf16", 2), (4, 2, 4, 8 * 1024, "bf16", 2)]       # (four parts a row, eight)
 BY_LEVEL = [(65, 4, 6, 1032, "bf16", 3), (2, 1, 3, 48008, "bf16", 2)]
 
 
