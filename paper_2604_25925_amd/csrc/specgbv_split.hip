@@ -855,7 +855,8 @@ hipError_t launch_typed(const Problem &p)
         // where that takes long (long rows, and the levels below them to be applied to every entry) the grid is large enough for
         // two, and has three per unit: 16 x 4 of 8, V = 128256 bfloat16 under three levels two / three / four per unit / as here
         // 271 / 259 / 254 / 246, 9 x 8 of 8, V = 129472 304 / 277 / 282 / 276, 14 x 5 of 8, V = 100000 245 / 233 / 229 / 222, 30 x 2 of
-        // 8, V = 128256 under two 207 / 194 / 199 / 193.  Not the first level (16 x 4 of 8 144 / 145 / 148), not where the levels are
+        // 8, V = 128256 under two 207 / 194 / 199 / 193.  Not the first level, although four workgroups of its instance are resident on a
+        // unit (16 x 4 of 8 148.4 / 149.3 / 149.6, 16 x 4 of 6, V = 70000 float32 120.7 / 122.9 / 121.5), not where the levels are
         // the library's own, most of which are empty (two iterations, 16 x 4 of 8, V = 64000 204 / 205 / 212), not of shorter rows (20 x 4
         // of 8, V = 8000 float32 under two levels 61.7 / 62.0 / 67.2), and in float32, whose sweeps are shorter, only where two per
         // unit are not enough for two workgroups a row (10 x 8 of 4, V = 70000 127 / 130 / 135, 9 x 8 of 8, V = 64000 234 / 223 / 230).

@@ -8,7 +8,7 @@ from test_gpu_pending import _state_tensor, check_pending
 
 pytestmark = pytest.mark.gpu
 
-# B, K, L, V, dtype, levels
+# B, K, L, V, dtype, levels: launched together up to six row pairs per compute unit, and of given levels up to 6000 vectors a row
 TOGETHER = [(3, 2, 5, 2049 * 4, "f32", 3), (5, 3, 4, 1029, "bf16", 2), (2, 2, 6, 4104, "bf16", 16),
             (4, 2, 4, 8 * 1023, "bf16", 2), (4, 2, 4, 8 * 1024, "bf16", 2)]       # (four parts a row, eight)
 BY_LEVEL = [(65, 4, 6, 1032, "bf16", 3), (2, 1, 3, 48008, "bf16", 2)]
@@ -37,13 +37,14 @@ def test_given_levels(B, K, L, V, dtype, levels, monkeypatch):
         _same(waited, run_gpu(t, d, tok, 0.8, 4, 1, pending=(carry, count)))
 
 
-# (72 row pairs: together; the others by level)
-@pytest.mark.parametrize("B,K,L,V,dtype,full", [(4, 3, 6, 4104, "f32", False), (65, 4, 7, 520, "f32", False), (65, 4, 7, 520, "f32", True),
-                                                 (130, 3, 5, 1030, "bf16", True)])
-def test_levels_of_a_state(B, K, L, V, dtype, full, monkeypatch):
-    """As given levels; full: every level modifies every row."""
+@pytest.mark.parametrize("B,K,L,V,dtype,full,together", [(4, 3, 6, 4104, "f32", False, True), (65, 4, 7, 520, "f32", False, False),
+                                                          (65, 4, 7, 520, "f32", True, False), (130, 3, 5, 1030, "bf16", True, False),
+                                                          (40, 4, 7, 1032, "bf16", True, True)])
+def test_levels_of_a_state(B, K, L, V, dtype, full, together, monkeypatch):
+    """As given levels; full: every level modifies every row.  together: there are as few row pairs as are launched together."""
     import torch
     import paper_2604_25925_amd as sg
+    assert (B * K * L <= 6 * _compute_units()) == together
     t, d, tok, carry, count = _case(B, K, L, V, dtype, L - 1)
     if full:
         count[:] = L
