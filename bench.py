@@ -211,7 +211,7 @@ def bench_iterate(a, w, sg, torch, sets, ws, out):
         "roofline": {"bound": "hbm", "achieved": achieved, "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": achieved / HBM_PEAK_GBS,
                      "traffic": committed_traffic("iterate_" + w.name) if len(sets) == 1 else None,
-                     "kernel": "k_row_stats + k_pend_norm (all levels) + k_ot_sum + k_final (whole call)",
+                     "kernel": "k_row_stats + k_pend_norm (each level) + k_ot_sum + k_final (whole call)",
                      "kernel_ms_avg": avg, "kernel_ms_min": ker[0], "algorithmic_bytes_per_launch": bytes_},
     }
 
