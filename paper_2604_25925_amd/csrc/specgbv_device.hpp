@@ -550,8 +550,10 @@ __device__ __forceinline__ void mask_repeated(float (&z)[N], int v, int V)
 // which nothing belongs to it: its vectors are loaded as they lie.
 // Us a call of the two-pass schedule, loaded as they lie / every lane loading its last entry / as here: 41 x 7 drafts of 6, V = 32003
 // 108.8 / 106.8 / 96.6, 40 x 8 of 8, V = 32001 149.5 / 146.2 / 129.0, 20 x 8 of 6, V = 50257 102.7 / 100.7 / 90.4; three iterations of
-// 8 x 4 of 8, V = 50257 219.4 with every lane's / 210.0.  (Rows moved by an entry, with masks at their ends, gain the same, and another
-// 1 - 2 % under levels, but give bits that depend on the address.)
+// 8 x 4 of 8, V = 50257 219.4 with every lane's / 210.0.  (Rows moved by an entry, with masks at their ends, gain another
+// 0.5 - 3 %, but give bits that depend on the address.  Not adopted: bodies of their own for each of a pair's four cases, 130 / 126 at
+// V = 32001 but 92.2 / 92.9 at 100 x 4 of 6, V = 20001, and spills under levels; 256 vectors in line for each wave, of which three of four
+// need no entry besides, 60 x 8 of 8, V = 9001 91 / 97; steps without the tests of the row's end, 88.6 / 90.2 there.)
 template <bool ODD> struct Loaded { U4 v; };
 template <> struct Loaded<true> { U4 v; uint32_t last; };
 template <typename T, bool ODD>
@@ -581,13 +583,24 @@ struct RowLoads {
         }
         return l;
     }
+    __device__ __forceinline__ uint32_t behind(const Loaded<ODD> &l, int v) const {
+        const uint32_t next = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(static_cast<int>(l.last), static_cast<int>(l.v.x), 0x130, 0xf, 0xf, false));   // (wave_shl:1)
+        return v >= own ? l.last : next;
+    }
     __device__ __forceinline__ U4 vector(const Loaded<ODD> &l, int v) const {
-        if constexpr (ODD) {
-            const uint32_t next = static_cast<uint32_t>(__builtin_amdgcn_update_dpp(static_cast<int>(l.last), static_cast<int>(l.v.x), 0x130, 0xf, 0xf, false));   // (wave_shl:1)
+        if constexpr (ODD)
             return U4{__builtin_amdgcn_alignbit(l.v.y, l.v.x, turn), __builtin_amdgcn_alignbit(l.v.z, l.v.y, turn),
-                      __builtin_amdgcn_alignbit(l.v.w, l.v.z, turn), __builtin_amdgcn_alignbit(v >= own ? l.last : next, l.v.w, turn)};
-        } else {
+                      __builtin_amdgcn_alignbit(l.v.w, l.v.z, turn), __builtin_amdgcn_alignbit(behind(l, v), l.v.w, turn)};
+        else
             return l.v;
+    }
+    // The entries of a vector of a row that is turned for certain (ODD) or loaded as it lies.
+    __device__ __forceinline__ void entries(const Loaded<ODD> &l, int v, float (&z)[Elem<T>::kPerVec]) const {
+        if constexpr (ODD) {
+            z[0] = bf16_hi(l.v.x); z[1] = bf16_lo(l.v.y); z[2] = bf16_hi(l.v.y); z[3] = bf16_lo(l.v.z);
+            z[4] = bf16_hi(l.v.z); z[5] = bf16_lo(l.v.w); z[6] = bf16_hi(l.v.w); z[7] = bf16_lo(behind(l, v));
+        } else {
+            Elem<T>::unpack(l.v, z);
         }
     }
 };

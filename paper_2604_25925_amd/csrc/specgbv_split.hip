@@ -60,14 +60,19 @@ constexpr int kAhead = 4;            // loads a thread of k_row_stats keeps in f
 
 // Vector v of a row into its running sum, without the drafted token and without entries the vector before holds.
 template <typename T>
-__device__ __forceinline__ void add_vector(RunningSum &acc, const U4 &raw, int v, int tok, int V, float c)
+__device__ __forceinline__ void add_entries(RunningSum &acc, float (&z)[Elem<T>::kPerVec], int v, int tok, int V, float c)
 {
     constexpr int PV = Elem<T>::kPerVec;
-    float z[PV];
-    Elem<T>::unpack(raw, z);
     mask_repeated<T>(z, v, V);
     leave_out(z, v == tok / PV, tok - vector_entry<T>(v, V));
     acc.add(z, c);
+}
+template <typename T>
+__device__ __forceinline__ void add_vector(RunningSum &acc, const U4 &raw, int v, int tok, int V, float c)
+{
+    float z[Elem<T>::kPerVec];
+    Elem<T>::unpack(raw, z);
+    add_entries<T>(acc, z, v, tok, V, c);
 }
 
 // grid (row pairs + pending levels, 2): blocks (pair, 0 / 1) reduce the target / draft row of the pair; with
@@ -127,11 +132,17 @@ k_row_stats(const T *__restrict__ target, const T *__restrict__ draft,
 #pragma unroll
                 for (int a = 0; a < kAhead; ++a) {
                     const int at = i + a * kStatThreads;
-                    if (at < nvec) add_vector<T>(acc, from.vector(v[a], at), at, tok, V, c);
+                    if (at < nvec) {
+                        float z[Elem<T>::kPerVec];
+                        from.entries(v[a], at, z);
+                        add_entries<T>(acc, z, at, tok, V, c);
+                    }
                 }
             }
         };
-        // (rows of an odd vocabulary that start at an even entry as all others: 97.4 / 96.6 us a call at 41 x 7 drafts of 6, V = 32003)
+        // (rows of an odd vocabulary that start at an even entry as all others: 97.4 / 96.6 us a call at 41 x 7 drafts of 6, V = 32003;
+        // the others' entries straight from what was loaded, without putting the vectors together before: 99.2 / 98.3, 40 x 8 of 8,
+        // V = 32001 130.2 / 129.2, 100 x 4 of 6, V = 20001 93.0 / 92.2)
         const RowLoads<T, ODD> from(row, V, nvec, pair == 0);
         if (from.turn != 0) sweep(from);
         else sweep(RowLoads<T, false>(row, V, nvec, false));
@@ -147,8 +158,8 @@ k_row_stats(const T *__restrict__ target, const T *__restrict__ draft,
     // over the workgroup (four barriers), library exponentials and the token's logit fetched here / as here: one level on 100 x 8
     // drafts of 8, V = 3000 float32 165.3 / 150.8, two on 128 x 4 of 8, V = 8000 bfloat16 159.3 / 151.3, three iterations of 128 x 8 of
     // 8, V = 8000 782 / 734, 8 x 4 of 8, V = 128256 294.4 / 292.1; 32 x 8 of 8, V = 24000 without levels 88.5 / 86.1, 41 x 7 of 6,
-    // V = 32003 96.5 / 95.9; 40 x 8 of 8, V = 32000 the same.  The logarithm stays the library's and
-    // gives the bits it gave (log2_series, no less exact, takes another 0.2 - 0.6 % off calls with levels, and other bits).
+    // V = 32003 96.5 / 95.9; 40 x 8 of 8, V = 32000 the same.  The logarithm stays the library's,
+    // the more exact one (off by 0.6e-16 for sums between 1/2 and 2, log2_series by 5.7e-16; that takes another 0.2 - 0.6 % off calls with levels).
     constexpr int kWaves = kStatThreads / kWave;
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wid = tid / kWave;
     const float wave_ref = integral_reference(wave_max(acc.m2), 1.0f);
