@@ -1,4 +1,4 @@
-"""bfloat16 rows that start at an odd entry are read from the entry in front of them on (two-pass schedule): the rows' first and
+"""Vectors of bfloat16 rows that start at an odd entry are loaded from the entry in front on and put together (two-pass schedule): the rows' first and
 last entries decide (drafted tokens there, and entries in front that would change every sum), with and without parts, and
 with tensors that themselves start at an odd entry.  Where a row starts makes no difference to a bit of its results."""
 import numpy as np
