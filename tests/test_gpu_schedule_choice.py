@@ -27,13 +27,15 @@ def _runs(B, K, L, V, dtype, algos):
             left.append(ws.cpu().numpy())
             kept = kept & (left[-1] == fill)
         res = sg.specgbv_read_intermediates(ws, B, K, L, V, code)
-        out.append(_Run(np.stack([res["lse_q"], res["lse_p"]]), ~kept, _parts_with_words(left[0], 165, B * K * L)))
+        out.append(_Run(np.stack([res["lse_q"], res["lse_p"]]), ~kept.reshape(-1, 256).all(1), _parts_with_words(left[0], 165, B * K * L)))
     return out
 
 
 class _Run:
     def __init__(self, normalisers, written, parts):
-        self.normalisers, self.written, self.parts = normalisers, written, parts      # (parts: 0 where there are no such words)
+        # (written: which 256 bytes; by the byte, what a final selection holds beyond its levels may be any value, a filling too.
+        # parts: 0 where there are no such words)
+        self.normalisers, self.written, self.parts = normalisers, written, parts
 
 
 def _parts_with_words(ws, fill, rows):
